@@ -184,7 +184,8 @@ Layout make_layout(const losa_config* c) {
   // aims at kTargetWorkgroups work items (or one per head if there are more heads than that).
   {
     const long few = kTargetItems * (long)(rows_max < (size_t)kSparseRows ? rows_max : (size_t)kSparseRows);
-    const long many = ((long)heads > kTargetWorkgroups ? (long)heads : kTargetWorkgroups) * (long)rows_max;
+    const long tiled = ((long)rows_max + kPartialTile - 1) / kPartialTile * kPartialTile;
+    const long many = ((long)heads > kTargetWorkgroups ? (long)heads : kTargetWorkgroups) * tiled;
     L.part_rows = few > many ? few : many;
   }
   L.delta = cv.take(rows * 4);
@@ -266,10 +267,10 @@ losa_status hip_fail(losa_ctx* ctx, const char* what, hipError_t e) {
 }
 
 // Number of equal shares a (sequence, KV head) page list of at most `upper` pages is split into,
-// when every work item holds `part_stride` rows of partials.
-int pick_nchunk(const losa_ctx* ctx, int batch, int upper, int row_groups, int part_stride) {
+// when every work item holds `part_stride` rows of partials and tiles hold `tile` tokens.
+int pick_nchunk(const losa_ctx* ctx, int batch, int upper, int row_groups, int part_stride, int tile) {
   const long heads = (long)batch * ctx->sh.Hkv;
-  const long tiles = (upper + (32 / ctx->sh.g) - 1) / (32 / ctx->sh.g);
+  const long tiles = (upper + (tile / ctx->sh.g) - 1) / (tile / ctx->sh.g);
   long want = ctx->target_workgroups / (heads * row_groups);
   const long fit = ctx->part_rows / (heads * part_stride);
   if (want > fit) want = fit;
@@ -365,38 +366,51 @@ losa_status sparse_attn_impl(losa_ctx* ctx, hipStream_t st, const KvView& kv, in
   const bool both_shapes = mfma && !hinted && ctx->sh.rows_max > 64 && ctx->sh.rows_max <= 256;
   // matrix-core kernel: up to 64 rows ride in one workgroup; more rows -> groups of 4 x 64 rows
   const int row_groups = mfma ? (rows_upper <= 64 ? 1 : (ctx->sh.rows_max + 255) / 256) : (ctx->sh.rows_max + 31) / 32;
+  // rows > 64 take the shared-stage kernel (unless switched off); it alone serves the launch when the host
+  // knows that no head can have fewer, or when the two shapes do not go together
+  const bool rows_kernel = mfma && ctx->shared_tiles && rows_upper > 64;
   // rows of partials per work item: what the host knows the row count cannot exceed
   Partials part = ctx->part;
   part.rows = hinted ? (rows_upper + 15) / 16 * 16 : ctx->sh.rows_max;
   if (part.rows > ctx->sh.rows_max) part.rows = ctx->sh.rows_max;
-  const int nchunk = pick_nchunk(ctx, batch, upper, mfma ? row_groups : 1, part.rows);
+  if (rows_kernel) part.rows = (rows_upper + kPartialTile - 1) / kPartialTile * kPartialTile;
+  const int many_tile = rows_kernel ? kManyRowStage : 32;
+  const int few_tile = rows_kernel && !both_shapes ? kManyRowStage : 32;
+  const int nchunk = pick_nchunk(ctx, batch, upper, mfma ? row_groups : 1, part.rows, few_tile);
   hipError_t e;
-  if (mfma && !prepared) {
+  // the dense step of the shared-stage kernel reads page table and queries where they are; everything else
+  // that is not prepared yet goes through attn_prepare
+  const bool dense_step = rows_kernel && !active_idx && !sel_pages;
+  if (mfma && !prepared && !dense_step) {
     StageTimer timer(ctx, st, LOSA_STAGE_TOPK);
     e = launch_attn_prepare(st, kv, ctx->sh, batch, q, active_idx, active_count, sel_pages, sel_count, cap, ctx->prep);
     if (e != hipSuccess) return hip_fail(ctx, "attn_prepare launch", e);
   }
   {
     StageTimer timer(ctx, st, LOSA_STAGE_ATTN, /*bind_to_dispatch=*/mfma && !both_shapes);
-    const int many_rows = !ctx->shared_tiles ? kManyRowsIndependent
-                                             : (ctx->half_values ? kManyRowsSharedHalf : kManyRowsSharedPair);
-    if (both_shapes) {
-      e = launch_attn_mfma(st, kv, ctx->sh, batch, ctx->prep, nchunk, 64, part, nullptr, nullptr, 0, 64, uni,
-                           many_rows);
-      if (e == hipSuccess)
-        e = launch_attn_mfma(st, kv, ctx->sh, batch, ctx->prep, nchunk, ctx->sh.rows_max, part, nullptr, nullptr,
-                             64, 0x7fffffff, nullptr, many_rows);
-    } else if (mfma)
-      e = launch_attn_mfma(st, kv, ctx->sh, batch, ctx->prep, nchunk, rows_upper, part, timer.start(),
-                           timer.stop(), 0, 0x7fffffff, uni, many_rows);
-    else
+    if (!mfma) {
       e = launch_attn_generic(st, ctx->cfg.dtype, kv, ctx->sh, batch, q, active_idx, active_count, sel_pages,
                               sel_count, cap, nchunk, part);
+    } else {
+      // (events are bound to a dispatch only when it is the only one)
+      const hipEvent_t e0 = both_shapes ? nullptr : timer.start(), e1 = both_shapes ? nullptr : timer.stop();
+      e = hipSuccess;
+      if (both_shapes || !rows_kernel)
+        e = launch_attn_mfma(st, kv, ctx->sh, batch, ctx->prep, nchunk, both_shapes ? 64 : rows_upper, part, e0, e1, 0,
+                             both_shapes ? 64 : 0x7fffffff, uni);
+      if (e == hipSuccess && rows_kernel)
+        e = launch_attn_rows(st, kv, ctx->sh, batch, ctx->prep, dense_step ? q : nullptr, nchunk, part, e0, e1, both_shapes ? 64 : 0,
+                             ctx->half_values);
+      else if (e == hipSuccess && both_shapes)
+        e = launch_attn_mfma(st, kv, ctx->sh, batch, ctx->prep, nchunk, ctx->sh.rows_max, part, nullptr, nullptr, 64,
+                             0x7fffffff, nullptr);
+    }
   }
   if (e != hipSuccess) return hip_fail(ctx, "attention launch", e);
   StageTimer timer(ctx, st, LOSA_STAGE_MERGE);
   e = launch_attn_merge(st, kv, ctx->sh, batch, active_idx, active_count, sel_count, cap, nchunk,
-                        mfma ? &ctx->prep : nullptr, part, o_p, lse_p, hinted ? rows_upper : 0);
+                        mfma ? &ctx->prep : nullptr, part, o_p, lse_p, hinted ? rows_upper : 0, few_tile,
+                        many_tile, dense_step);
   if (e != hipSuccess) return hip_fail(ctx, "attn_merge launch", e);
   return LOSA_OK;
 }

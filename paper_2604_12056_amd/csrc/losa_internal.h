@@ -133,21 +133,27 @@ hipError_t launch_attn_generic(hipStream_t st, int dtype, const KvView& kv, cons
 hipError_t launch_attn_prepare(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const void* q,
                                const int32_t* active_idx, const int32_t* active_count, const int32_t* sel_pages,
                                const int32_t* sel_count, int cap, const AttnPrepared& prep);
-// The attention kernel's form above 64 query rows per KV head.
-enum ManyRowForm : int {
-  kManyRowsIndependent = 0,   // 4 wavefronts of 64 rows, each loading every tile itself; P as a bfloat16 pair
-  kManyRowsSharedHalf = 1,    // 8 wavefronts of 32 rows, tiles shared through LDS, value product in half precision
-  kManyRowsSharedPair = 2     // the same sharing, P as a bfloat16 pair (values keep bfloat16's range)
-};
 // e0/e1 (both or neither): events bound to the dispatch itself, for exact kernel timing.
 hipError_t launch_attn_mfma(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnPrepared& prep,
                             int nchunk, int rows_upper, const Partials& part, hipEvent_t e0, hipEvent_t e1,
                             int m_lo = 0, int m_hi = 0x7fffffff,   // serves (sequence, head) pairs with m_lo < rows <= m_hi
-                            const UnionInKernel* uni = nullptr, int many_rows = kManyRowsSharedHalf);
+                            const UnionInKernel* uni = nullptr);
+// sparse_attn_rows.hip: more than 64 query rows per KV head, eight wavefronts sharing stages of kManyRowStage
+// tokens through LDS; serves (sequence, head) pairs with more than m_lo rows.  Its partials are laid out by
+// fragments: per 32 rows (kPartialTile; part.rows is a multiple of it) and 8 channels, 64 lanes x 4 floats,
+// lane = row of the tile + 32 * (second half of the 8 channels).
+constexpr int kManyRowStage = 64;
+constexpr int kPartialTile = 32;
+// dense_query: the query tensor of a dense step, which needs no prepared inputs; NULL otherwise.
+hipError_t launch_attn_rows(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnPrepared& prep,
+                            const void* dense_query, int nchunk, const Partials& part, hipEvent_t e0, hipEvent_t e1, int m_lo, bool half_values);
+// few_tile / many_tile: tokens per tile that the partials of a head with at most / more than 64 query rows were
+// dealt in (they decide which of the nchunk work items exist); kManyRowStage: partials laid out by fragments.
 hipError_t launch_attn_merge(hipStream_t st, const KvView& kv, const Shape& sh, int batch,
                              const int32_t* active_idx, const int32_t* active_count,
                              const int32_t* sel_count, int cap, int nchunk, const AttnPrepared* prep,
-                             const Partials& part, float* o_p, float* lse_p, int rows_hint);
+                             const Partials& part, float* o_p, float* lse_p, int rows_hint, int few_tile, int many_tile,
+                             bool dense_step);   // dense_step: no counts were prepared (launch_attn_rows with dense_query)
 
 // ---- block_merge.hip
 hipError_t launch_block_merge(hipStream_t st, int dtype, const Shape& sh, int batch, const void* q, const void* k_b,

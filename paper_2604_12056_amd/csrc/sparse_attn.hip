@@ -190,6 +190,92 @@ __global__ __launch_bounds__(256) void attn_partials_generic_kernel(
   }
 }
 
+// Partials laid out by fragments (sparse_attn_rows.hip), 32 rows x 8 channels each; every load is 1 KiB contiguous
+// per wavefront.  With few chunks a wavefront takes a fragment and all of its chunks; with more, the
+// workgroup's four wavefronts take every fourth chunk of one fragment and meet in LDS, in wavefront order.
+// `block` counts (row tile, group of fragments) pairs.
+constexpr int kFragBatch = 8;   // chunks a wavefront has in flight
+__host__ __device__ constexpr int fragments_per_block(int nchunk) { return nchunk <= kFragBatch ? 4 : 1; }
+template <int D>
+__device__ __forceinline__ void merge_fragments(const Shape& sh, const int32_t* __restrict__ active_idx, int b, int j,
+                                                int block, int M, int live, int nchunk, const Partials& part,
+                                                float* __restrict__ o_p, float* __restrict__ lse_p, float* lds) {
+  typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+  constexpr int KB = kFragBatch;
+  const int fpb = fragments_per_block(nchunk), groups = D / 8 / fpb;
+  const bool split = fpb == 1;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, half = lane >> 5;
+  const int tile = block / groups, frag = block % groups * fpb + (split ? 0 : wave);
+  const int c_first = split ? wave : 0, c_step = split ? 4 : 1;
+  const int r = tile * kPartialTile + l32;
+  const size_t item0 = ((size_t)b * sh.Hkv + j) * nchunk;
+  const int tok = active_idx ? active_idx[(size_t)b * sh.B + min(r / sh.G, sh.B - 1)] : r / sh.G;
+  float m = -INFINITY, l = 0.f;
+  f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+  for (int c0 = c_first; c0 < live; c0 += c_step * KB) {
+    float mk[KB], lk[KB];
+    f32x4_t x[KB];
+#pragma unroll
+    for (int k = 0; k < KB; ++k) {   // all loads of the batch go out before the first is used
+      mk[k] = -INFINITY;
+      lk[k] = 0.f;
+      x[k] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+      if (c0 + c_step * k >= live) continue;   // (uniform over the wavefront)
+      const size_t prow = (item0 + c0 + c_step * k) * part.rows + tile * kPartialTile;
+      mk[k] = part.m[prow + l32];
+      lk[k] = part.l[prow + l32];
+      x[k] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(part.o + prow * D + frag * 256 + lane * 4));
+    }
+    float m_new = m;
+#pragma unroll
+    for (int k = 0; k < KB; ++k) m_new = fmaxf(m_new, mk[k]);
+    const float keep = exp2f(m - m_new);   // (m_new is finite: references are -1e30 at least)
+    m = m_new;
+    l *= keep;
+    acc *= keep;
+#pragma unroll
+    for (int k = 0; k < KB; ++k) {
+      const float w = exp2f(mk[k] - m);
+      l = fmaf(lk[k], w, l);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[e] = fmaf(x[k][e], w, acc[e]);
+    }
+  }
+  if (split) {
+    float* slot = lds + wave * (256 + 64);
+    if (wave) {
+      *reinterpret_cast<f32x4_t*>(slot + lane * 4) = acc;
+      if (half == 0) {
+        slot[256 + l32] = m;
+        slot[256 + 32 + l32] = l;
+      }
+    }
+    __syncthreads();
+    if (wave) return;
+    float mw[4], wt[4], l_tot = 0.f;
+    mw[0] = m;
+#pragma unroll
+    for (int w = 1; w < 4; ++w) mw[w] = lds[w * (256 + 64) + 256 + l32];
+    m = fmaxf(fmaxf(mw[0], mw[1]), fmaxf(mw[2], mw[3]));
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      wt[w] = mw[w] > -INFINITY ? exp2f(mw[w] - m) : 0.f;
+      l_tot = fmaf(w ? lds[w * (256 + 64) + 256 + 32 + l32] : l, wt[w], l_tot);
+    }
+    l = l_tot;
+    acc *= wt[0];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) acc += *reinterpret_cast<const f32x4_t*>(lds + w * (256 + 64) + lane * 4) * wt[w];
+  }
+  if (r >= M || (unsigned)tok >= (unsigned)sh.B) return;
+  const size_t orow = ((size_t)b * sh.B + tok) * sh.Hq + j * sh.G + r % sh.G;
+  const bool any = m > -1.0e29f;   // no valid token at all: the neutral element of the merge
+  const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+  *reinterpret_cast<f32x4_t*>(o_p + orow * D + frag * 8 + half * 4) = any ? acc / l : zero;
+  if (frag == 0 && half == 0) lse_p[orow] = any ? (m + log2f(l)) * 0.6931471805599453f : -INFINITY;
+}
+
 // Combine the chunk partials of one query row with the log-sum-exp rule, normalise, and
 // write (o_p, lse_p) at the active token's row.  256 threads = CL chunk lanes x D/4 channel
 // quads: every chunk lane sums its chunks c = lane, lane+CL, ... (independent loads), then
@@ -197,20 +283,34 @@ __global__ __launch_bounds__(256) void attn_partials_generic_kernel(
 // LOG2: partial maxima are in log2 units (scores scaled by sm_scale*log2(e)) and sums are
 // float; otherwise natural units and double sums (the element-generic kernel, which also
 // serves the float mode).
-template <int D, bool LOG2>
+// FRAGS: some heads' partials are laid out by fragments (a template argument: its code and registers would cost
+// the plain form 0.3 us of its 4).
+template <int D, bool LOG2, bool FRAGS>
 __global__ __launch_bounds__(256) void attn_merge_kernel(KvView kv, Shape sh, const int32_t* __restrict__ active_idx,
                                                          const int32_t* __restrict__ active_count,
                                                          const int32_t* __restrict__ sel_count, int cap, int nchunk,
                                                          const int32_t* __restrict__ ucount,
                                                          const int32_t* __restrict__ mrows, Partials part,
                                                          float* __restrict__ o_p, float* __restrict__ lse_p,
-                                                         int rows_known) {
+                                                         int rows_known, int few_tile, int many_tile) {
   typedef typename std::conditional<LOG2, float, double>::type Acc;
   constexpr int C4 = D / 4, CL = 256 / C4;
-  __shared__ Acc red[CL][D];
+  __shared__ __attribute__((aligned(16))) Acc red[CL][D];
   __shared__ Acc lred[CL];
   __shared__ float wmax[CL];
   const int r = blockIdx.x, j = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
+  if constexpr (FRAGS) {   // heads with more than 64 rows, or every head (few_tile)
+    // (no counts prepared: the dense step, every row and every page)
+    const int M = min(mrows ? min(mrows[b * sh.Hkv + j], sh.rows_max) : sh.rows_max, part.rows);
+    if (few_tile == kManyRowStage || M > kUnionRows) {
+      __shared__ __attribute__((aligned(16))) float frag_lds[4 * (256 + 64)];
+      if (r / (D / 8 / fragments_per_block(nchunk)) * kPartialTile >= M) return;
+      const int U = ucount ? min(ucount[b * sh.Hkv + j], sh.max_pages) : seq_pages(kv, sh, b), pps = kManyRowStage / sh.g;
+      merge_fragments<D>(sh, active_idx, b, j, r, M, min(nchunk, (U + pps - 1) / pps), nchunk, part, o_p, lse_p, frag_lds);
+      return;
+    }
+    if (r >= M) return;
+  }
   // A grid sized without knowing the row count (threshold / cumulative-mass selection) has a
   // workgroup for every possible row: those look at the count first and leave, instead of
   // fetching partials nobody wrote (a block of 224 possible rows with 35 active ones would fetch
@@ -252,7 +352,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(KvView kv, Shape sh, co
   const int hg = r % sh.G;
   const int tok = tok_early;   // r < M <= B*G here, so the index above was not clamped
   if ((unsigned)tok >= (unsigned)sh.B) return;
-  const int ppt = 32 / sh.g;
+  const int ppt = (M <= kUnionRows ? few_tile : many_tile) / sh.g;
   const int ntiles = (U + ppt - 1) / ppt;
   const int live = min(nchunk, ntiles);   // work item c exists iff tile c does
   const size_t item0 = ((size_t)b * sh.Hkv + j) * nchunk;
@@ -348,25 +448,27 @@ hipError_t launch_attn_generic(hipStream_t st, int dtype, const KvView& kv, cons
 
 hipError_t launch_attn_merge(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const int32_t* active_idx,
                              const int32_t* active_count, const int32_t* sel_count, int cap, int nchunk,
-                             const AttnPrepared* prep, const Partials& part, float* o_p, float* lse_p, int rows_hint) {
+                             const AttnPrepared* prep, const Partials& part, float* o_p, float* lse_p, int rows_hint,
+                             int few_tile, int many_tile, bool dense_step) {
   if (batch <= 0) return hipSuccess;
   // rows_hint: an upper bound on the active rows per KV head the host happens to know (0: none);
   // rows past it get no workgroup (they would only fetch partials speculatively and exit)
-  dim3 grid(rows_hint >= 1 && rows_hint < sh.rows_max ? rows_hint : sh.rows_max, sh.Hkv, batch);
-  const int32_t* uc = prep ? prep->ucount : nullptr;
-  const int32_t* mr = prep ? prep->mrows : nullptr;
-  const int known = rows_hint >= 1 || !active_idx;   // (no list of active tokens: every row exists)
-  if (sh.d == 128) {
-    if (prep)
-      attn_merge_kernel<128, true><<<grid, 256, 0, st>>>(kv, sh, active_idx, active_count, sel_count, cap, nchunk, uc, mr, part, o_p, lse_p, known);
-    else
-      attn_merge_kernel<128, false><<<grid, 256, 0, st>>>(kv, sh, active_idx, active_count, sel_count, cap, nchunk, uc, mr, part, o_p, lse_p, known);
-  } else {
-    if (prep)
-      attn_merge_kernel<64, true><<<grid, 256, 0, st>>>(kv, sh, active_idx, active_count, sel_count, cap, nchunk, uc, mr, part, o_p, lse_p, known);
-    else
-      attn_merge_kernel<64, false><<<grid, 256, 0, st>>>(kv, sh, active_idx, active_count, sel_count, cap, nchunk, uc, mr, part, o_p, lse_p, known);
+  const int rows = rows_hint >= 1 && rows_hint < sh.rows_max ? rows_hint : sh.rows_max;
+  int gx = rows;
+  if (many_tile == kManyRowStage) {   // fragments: see merge_fragments; heads of at most 64 rows: a workgroup per row
+    gx = (rows + kPartialTile - 1) / kPartialTile * (sh.d / 8 / fragments_per_block(nchunk));
+    if (few_tile != kManyRowStage) gx = max(gx, min(rows, kUnionRows));
   }
+  dim3 grid(gx, sh.Hkv, batch);
+  const int32_t* uc = prep && !dense_step ? prep->ucount : nullptr;
+  const int32_t* mr = prep && !dense_step ? prep->mrows : nullptr;
+  const int known = rows_hint >= 1 || !active_idx;   // (no list of active tokens: every row exists)
+  auto kern = sh.d == 128 ? (!prep ? attn_merge_kernel<128, false, false>
+                             : many_tile == kManyRowStage ? attn_merge_kernel<128, true, true> : attn_merge_kernel<128, true, false>)
+                          : (!prep ? attn_merge_kernel<64, false, false>
+                             : many_tile == kManyRowStage ? attn_merge_kernel<64, true, true> : attn_merge_kernel<64, true, false>);
+  kern<<<grid, 256, 0, st>>>(kv, sh, active_idx, active_count, sel_count, cap, nchunk, uc, mr, part, o_p, lse_p, known, few_tile,
+                             many_tile);
   return hipGetLastError();
 }
 

@@ -22,10 +22,8 @@
 //       interleaved tiles, K/V go global -> registers in operand layout one tile ahead (no LDS
 //       and no barrier in the main loop), and the four combine their (reference, sum, O)
 //       through LDS at the end, so one partial leaves the workgroup;
-//   many rows (rows > 64, e.g. the dense initialisation): eight wavefronts of 32 rows walk the
-//       same tiles; a tile is fetched from memory once per workgroup, its values converted to
-//       half precision, and shared through LDS (one barrier per tile).  Four independent
-//       wavefronts of 64 rows, each loading every tile itself, remain as a switchable fallback.
+//   many rows: four independent wavefronts of 64 rows, each loading every tile itself.  More than 64
+//       rows normally take sparse_attn_rows.hip; this form is what LOSA_TUNE_SHARED_TILES = 0 selects.
 // Tiles of a (sequence, head) list are dealt round-robin to its workgroups, so every
 // workgroup gets the same number of tiles (within one) whatever the union size turns out to be.
 #include <hip/hip_ext.h>
@@ -41,7 +39,6 @@ namespace losa {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(8))) float f32x8_t;
-typedef __attribute__((ext_vector_type(8))) _Float16 f16x8_t;
 typedef uint32_t u32x4v_t __attribute__((ext_vector_type(4)));   // a plain vector value (stays in registers)
 
 constexpr float kNegBig = -1.0e30f;   // finite stand-in for "no token seen yet"
@@ -83,16 +80,6 @@ struct MergeSlot {   // LDS image of one wavefront's state: O as [row tile][chan
 // so that a wavefront can issue its page-entry loads, its query loads and the two counts all
 // at once when it starts: the only dependent memory round trip left before key/value data
 // flows is entries -> pages.
-// F16V (shared-tile shape only): the value product runs in half precision.  The value tile is
-// converted bfloat16 -> half once per workgroup while it is staged into LDS (exact for
-// 2^-14 <= |v| <= 65504, truncated towards zero below that range, i.e. off by less than 2^-24,
-// and held at +-65504 above it), and the numerators go to the matrix core as ONE half-precision
-// operand (11 significant bits, round to nearest) instead of a bfloat16 hi + lo pair: a third
-// fewer matrix products per tile and no hi/lo split on the vector ALUs.  The reference point of
-// the exponentials sits 7 (log2 units) above where it would otherwise be, so that numerators use
-// the upper end of the half-precision range (they stay <= 2^15) and only values below 2^-31 of
-// a row's largest fall into its subnormals.
-//
 // UNION (split-pages shape only): there is no prepared page list.  The selection kernel left the
 // pick bitmap of every query row (word-major) and a copy of the head's page table; the four
 // wavefronts of a workgroup fetch a quarter of each, meet in LDS (one barrier), and then every
@@ -107,8 +94,7 @@ constexpr int kTablePagesInLds = 2048;   // the first so many entries of a head'
 // LDS of the split-pages shape, in floats: the four wavefronts' merge slots, then (UNION) an area the
 // workgroup fills together at start-up: each wavefront's share of the bitmap OR, and the page table.
 constexpr int kUnionShared = 4 * kMaxUnionWords + kTablePagesInLds;
-template <int D, int GP, int R, bool SPLIT_PAGES, int NBUF, int NWAVE = 4, bool LDS_TILES = false, bool F16V = false,
-          bool UNION = false>
+template <int D, int GP, int R, bool SPLIT_PAGES, int NBUF, bool UNION = false>
 __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, int nrbg, Shape sh, KvView kv, Partials part,
                                                float scale_log2e, int m_lo, int m_hi, UnionInKernel uni, float* lds) {
   static_assert(!UNION || SPLIT_PAGES, "the union is built in the kernel only in the split-pages shape");
@@ -125,7 +111,7 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
   const int l16 = lane & 15, qd = lane >> 4;
   const int chunk = blockIdx.x, b = blockIdx.z;
   const int j = SPLIT_PAGES ? blockIdx.y : blockIdx.y / nrbg;
-  const int rb = SPLIT_PAGES ? 0 : (blockIdx.y % nrbg) * NWAVE + wave;
+  const int rb = SPLIT_PAGES ? 0 : (blockIdx.y % nrbg) * 4 + wave;
   const int head = b * sh.Hkv + j;
 
   // Tiles are dealt round-robin: workgroup `chunk` owns tiles chunk, chunk+nchunk, ... of the
@@ -238,10 +224,7 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
   // fourth: this launch only serves row counts in (m_lo, m_hi] (the host may not know the count
   // and then launches both work shapes, each taking its own range)
   const bool has_rows = SPLIT_PAGES || rb * (R * 16) < M;
-  // shared-tile shape: a workgroup none of whose wavefronts has rows leaves; one with some rows
-  // keeps its row-less wavefronts (they help with staging and keep the barriers)
-  const bool group_has_rows = !LDS_TILES || (int)(blockIdx.y % nrbg) * (NWAVE * R * 16) < M;
-  if ((M <= 0) | (chunk >= ntiles) | (!LDS_TILES && !has_rows) | !group_has_rows | (M <= m_lo) | (M > m_hi)) return;
+  if ((M <= 0) | (chunk >= ntiles) | !has_rows | (M <= m_lo) | (M > m_hi)) return;
   const int ntw = tfirst < ntiles ? (ntiles - 1 - tfirst) / tstep + 1 : 0;   // this wavefront's tiles
 
   bf16x8_t qf[R][KS];
@@ -259,7 +242,6 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
 
   float m_run[R], l_run[R], up_thr[R];   // up_thr: the raw score above which a row's reference has to move
   const float inv_scale_log2e = 1.0f / scale_log2e;
-  [[maybe_unused]] const f16x8_t ones_h = {1, 1, 1, 1, 1, 1, 1, 1};
   f32x4_t o[R][NT];
 #pragma unroll
   for (int mt = 0; mt < R; ++mt) {
@@ -367,7 +349,6 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
   // maximum overtakes its reference by more than that, which after the first tile is rare.
   // exp2(kLag) = 256 is far inside float / bfloat16 range, and (m_run, l, O) stay consistent.
   constexpr float kLag = 8.0f;
-  constexpr float kRefBias = F16V ? 7.0f : 0.0f;   // numerators are exp2(s - m_run) with m_run = reference - kRefBias
 
   // all score products of a tile, back to back: S^T = K_tile . Q^T for both 16-row halves
   auto score_products = [&](const bf16x8_t (&k)[2][KS], f32x4_t (&sc)[R][2]) {
@@ -383,12 +364,8 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
     }
   };
 
-  // Softmax update and value products of a tile whose scores `sc` are given.  `between` is code
-  // the caller wants issued after the rescale decision, in the same straight-line region as the
-  // numerators (the shared-tile loop puts the NEXT tile's score products there, so that the matrix
-  // core works on them while the vector ALU takes this tile's exponentials).
-  auto softmax_values = [&](Tile& t, f32x4_t (&sc)[R][2], auto&& between, auto mfma_between_c) {
-    constexpr int MB = decltype(mfma_between_c)::value;   // matrix instructions `between` issues
+  // softmax update and value products of a tile whose scores are given
+  auto softmax_values = [&](Tile& t, f32x4_t (&sc)[R][2]) {
     // valid tokens among this lane's 8 (tile tokens 8*qd .. 8*qd+7)
     int lane_valid;
     bool full;
@@ -399,7 +376,7 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
       full = t.nv[0] == 32;
       lane_valid = t.nv[0] - 8 * qd;
     }
-    if (!LDS_TILES && !full) {   // (the shared-tile shape clears them once per workgroup, while staging the tile)
+    if (!full) {
       // slots past the end of the sequence may hold anything: clear them in V (0 * NaN = NaN)
       const int cnt = max(0, min(8, lane_valid));
       const uint32_t m0 = cnt >= 2 ? ~0u : (cnt == 1 ? 0xFFFFu : 0u);
@@ -441,11 +418,11 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
     if (__any(any_up)) {
 #pragma unroll
       for (int mt = 0; mt < R; ++mt) {
-        const float m_cand = max_over_lane_groups(tm[mt]) * scale_log2e - kRefBias;
+        const float m_cand = max_over_lane_groups(tm[mt]) * scale_log2e;
         const bool up = m_cand > m_run[mt] + kLag;
         const float alpha = up ? fast_exp2(m_run[mt] - m_cand) : 1.0f;
         m_run[mt] = up ? m_cand : m_run[mt];
-        up_thr[mt] = (m_run[mt] + (kLag + kRefBias)) * inv_scale_log2e;
+        up_thr[mt] = (m_run[mt] + kLag) * inv_scale_log2e;
         l_run[mt] *= alpha;
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) o[mt][nt] *= alpha;
@@ -458,33 +435,6 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
     // The hi products of a row tile are issued right after its numerators, so the matrix core
     // works while the vector ALU does the next row tile; all lo products come last, far from
     // the hi product that feeds the same accumulator.
-    between();
-    if constexpr (F16V) {
-      // half-precision form: one operand per row tile (the value tile in t.v is already half precision)
-#pragma unroll
-      for (int mt = 0; mt < R; ++mt) {
-        const float neg_m = -m_run[mt];
-        f32x8_t p;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) p[e] = fast_exp2(fmaf(sc[mt][e >> 2][e & 3], scale_log2e, neg_m));
-        const f16x8_t ph = __builtin_convertvector(p, f16x8_t);
-        // The row sum comes from the matrix core as well: a product with an all-ones operand sums the
-        // (rounded) numerators of the tile's 32 tokens into every element of the result, so the
-        // normaliser is exactly the sum of the weights the value product uses, and the vector ALU
-        // adds one number per row tile instead of eight.
-        const f32x4_t rs = __builtin_amdgcn_mfma_f32_16x16x32_f16(ones_h, ph, (f32x4_t){0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-          o[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8_t, t.v[nt]), ph, o[mt][nt], 0, 0, 0);
-        l_run[mt] += rs[0];
-      }
-      // scheduling hint for this region: one matrix instruction, then a few vector instructions
-#pragma unroll
-      for (int i = 0; i < R * NT + R + MB; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // 1 MFMA
-        __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);   // 3 VALU
-      }
-    } else {
     bf16x8_t p_lo[R];
 #pragma unroll
     for (int mt = 0; mt < R; ++mt) {
@@ -524,12 +474,11 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // 1 MFMA
       __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);   // 3 VALU
     }
-    }
   };
   auto compute_tile = [&](Tile& t) {
     f32x4_t sc[R][2];
     score_products(t.k, sc);
-    softmax_values(t, sc, [] {}, std::integral_constant<int, 0>{});
+    softmax_values(t, sc);
   };
 
   // ---- main loop: NBUF tile buffers in registers, NBUF-1 tiles of lookahead (how many: see
@@ -537,161 +486,7 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
   // lookahead, not by occupancy.  Every load is issued unconditionally (see load_tile) so that
   // the number of loads in flight at each use is a compile-time constant: a load behind a
   // branch would force a full drain at the join.
-  if constexpr (LDS_TILES) {
-    // ---- shared-tile variant (many rows, 8 wavefronts of R*16 rows, 2 per SIMD): every
-    // wavefront of the workgroup walks the same tiles, so a tile is fetched from memory once per
-    // workgroup (not once per wavefront), put into LDS and read from there by all.  Measured on
-    // the dense initialisation this is 9-14% faster than 4 independent wavefronts of 64 rows.
-    // What it does not buy is overlap of matrix and vector work: counters show matrix-core busy
-    // plus vector-ALU busy adding up to the run time with one or two wavefronts per SIMD, also
-    // when the two of a SIMD are made to alternate their matrix and vector pieces with barriers
-    // (tried: same time), so the many-row shape is bound by the sum of the two, not by memory.
-    //
-    // LDS image of a tile: the matrix-core operands themselves, one 1 KiB block per operand
-    // (2*KS key blocks: half h, k-step ks; then NT value blocks), lane L's 16 bytes at L*16.
-    // Writes and reads are then both lane-linear, hence free of bank conflicts whichever way
-    // the hardware groups lanes; the permutation lives in the global addresses, where it only
-    // costs some coalescing.  Each wavefront fetches BPW of the blocks.  Two LDS buffers: tile
-    // n+1 is written while tile n is computed on; one barrier per tile.
-    constexpr int NBLK = 2 * KS + NT;          // operand blocks per tile
-    constexpr int BPW = NBLK / NWAVE;          // blocks fetched by each wavefront
-    constexpr int BUF = NBLK * 1024;           // bytes of one tile image
-    static_assert(NBLK % NWAVE == 0 && (BPW == 1 || BPW == 2), "operand blocks do not split evenly over the wavefronts");
-    unsigned char* lbase = reinterpret_cast<unsigned char*>(lds);
-    // PD tiles are in flight per workgroup: one register set each (this lane's 16-byte pieces
-    // of its blocks and, in scalar registers, the tile's valid-token counts).  Tile n sits in set
-    // n % PD; all indices below are compile-time constants once the loops are unrolled.
-    constexpr int PD = 2;
-    static_assert(PD <= TPR, "the first PD tiles come from the first batch of page entries");
-    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));   // a plain vector value: stays in registers
-    struct Stage {
-      u32x4_t v[BPW];
-      int nv[2];
-    };
-    Stage g[PD];
-    // Byte offset of this lane's piece of block i (of this wavefront) inside its page, and which
-    // of the tile's pages it is in (0 or 1): fixed for the whole kernel.
-    int piece_off[BPW];
-    bool piece_second[BPW], piece_is_k[BPW];
-#pragma unroll
-    for (int i = 0; i < BPW; ++i) {
-      const int blk = wave + NWAVE * i;
-      piece_is_k[i] = blk < 2 * KS;
-      if (piece_is_k[i]) {
-        const int h = blk / KS, ks = blk % KS;
-        const int r = 8 * (l16 >> 2) + 4 * h + (l16 & 3);   // token row tt(h, l16) of the tile
-        piece_second[i] = GP == 16 && r >= 16;
-        piece_off[i] = (r % GP) * (D * 2) + ks * 64 + qd * 16;
-      } else {
-        const int ch = (blk - 2 * KS) * 16 + l16;           // value channel
-        piece_second[i] = GP == 16 && qd >= 2;
-        piece_off[i] = ch * (GP * 2) + (GP == 16 ? (qd & 1) : qd) * 16;
-      }
-    }
-    // tile n of this workgroup -> registers.  n >= ntw asks for a tile that does not exist: the
-    // loads are issued all the same (no load behind a branch, so the number in flight at every
-    // wait is a compile-time constant) but read the first page of the pool.
-    auto gload = [&](Stage& st, int n) {
-      const bool real = n < ntw;
-      const int slot = (n * PPT) & 63;
-      const int pa = real ? __builtin_amdgcn_readlane(pg_phys, slot) : 0;
-      const int pb = real ? __builtin_amdgcn_readlane(pg_phys, slot + PPT - 1) : 0;
-      st.nv[0] = real ? __builtin_amdgcn_readlane(pg_valid, slot) : 0;
-      st.nv[1] = real ? __builtin_amdgcn_readlane(pg_valid, slot + PPT - 1) : 0;
-#pragma unroll
-      for (int i = 0; i < BPW; ++i) {
-        const size_t tile = (size_t)(piece_second[i] ? pb : pa) * sh.Hkv + j;
-        const unsigned char* src = reinterpret_cast<const unsigned char*>(piece_is_k[i] ? kv.k_pages : kv.v_pages) +
-                                   tile * (size_t)(GP * D * 2) + piece_off[i];
-        st.v[i] = *reinterpret_cast<const u32x4_t*>(src);
-      }
-    };
-    // bfloat16 pair -> half pair, towards zero: exact inside the half range, never infinite
-    auto to_half2 = [](uint32_t two_bf16) -> uint32_t {
-      const auto h = __builtin_amdgcn_cvt_pkrtz(__uint_as_float(two_bf16 << 16), __uint_as_float(two_bf16 & 0xFFFF0000u));
-      return __builtin_bit_cast(uint32_t, h);
-    };
-    auto lstore = [&](const Stage& st, int buf) {
-      // a tile that ends inside its page(s): the value slots past the end may hold anything and are
-      // cleared here, once per workgroup, so that the consumers need not look at them (0 * NaN = NaN)
-      const bool full = GP == 16 ? (st.nv[0] == 16) && (st.nv[1] == 16) : st.nv[0] == 32;
-#pragma unroll
-      for (int i = 0; i < BPW; ++i) {
-        u32x4_t x = st.v[i];
-        if (!full && !piece_is_k[i]) {
-          // this lane's piece of a value block: 8 consecutive tokens of one channel
-          const int first = GP == 16 ? 8 * (qd & 1) : 8 * qd;
-          const int cnt = max(0, min(8, (GP == 16 && qd >= 2 ? st.nv[1] : st.nv[0]) - first));
-          x[0] &= cnt >= 2 ? ~0u : (cnt == 1 ? 0xFFFFu : 0u);
-          x[1] &= cnt >= 4 ? ~0u : (cnt == 3 ? 0xFFFFu : 0u);
-          x[2] &= cnt >= 6 ? ~0u : (cnt == 5 ? 0xFFFFu : 0u);
-          x[3] &= cnt >= 8 ? ~0u : (cnt == 7 ? 0xFFFFu : 0u);
-        }
-        if (F16V && !piece_is_k[i]) {   // (uniform over the wavefront: a block is all keys or all values)
-          x[0] = to_half2(x[0]);
-          x[1] = to_half2(x[1]);
-          x[2] = to_half2(x[2]);
-          x[3] = to_half2(x[3]);
-        }
-        *reinterpret_cast<u32x4_t*>(lbase + buf * BUF + (wave + NWAVE * i) * 1024 + lane * 16) = x;
-      }
-    };
-    auto lread = [&](Tile& t, int buf) {
-      const unsigned char* tb_ = lbase + buf * BUF + lane * 16;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        t.k[0][ks] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(tb_ + ks * 1024));
-        t.k[1][ks] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(tb_ + (KS + ks) * 1024));
-      }
-#pragma unroll
-      for (int nt = 0; nt < NT; ++nt) t.v[nt] = *reinterpret_cast<const uint4*>(tb_ + (2 * KS + nt) * 1024);
-    };
-    // rows past M hold whatever the workspace held: make them zero queries
-#pragma unroll
-    for (int mt = 0; mt < R; ++mt) {
-      const uint32_t keep = rb * (R * 16) + mt * 16 + l16 < M ? 0xFFFFFFFFu : 0u;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        uint4 x = __builtin_bit_cast(uint4, qf[mt][ks]);
-        x.x &= keep;
-        x.y &= keep;
-        x.z &= keep;
-        x.w &= keep;
-        qf[mt][ks] = __builtin_bit_cast(bf16x8_t, x);
-      }
-    }
-    decode_entries(0);
-#pragma unroll
-    for (int k = 0; k < PD; ++k) gload(g[k], k);
-    lstore(g[0], 0);   // waits for tile 0 only
-    __syncthreads();
-    Tile t;
-    // Iteration n: request tile n + PD into the set tile n has just left, compute on tile n from
-    // LDS buffer n & 1, move tile n + 1 (requested PD - 1 iterations ago) from its registers into
-    // the other buffer, barrier.  The loop runs in groups of PD iterations so that set indices
-    // are constants; iterations past the last tile of a group only keep the barriers in step.
-    for (int n0 = 0; n0 < ntw; n0 += PD) {
-#pragma unroll
-      for (int k = 0; k < PD; ++k) {
-        const int n = n0 + k;
-        t.nv[0] = g[k].nv[0];
-        t.nv[1] = g[k].nv[1];
-        // page entries come in batches of TPR tiles, requested one iteration before they are decoded
-        if ((n + PD) % TPR == 0 && n + PD < ntw) decode_entries(n + PD);
-        if ((n + PD + 1) % TPR == 0) fetch_entries(n + PD + 1);
-        gload(g[k], n + PD);
-        if (has_rows && n < ntw) {
-          lread(t, n & 1);
-          compute_tile(t);
-        }
-        lstore(g[(k + 1) % PD], (n + 1) & 1);
-        __syncthreads();
-      }
-    }
-    if (!has_rows) return;
-  }
   Tile tb[NBUF];
-  if constexpr (!LDS_TILES) {
   decode_entries(0);
 #pragma unroll
   for (int k = 0; k < NBUF - 1; ++k) load_tile(tb[k], k, min(ntw, TPR));
@@ -726,14 +521,10 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
       }
     }
   }
-  }   // !LDS_TILES
 
-  // each lane summed its own tokens; rows are spread over the 4 lane groups (the half-precision
-  // form took whole-row sums from the matrix core: nothing to add up)
-  if constexpr (!F16V) {
+  // each lane summed its own tokens; rows are spread over the 4 lane groups
 #pragma unroll
-    for (int mt = 0; mt < R; ++mt) l_run[mt] = sum_over_lane_groups(l_run[mt]);
-  }
+  for (int mt = 0; mt < R; ++mt) l_run[mt] = sum_over_lane_groups(l_run[mt]);
 
   const size_t item = ((size_t)head * nchunk + chunk);
   if (SPLIT_PAGES) {
@@ -845,13 +636,12 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
   }
 }
 
-template <int D, int GP, int R, bool SPLIT_PAGES, int NBUF, int NWAVE = 4, bool LDS_TILES = false, bool F16V = false,
-          bool UNION = false>
-__global__ __launch_bounds__(64 * NWAVE) void attn_mfma_kernel(AttnPrepared prep, int nchunk, int nrbg, Shape sh, KvView kv,
+template <int D, int GP, int R, bool SPLIT_PAGES, int NBUF, bool UNION = false>
+__global__ __launch_bounds__(256) void attn_mfma_kernel(AttnPrepared prep, int nchunk, int nrbg, Shape sh, KvView kv,
                                                         Partials part, float scale_log2e, int m_lo, int m_hi,
                                                         UnionInKernel uni) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
-  attn_mfma_body<D, GP, R, SPLIT_PAGES, NBUF, NWAVE, LDS_TILES, F16V, UNION>(prep, nchunk, nrbg, sh, kv, part, scale_log2e,
+  attn_mfma_body<D, GP, R, SPLIT_PAGES, NBUF, UNION>(prep, nchunk, nrbg, sh, kv, part, scale_log2e,
                                                                             m_lo, m_hi, uni, lds);
 }
 
@@ -867,13 +657,13 @@ __global__ __launch_bounds__(256) void attn_mfma_rows_kernel(AttnPrepared prep, 
   const int M = __builtin_amdgcn_readfirstlane(prep.mrows[blockIdx.z * sh.Hkv + blockIdx.y]);
   if (M <= 0 || M > kUnionRows) return;
   if (M <= 16)
-    attn_mfma_body<D, GP, 1, true, 2, 4, false, false, true>(prep, nchunk, 1, sh, kv, part, scale_log2e, m_lo, m_hi, uni, lds);
+    attn_mfma_body<D, GP, 1, true, 2, true>(prep, nchunk, 1, sh, kv, part, scale_log2e, m_lo, m_hi, uni, lds);
   else if (M <= 32)
-    attn_mfma_body<D, GP, 2, true, 2, 4, false, false, true>(prep, nchunk, 1, sh, kv, part, scale_log2e, m_lo, m_hi, uni, lds);
+    attn_mfma_body<D, GP, 2, true, 2, true>(prep, nchunk, 1, sh, kv, part, scale_log2e, m_lo, m_hi, uni, lds);
   else if (M <= 48)
-    attn_mfma_body<D, GP, 3, true, 2, 4, false, false, true>(prep, nchunk, 1, sh, kv, part, scale_log2e, m_lo, m_hi, uni, lds);
+    attn_mfma_body<D, GP, 3, true, 2, true>(prep, nchunk, 1, sh, kv, part, scale_log2e, m_lo, m_hi, uni, lds);
   else
-    attn_mfma_body<D, GP, 4, true, 2, 4, false, false, true>(prep, nchunk, 1, sh, kv, part, scale_log2e, m_lo, m_hi, uni, lds);
+    attn_mfma_body<D, GP, 4, true, 2, true>(prep, nchunk, 1, sh, kv, part, scale_log2e, m_lo, m_hi, uni, lds);
 }
 
 // Builds the prepared inputs of attn_mfma_kernel when the selection kernel has not done so
@@ -937,29 +727,21 @@ hipError_t launch_attn_prepare(hipStream_t st, const KvView& kv, const Shape& sh
   return hipGetLastError();
 }
 
-// Bytes of LDS the shared-tile variant needs: two images of a 32-token tile (keys and values).
-template <int D, int GP>
-constexpr size_t shared_tile_lds_bytes() {
-  return 2 * (2 * 32 * D * 2);
-}
-
-template <int D, int GP, int R, bool SPLIT, int NWAVE = 4, bool LDS_TILES = false, bool F16V = false, bool UNION = false>
+template <int D, int GP, int R, bool SPLIT, bool UNION = false>
 static hipError_t launch_one(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnPrepared& prep,
                              int nchunk, const Partials& part, hipEvent_t ev_start, hipEvent_t ev_stop, int m_lo,
                              int m_hi, const UnionInKernel& uni = UnionInKernel{nullptr, nullptr}) {
-  static_assert(!(SPLIT && LDS_TILES) && (SPLIT ? NWAVE == 4 : true), "the split-pages combine is written for 4 wavefronts");
-  const int nrbg = SPLIT ? 1 : (sh.rows_max + R * 16 * NWAVE - 1) / (R * 16 * NWAVE);
+  const int nrbg = SPLIT ? 1 : (sh.rows_max + R * 64 - 1) / (R * 64);
   const size_t lds_bytes = SPLIT ? (4 * MergeSlot<D, R>::kFloats + (UNION ? kUnionShared : 0)) * sizeof(float)
-                                 : (LDS_TILES ? shared_tile_lds_bytes<D, GP>() : 0);
+                                 : 0;
   // Tile buffers per wavefront (one is being computed on, the others are in flight).  The sparse
   // shape wants exactly one tile of lookahead: with more, every wavefront has its whole share
   // of the list requested at once, the memory system completes those requests in no useful
   // order, and the first tile of every wavefront lands only near the end of the stream, so
   // nothing is left to overlap the arithmetic with (C1: 17.9 us with 3 tiles of lookahead,
   // 15.2 us with 1).  The dense shape has arithmetic to hide behind and keeps a deeper queue.
-  constexpr int NBUF = (SPLIT || LDS_TILES) ? 2 : ((D == 128 && R == 4) ? 3 : 4);
-  static_assert(!F16V || LDS_TILES, "the half-precision value product converts the tile while staging it");
-  auto kern = attn_mfma_kernel<D, GP, R, SPLIT, NBUF, NWAVE, LDS_TILES, F16V, UNION>;
+  constexpr int NBUF = SPLIT ? 2 : ((D == 128 && R == 4) ? 3 : 4);
+  auto kern = attn_mfma_kernel<D, GP, R, SPLIT, NBUF, UNION>;
   static bool attr_set = false;   // per instantiation
   if (lds_bytes > 48 * 1024 && !attr_set) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -970,19 +752,18 @@ static hipError_t launch_one(hipStream_t st, const KvView& kv, const Shape& sh, 
   const float scale_log2e = sh.sm_scale * 1.4426950408889634f;
   dim3 grid(nchunk, sh.Hkv * nrbg, batch);
   if (ev_start && ev_stop)   // events bound to this dispatch: they read the kernel's own begin and end
-    hipExtLaunchKernelGGL(kern, grid, dim3(64 * NWAVE), (uint32_t)lds_bytes, st, ev_start, ev_stop, 0, prep, nchunk,
+    hipExtLaunchKernelGGL(kern, grid, dim3(256), (uint32_t)lds_bytes, st, ev_start, ev_stop, 0, prep, nchunk,
                           nrbg, sh, kv, part, scale_log2e, m_lo, m_hi, uni);
   else
-    kern<<<grid, 64 * NWAVE, lds_bytes, st>>>(prep, nchunk, nrbg, sh, kv, part, scale_log2e, m_lo, m_hi, uni);
+    kern<<<grid, 256, lds_bytes, st>>>(prep, nchunk, nrbg, sh, kv, part, scale_log2e, m_lo, m_hi, uni);
   return hipGetLastError();
 }
 
-// Many rows (many_rows: ManyRowForm): 8 wavefronts of 32 rows sharing tiles through LDS, with the value
-// product in half precision or as a bfloat16 pair, or 4 independent wavefronts of 64 rows.
+// More than 64 rows: 4 independent wavefronts of 64 rows.
 template <int D, int GP>
 static hipError_t launch_dg(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnPrepared& prep,
                             int nchunk, int rows_upper, const Partials& part, hipEvent_t e0, hipEvent_t e1, int m_lo,
-                            int m_hi, const UnionInKernel* uni, int many_rows) {
+                            int m_hi, const UnionInKernel* uni) {
   if (uni && uni->rowmaps && uni->rows_on_device) {   // ... and takes every head's row-tile count from the device
     const size_t lds_bytes = (4 * MergeSlot<D, 4>::kFloats + kUnionShared) * sizeof(float);
     auto kern = attn_mfma_rows_kernel<D, GP>;
@@ -998,36 +779,29 @@ static hipError_t launch_dg(hipStream_t st, const KvView& kv, const Shape& sh, i
     return hipGetLastError();
   }
   if (uni && uni->rowmaps) {   // the kernel builds the union from the row bitmaps itself
-    if (rows_upper <= 16) return launch_one<D, GP, 1, true, 4, false, false, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi, *uni);
-    if (rows_upper <= 32) return launch_one<D, GP, 2, true, 4, false, false, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi, *uni);
-    if (rows_upper <= 48) return launch_one<D, GP, 3, true, 4, false, false, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi, *uni);
-    if (rows_upper <= 64) return launch_one<D, GP, 4, true, 4, false, false, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi, *uni);
+    if (rows_upper <= 16) return launch_one<D, GP, 1, true, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi, *uni);
+    if (rows_upper <= 32) return launch_one<D, GP, 2, true, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi, *uni);
+    if (rows_upper <= 48) return launch_one<D, GP, 3, true, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi, *uni);
+    if (rows_upper <= 64) return launch_one<D, GP, 4, true, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi, *uni);
     return hipErrorInvalidValue;
   }
   if (rows_upper <= 16) return launch_one<D, GP, 1, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi);
   if (rows_upper <= 32) return launch_one<D, GP, 2, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi);
   if (rows_upper <= 48) return launch_one<D, GP, 3, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi);
   if (rows_upper <= 64) return launch_one<D, GP, 4, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi);
-  // (16 rows per wavefront for up to 128 rows, so that all 8 wavefronts have work, was measured
-  // and is slower than 4 busy wavefronts of 32 rows: every wavefront reads the whole tile from
-  // LDS whatever its row count, so halving the rows halves the reuse of each operand read.)
-  if (many_rows == kManyRowsSharedHalf)
-    return launch_one<D, GP, 2, false, 8, true, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi);
-  if (many_rows == kManyRowsSharedPair)
-    return launch_one<D, GP, 2, false, 8, true, false>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi);
   return launch_one<D, GP, 4, false>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi);
 }
 
 hipError_t launch_attn_mfma(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnPrepared& prep,
                             int nchunk, int rows_upper, const Partials& part, hipEvent_t e0, hipEvent_t e1, int m_lo,
-                            int m_hi, const UnionInKernel* uni, int many_rows) {
+                            int m_hi, const UnionInKernel* uni) {
   if (batch <= 0 || nchunk <= 0) return hipSuccess;
   if (sh.d == 128) {
-    if (sh.g == 16) return launch_dg<128, 16>(st, kv, sh, batch, prep, nchunk, rows_upper, part, e0, e1, m_lo, m_hi, uni, many_rows);
-    return launch_dg<128, 32>(st, kv, sh, batch, prep, nchunk, rows_upper, part, e0, e1, m_lo, m_hi, uni, many_rows);
+    if (sh.g == 16) return launch_dg<128, 16>(st, kv, sh, batch, prep, nchunk, rows_upper, part, e0, e1, m_lo, m_hi, uni);
+    return launch_dg<128, 32>(st, kv, sh, batch, prep, nchunk, rows_upper, part, e0, e1, m_lo, m_hi, uni);
   }
-  if (sh.g == 16) return launch_dg<64, 16>(st, kv, sh, batch, prep, nchunk, rows_upper, part, e0, e1, m_lo, m_hi, uni, many_rows);
-  return launch_dg<64, 32>(st, kv, sh, batch, prep, nchunk, rows_upper, part, e0, e1, m_lo, m_hi, uni, many_rows);
+  if (sh.g == 16) return launch_dg<64, 16>(st, kv, sh, batch, prep, nchunk, rows_upper, part, e0, e1, m_lo, m_hi, uni);
+  return launch_dg<64, 32>(st, kv, sh, batch, prep, nchunk, rows_upper, part, e0, e1, m_lo, m_hi, uni);
 }
 
 }  // namespace losa

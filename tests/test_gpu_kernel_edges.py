@@ -1,0 +1,58 @@
+"""Kernels and dispatch branches at the sizes where they can go wrong - edges of tiles and of row groups,
+remainders, the smallest and largest of a range - each against the CPU oracle.  Tolerances are those of
+parity_util (2e-2 for bfloat16 inputs, 1e-4 for float inputs, sets exact up to verified near-ties)."""
+import numpy as np
+import pytest
+
+from oracle import losa_oracle as orc
+from paper_2604_12056_amd import binding as L
+from paper_2604_12056_amd import synth
+
+from parity_util import Rig, check_page_bounds, check_sparse_attn, run_steps_end_to_end
+
+pytestmark = pytest.mark.gpu
+
+
+def workload(B, G, Hkv, d, g, lens, n, topk=6, dtype="bf16", T=3):
+    return synth.config(0).replace(B=B, Hq=Hkv * G, Hkv=Hkv, d=d, g=g, batch=len(lens), seq_lens=tuple(lens), n_active=n,
+                                   topk_pages=topk, T=T, outliers="lognormal", dtype=dtype,
+                                   name=f"edge-B{B}-G{G}-d{d}-g{g}-{dtype}")
+
+
+@pytest.mark.parametrize("half_values", [1, 0])
+@pytest.mark.parametrize("B,G,d,g,n", [
+    (13, 5, 128, 16, 13),     # 65 rows: the smallest count the many-row kernel serves, three row wavefronts of 32
+    (32, 4, 128, 32, 32),     # 128 rows: the last count its two token groups serve
+    (43, 3, 128, 16, 43),     # 129 rows: the first with one token group, a last row wavefront of one row
+    (64, 4, 64, 32, 33),      # 132 of 256 rows active
+    (64, 4, 128, 32, 64),     # 256 rows: a full row group
+    (37, 7, 64, 16, 37)])     # 259 rows: a second row group of three rows
+def test_many_row_kernel_at_the_edges_of_its_row_counts(B, G, d, g, n, half_values):
+    """Stages of 64 tokens: prefixes one token around a stage, a page and a block of 32, one that leaves
+    whole workgroups without a stage, and page lists that end inside a stage."""
+    w = workload(B, G, 2, d, g, (63, 64, 65, 97, 64 * 9 + 1, 1500), n)
+    r = Rig(w, tuning={L.LOSA_TUNE_HALF_PRECISION_VALUES: half_values})
+    try:
+        check_page_bounds(r)
+        check_sparse_attn(r, 0, None, None, dense=True)
+        rng = np.random.Generator(np.random.Philox(B * G))
+        active = [np.sort(rng.permutation(B)[:n]).astype(np.int32) for _ in range(w.batch)]
+        lists = {(b, j): np.sort(rng.permutation(P)[:max(1, P - 1 - j)]).astype(np.int32)
+                 for b, P in enumerate(w.pages_per_seq) for j in range(w.Hkv)}
+        check_sparse_attn(r, 1, active, lists)
+        run_steps_end_to_end(r, range(2), orc.SEL_TOPK, float(n), w.topk_pages)
+        run_steps_end_to_end(r, [2], orc.SEL_MASS, 1.0, w.topk_pages)      # the count stays on the device
+    finally:
+        r.close()
+
+
+@pytest.mark.parametrize("workgroups", [8, 9, 12, 64, 1024])
+def test_merge_of_partials_laid_out_by_fragments(workgroups):
+    """Chunk counts around the line between the merge's two forms (up to 8 chunks, more), and more chunks than
+    one batch of a split workgroup's wavefronts holds."""
+    w = workload(32, 7, 1, 128, 16, (64 * 70 + 5,), 32)
+    r = Rig(w, tuning={L.LOSA_TUNE_ATTN_WORKGROUPS: workgroups})
+    try:
+        check_sparse_attn(r, 0, None, None, dense=True)
+    finally:
+        r.close()
