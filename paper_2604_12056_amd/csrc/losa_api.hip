@@ -99,6 +99,7 @@ namespace {
 
 constexpr long kTargetItems = 1024;       // most split-K work items a sparse step may be given
 constexpr long kTargetWorkgroups = 256;   // attention workgroups aimed at per launch: one per CU
+constexpr long kFloatGroups = 2;          // float-mode workgroups per bfloat16 attention workgroup aimed at: two fit a CU
 constexpr int kSparseRows = 64;           // query rows per KV head up to which the split-pages work shape is used
 
 thread_local char g_create_err[256] = "";
@@ -268,10 +269,10 @@ losa_status hip_fail(losa_ctx* ctx, const char* what, hipError_t e) {
 
 // Number of equal shares a (sequence, KV head) page list of at most `upper` pages is split into,
 // when every work item holds `part_stride` rows of partials and tiles hold `tile` tokens.
-int pick_nchunk(const losa_ctx* ctx, int batch, int upper, int row_groups, int part_stride, int tile) {
+int pick_nchunk(const losa_ctx* ctx, int batch, int upper, long target, int row_groups, int part_stride, int tile) {
   const long heads = (long)batch * ctx->sh.Hkv;
   const long tiles = (upper + (tile / ctx->sh.g) - 1) / (tile / ctx->sh.g);
-  long want = ctx->target_workgroups / (heads * row_groups);
+  long want = target / (heads * row_groups);
   const long fit = ctx->part_rows / (heads * part_stride);
   if (want > fit) want = fit;
   if (want > tiles) want = tiles;
@@ -365,7 +366,8 @@ losa_status sparse_attn_impl(losa_ctx* ctx, hipStream_t st, const KvView& kv, in
   // the two shapes to agree on the number of chunks, which they do up to 256 rows.
   const bool both_shapes = mfma && !hinted && ctx->sh.rows_max > 64 && ctx->sh.rows_max <= 256;
   // matrix-core kernel: up to 64 rows ride in one workgroup; more rows -> groups of 4 x 64 rows
-  const int row_groups = mfma ? (rows_upper <= 64 ? 1 : (ctx->sh.rows_max + 255) / 256) : (ctx->sh.rows_max + 31) / 32;
+  // (float mode: a workgroup per 16 rows)
+  const int row_groups = mfma ? (rows_upper <= 64 ? 1 : (ctx->sh.rows_max + 255) / 256) : (rows_upper + 15) / 16;
   // rows > 64 take the shared-stage kernel (unless switched off); it alone serves the launch when the host
   // knows that no head can have fewer, or when the two shapes do not go together
   const bool rows_kernel = mfma && ctx->shared_tiles && rows_upper > 64;
@@ -374,9 +376,13 @@ losa_status sparse_attn_impl(losa_ctx* ctx, hipStream_t st, const KvView& kv, in
   part.rows = hinted ? (rows_upper + 15) / 16 * 16 : ctx->sh.rows_max;
   if (part.rows > ctx->sh.rows_max) part.rows = ctx->sh.rows_max;
   if (rows_kernel) part.rows = (rows_upper + kPartialTile - 1) / kPartialTile * kPartialTile;
-  const int many_tile = rows_kernel ? kManyRowStage : 32;
-  const int few_tile = rows_kernel && !both_shapes ? kManyRowStage : 32;
-  const int nchunk = pick_nchunk(ctx, batch, upper, mfma ? row_groups : 1, part.rows, few_tile);
+  const int many_tile = !mfma ? ctx->sh.g : rows_kernel ? kManyRowStage : 32;
+  const int few_tile = !mfma ? ctx->sh.g : rows_kernel && !both_shapes ? kManyRowStage : 32;
+  int nchunk = pick_nchunk(ctx, batch, upper, ctx->target_workgroups * (mfma ? 1 : kFloatGroups), row_groups, part.rows,
+                           few_tile);
+  // float mode: workgroups of the same share and different row blocks are nchunk apart in the grid; a multiple of
+  // the die count (8) puts them on one die, so that its L2 serves all but the first
+  if (!mfma && nchunk >= 8) nchunk &= ~7;
   hipError_t e;
   // the dense step of the shared-stage kernel reads page table and queries where they are; everything else
   // that is not prepared yet goes through attn_prepare
@@ -389,8 +395,7 @@ losa_status sparse_attn_impl(losa_ctx* ctx, hipStream_t st, const KvView& kv, in
   {
     StageTimer timer(ctx, st, LOSA_STAGE_ATTN, /*bind_to_dispatch=*/mfma && !both_shapes);
     if (!mfma) {
-      e = launch_attn_generic(st, ctx->cfg.dtype, kv, ctx->sh, batch, q, active_idx, active_count, sel_pages,
-                              sel_count, cap, nchunk, part);
+      e = launch_attn_f32(st, kv, ctx->sh, batch, q, active_idx, active_count, sel_pages, sel_count, cap, nchunk, part);
     } else {
       // (events are bound to a dispatch only when it is the only one)
       const hipEvent_t e0 = both_shapes ? nullptr : timer.start(), e1 = both_shapes ? nullptr : timer.stop();

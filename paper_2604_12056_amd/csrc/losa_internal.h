@@ -123,13 +123,12 @@ hipError_t launch_select_pages(hipStream_t st, const KvView& kv, const Shape& sh
                                const AttnPrepared* prep, int rows_hint, long workgroups_per_round,
                                bool bitmaps_only = false);
 
-// ---- sparse_attn.hip (element-generic kernel, merge) and sparse_attn_mfma.hip (bfloat16 matrix-core kernel)
-// Both deal the 32-token tiles of a (sequence, KV head) page list round-robin to `nchunk` work items.
-// launch_attn_merge: prep != NULL means the partials came from the matrix-core kernel.
-hipError_t launch_attn_generic(hipStream_t st, int dtype, const KvView& kv, const Shape& sh, int batch,
-                               const void* q, const int32_t* active_idx, const int32_t* active_count,
-                               const int32_t* sel_pages, const int32_t* sel_count, int cap, int nchunk,
-                               const Partials& part);
+// ---- sparse_attn.hip (float mode, merge) and sparse_attn_mfma.hip (bfloat16)
+// Tiles of a (sequence, KV head) page list are dealt round-robin to `nchunk` work items: tiles of 32 tokens
+// (bfloat16), single pages (float mode).  launch_attn_merge: prep != NULL means bfloat16 partials.
+hipError_t launch_attn_f32(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const void* q,
+                           const int32_t* active_idx, const int32_t* active_count, const int32_t* sel_pages,
+                           const int32_t* sel_count, int cap, int nchunk, const Partials& part);
 hipError_t launch_attn_prepare(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const void* q,
                                const int32_t* active_idx, const int32_t* active_count, const int32_t* sel_pages,
                                const int32_t* sel_count, int cap, const AttnPrepared& prep);

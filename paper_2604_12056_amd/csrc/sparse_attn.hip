@@ -1,16 +1,29 @@
-// Paged sparse prefix attention for the active queries, split over page chunks
+// Paged sparse prefix attention in float mode, and the merge of split-K partials that all attention kernels share
 // (paper: Preliminaries, Attention Decomposition With Online Softmax; Methodology, eq. update_rule).
 //
-// Work item = (sequence b, KV head j, block of query rows, chunk of the KV head's page list).
-// Each item keeps a running (max, sum, un-normalised output) per row and writes it as a
-// partial; attn_merge combines the chunks of a row in chunk order with the same
-// log-sum-exp rule the paper uses to merge prefix and block parts, normalises, and writes
-// (o_p, lse_p) at the active token's row.  No float atomics anywhere: results do not
-// depend on scheduling.
+// Float mode accumulates in float64: with outlier channels |q.k| reaches hundreds, and float summation alone
+// would come within reach of the mode's 1e-4 bound.  Both contractions run on the float64 matrix
+// instructions (v_mfma_f64_16x16x4_f64).  A workgroup takes 16 query rows of a KV head and a share of its page
+// list; its four wavefronts deal the pages of the share out, 16 tokens at a time, and combine their states
+// through LDS at the end (two workgroups per CU: one wavefront's exponentials run under another's products):
 //
-// This file holds the float-mode kernel (vector ALUs, K/V tiles staged in LDS, float64
-// accumulation) and the merge kernel both precisions share; bfloat16 inputs always take the
-// matrix-core kernel.
+//   S^T = K . Q^T        A operand: key rows, B operand: the queries, both widened from float as they are used
+//   O^T += V^T . P^T     A operand: channel-major values, B operand: the numerators, as S^T leaves them
+//
+// A result holds, per lane, rows 4*r + lane/16 (r = 0..3) of column lane % 16.  Key row m is token
+// 4*(m%4) + m/4 of the 16, so that lane group qd ends up with tokens 4*qd .. 4*qd+3, one per register: k-step r
+// of the second product then takes register r of S^T and element r of a 16-byte piece of 4 consecutive
+// tokens of a value channel.  Channels of O are dealt the same way, so that a lane stores 16 bytes.
+// Keys of the next 16 tokens are requested when the score products of the current ones have been issued, values
+// when the value products have: one register set each, and the latency lies under the other half.
+//
+// What bounds it: the float64 products; a register-only loop of them reaches 69 TFLOP/s, and the
+// wavefronts' own start and end.  42 rows x 4 KV heads over 0.9 of 8001 tokens: 25 us (10 of them products;
+// 108 us on the vector ALUs with keys and values staged through LDS).
+//
+// attn_merge combines the chunks of a row in chunk order with the log-sum-exp rule the paper uses to merge
+// prefix and block parts, normalises, and writes (o_p, lse_p) at the active token's row.  No float atomics
+// anywhere: results do not depend on scheduling.
 #include <math.h>
 
 #include <type_traits>
@@ -20,173 +33,194 @@
 
 namespace losa {
 
-constexpr int kRowBlock = 32;  // query rows per work item (generic kernel)
-constexpr int kTileTok = 32;   // tokens per LDS tile
+constexpr int kFloatRows = 16;   // query rows per workgroup
+constexpr float kLag = 16.0f;    // natural-log units
+typedef __attribute__((ext_vector_type(4))) double f64x4_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4v_t;
 
-// Accumulation type of the generic kernel.  bfloat16 inputs: float (products are exact, the
-// 2e-2 bound is far away).  float inputs: double, because the float mode's 1e-4 bound is
-// within reach of float summation error once outlier channels push |q.k| into the hundreds.
-template <typename T> struct AccOf { typedef float type; };
-template <> struct AccOf<float> { typedef double type; };
-
-template <typename T, int D, int GP>
-__global__ __launch_bounds__(256) void attn_partials_generic_kernel(
-    KvView kv, Shape sh, const T* __restrict__ q, const int32_t* __restrict__ active_idx,
-    const int32_t* __restrict__ active_count, const int32_t* __restrict__ sel_pages,
-    const int32_t* __restrict__ sel_count, int cap, int nchunk, int nrb, Partials part) {
-  constexpr int V = Vec16<T>::n;
-  constexpr int VPR = D / V;           // 16-byte vectors per key row
-  constexpr int PPT = kTileTok / GP;   // pages per tile
-  constexpr int VPC = GP / V;          // 16-byte vectors per value channel row of a page
-  constexpr int CPT = D / 8;           // output channels per thread
-  __shared__ float qs[kRowBlock][D + 1];
-  __shared__ float ks[kTileTok][D + 1];
-  __shared__ float vs[kTileTok][D + 1];
-  __shared__ typename AccOf<T>::type ps[kRowBlock][kTileTok + 1];
-  __shared__ int tok_ok[kTileTok];
-
-  const int chunk = blockIdx.x, j = blockIdx.y / nrb, rb = blockIdx.y % nrb, b = blockIdx.z, tid = threadIdx.x;
-  const int n = active_idx ? min(active_count[b], sh.B) : sh.B;
-  const int M = min(n * sh.G, part.rows), r0 = rb * kRowBlock;
+template <int D, int GP>
+__global__ __launch_bounds__(256, 2) void attn_f32_kernel(KvView kv, Shape sh, const float* __restrict__ q,
+                                                      const int32_t* __restrict__ active_idx,
+                                                      const int32_t* __restrict__ active_count,
+                                                      const int32_t* __restrict__ sel_pages,
+                                                      const int32_t* __restrict__ sel_count, int cap, int nchunk, int row_blocks,
+                                                      Partials part) {
+  constexpr int NC = D / 16;    // 16-channel groups: pieces of keys and of values per lane and 16 tokens
+  constexpr int SUB = GP / 16;  // 16-token tiles per page
+  extern __shared__ __attribute__((aligned(16))) double fsm[];
+  double* so = fsm;                                                    // [4][NC][4][64]: O of every wavefront
+  double* sl = so + 4 * NC * 4 * 64;                                   // [4][16]
+  float* sm = reinterpret_cast<float*>(sl + 4 * 16);                   // [4][16]
+  float* sq = sm + 4 * 16;                                             // [NC][64][4]: query pieces in operand order
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, qd = lane >> 4;
+  const int chunk = blockIdx.x, j = blockIdx.y / row_blocks, b = blockIdx.z;
+  const int r0 = blockIdx.y % row_blocks * kFloatRows;
+  const int32_t* list = sel_pages ? sel_pages + ((size_t)b * sh.Hkv + j) * cap : nullptr;
+  // (the first list entries travel with the counts they are checked against)
+  auto list_position = [&](int first) { return chunk + (long)((first + lane) * 4 + wave) * nchunk; };
+  int first_logical = (int)min(list_position(0), (long)0x7fffffff);
+  if (list) first_logical = list_position(0) < cap ? list[list_position(0)] : -1;
+  const int n_act = active_idx ? min(active_count[b], sh.B) : sh.B;
+  const int M = min(n_act * sh.G, part.rows);
   if (r0 >= M) return;
   const int base = kv.page_indptr[b];
   const int P = seq_pages(kv, sh, b);
   const int L = kv.seq_lens[b];
-  const int32_t* list = sel_pages ? sel_pages + ((size_t)b * sh.Hkv + j) * cap : nullptr;
   const int U = list ? min(sel_count[b * sh.Hkv + j], cap) : P;
-  const int ntiles = (U + PPT - 1) / PPT;
-  if (chunk >= ntiles) return;   // tiles are dealt round-robin: chunk, chunk + nchunk, ...
-  const int c1 = U;
+  if (chunk >= U) return;   // pages are dealt round-robin: chunk, chunk + nchunk, ...
+  // ... and this wavefront's are the wave-th, (wave + 4)-th, ... of those
+  const int npages = max(0, ((U - 1 - chunk) / nchunk + 1 - wave + 3) / 4);
 
-  for (int v = tid; v < kRowBlock * VPR; v += 256) {
-    const int rr = v / VPR, cv = v % VPR, r = r0 + rr;
-    float f[V];
+  // queries of row r0 + l16 (zero past M), channels 16*c + 4*qd .., shared by the wavefronts through LDS
+  // (in registers they would cost the second wavefront per SIMD)
+  {
+    const int r = r0 + l16;
+    const int tok = r < M ? (active_idx ? active_idx[(size_t)b * sh.B + r / sh.G] : r / sh.G) : -1;
+    const bool ok = (unsigned)tok < (unsigned)sh.B;
+    const float* row = q + (((size_t)b * sh.B + (ok ? tok : 0)) * sh.Hq + j * sh.G + r % sh.G) * D + 4 * qd;
+    const f32x4v_t zero = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int e = 0; e < V; ++e) f[e] = 0.f;
-    if (r < M) {
-      const int a = r / sh.G, hg = r % sh.G;
-      const int tok = active_idx ? active_idx[(size_t)b * sh.B + a] : a;
-      if ((unsigned)tok < (unsigned)sh.B) {
-        const uint4 raw = reinterpret_cast<const uint4*>(q + (((size_t)b * sh.B + tok) * sh.Hq + j * sh.G + hg) * D)[cv];
-        widen16(raw, f, T());
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < V; ++e) qs[rr][cv * V + e] = f[e];
+    for (int c = 0; c < NC / 4; ++c)
+      *reinterpret_cast<f32x4v_t*>(sq + ((wave * (NC / 4) + c) * 64 + lane) * 4) =
+          ok ? *reinterpret_cast<const f32x4v_t*>(row + 16 * (wave * (NC / 4) + c)) : zero;
   }
 
-  typedef typename AccOf<T>::type Acc;
-  const int row = tid / 8, sub = tid % 8;
-  float m = -INFINITY;   // running reference point of the exponentials (any value near the max works)
-  Acc l = 0, acc[CPT];
-#pragma unroll
-  for (int k = 0; k < CPT; ++k) acc[k] = 0;
+  // pages of this workgroup, 64 at a time: lane i resolves page i (physical id, valid tokens)
+  int pg_phys = 0, pg_valid = 0;
+  auto resolve = [&](int first) {
+    const long lp = list_position(first);
+    pg_phys = 0;
+    pg_valid = 0;
+    if (lp < U) {
+      const int logical = first == 0 ? first_logical : list ? list[lp] : (int)lp;
+      if ((unsigned)logical < (unsigned)P) {
+        const int ph = kv.page_indices[base + logical];
+        if ((unsigned)ph < (unsigned)kv.num_pages) {
+          pg_phys = ph;
+          pg_valid = max(0, min(GP, L - logical * GP));
+        }
+      }
+    }
+  };
+  resolve(0);
 
-  for (int tile = chunk; tile < ntiles; tile += nchunk) {
-    const int pp = tile * PPT;
-    __syncthreads();
-    // ---- stage one tile of keys (token-major pages) and values (channel-major pages)
-    for (int v = tid; v < kTileTok * VPR; v += 256) {
-      const int ts = v / VPR, cv = v % VPR;
-      const int lp = pp + ts / GP, tin = ts % GP;
-      float f[V];
+  const int turn = 4 * (l16 & 3) + (l16 >> 2);   // token / channel this lane's operand row stands for (of 16)
+  f32x4v_t kf[NC], vf[NC];
+  auto load_keys = [&](int ph, int sub) {
+    const float* src = (const float*)kv.k_pages + (((size_t)ph * sh.Hkv + j) * GP + 16 * sub + turn) * D + 4 * qd;
 #pragma unroll
-      for (int e = 0; e < V; ++e) f[e] = 0.f;
-      int ok = 0;
-      if (lp < c1) {
-        const int logical = list ? list[lp] : lp;
-        if ((unsigned)logical < (unsigned)P && logical * GP + tin < L) {
-          const int phys = kv.page_indices[base + logical];
-          if ((unsigned)phys < (unsigned)kv.num_pages) {
-            ok = 1;
-            const uint4 raw = reinterpret_cast<const uint4*>((const T*)kv.k_pages + (((size_t)phys * sh.Hkv + j) * GP + tin) * D)[cv];
-            widen16(raw, f, T());
-          }
-        }
-      }
-      if (cv == 0) tok_ok[ts] = ok;
+    for (int c = 0; c < NC; ++c) kf[c] = *reinterpret_cast<const f32x4v_t*>(src + 16 * c);
+  };
+  auto load_values = [&](int ph, int sub) {
+    const float* src = (const float*)kv.v_pages + (((size_t)ph * sh.Hkv + j) * D + turn) * GP + 16 * sub + 4 * qd;
 #pragma unroll
-      for (int e = 0; e < V; ++e) ks[ts][cv * V + e] = f[e];
+    for (int c = 0; c < NC; ++c) vf[c] = *reinterpret_cast<const f32x4v_t*>(src + (size_t)16 * c * GP);
+  };
+  const int ntiles = npages * SUB;
+  auto tile_phys = [&](int t) { return __builtin_amdgcn_readlane(pg_phys, (t / SUB) & 63); };
+
+  float m = -INFINITY;   // running reference of the exponentials of row l16 (any value near the maximum works)
+  double l = 0.0;        // sum over this lane's own tokens
+  f64x4_t o[NC];
+#pragma unroll
+  for (int c = 0; c < NC; ++c) o[c] = (f64x4_t){0.0, 0.0, 0.0, 0.0};
+  load_keys(tile_phys(0), 0);
+  load_values(tile_phys(0), 0);
+  __syncthreads();
+  for (int t = 0; t < ntiles; ++t) {
+    const int nv = __builtin_amdgcn_readlane(pg_valid, (t / SUB) & 63) - 16 * (t % SUB);   // valid tokens of this tile (may be <= 0 or > 16)
+    f64x4_t sc = {0.0, 0.0, 0.0, 0.0};   // (dependent float64 products issue back to back: one sum is enough)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const f32x4v_t qf = *reinterpret_cast<const f32x4v_t*>(sq + (c * 64 + lane) * 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        sc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)kf[c][e], (double)qf[e], sc, 0, 0, 0);
     }
-    for (int v = tid; v < PPT * D * VPC; v += 256) {
-      const int pgi = v / (D * VPC), rem = v % (D * VPC), c = rem / VPC, tv = rem % VPC;
-      const int lp = pp + pgi;
-      float f[V];
-#pragma unroll
-      for (int e = 0; e < V; ++e) f[e] = 0.f;
-      int logical = -1;
-      if (lp < c1) {
-        logical = list ? list[lp] : lp;
-        if ((unsigned)logical < (unsigned)P) {
-          const int phys = kv.page_indices[base + logical];
-          if ((unsigned)phys < (unsigned)kv.num_pages) {
-            const uint4 raw = reinterpret_cast<const uint4*>((const T*)kv.v_pages + (((size_t)phys * sh.Hkv + j) * D + c) * GP)[tv];
-            widen16(raw, f, T());
-          } else {
-            logical = -1;
-          }
-        } else {
-          logical = -1;
-        }
-      }
-#pragma unroll
-      for (int e = 0; e < V; ++e) {
-        const int tin = tv * V + e;
-        const bool ok = logical >= 0 && logical * GP + tin < L;
-        vs[pgi * GP + tin][c] = ok ? f[e] : 0.f;   // slots past the sequence end may hold NaN
-      }
-    }
-    __syncthreads();
-    // ---- scores of this thread's row against 4 tokens
-    Acc s[4];
+    // the page batch is exhausted: the next tile's pages have to be resolved before it can be requested
+    const int tn = t + 1;
+    const bool more = tn < ntiles;
+    if (more && tn % (64 * SUB) == 0) resolve(tn / SUB);
+    const int ph_next = more ? tile_phys(tn) : 0;
+    if (more) load_keys(ph_next, tn % SUB);
+    double s[4];
     float tmax = -INFINITY;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const int ts = sub + 8 * k;
-      Acc dot = 0;
-#pragma unroll 8
-      for (int c = 0; c < D; ++c) dot += (Acc)qs[row][c] * (Acc)ks[ts][c];
-      s[k] = tok_ok[ts] ? dot * (Acc)sh.sm_scale : (Acc)-INFINITY;
-      tmax = fmaxf(tmax, (float)s[k]);
+    for (int e = 0; e < 4; ++e) {
+      s[e] = 4 * qd + e < nv ? sc[e] * (double)sh.sm_scale : -INFINITY;
+      tmax = fmaxf(tmax, (float)s[e]);
     }
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 1, 64));
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 2, 64));
-    tmax = fmaxf(tmax, __shfl_xor(tmax, 4, 64));
-    const float m_new = fmaxf(m, tmax);
-    const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-    const Acc alpha = exp_acc((Acc)m - (Acc)m_use);
-    Acc psum = 0;
+    tmax = __uint_as_float(across_rows(__float_as_uint(tmax), [](uint32_t x, uint32_t y) {
+      return __float_as_uint(fmaxf(__uint_as_float(x), __uint_as_float(y)));
+    }));
+    // the reference lags the maximum by up to kLag (e^16 is nothing to float64 sums and harmless to the float
+    // partials), so after the first tile it hardly ever moves
+    if (__any(tmax > m + kLag)) {
+      const float m_new = fmaxf(m, tmax);
+      const double alpha = m == -INFINITY ? 0.0 : exp((double)m - (double)m_new);
+      m = m_new;
+      l *= alpha;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      const Acc p = exp_acc(s[k] - (Acc)m_use);
-      ps[row][sub + 8 * k] = p;
-      psum += p;
+      for (int c = 0; c < NC; ++c) o[c] *= alpha;
     }
-    psum += __shfl_xor(psum, 1, 64);
-    psum += __shfl_xor(psum, 2, 64);
-    psum += __shfl_xor(psum, 4, 64);
-    l = l * alpha + psum;
-    m = m_new;
-    __syncthreads();
-    // ---- output channels sub, sub+8, ... of this thread's row
+    const double m_use = m == -INFINITY ? 0.0 : (double)m;
+    double p[4];
 #pragma unroll
-    for (int k = 0; k < CPT; ++k) {
-      Acc a = acc[k] * alpha;
-#pragma unroll 8
-      for (int ts = 0; ts < kTileTok; ++ts) a += (Acc)ps[row][ts] * (Acc)vs[ts][sub + 8 * k];
-      acc[k] = a;
+    for (int e = 0; e < 4; ++e) {
+      p[e] = exp(s[e] - m_use);
+      l += p[e];
     }
+    if (nv < 16) {   // slots past the end of the sequence may hold NaN
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) vf[c][e] = 4 * qd + e < nv ? vf[c][e] : 0.f;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) o[c] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)vf[c][e], p[e], o[c], 0, 0, 0);
+    if (more) load_values(ph_next, tn % SUB);
   }
-  const int r = r0 + row;
-  if (r < M) {
-    const size_t item = ((size_t)b * sh.Hkv + j) * nchunk + chunk;
-    const size_t prow = item * part.rows + r;
+  // the row's tokens lie in the four lane groups
+  l += __shfl_xor(l, 16, 64);
+  l += __shfl_xor(l, 32, 64);
+  // ---- the four wavefronts' states meet in LDS; wavefront w combines and stores the w-th quarter of the channels
 #pragma unroll
-    for (int k = 0; k < CPT; ++k) part.o[prow * D + sub + 8 * k] = (float)acc[k];
-    if (sub == 0) {
-      part.m[prow] = m;
-      part.l[prow] = (float)l;
-    }
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) so[((wave * NC + c) * 4 + e) * 64 + lane] = o[c][e];
+  if (qd == 0) {
+    sm[wave * 16 + l16] = m;
+    sl[wave * 16 + l16] = l;
+  }
+  __syncthreads();
+  const int r = r0 + l16;
+  if (r >= M) return;
+  float m_all = sm[l16];
+#pragma unroll
+  for (int w = 1; w < 4; ++w) m_all = fmaxf(m_all, sm[w * 16 + l16]);
+  double wgt[4], l_all = 0.0;
+#pragma unroll
+  for (int w = 0; w < 4; ++w) {
+    const float mw = sm[w * 16 + l16];
+    wgt[w] = mw == -INFINITY ? 0.0 : exp((double)mw - (double)m_all);
+    l_all += wgt[w] * sl[w * 16 + l16];
+  }
+  const size_t prow = (((size_t)b * sh.Hkv + j) * nchunk + chunk) * part.rows + r;
+#pragma unroll
+  for (int c0 = 0; c0 < NC / 4; ++c0) {
+    const int c = wave * (NC / 4) + c0;
+    double x[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int w = 0; w < 4; ++w)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) x[e] += wgt[w] * so[((w * NC + c) * 4 + e) * 64 + lane];
+    *reinterpret_cast<f32x4v_t*>(part.o + prow * D + 16 * c + 4 * qd) = (f32x4v_t){(float)x[0], (float)x[1], (float)x[2], (float)x[3]};
+  }
+  if (wave == 0 && qd == 0) {
+    part.m[prow] = m_all;
+    part.l[prow] = (float)l_all;
   }
 }
 
@@ -420,30 +454,32 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(KvView kv, Shape sh, co
   }
 }
 
-template <typename T, int D>
-static hipError_t launch_generic(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const void* q,
-                                 const int32_t* active_idx, const int32_t* active_count, const int32_t* sel_pages,
-                                 const int32_t* sel_count, int cap, int nchunk, const Partials& part) {
-  const int nrb = (sh.rows_max + kRowBlock - 1) / kRowBlock;
-  dim3 grid(nchunk, sh.Hkv * nrb, batch);
-  if (sh.g == 16)
-    attn_partials_generic_kernel<T, D, 16><<<grid, 256, 0, st>>>(kv, sh, (const T*)q, active_idx, active_count,
-                                                                 sel_pages, sel_count, cap, nchunk, nrb, part);
-  else
-    attn_partials_generic_kernel<T, D, 32><<<grid, 256, 0, st>>>(kv, sh, (const T*)q, active_idx, active_count,
-                                                                 sel_pages, sel_count, cap, nchunk, nrb, part);
+template <int D, int GP>
+static hipError_t launch_f32(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const float* q,
+                             const int32_t* active_idx, const int32_t* active_count, const int32_t* sel_pages,
+                             const int32_t* sel_count, int cap, int nchunk, const Partials& part) {
+  constexpr size_t lds_bytes = 4 * (D / 16) * 4 * 64 * sizeof(double) + 4 * 16 * (sizeof(double) + sizeof(float)) + 16 * D * sizeof(float);
+  const int row_blocks = (part.rows + kFloatRows - 1) / kFloatRows;
+  auto kern = attn_f32_kernel<D, GP>;
+  static bool attr_set = false;   // per instantiation
+  if (lds_bytes > 48 * 1024 && !attr_set) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)lds_bytes);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  kern<<<dim3(nchunk, sh.Hkv * row_blocks, batch), 256, lds_bytes, st>>>(kv, sh, q, active_idx, active_count, sel_pages,
+                                                                         sel_count, cap, nchunk, row_blocks, part);
   return hipGetLastError();
 }
 
-hipError_t launch_attn_generic(hipStream_t st, int dtype, const KvView& kv, const Shape& sh, int batch, const void* q,
-                               const int32_t* active_idx, const int32_t* active_count, const int32_t* sel_pages,
-                               const int32_t* sel_count, int cap, int nchunk, const Partials& part) {
+hipError_t launch_attn_f32(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const void* q,
+                           const int32_t* active_idx, const int32_t* active_count, const int32_t* sel_pages,
+                           const int32_t* sel_count, int cap, int nchunk, const Partials& part) {
   if (batch <= 0 || nchunk <= 0) return hipSuccess;
-  if (dtype != LOSA_F32) return hipErrorInvalidValue;   // bfloat16 takes the matrix-core kernel
-  return sh.d == 128 ? launch_generic<float, 128>(st, kv, sh, batch, q, active_idx, active_count, sel_pages, sel_count,
-                                                  cap, nchunk, part)
-                     : launch_generic<float, 64>(st, kv, sh, batch, q, active_idx, active_count, sel_pages, sel_count,
-                                                 cap, nchunk, part);
+  auto launch = sh.d == 128 ? (sh.g == 16 ? launch_f32<128, 16> : launch_f32<128, 32>)
+                            : (sh.g == 16 ? launch_f32<64, 16> : launch_f32<64, 32>);
+  return launch(st, kv, sh, batch, (const float*)q, active_idx, active_count, sel_pages, sel_count, cap, nchunk, part);
 }
 
 hipError_t launch_attn_merge(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const int32_t* active_idx,

@@ -56,3 +56,23 @@ def test_merge_of_partials_laid_out_by_fragments(workgroups):
         check_sparse_attn(r, 0, None, None, dense=True)
     finally:
         r.close()
+
+
+@pytest.mark.parametrize("B,G,d,g,n,workgroups", [
+    (8, 5, 128, 16, 3, 256),     # 15 rows: one short of a row block
+    (8, 2, 64, 32, 8, 256),      # 16 rows, pages of two 16-token tiles
+    (17, 1, 128, 32, 17, 7),     # 17 rows: a second row block of one row, a few shares
+    (32, 7, 64, 16, 7, 1024),    # 49 rows, more shares than pages in the short prefixes
+    (9, 13, 64, 16, 5, 256),     # 65 rows: the scoring kernel's second chunk of rows is one row
+    (8, 4, 128, 16, 4, 1)])      # one share: more than 64 pages per wavefront, a second batch of page entries
+def test_float_mode_at_the_edges_of_rows_pages_and_shares(B, G, d, g, n, workgroups):
+    """Prefixes around a 16-token tile, a page, the scoring kernel's 8 pages and the share count."""
+    w = workload(B, G, 1, d, g, (1, 15, 17, 33, 8 * g + 1, 4900), n, dtype="f32")
+    r = Rig(w, tuning={L.LOSA_TUNE_ATTN_WORKGROUPS: workgroups})
+    try:
+        check_page_bounds(r)
+        run_steps_end_to_end(r, range(w.T), orc.SEL_TOPK, float(n), w.topk_pages)
+        check_sparse_attn(r, 1, [r.inp.picked[1, b] for b in range(w.batch)],
+                          {(b, 0): np.arange(0, P, 2, dtype=np.int32) for b, P in enumerate(w.pages_per_seq)})
+    finally:
+        r.close()
