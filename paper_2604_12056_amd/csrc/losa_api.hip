@@ -72,6 +72,7 @@ struct losa_ctx {
   int32_t* active_count;
   float* scores;
   uint32_t* rowmaps;
+  uint32_t* union_bits;
   int32_t* tickets;
   int32_t* seq_tickets;   // [max_batch], kept at zero between launches
   bool seq_tickets_clean = false;
@@ -167,7 +168,7 @@ struct Carve {
 };
 
 struct Layout {
-  size_t delta, mask, active_idx, active_count, scores, rowmaps, tickets, sel_pages, sel_count, po, pm, pl;
+  size_t delta, mask, active_idx, active_count, scores, rowmaps, union_bits, tickets, sel_pages, sel_count, po, pm, pl;
   size_t entries, q_act, ucount, mrows, seq_tickets, total;
   long part_rows;   // capacity of the split-K partial buffers, in (work item, query row) pairs
 };
@@ -194,7 +195,8 @@ Layout make_layout(const losa_config* c) {
   L.active_idx = cv.take(rows * 4);
   L.active_count = cv.take((size_t)c->max_batch * 4);
   L.scores = cv.take(heads * rows_max * c->max_pages_per_seq * 4);
-  L.rowmaps = cv.take(heads * (rows_max > (size_t)kUnionRows ? rows_max : (size_t)kUnionRows) * words * 4);   // row-major [rows_max] or word-major [kUnionRows] per word
+  L.rowmaps = cv.take(heads * rows_max * words * 4);
+  L.union_bits = cv.take(heads * (size_t)union_words(c->max_pages_per_seq) * 4);
   L.tickets = cv.take(heads * 4);
   L.sel_pages = cv.take(heads * c->max_pages_per_seq * 4);
   L.sel_count = cv.take(heads * 4);
@@ -334,19 +336,19 @@ losa_status select_active_impl(losa_ctx* ctx, hipStream_t st, int batch, const v
 losa_status score_pages_impl(losa_ctx* ctx, hipStream_t st, const KvView& kv, int batch, int max_seq_pages,
                              const void* q, const int32_t* active_idx, const int32_t* active_count, int topk,
                              int32_t* topk_out, int32_t* sel_pages, int32_t* sel_count, int cap, bool prepare_attn,
-                             int rows_upper, const InKernelRanking* ranking = nullptr, bool bitmaps_only = false) {
+                             int rows_upper, const InKernelRanking* ranking = nullptr, uint32_t* union_bits = nullptr) {
   const AttnPrepared* prep = prepare_attn ? &ctx->prep : nullptr;
   hipError_t e;
   {
     StageTimer timer(ctx, st, LOSA_STAGE_SCORE);
     e = launch_page_scores(st, ctx->cfg.dtype, kv, ctx->sh, batch, max_seq_pages, q, active_idx, active_count,
-                           ctx->scores, ctx->tickets, sel_count, prep, ranking, ctx->score_round);
+                           ctx->scores, ctx->tickets, sel_count, prep, ranking, ctx->score_round, union_bits);
   }
   if (e != hipSuccess) return hip_fail(ctx, "page_scores launch", e);
   StageTimer timer(ctx, st, LOSA_STAGE_TOPK);
   e = launch_select_pages(st, kv, ctx->sh, batch, max_seq_pages, q, active_idx, active_count, ctx->scores, topk,
                           topk_out, sel_pages, sel_count, cap, ctx->rowmaps, ctx->tickets, prep, rows_upper,
-                          ctx->select_round, bitmaps_only);
+                          ctx->select_round, union_bits);
   if (e != hipSuccess) return hip_fail(ctx, "select_pages launch", e);
   return LOSA_OK;
 }
@@ -462,6 +464,7 @@ losa_status losa_create(const losa_config* cfg, void* workspace, size_t workspac
   ctx->active_count = (int32_t*)(base + L.active_count);
   ctx->scores = (float*)(base + L.scores);
   ctx->rowmaps = (uint32_t*)(base + L.rowmaps);
+  ctx->union_bits = (uint32_t*)(base + L.union_bits);
   ctx->tickets = (int32_t*)(base + L.tickets);
   ctx->sel_pages = (int32_t*)(base + L.sel_pages);
   ctx->sel_count = (int32_t*)(base + L.sel_count);
@@ -738,10 +741,10 @@ losa_status losa_step(losa_ctx* ctx, void* stream, const losa_kv* kv, int32_t st
   const bool union_counted = fuse_prepare && counted && rows_upper >= 1 && rows_upper <= 64 && ctx->union_in_attention;
   const bool union_on_device = fuse_prepare && !counted && ctx->sh.rows_max <= 256 && ctx->union_in_attention;
   const bool union_in_attn = union_counted || union_on_device;
-  const UnionInKernel uni{ctx->rowmaps, sc, union_on_device};
+  const UnionInKernel uni{ctx->union_bits, sc, union_on_device};
   s = score_pages_impl(ctx, st, view, kv->batch, msp, q, ctx->active_idx, ctx->active_count, topk_pages, nullptr,
                        ctx->sel_pages, sc, cap, fuse_prepare, rows_upper, rank_in_scores ? &ranking : nullptr,
-                       union_in_attn);
+                       union_in_attn ? ctx->union_bits : nullptr);
   if (s != LOSA_OK) return s;
   return sparse_attn_impl(ctx, st, view, kv->batch, msp, q, ctx->active_idx, ctx->active_count, ctx->sel_pages, sc,
                           cap, rows_upper, fuse_prepare, (float*)o_p, lse_p, union_in_attn ? &uni : nullptr);

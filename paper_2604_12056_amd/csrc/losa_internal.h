@@ -55,26 +55,21 @@ struct AttnPrepared {
   int32_t* mrows;     // [heads] query rows (|A| * G)
 };
 // The other way the matrix-core kernel can get its page list (sparse steps of losa_step with at
-// most 64 query rows per KV head): the selection kernel leaves only the per-row pick bitmaps, and
-// every attention workgroup ORs them, ranks the union and resolves its own pages itself while it
+// most 64 query rows per KV head): the selection workgroups OR their row's picks into one bitmap per
+// head, and every attention workgroup ranks that union and resolves its own pages itself while it
 // starts up.  That takes the selection kernel's serial tail (bitmap hand-over to one workgroup per
 // head, union, list) out of the chain of launches.  When the host does not know the row count
 // (threshold / cumulative-mass selection) the selection kernel decides per (sequence, KV head),
 // by the count it finds, which of the two forms it leaves, and the attention launch takes each
 // head's row-tile count from the device (rows_on_device).
-constexpr int kUnionRows = 64;   // row slots per bitmap word in that layout (the most rows the split-pages shape serves)
+constexpr int kUnionRows = 64;   // the most rows the split-pages shape serves
 struct UnionInKernel {
-  const uint32_t* rowmaps;   // [heads][words, kUnionRows] pick bitmaps, word-major: slot r of word w is row r's
-                             // word w, slots past the head's row count are zero; NULL: use AttnPrepared::entries.
-                             // A head's region is union_region_words() wide (it can hold the row-major form too).
+  const uint32_t* bits;      // [heads][union_words()] union of the head's picks; NULL: use AttnPrepared::entries
   int32_t* sel_count;        // [heads] out: pages in the union (written by the head's first workgroup)
   bool rows_on_device;       // host side only: launch the form that sizes itself by AttnPrepared::mrows
 };
-// 32-bit words of one (sequence, KV head) region of the row-bitmap buffer: `words` per row, for the
-// larger of the block's row count and the word-major layout's 64 slots
-__host__ __device__ inline size_t union_region_words(int rows_max, int words) {
-  return (size_t)words * (size_t)(rows_max > kUnionRows ? rows_max : kUnionRows);
-}
+// 32-bit words of one (sequence, KV head) union bitmap: whole 16-byte pieces
+__host__ __device__ inline int union_words(int max_pages) { return ((max_pages + 31) / 32 + 3) & ~3; }
 
 // ---- losa_api.hip
 // Sets `n` ints to zero with a small fill kernel (safe to record into a captured graph).
@@ -115,13 +110,13 @@ struct InKernelRanking {
 hipError_t launch_page_scores(hipStream_t st, int dtype, const KvView& kv, const Shape& sh, int batch, int max_seq_pages,
                               const void* q, const int32_t* active_idx, const int32_t* active_count,
                               float* scores, int32_t* tickets, int32_t* sel_count, const AttnPrepared* prep,
-                              const InKernelRanking* ranking, long workgroups_per_round);
+                              const InKernelRanking* ranking, long workgroups_per_round, uint32_t* union_bits = nullptr);
 hipError_t launch_select_pages(hipStream_t st, const KvView& kv, const Shape& sh, int batch, int max_seq_pages,
                                const void* q, const int32_t* active_idx, const int32_t* active_count,
                                const float* scores, int topk, int32_t* topk_out, int32_t* sel_pages,
                                int32_t* sel_count, int cap, uint32_t* rowmaps, int32_t* tickets,
                                const AttnPrepared* prep, int rows_hint, long workgroups_per_round,
-                               bool bitmaps_only = false);
+                               uint32_t* union_bits = nullptr);
 
 // ---- sparse_attn.hip (float mode, merge) and sparse_attn_mfma.hip (bfloat16)
 // Tiles of a (sequence, KV head) page list are dealt round-robin to `nchunk` work items: tiles of 32 tokens

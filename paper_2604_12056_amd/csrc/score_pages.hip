@@ -25,6 +25,13 @@ struct ScoreAux {
   int32_t* sel_count;
   int32_t* ucount;   // nullable
   int32_t* mrows;    // nullable
+  uint32_t* union_bits;   // nullable: union bitmap per head, cleared here for the selection to OR into
+  int union_len;          // its words per head
+  // every thread of one workgroup per head
+  __device__ void clear_union(int head) const {
+    if (union_bits)
+      for (int w = threadIdx.x; w < union_len; w += 256) union_bits[(size_t)head * union_len + w] = 0u;
+  }
   __device__ void reset(int head, int M) const {
     tickets[head] = 0;
     if (M <= 0) {
@@ -184,6 +191,7 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape 
     return (unsigned)ph < (unsigned)kv.num_pages ? ph : 0;
   };
   if (bx * 64 >= P && !writes_active) {                      // no pages here and nothing to publish
+    if (bx == 0) aux.clear_union(b * sh.Hkv + j);
     if (bx == 0 && tid == 0) aux.reset(b * sh.Hkv + j, 0);   // (P == 0: nothing will be selected either)
     return;
   }
@@ -271,6 +279,7 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape 
   } else {
     M = min(active_count[b], sh.B) * sh.G;
   }
+  if (bx == 0) aux.clear_union(b * sh.Hkv + j);
   if (bx == 0 && tid == 0) aux.reset(b * sh.Hkv + j, M);
   if (bx * 64 >= P) return;   // whole workgroup (only the publishing one gets here without pages)
   if (M <= 0) return;
@@ -390,7 +399,8 @@ struct SelectOut {
   const void* q;        // query tensor (for the gather into prep.q_act)
   const int32_t* active_idx;
   bool rows_known;      // the grid has exactly one workgroup per existing row (+ the gather workgroup)
-  bool bitmaps_only;    // heads with at most kUnionRows rows: leave the row bitmaps to the attention kernel (no hand-over, no union, no list)
+  uint32_t* union_bits; // non-NULL: heads with at most kUnionRows rows only OR their picks into this bitmap
+                        // ([heads, union_words()], cleared by the scoring kernel): no hand-over, no list
 };
 
 // Inclusive suffix scan over 256 histogram buckets by one wavefront: lane l owns buckets
@@ -627,13 +637,9 @@ __global__ __launch_bounds__(NT) void select_pages_kernel(KvView kv, Shape sh, c
     // the dense buffer the attention kernel reads, off the path of the selection.  Indices are
     // clamped so that every load can be issued before the one it depends on has been checked.
     if (out.prep.entries == nullptr || M <= 0) return;
-    if (out.bitmaps_only && M <= kUnionRows) {
-      // nobody builds the union here, who would otherwise publish the row count; and the row slots
-      // past it are cleared, so that the attention kernel can OR all slots without looking at the count
+    if (out.union_bits && M <= kUnionRows) {
+      // nobody builds the list here, who would otherwise publish the row count
       if (tid == 0) out.prep.mrows[head] = M;
-      const int wds = (sh.max_pages + 31) / 32, spare = kUnionRows - min(M, kUnionRows);
-      uint32_t* slots = out.rowmaps + (size_t)head * union_region_words(sh.rows_max, wds);
-      for (int i = tid; i < wds * spare; i += NT) slots[(size_t)(i / spare) * kUnionRows + (kUnionRows - spare) + i % spare] = 0u;
       // ... and the head gets its page table in the form the attention kernel consumes (physical id
       // and valid-token count of every logical page), at an address that kernel knows when it starts
       int32_t* tab = out.prep.entries + (size_t)head * sh.max_pages;
@@ -747,11 +753,12 @@ __global__ __launch_bounds__(NT) void select_pages_kernel(KvView kv, Shape sh, c
     // per-die L2 slices); ordering is "my stores have completed (wait count zero), then my
     // ticket".  A full agent-scope fence would also work but writes back and invalidates whole
     // L2 slices, once per workgroup.
-    uint32_t* myrow = out.rowmaps + (size_t)head * union_region_words(sh.rows_max, words) + (size_t)r * words;
-    if (out.bitmaps_only && M <= kUnionRows) {   // read by the next launch: ordinary stores, into the word-major layout
-      uint32_t* slots = out.rowmaps + (size_t)head * union_region_words(sh.rows_max, words);
-      if (r < kUnionRows)
-        for (int w = tid; w < words; w += NT) slots[(size_t)w * kUnionRows + r] = w < WORDS ? rowbits[w] : 0u;
+    uint32_t* myrow = out.rowmaps + ((size_t)head * sh.rows_max + r) * words;
+    if (out.union_bits && M <= kUnionRows) {
+      // read by the next launch; nothing waits for the atomics here (an OR has no order)
+      uint32_t* u = out.union_bits + (size_t)head * union_words(sh.max_pages);
+      for (int w = tid; w < min(words, WORDS); w += NT)
+        if (rowbits[w]) __hip_atomic_fetch_or(&u[w], rowbits[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else {
       for (int w = tid; w < words; w += NT)
         __hip_atomic_store(&myrow[w], w < WORDS ? rowbits[w] : 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -764,7 +771,7 @@ __global__ __launch_bounds__(NT) void select_pages_kernel(KvView kv, Shape sh, c
       if (tid < 256) rl.hist[tid] = 0u;
     }
   }
-  if (out.bitmaps_only && M <= kUnionRows) return;
+  if (out.union_bits && M <= kUnionRows) return;
   const int rows_done = (r_end - 1 - r_first) / r_step + 1;
   __builtin_amdgcn_s_waitcnt(0);
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
@@ -790,7 +797,7 @@ __global__ __launch_bounds__(NT) void select_pages_kernel(KvView kv, Shape sh, c
     for (int i = 0; i < E; ++i)   // (an empty sequence has no entry of its own in the page table)
       phys[i] = P > 0 ? kv.page_indices[base + min(tid + NT * i, P - 1)] : 0;
   }
-  const uint32_t* maps = out.rowmaps + (size_t)head * union_region_words(sh.rows_max, words);
+  const uint32_t* maps = out.rowmaps + (size_t)head * sh.rows_max * words;
   {
     // Thread t ORs bitmap word (t mod nw) of every `groups`-th row in registers, 16 independent
     // loads at a time (a loop of load-then-use would pay one memory latency per iteration),
@@ -965,9 +972,12 @@ __global__ __launch_bounds__(NT) void shared_select_kernel(KvView kv, Shape sh, 
 hipError_t launch_page_scores(hipStream_t st, int dtype, const KvView& kv, const Shape& sh, int batch,
                               int max_seq_pages, const void* q, const int32_t* active_idx,
                               const int32_t* active_count, float* scores, int32_t* tickets, int32_t* sel_count,
-                              const AttnPrepared* prep, const InKernelRanking* ranking, long workgroups_per_round) {
+                              const AttnPrepared* prep, const InKernelRanking* ranking, long workgroups_per_round,
+                              uint32_t* union_bits) {
   if (batch <= 0) return hipSuccess;
-  ScoreAux aux{tickets, sel_count, prep ? prep->ucount : nullptr, prep ? prep->mrows : nullptr};
+  if (union_bits && dtype != LOSA_BF16) return hipErrorInvalidValue;
+  ScoreAux aux{tickets, sel_count, prep ? prep->ucount : nullptr, prep ? prep->mrows : nullptr, union_bits,
+               union_words(sh.max_pages)};
   RankArgs ra{nullptr, 0, 0, 0.f, nullptr, nullptr, nullptr};
   if (ranking) {
     if (dtype != LOSA_BF16 || sh.B > kRankTokens) return hipErrorInvalidValue;
@@ -1006,11 +1016,11 @@ hipError_t launch_select_pages(hipStream_t st, const KvView& kv, const Shape& sh
                                const void* q, const int32_t* active_idx, const int32_t* active_count,
                                const float* scores, int topk, int32_t* topk_out, int32_t* sel_pages,
                                int32_t* sel_count, int cap, uint32_t* rowmaps, int32_t* tickets,
-                               const AttnPrepared* prep, int rows_hint, long workgroups_per_round, bool bitmaps_only) {
+                               const AttnPrepared* prep, int rows_hint, long workgroups_per_round, uint32_t* union_bits) {
   if (batch <= 0) return hipSuccess;
-  if (bitmaps_only && (!prep || topk_out)) return hipErrorInvalidValue;
+  if (union_bits && (!prep || topk_out)) return hipErrorInvalidValue;
   SelectOut out;
-  out.bitmaps_only = bitmaps_only;
+  out.union_bits = union_bits;
   out.topk_out = topk_out;
   out.sel_pages = sel_pages;
   out.sel_count = sel_count;
@@ -1030,7 +1040,7 @@ hipError_t launch_select_pages(hipStream_t st, const KvView& kv, const Shape& sh
   const bool small = pages <= 256 * 8;
   // (without the union hand-over at its end a workgroup is short enough that a grid somewhat past
   // one round still beats two rows per workgroup: measured on 16 sequences of 36 rows x 4 heads)
-  const long fit_one = workgroups_per_round > 0 ? workgroups_per_round : (small ? (bitmaps_only ? 10L : 7L) * 256 : 256L);
+  const long fit_one = workgroups_per_round > 0 ? workgroups_per_round : (small ? (union_bits ? 10L : 7L) * 256 : 256L);
   const long fit_many = workgroups_per_round > 0 ? workgroups_per_round : (small ? 5L * 256 : 256L);
   // (a count the host does not know: the grid has a workgroup for every possible row, and those past
   // the count leave at once; sized as if a quarter of the rows existed, so that a typical active set

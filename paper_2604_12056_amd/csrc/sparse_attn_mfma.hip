@@ -81,19 +81,17 @@ struct MergeSlot {   // LDS image of one wavefront's state: O as [row tile][chan
 // at once when it starts: the only dependent memory round trip left before key/value data
 // flows is entries -> pages.
 // UNION (split-pages shape only): there is no prepared page list.  The selection kernel left the
-// pick bitmap of every query row (word-major) and a copy of the head's page table; the four
-// wavefronts of a workgroup fetch a quarter of each, meet in LDS (one barrier), and then every
-// wavefront ORs the quarters (lane = bitmap word), ranks the union with a popcount prefix sum,
-// keeps words and ranks in LDS (in its own merge slot, which is idle until the combine), and finds
+// union of the head's picks as a bitmap and a copy of the head's page table (which the four wavefronts
+// bring to LDS together); every wavefront ranks the union with a popcount prefix sum (lane = bitmap
+// word), keeps words and ranks in LDS (in its own merge slot, which is idle until the combine), and finds
 // the pages of its own tiles by rank: a binary search over the word ranks, a 5-step search inside
 // the word, then the page's entry from the table in LDS (from memory for pages beyond the first
-// 2048).  That is more start-up work than with a prepared list (about 2 us at 2048 pages), in
+// 2048).  That is more start-up work than with a prepared list (about 1.5 us at 2048 pages), in
 // exchange for the selection kernel's whole hand-over tail (about 4 us).
 constexpr int kMaxUnionWords = kMaxSelectPages / 32;
 constexpr int kTablePagesInLds = 2048;   // the first so many entries of a head's page table are kept in LDS
-// LDS of the split-pages shape, in floats: the four wavefronts' merge slots, then (UNION) an area the
-// workgroup fills together at start-up: each wavefront's share of the bitmap OR, and the page table.
-constexpr int kUnionShared = 4 * kMaxUnionWords + kTablePagesInLds;
+// LDS of the split-pages shape, in floats: the four wavefronts' merge slots, then (UNION) the page table.
+constexpr int kUnionShared = kTablePagesInLds;
 template <int D, int GP, int R, bool SPLIT_PAGES, int NBUF, bool UNION = false>
 __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, int nrbg, Shape sh, KvView kv, Partials part,
                                                float scale_log2e, int m_lo, int m_hi, UnionInKernel uni, float* lds) {
@@ -135,20 +133,16 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
       pg_entry = lp < sh.max_pages ? ent[lp] : 0;   // inside the array whatever U is; checked against U at use
     }
   };
-  // UNION: words and ranks of the head's union, in this wavefront's own merge slot; the page table and
-  // the staging of the OR in the area behind the slots
+  // UNION: words and ranks of the head's union, in this wavefront's own merge slot; the page table behind the slots
   [[maybe_unused]] uint32_t* u_bits = reinterpret_cast<uint32_t*>(lds + (SPLIT_PAGES ? wave : 0) * kSlotStride);
   [[maybe_unused]] int* u_base = reinterpret_cast<int*>(u_bits) + kMaxUnionWords;
-  [[maybe_unused]] uint32_t* u_stage = reinterpret_cast<uint32_t*>(lds + 4 * kSlotStride);   // [4][kMaxUnionWords]
-  [[maybe_unused]] int* u_tab = reinterpret_cast<int*>(u_stage) + 4 * kMaxUnionWords;     // entries by logical page
+  [[maybe_unused]] int* u_tab = reinterpret_cast<int*>(lds + 4 * kSlotStride);   // entries by logical page
   [[maybe_unused]] int u_words = 0;
   // pages whose entries the LDS copy holds: whole 16-byte pieces of the table, up to what fits
   [[maybe_unused]] const int tab_lds_pages = min(sh.max_pages & ~3, kTablePagesInLds);
   if constexpr (UNION) {
-    // The four wavefronts share the start-up fetches (every workgroup of a head needs the same
-    // 16 KiB of bitmaps and 8 KiB of page table; fetched once per wavefront they cost the compute
-    // unit four times the traffic): each takes a quarter of the row slots and of the table, the
-    // pieces meet in LDS, one barrier.
+    // The four wavefronts share the fetch of the page table (8 KiB; once per wavefront it would cost the
+    // compute unit four times the traffic): a quarter each, one barrier.
     const int words = (sh.max_pages + 31) >> 5;
     // the head's page table, written by the selection kernel at an address known here: its first
     // kTablePagesInLds entries go to LDS, so that resolving a page needs no dependent load
@@ -160,52 +154,38 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
       const int i4 = min(wave * (64 * TPW) + lane + 64 * k, max(sh.max_pages / 4 - 1, 0));   // clamped inside the head's table
       tabv[k] = reinterpret_cast<const u32x4v_t*>(ent)[i4];
     }
-    // word-major bitmaps: the kUnionRows row slots of one bitmap word are contiguous (slots past the
-    // head's row count were cleared by the selection kernel), so a lane ORs its word over rows with
-    // 16-byte loads at constant offsets: one memory latency, no per-row addressing
-    const uint32_t* maps = uni.rowmaps + (size_t)head * union_region_words(sh.rows_max, words);
-    // (the loads of up to four groups of 64 words are issued before the first is used: taken one
-    // group at a time, each group costs a memory round trip of its own - 8192 pages are four groups)
+    // the head's union bitmap: up to four words per lane in flight (8192 pages are one memory round trip)
+    const uint32_t* head_bits = uni.bits + (size_t)head * union_words(sh.max_pages);
     constexpr int kGroupsInFlight = 4;
-    for (int g0 = 0; g0 < words; g0 += 64 * kGroupsInFlight) {
-      u32x4v_t v[kGroupsInFlight][R];
+    uint32_t ub[kGroupsInFlight];
 #pragma unroll
-      for (int u = 0; u < kGroupsInFlight; ++u) {
-        if (g0 + 64 * u < words) {   // uniform over the workgroup
-          const int w = g0 + 64 * u + lane;
-          const u32x4v_t* col = reinterpret_cast<const u32x4v_t*>(maps + (size_t)min(w, words - 1) * kUnionRows) + wave * R;
-#pragma unroll
-          for (int k = 0; k < R; ++k) v[u][k] = col[k];   // this wavefront's quarter of the R * 16 row slots
-        }
-      }
-#pragma unroll
-      for (int u = 0; u < kGroupsInFlight; ++u) {
-        if (g0 + 64 * u < words) {
-          const int w = g0 + 64 * u + lane;
-          uint32_t acc = 0u;
-#pragma unroll
-          for (int k = 0; k < R; ++k) acc |= (v[u][k][0] | v[u][k][1]) | (v[u][k][2] | v[u][k][3]);
-          if (w < words) u_stage[wave * kMaxUnionWords + w] = acc;   // words <= kMaxUnionWords: max_pages <= 32 * kMaxUnionWords
-        }
-      }
-    }
+    for (int u = 0; u < kGroupsInFlight; ++u) ub[u] = 64 * u < words ? head_bits[min(64 * u + lane, words - 1)] : 0u;
 #pragma unroll
     for (int k = 0; k < TPW; ++k) reinterpret_cast<u32x4v_t*>(u_tab)[wave * (64 * TPW) + lane + 64 * k] = tabv[k];
     const int P = seq_pages(kv, sh, b);
     u_words = (P + 31) >> 5;
     __syncthreads();
     int total = 0;
-    for (int g0 = 0; g0 < words; g0 += 64) {
-      const int w = g0 + lane;
-      uint32_t acc = (u_stage[w] | u_stage[kMaxUnionWords + w]) | (u_stage[2 * kMaxUnionWords + w] | u_stage[3 * kMaxUnionWords + w]);
-      // pages past the sequence's last one are never picked; the masks only keep a stale bitmap harmless
-      if (w >= u_words) acc = 0u;
-      if (w == u_words - 1 && (P & 31)) acc &= (1u << (P & 31)) - 1u;
-      const int c = __popc(acc);
-      const int incl = wave_inclusive_scan(c);
-      u_bits[w] = acc;
-      u_base[w] = total + incl - c;
-      total += __builtin_amdgcn_readlane(incl, 63);
+    for (int g0 = 0; g0 < words; g0 += 64 * kGroupsInFlight) {
+      if (g0) {
+#pragma unroll
+        for (int u = 0; u < kGroupsInFlight; ++u)
+          ub[u] = g0 + 64 * u < words ? head_bits[min(g0 + 64 * u + lane, words - 1)] : 0u;
+      }
+#pragma unroll
+      for (int u = 0; u < kGroupsInFlight; ++u) {
+        if (g0 + 64 * u >= words) break;   // uniform
+        const int w = g0 + 64 * u + lane;
+        uint32_t acc = ub[u];
+        // pages past the sequence's last one are never picked; the masks only keep a stale bitmap harmless
+        if (w >= u_words) acc = 0u;
+        if (w == u_words - 1 && (P & 31)) acc &= (1u << (P & 31)) - 1u;
+        const int c = __popc(acc);
+        const int incl = wave_inclusive_scan(c);
+        u_bits[w] = acc;
+        u_base[w] = total + incl - c;
+        total += __builtin_amdgcn_readlane(incl, 63);
+      }
     }
     U_raw = total;
     if (chunk == 0 && threadIdx.x == 0 && M_raw > 0) {   // for the merge kernel and the caller's diagnostics
@@ -764,7 +744,7 @@ template <int D, int GP>
 static hipError_t launch_dg(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnPrepared& prep,
                             int nchunk, int rows_upper, const Partials& part, hipEvent_t e0, hipEvent_t e1, int m_lo,
                             int m_hi, const UnionInKernel* uni) {
-  if (uni && uni->rowmaps && uni->rows_on_device) {   // ... and takes every head's row-tile count from the device
+  if (uni && uni->bits && uni->rows_on_device) {   // ... and takes every head's row-tile count from the device
     const size_t lds_bytes = (4 * MergeSlot<D, 4>::kFloats + kUnionShared) * sizeof(float);
     auto kern = attn_mfma_rows_kernel<D, GP>;
     static bool attr_set = false;   // per instantiation
@@ -778,7 +758,7 @@ static hipError_t launch_dg(hipStream_t st, const KvView& kv, const Shape& sh, i
                                                               m_lo, m_hi, *uni);
     return hipGetLastError();
   }
-  if (uni && uni->rowmaps) {   // the kernel builds the union from the row bitmaps itself
+  if (uni && uni->bits) {   // the kernel builds the union from the row bitmaps itself
     if (rows_upper <= 16) return launch_one<D, GP, 1, true, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi, *uni);
     if (rows_upper <= 32) return launch_one<D, GP, 2, true, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi, *uni);
     if (rows_upper <= 48) return launch_one<D, GP, 3, true, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi, *uni);
