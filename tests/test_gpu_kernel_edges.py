@@ -3,6 +3,7 @@ remainders, the smallest and largest of a range - each against the CPU oracle.  
 parity_util (2e-2 for bfloat16 inputs, 1e-4 for float inputs, sets exact up to verified near-ties)."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import losa_oracle as orc
 from paper_2604_12056_amd import binding as L
@@ -76,3 +77,30 @@ def test_float_mode_at_the_edges_of_rows_pages_and_shares(B, G, d, g, n, workgro
                           {(b, 0): np.arange(0, P, 2, dtype=np.int32) for b, P in enumerate(w.pages_per_seq)})
     finally:
         r.close()
+
+
+@pytest.mark.parametrize("Hq,Hkv,d,batch", [
+    (6, 2, 128, 1), (6, 2, 64, 3),   # channels of a head spread over workgroups
+    (64, 8, 128, 1),                 # the last head count they are spread for ...
+    (65, 5, 128, 1), (43, 1, 64, 3)])   # ... and the first ones a workgroup takes all channels of
+@pytest.mark.parametrize("B", [1, 2, 15, 16, 17, 31, 32, 33, 48, 49, 63, 64])
+def test_block_merge_at_the_edges_of_row_and_key_tiles(B, Hq, Hkv, d, batch):
+    """Row tiles of 16, key tiles of 32, tokens staged in pairs; one sequence has an empty prefix."""
+    ctx = L.losa_create(L.make_config(max_batch=batch, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, hidden_size=Hq * d,
+                                      page_size=16, block_size=B, max_pages_per_seq=4, max_topk_pages=1,
+                                      dtype=L.LOSA_BF16), torch.device("cuda"))
+    gen = torch.Generator().manual_seed(B * Hq + d)
+    q, k, v = (torch.randn((batch * B, n, d), generator=gen).to(torch.bfloat16) for n in (Hq, Hkv, Hkv))
+    o_p, lse_p = torch.randn((batch * B, Hq, d), generator=gen), torch.randn((batch * B, Hq), generator=gen) + 3
+    o_p[-B:], lse_p[-B:] = float("nan"), float("-inf")
+    dev = [x.cuda() for x in (q, k, v, o_p, lse_p)]
+    out, o_b, lse_b = torch.empty_like(dev[3]), torch.empty_like(dev[3]), torch.empty_like(dev[4])
+    try:
+        L.losa_block_merge(ctx, *dev, out, o_b, lse_b)
+        torch.cuda.synchronize()
+    finally:
+        ctx.close()
+    ref = orc.block_attention_and_merge(q.float().numpy(), k.float().numpy(), v.float().numpy(), np.nan_to_num(o_p.numpy()),
+                                        lse_p.numpy(), B)
+    for got, want in zip((out, o_b, lse_b), ref):
+        assert np.abs(got.cpu().numpy() - want).max() <= 2e-2
