@@ -106,4 +106,26 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* wave_tot, int* t
   return base + incl - v;
 }
 
+// Cumulative-mass rule.  `sorted`: B scores in descending order, zeros up to a multiple of four, 16-byte aligned;
+// prefix[k] = sorted[0] + ... + sorted[k], summed in that order by the one thread that calls this.
+__device__ __forceinline__ void sorted_prefix_sums(const float* sorted, float* prefix, int B) {
+  float run = 0.f;
+#pragma unroll 4
+  for (int k = 0; k < B; k += 4) {   // a step is one LDS read, four dependent adds and one LDS write
+    const float4 x = *reinterpret_cast<const float4*>(sorted + k);
+    float4 s;
+    s.x = run + x.x;
+    s.y = s.x + x.y;
+    s.z = s.y + x.z;
+    s.w = run = s.z + x.w;
+    *reinterpret_cast<float4*>(prefix + k) = s;
+  }
+}
+// Scores are not negative, so their prefix sums do not fall: the shortest prefix that reaches tau * total holds the
+// ranks before which the target has not been reached (nothing if the total or tau is not positive).
+__device__ __forceinline__ int mass_takes(const float* prefix, int rank, int B, float tau) {
+  const float total = prefix[B - 1];
+  return (total > 0.f) & (tau > 0.f) & ((rank == 0) || prefix[max(rank - 1, 0)] < tau * total);
+}
+
 }  // namespace losa

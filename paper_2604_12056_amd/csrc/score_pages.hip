@@ -234,37 +234,21 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape 
           rank += (int)(dk[e] > my_delta) | ((int)(dk[e] == my_delta) & (int)(k + e < tid));
       }
     }
-    int n_take = ra.n;
     if (ra.mode == LOSA_SEL_MASS) {
-      // Cumulative-mass rule, as in the stand-alone kernel: scores in descending order, summed
-      // in that order in float by one thread; A is the shortest prefix reaching tau * total.
-      __shared__ float sorted[kRankTokens];
-      __shared__ int s_take;
+      // Cumulative-mass rule, as in the stand-alone kernel: prefix sums of the scores in descending order, taken
+      // in that order in float by one thread; a token is in A if the sums before it stay below tau * total.
+      // One pass with four scores per LDS read, a chain of adds, instead of two of an LDS read per token: step with 64 tokens
+      // 31.3 -> 31.0 us, 16 tokens 35.1 -> 34.9.
+      __shared__ __attribute__((aligned(16))) float sorted[kRankTokens], prefix[kRankTokens];
       if (tid < B) sorted[rank] = my_delta;
+      if (tid < ((4 - (B & 3)) & 3)) sorted[B + tid] = 0.f;
       __syncthreads();
-      if (tid == 0) {
-        float total = 0.f;
-        for (int k = 0; k < B; ++k) total += sorted[k];
-        const float target = ra.tau * total;
-        int cnt = 0;
-        if (total > 0.f) {
-          float run = 0.f;
-          cnt = B;
-          for (int k = 0; k < B; ++k) {
-            run += sorted[k];
-            if (run >= target) {
-              cnt = k + 1;
-              break;
-            }
-          }
-          if (!(ra.tau > 0.f)) cnt = 0;
-        }
-        s_take = cnt;
-      }
+      if (tid == 0) sorted_prefix_sums(sorted, prefix, B);
       __syncthreads();
-      n_take = s_take;
+      if (tid < B) act = mass_takes(prefix, rank, B, ra.tau);
+    } else if (tid < B) {
+      act = ra.mode == LOSA_SEL_THRESHOLD ? my_delta > ra.tau : rank < ra.n;
     }
-    if (tid < B) act = ra.mode == LOSA_SEL_THRESHOLD ? my_delta > ra.tau : rank < n_take;
     int n_act;
     const int pos = block_exclusive_scan(act, rscan, &n_act);
     if (act) act_list[pos] = tid;

@@ -87,12 +87,11 @@ __global__ __launch_bounds__(256) void locality_select_kernel(const T* __restric
   for (int i = tid; i < B; i += 256)
     sd[i] = __hip_atomic_load(&delta[(size_t)b * B + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
+  __shared__ __attribute__((aligned(16))) float sorted[1024], prefix[1024];   // cumulative-mass rule only
   if (mode == LOSA_SEL_MASS) {
     // Cumulative-mass rule: scores in descending order, summed in that order in float; A is
     // the shortest prefix whose sum reaches tau * total.  Done as rank -> sorted copy -> one
-    // sequential pass, so the float sums are taken in a defined order.
-    __shared__ float sorted[1024];
-    __shared__ int s_n;
+    // sequential pass of prefix sums, so the float sums are taken in a defined order.
     for (int i = tid; i < B; i += 256) {
       const float di = sd[i];
       int rank = 0;
@@ -102,28 +101,10 @@ __global__ __launch_bounds__(256) void locality_select_kernel(const T* __restric
       }
       sorted[rank] = di;
     }
+    if (tid < ((4 - (B & 3)) & 3)) sorted[B + tid] = 0.f;
     __syncthreads();
-    if (tid == 0) {
-      float total = 0.f;
-      for (int k = 0; k < B; ++k) total += sorted[k];
-      const float target = tau * total;
-      int cnt = 0;
-      if (total > 0.f) {
-        float run = 0.f;
-        cnt = B;
-        for (int k = 0; k < B; ++k) {
-          run += sorted[k];
-          if (run >= target) {
-            cnt = k + 1;
-            break;
-          }
-        }
-        if (!(tau > 0.f)) cnt = 0;
-      }
-      s_n = cnt;
-    }
+    if (tid == 0) sorted_prefix_sums(sorted, prefix, B);
     __syncthreads();
-    n = s_n;
   }
   int base_out = 0;
   for (int i0 = 0; i0 < B; i0 += 256) {
@@ -139,7 +120,7 @@ __global__ __launch_bounds__(256) void locality_select_kernel(const T* __restric
           const float dk = sd[k];
           rank += (int)(dk > di) | ((int)(dk == di) & (int)(k < i));   // bitwise: no branch per element
         }
-        act = rank < n;
+        act = mode == LOSA_SEL_MASS ? mass_takes(prefix, rank, B, tau) : rank < n;
       }
       mask[(size_t)b * B + i] = (uint8_t)act;
     }

@@ -315,8 +315,7 @@ __device__ __forceinline__ void merge_fragments(const Shape& sh, const int32_t* 
 // quads: every chunk lane sums its chunks c = lane, lane+CL, ... (independent loads), then
 // the lanes are added in a fixed order, so the result does not depend on scheduling.
 // LOG2: partial maxima are in log2 units (scores scaled by sm_scale*log2(e)) and sums are
-// float; otherwise natural units and double sums (the element-generic kernel, which also
-// serves the float mode).
+// float; otherwise natural units and double sums (float mode).
 // FRAGS: some heads' partials are laid out by fragments (a template argument: its code and registers would cost
 // the plain form 0.3 us of its 4).
 template <int D, bool LOG2, bool FRAGS>

@@ -104,3 +104,31 @@ def test_block_merge_at_the_edges_of_row_and_key_tiles(B, Hq, Hkv, d, batch):
                                         lse_p.numpy(), B)
     for got, want in zip((out, o_b, lse_b), ref):
         assert np.abs(got.cpu().numpy() - want).max() <= 2e-2
+
+
+@pytest.mark.parametrize("B", [1, 2, 4, 5, 16, 63, 255, 256, 257, 1023, 1024])
+def test_cumulative_mass_at_the_edges_of_its_prefix_sums(B):
+    """Block sizes around the four scores per read and the 256 tokens the scoring kernel ranks for itself.  Scores
+    are squares of small integers, so every sum is exact and the sets, full of ties, have to be equal."""
+    rng, H, dev = np.random.Generator(np.random.Philox(B)), 64, "cuda:0"
+    v = rng.integers(0, 8, size=(3, B)).astype(np.float32)
+    v[2] = 0.0                                      # a sequence without any change
+    h = torch.from_numpy(np.repeat(v.reshape(-1, 1), H, axis=1)).to(dev, torch.bfloat16)
+    out = (torch.zeros(3 * B, device=dev), torch.zeros(3 * B, dtype=torch.uint8, device=dev),
+           torch.zeros(3 * B, dtype=torch.int32, device=dev), torch.zeros(3, dtype=torch.int32, device=dev))
+    for tau in (0.0, 2.0 ** -20, 0.25, 0.5, 0.75, 1.0):   # (products with the total are exact too)
+        L.losa_select_active_static(L.LOSA_BF16, 3, B, H, h, torch.zeros_like(h), orc.SEL_MASS, tau, *out)
+        mask, idx, count = (x.cpu().numpy() for x in out[1:])
+        for b in range(3):
+            A = orc.active_set(v[b] ** 2, orc.SEL_MASS, tau)
+            assert np.array_equal(idx[b * B:b * B + count[b]], A) and np.all(idx[b * B + count[b]:(b + 1) * B] == -1)
+            assert np.array_equal(np.nonzero(mask[b * B:(b + 1) * B])[0], A)
+    if B <= 64:
+        w = workload(B, 1, 1, 64, 16, (33, 300), max(1, B // 3))
+        r = Rig(w)
+        try:
+            check_page_bounds(r)
+            run_steps_end_to_end(r, range(2), orc.SEL_MASS, 0.5, w.topk_pages)
+            run_steps_end_to_end(r, [2], orc.SEL_MASS, 1.0, w.topk_pages)
+        finally:
+            r.close()
