@@ -99,11 +99,21 @@ def _ptr(t) -> Optional[int]:
     return None if t is None else t.data_ptr()
 
 
+# The handle of the current device's current stream, asked for at every call.  A torch.cuda.Stream object made for each
+# call only to read its handle takes 2.8 us of host time, this 0.36, and the smallest steps take as long to issue as to run
+# (2048 tokens, 4 heads: 22.6 -> 20.9 us per step).
+_current_raw_stream = None
+
+
 def _stream(stream) -> Optional[int]:
     if stream is not None:
         return int(stream) or None
-    import torch
-    return torch.cuda.current_stream().cuda_stream or None
+    global _current_raw_stream
+    if _current_raw_stream is None:
+        import torch
+        current_device, raw_stream = torch.cuda.current_device, torch._C._cuda_getCurrentRawStream
+        _current_raw_stream = lambda: raw_stream(current_device())
+    return _current_raw_stream() or None
 
 
 class PagedKV:
