@@ -49,6 +49,7 @@ typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef __attribute__((ext_vector_type(8))) float f32x8_t;
 typedef __attribute__((ext_vector_type(16))) float f32x16_t;
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8_t;
+typedef __attribute__((ext_vector_type(2))) _Float16 f16x2_t;
 typedef uint32_t u32x4v_t __attribute__((ext_vector_type(4)));   // a plain vector value (stays in registers)
 
 constexpr int kRowsPerWave = 32;
@@ -79,9 +80,12 @@ __device__ __forceinline__ uint32_t bf16_pair_to_half(uint32_t two_bf16) {
 // HALF: the value product runs in half precision.  Values are converted bfloat16 -> half while they are
 // staged (exact for 2^-14 <= |v| <= 65504, truncated towards zero below that range and held at +-65504
 // above it), the numerators enter as ONE half-precision operand (11 significant bits, round to nearest).
-// The reference of the exponentials then sits 7 (log2 units) above where it would otherwise be, so that
-// the numerators use the upper end of the half-precision range.  Otherwise P is a bfloat16 pair
-// hi + lo and values stay bfloat16.
+// The reference of the exponentials then sits 7 (log2 units) below where it would otherwise be, so that
+// the numerators use the upper end of the half-precision range.  O is normalised with the sum of the ROUNDED
+// numerators, the weights it was made with: what the roundings have in common cancels, so a row that one
+// token dominates and a channel whose values are alike come out exact (with the unrounded sum they are off by up
+// to 2^-11 of the value).  The log-sum-exp and the weight of a chunk among chunks take the unrounded sum.
+// Otherwise P is a bfloat16 pair hi + lo and values stay bfloat16.
 //
 // TG token groups: with up to 128 rows four wavefronts hold all of them, and the other four take the
 // second 32-token block of every stage instead of idling; the two halves meet through LDS at the end.
@@ -217,6 +221,7 @@ __device__ __forceinline__ void attn_rows_body(int nchunk, int row_group, int j,
 
   // ---- running state of this wavefront's rows (row l32, both lane halves hold the same reference)
   float m_run = kNoReference, l_run = 0.f;   // l_run: sum over this lane's own tokens
+  [[maybe_unused]] float l_half = 0.f;       // HALF: the same sum of the rounded numerators
   f32x16_t o[CB];
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb)
@@ -287,6 +292,7 @@ __device__ __forceinline__ void attn_rows_body(int nchunk, int row_group, int j,
       const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
       m_run = m_new;
       l_run *= alpha;
+      if constexpr (HALF) l_half *= alpha;
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) o[cb] *= alpha;
       sum = numerators(s, p);
@@ -301,6 +307,12 @@ __device__ __forceinline__ void attn_rows_body(int nchunk, int row_group, int j,
       for (int e = 0; e < 8; ++e) pv[e] = p[8 * ks + e];
       if constexpr (HALF) {
         const f16x8_t ph = __builtin_convertvector(pv, f16x8_t);
+        // (two numerators per instruction, exact products, subnormals kept)
+        const f16x2_t ones = {1, 1};
+        l_half = __builtin_amdgcn_fdot2(__builtin_shufflevector(ph, ph, 0, 1), ones, l_half, false);
+        l_half = __builtin_amdgcn_fdot2(__builtin_shufflevector(ph, ph, 2, 3), ones, l_half, false);
+        l_half = __builtin_amdgcn_fdot2(__builtin_shufflevector(ph, ph, 4, 5), ones, l_half, false);
+        l_half = __builtin_amdgcn_fdot2(__builtin_shufflevector(ph, ph, 6, 7), ones, l_half, false);
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb)
           o[cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8_t, vf[ks][cb]), ph, o[cb], 0, 0, 0);
@@ -437,6 +449,13 @@ __device__ __forceinline__ void attn_rows_body(int nchunk, int row_group, int j,
   {
     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
     l_run = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+  }
+  if constexpr (HALF) {   // O leaves with its weights adding up to l_run
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_half), __float_as_uint(l_half), false, false);
+    l_half = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+    const float to_l_run = l_half > 0.f ? l_run / l_half : 1.0f;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb) o[cb] *= to_l_run;
   }
   if constexpr (TG == 2) {
     // the second token group hands its state over through LDS (the stage buffers are free now):

@@ -132,3 +132,56 @@ def test_cumulative_mass_at_the_edges_of_its_prefix_sums(B):
             run_steps_end_to_end(r, [2], orc.SEL_MASS, 1.0, w.topk_pages)
         finally:
             r.close()
+
+
+@pytest.mark.parametrize("page", [16, 32])
+@pytest.mark.parametrize("B,G,d", [
+    (13, 5, 128),     # 65 rows: two token groups
+    (32, 4, 64),      # 128 rows
+    (43, 3, 64),      # 129 rows: one token group
+    (64, 4, 128)])    # 256 rows
+def test_many_row_kernel_normalises_with_the_weights_it_applies(B, G, d, page):
+    """Half-precision numerators: what their roundings have in common has to cancel.  One token carries a row and
+    arrives after the reference was taken, 4 to 7.5 log2 units above it, so that its numerator is rounded at every
+    place of the half-precision grid; its value is 100 in half of the channels, and one channel is 3 in every token.
+    With weights w_i (1 + e_i), |e_i| <= 2^-11, divided by their own sum, an output is off by at most
+    2^-11 * sum w_i |v_i - o| to first order, plus float arithmetic (1e-4 at |v| = 100)."""
+    n, Hkv, rows, unit = 200, 2, B * G, np.log(2.0) * np.sqrt(d)
+    rng = np.random.Generator(np.random.Philox(B * G + page))
+    bf = lambda x: torch.from_numpy(np.ascontiguousarray(x, dtype=np.float32)).to(torch.bfloat16)
+    q = np.zeros((B, Hkv * G, d))
+    q[:, :, 0], q[:, :, 1] = 1.0, rng.random((B, Hkv * G))
+    k = np.zeros((n, d))
+    k[:, 0] = -20 * unit
+    k[[0, 32], 0] = 0.0                             # the reference of either token group
+    k[70, :2] = 4 * unit, 3.5 * unit
+    v = rng.standard_normal((n, d))
+    v[70, :d // 2], v[:, d - 1] = 100.0, 3.0
+    q, k, v = bf(q), bf(k), bf(v)
+    pages = -(-n // page)
+    kp, vp = torch.zeros((pages * page, d), dtype=torch.bfloat16), torch.zeros((pages * page, d), dtype=torch.bfloat16)
+    kp[:n], vp[:n] = k, v
+    kp = kp.reshape(pages, 1, page, d).expand(-1, Hkv, -1, -1).contiguous().cuda()
+    vp = vp.reshape(pages, 1, page, d).transpose(2, 3).expand(-1, Hkv, -1, -1).contiguous().cuda()
+    ints = lambda *x: torch.tensor(x, dtype=torch.int32, device="cuda")
+    kv = L.PagedKV(kp, vp, torch.zeros((pages, Hkv, 2, d), dtype=torch.bfloat16, device="cuda"), ints(0, pages),
+                   torch.arange(pages, dtype=torch.int32, device="cuda"), ints(n))
+    ctx = L.losa_create(L.make_config(max_batch=1, num_q_heads=Hkv * G, num_kv_heads=Hkv, head_dim=d, hidden_size=Hkv * G * d,
+                                      page_size=page, block_size=B, max_pages_per_seq=pages, max_topk_pages=1), "cuda:0")
+    o_p, lse_p = torch.zeros((B, Hkv * G, d), device="cuda"), torch.zeros((B, Hkv * G), device="cuda")
+    try:
+        L.losa_set_tuning(ctx, L.LOSA_TUNE_ATTN_WORKGROUPS, 1)      # one workgroup walks all of the tokens
+        L.losa_sparse_attn(ctx, kv, q.cuda(), None, None, None, None, 0, o_p, lse_p)
+        torch.cuda.synchronize()
+    finally:
+        ctx.close()
+    q64, k64, v64 = (x.double().numpy() for x in (q.reshape(-1, d), k, v))
+    s = q64 @ k64.T / np.sqrt(d)
+    top = s.max(axis=1, keepdims=True)
+    lse = np.log(np.exp(s - top).sum(axis=1)) + top[:, 0]
+    w = np.exp(s - lse[:, None])
+    o = w @ v64
+    bound = np.stack([2.0 ** -11 * (w[r][:, None] * np.abs(v64 - o[r])).sum(axis=0) for r in range(len(w))]) + 1e-4
+    err = np.abs(o_p.cpu().double().numpy().reshape(-1, d) - o)
+    assert len(w) == Hkv * rows and (err <= bound).all(), f"off by {(err / bound).max():.1f} times the bound, {err.max():.3g}"
+    assert np.abs(lse_p.cpu().numpy().reshape(-1) - lse).max() <= 2e-5      # the unrounded sum
