@@ -153,8 +153,8 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(KvView kv, Shape sh, c
     tmax = __uint_as_float(across_rows(__float_as_uint(tmax), [](uint32_t x, uint32_t y) {
       return __float_as_uint(fmaxf(__uint_as_float(x), __uint_as_float(y)));
     }));
-    // the reference lags the maximum by up to kLag (e^16 is nothing to float64 sums and harmless to the float
-    // partials), so after the first tile it hardly ever moves
+    // the reference lags the maximum by up to kLag (e^16 is nothing to float64 sums), so after the first tile it
+    // hardly ever moves
     if (__any(tmax > m + kLag)) {
       const float m_new = fmaxf(m, tmax);
       const double alpha = m == -INFINITY ? 0.0 : exp((double)m - (double)m_new);
@@ -206,6 +206,16 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(KvView kv, Shape sh, c
     const float mw = sm[w * 16 + l16];
     wgt[w] = mw == -INFINITY ? 0.0 : exp((double)mw - (double)m_all);
     l_all += wgt[w] * sl[w * 16 + l16];
+  }
+  // the reference may lag the maximum by kLag: float partials of values past 1e31 would overflow at weights of e^16,
+  // so they leave with weights that add up to about 1
+  if (l_all > 1.0) {
+    const float m_out = m_all + logf((float)l_all);
+    const double f = exp((double)m_all - (double)m_out);
+    m_all = m_out;
+    l_all *= f;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) wgt[w] *= f;
   }
   const size_t prow = (((size_t)b * sh.Hkv + j) * nchunk + chunk) * part.rows + r;
 #pragma unroll

@@ -185,3 +185,39 @@ def test_many_row_kernel_normalises_with_the_weights_it_applies(B, G, d, page):
     err = np.abs(o_p.cpu().double().numpy().reshape(-1, d) - o)
     assert len(w) == Hkv * rows and (err <= bound).all(), f"off by {(err / bound).max():.1f} times the bound, {err.max():.3g}"
     assert np.abs(lse_p.cpu().numpy().reshape(-1) - lse).max() <= 2e-5      # the unrounded sum
+
+
+@pytest.mark.parametrize("d,page", [(64, 16), (128, 32)])
+def test_float_mode_keeps_values_near_the_end_of_the_range(d, page):
+    """Values of 1e33 under a token that scores 15 above the reference its wavefront took first: a weight of e^15
+    times the value is past the range of a float, their quotient is not.  Relative bound 1e-4, the mode's."""
+    B, heads, pages = 4, 2, 9
+    n, unit = pages * page - 3, np.sqrt(d)
+    rng = np.random.Generator(np.random.Philox(d))
+    q, k = np.zeros((B, heads, d), np.float32), np.zeros((n, d), np.float32)
+    q[:, :, 0] = 1.0
+    k[:, 0] = -30 * unit
+    k[::4 * page, 0] = (0, -unit, 15 * unit)        # pages 0 and 8 belong to one wavefront of the first workgroup
+    v = (rng.standard_normal((n, d)) * 1e33).astype(np.float32)
+    kp, vp = np.zeros((pages * page, d), np.float32), np.full((pages * page, d), np.nan, np.float32)
+    kp[:n], vp[:n] = k, v
+    dev = lambda x: torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    kv = L.PagedKV(dev(kp.reshape(pages, 1, page, d)), dev(vp.reshape(pages, 1, page, d).transpose(0, 1, 3, 2)),
+                   torch.zeros((pages, 1, 2, d), device="cuda"), dev(np.array([0, pages], np.int32)),
+                   dev(np.arange(pages, dtype=np.int32)), dev(np.array([n], np.int32)))
+    ctx = L.losa_create(L.make_config(max_batch=1, num_q_heads=heads, num_kv_heads=1, head_dim=d, hidden_size=heads * d,
+                                      page_size=page, block_size=B, max_pages_per_seq=pages, max_topk_pages=1,
+                                      dtype=L.LOSA_F32), "cuda:0")
+    o_p, lse_p = torch.zeros((B, heads, d), device="cuda"), torch.zeros((B, heads), device="cuda")
+    try:
+        for workgroups in (1, 256):
+            L.losa_set_tuning(ctx, L.LOSA_TUNE_ATTN_WORKGROUPS, workgroups)
+            L.losa_sparse_attn(ctx, kv, dev(q), None, None, None, None, 0, o_p, lse_p)
+            torch.cuda.synchronize()
+            s = (q.reshape(-1, d).astype(np.float64) @ k.T.astype(np.float64)) / unit
+            w = np.exp(s - 15.0)
+            o, lse = (w @ v.astype(np.float64)) / w.sum(axis=1, keepdims=True), 15.0 + np.log(w.sum(axis=1))
+            assert np.abs(o_p.cpu().numpy().reshape(-1, d) - o).max() <= 1e-4 * 1e33
+            assert np.abs(lse_p.cpu().numpy().reshape(-1) - lse).max() <= 1e-4
+    finally:
+        ctx.close()
