@@ -308,7 +308,8 @@ hipError_t launch_block_merge(hipStream_t st, int dtype, const Shape& sh, int ba
     // Channels are spread over workgroups while there is at most one per CU: 32 heads, B = 64,
     // whole against four times as many workgroups: 1 sequence 7.2 -> 5.2 us, 2 sequences 7.6 -> 5.7, 4
     // sequences (512 spread workgroups) 8.0 -> 8.7, the repeated scores and keys cost more than they save.
-    const bool spread = (long)sh.Hq * batch * (sh.d / kSpreadChannels) <= kSpreadWorkgroups;
+    // (not where lse_b replaces lse_p in place: one workgroup's store would race with another's load of it)
+    const bool spread = lse_b != lse_p && (long)sh.Hq * batch * (sh.d / kSpreadChannels) <= kSpreadWorkgroups;
     const auto kernel = sh.d == 128 ? (sh.B <= 32 ? (spread ? block_merge_mfma_kernel<128, 1, kSpreadChannels> : block_merge_mfma_kernel<128, 1, 128>)
                                                   : (spread ? block_merge_mfma_kernel<128, 2, kSpreadChannels> : block_merge_mfma_kernel<128, 2, 128>))
                                     : (sh.B <= 32 ? (spread ? block_merge_mfma_kernel<64, 1, kSpreadChannels> : block_merge_mfma_kernel<64, 1, 64>)

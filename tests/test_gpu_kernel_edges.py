@@ -106,6 +106,29 @@ def test_block_merge_at_the_edges_of_row_and_key_tiles(B, Hq, Hkv, d, batch):
         assert np.abs(got.cpu().numpy() - want).max() <= 2e-2
 
 
+@pytest.mark.parametrize("B", [16, 64])
+def test_block_merge_in_place(B):
+    """The result and the block's log-sum-exp written over the prefix statistics they are merged with, at a size whose
+    channels are otherwise spread over workgroups (8 heads: 32 of them): bit for bit those of separate buffers."""
+    Hq, Hkv, d = 8, 2, 128
+    ctx = L.losa_create(L.make_config(max_batch=1, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, hidden_size=Hq * d,
+                                      page_size=16, block_size=B, max_pages_per_seq=4, max_topk_pages=1,
+                                      dtype=L.LOSA_BF16), torch.device("cuda"))
+    gen = torch.Generator().manual_seed(B)
+    q, k, v = (torch.randn((B, n, d), generator=gen).to(torch.bfloat16).cuda() for n in (Hq, Hkv, Hkv))
+    o_p, lse_p = torch.randn((B, Hq, d), generator=gen).cuda(), torch.randn((B, Hq), generator=gen).cuda() + 3
+    out, o_b, lse_b = torch.empty_like(o_p), torch.empty_like(o_p), torch.empty_like(lse_p)
+    try:
+        L.losa_block_merge(ctx, q, k, v, o_p, lse_p, out, o_b, lse_b)
+        for _ in range(20):
+            o_io, lse_io = o_p.clone(), lse_p.clone()
+            L.losa_block_merge(ctx, q, k, v, o_io, lse_io, o_io, None, lse_io)
+            torch.cuda.synchronize()
+            assert torch.equal(o_io, out) and torch.equal(lse_io, lse_b)
+    finally:
+        ctx.close()
+
+
 @pytest.mark.parametrize("B", [1, 2, 4, 5, 16, 63, 255, 256, 257, 1023, 1024])
 def test_cumulative_mass_at_the_edges_of_its_prefix_sums(B):
     """Block sizes around the four scores per read and the 256 tokens the scoring kernel ranks for itself.  Scores
