@@ -234,61 +234,77 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(KvView kv, Shape sh, c
   }
 }
 
-// Partials laid out by fragments (sparse_attn_rows.hip), 32 rows x 8 channels each; every load is 1 KiB contiguous
-// per wavefront.  With few chunks a wavefront takes a fragment and all of its chunks; with more, the
-// workgroup's four wavefronts take every fourth chunk of one fragment and meet in LDS, in wavefront order.
-// `block` counts (row tile, group of fragments) pairs.
-constexpr int kFragBatch = 8;   // chunks a wavefront has in flight
-__host__ __device__ constexpr int fragments_per_block(int nchunk) { return nchunk <= kFragBatch ? 4 : 1; }
-template <int D>
-__device__ __forceinline__ void merge_fragments(const Shape& sh, const int32_t* __restrict__ active_idx, int b, int j,
-                                                int block, int M, int live, int nchunk, const Partials& part,
+// Merge of partials laid out by fragments (sparse_attn_rows.hip), 32 rows x 8 channels each, every load 1 KiB
+// contiguous.  PER wavefronts deal the chunks of a fragment out, KB in flight each, and meet in LDS, in wavefront
+// order; a workgroup of WAVES takes WAVES / PER fragments.  `block` counts (row tile, group of fragments) pairs.
+// SPECULATE: slots exist for every row and chunk of the launch, so the first batch is requested before it is known
+// which of them were written, and counts(M, live) asked for behind it; otherwise M and live are known.
+constexpr int kFragSlot = 256 + 64;   // floats a wavefront leaves in LDS: fragment, references, sums
+template <int D, int WAVES, int PER, int KB, bool SPECULATE, typename Counts>
+__device__ __forceinline__ void merge_fragments(const Shape& sh, const int32_t* __restrict__ active_idx, int b, int j, int block,
+                                                int M, int live, Counts counts, int nchunk, const Partials& part,
                                                 float* __restrict__ o_p, float* __restrict__ lse_p, float* lds) {
   typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-  constexpr int KB = kFragBatch;
-  const int fpb = fragments_per_block(nchunk), groups = D / 8 / fpb;
-  const bool split = fpb == 1;
+  constexpr int FPB = WAVES / PER;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int l32 = lane & 31, half = lane >> 5;
-  const int tile = block / groups, frag = block % groups * fpb + (split ? 0 : wave);
-  const int c_first = split ? wave : 0, c_step = split ? 4 : 1;
+  const int l32 = lane & 31, half = lane >> 5, share = wave % PER;
+  const int tile = block / (D / 8 / FPB), frag = block % (D / 8 / FPB) * FPB + wave / PER;
   const int r = tile * kPartialTile + l32;
-  const size_t item0 = ((size_t)b * sh.Hkv + j) * nchunk;
-  const int tok = active_idx ? active_idx[(size_t)b * sh.B + min(r / sh.G, sh.B - 1)] : r / sh.G;
-  float m = -INFINITY, l = 0.f;
+  float m = -1.0e30f, l = 0.f;   // ("no token seen", as the partials have it)
   f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
-  for (int c0 = c_first; c0 < live; c0 += c_step * KB) {
+  int tok = 0;
+  const int last = SPECULATE ? nchunk : live;
+  if constexpr (SPECULATE) live = nchunk;
+  else tok = active_idx ? active_idx[(size_t)b * sh.B + min(r / sh.G, sh.B - 1)] : r / sh.G;
+  // scalar addresses that move on by a constant, plus a lane offset
+  const size_t row0 = (((size_t)b * sh.Hkv + j) * nchunk + min(share, nchunk - 1)) * part.rows + tile * kPartialTile;
+  const uint32_t step = (uint32_t)PER * part.rows;
+  const float* pm = part.m + row0;
+  const float* pl = part.l + row0;
+  const float* po = part.o + row0 * D + frag * 256;
+  for (int c0 = share; c0 < live; c0 += PER * KB) {
     float mk[KB], lk[KB];
     f32x4_t x[KB];
 #pragma unroll
-    for (int k = 0; k < KB; ++k) {   // all loads of the batch go out before the first is used
-      mk[k] = -INFINITY;
-      lk[k] = 0.f;
-      x[k] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
-      if (c0 + c_step * k >= live) continue;   // (uniform over the wavefront)
-      const size_t prow = (item0 + c0 + c_step * k) * part.rows + tile * kPartialTile;
-      mk[k] = part.m[prow + l32];
-      lk[k] = part.l[prow + l32];
-      x[k] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(part.o + prow * D + frag * 256 + lane * 4));
+    for (int k = 0; k < KB; ++k) {   // no branches: a load behind one is waited for before the next goes out
+      mk[k] = pm[l32];
+      lk[k] = pl[l32];
+      x[k] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(po + lane * 4));
+      const uint32_t on = c0 + PER * (k + 1) < last ? step : 0;   // (past the end: the last chunk again)
+      pm += on;
+      pl += on;
+      po += (size_t)on * D;
     }
+    if constexpr (SPECULATE) {
+      if (c0 == share) {
+        counts(M, live);
+        tok = active_idx ? active_idx[(size_t)b * sh.B + min(r / sh.G, sh.B - 1)] : r / sh.G;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < KB; ++k)
+      if (c0 + PER * k >= live) {   // not a chunk, or leftovers of earlier launches, NaN included
+        mk[k] = -INFINITY;
+        lk[k] = 0.f;
+        x[k] = (f32x4_t){0.f, 0.f, 0.f, 0.f};
+      }
     float m_new = m;
 #pragma unroll
     for (int k = 0; k < KB; ++k) m_new = fmaxf(m_new, mk[k]);
-    const float keep = exp2f(m - m_new);   // (m_new is finite: references are -1e30 at least)
+    const float keep = __builtin_amdgcn_exp2f(m - m_new);
     m = m_new;
     l *= keep;
     acc *= keep;
 #pragma unroll
     for (int k = 0; k < KB; ++k) {
-      const float w = exp2f(mk[k] - m);
+      const float w = __builtin_amdgcn_exp2f(mk[k] - m);
       l = fmaf(lk[k], w, l);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[e] = fmaf(x[k][e], w, acc[e]);
+      acc += x[k] * w;
     }
   }
-  if (split) {
-    float* slot = lds + wave * (256 + 64);
-    if (wave) {
+  if constexpr (PER > 1) {
+    float* slot = lds + wave * kFragSlot;
+    if (share) {
       *reinterpret_cast<f32x4_t*>(slot + lane * 4) = acc;
       if (half == 0) {
         slot[256 + l32] = m;
@@ -296,21 +312,27 @@ __device__ __forceinline__ void merge_fragments(const Shape& sh, const int32_t* 
       }
     }
     __syncthreads();
-    if (wave) return;
-    float mw[4], wt[4], l_tot = 0.f;
-    mw[0] = m;
+    if (share) return;
+    float mw[PER], lw[PER], m_all = m;
+    f32x4_t xw[PER];
 #pragma unroll
-    for (int w = 1; w < 4; ++w) mw[w] = lds[w * (256 + 64) + 256 + l32];
-    m = fmaxf(fmaxf(mw[0], mw[1]), fmaxf(mw[2], mw[3]));
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      wt[w] = mw[w] > -INFINITY ? exp2f(mw[w] - m) : 0.f;
-      l_tot = fmaf(w ? lds[w * (256 + 64) + 256 + 32 + l32] : l, wt[w], l_tot);
+    for (int w = 1; w < PER; ++w) {
+      mw[w] = slot[w * kFragSlot + 256 + l32];
+      lw[w] = slot[w * kFragSlot + 256 + 32 + l32];
+      xw[w] = *reinterpret_cast<const f32x4_t*>(slot + w * kFragSlot + lane * 4);
     }
-    l = l_tot;
-    acc *= wt[0];
 #pragma unroll
-    for (int w = 1; w < 4; ++w) acc += *reinterpret_cast<const f32x4_t*>(lds + w * (256 + 64) + lane * 4) * wt[w];
+    for (int w = 1; w < PER; ++w) m_all = fmaxf(m_all, mw[w]);
+    const float keep = __builtin_amdgcn_exp2f(m - m_all);
+    m = m_all;
+    l *= keep;
+    acc *= keep;
+#pragma unroll
+    for (int w = 1; w < PER; ++w) {
+      const float wt = __builtin_amdgcn_exp2f(mw[w] - m);
+      l = fmaf(lw[w], wt, l);
+      acc += xw[w] * wt;
+    }
   }
   if (r >= M || (unsigned)tok >= (unsigned)sh.B) return;
   const size_t orow = ((size_t)b * sh.B + tok) * sh.Hq + j * sh.G + r % sh.G;
@@ -320,15 +342,33 @@ __device__ __forceinline__ void merge_fragments(const Shape& sh, const int32_t* 
   if (frag == 0 && half == 0) lse_p[orow] = any ? (m + log2f(l)) * 0.6931471805599453f : -INFINITY;
 }
 
+// Every head's partials are laid out by fragments.  DENSE: no counts were prepared (every row, every page).
+template <int D, int WAVES, int PER, int KB, bool DENSE>
+__global__ __launch_bounds__(64 * WAVES) void attn_merge_fragments_kernel(KvView kv, Shape sh, const int32_t* __restrict__ active_idx,
+                                                                          int nchunk, const int32_t* __restrict__ ucount,
+                                                                          const int32_t* __restrict__ mrows, Partials part,
+                                                                          float* __restrict__ o_p, float* __restrict__ lse_p,
+                                                                          int rows_known) {
+  __shared__ __attribute__((aligned(16))) float lds[PER > 1 ? WAVES * kFragSlot : 4];
+  const int j = blockIdx.y, b = blockIdx.z, head = b * sh.Hkv + j;
+  const auto counts = [&](int& M, int& live) {
+    M = min(DENSE ? sh.rows_max : min(mrows[head], sh.rows_max), part.rows);
+    const int pages = DENSE ? seq_pages(kv, sh, b) : min(ucount[head], sh.max_pages), pps = kManyRowStage / sh.g;
+    live = min(nchunk, (pages + pps - 1) / pps);
+  };
+  if (!DENSE && !rows_known && (int)blockIdx.x / (D / 8 / (WAVES / PER)) * kPartialTile >= mrows[head]) return;   // surplus workgroup
+  merge_fragments<D, WAVES, PER, KB, true>(sh, DENSE ? nullptr : active_idx, b, j, blockIdx.x, 0, 0, counts, nchunk, part, o_p, lse_p, lds);
+}
+
 // Combine the chunk partials of one query row with the log-sum-exp rule, normalise, and
 // write (o_p, lse_p) at the active token's row.  256 threads = CL chunk lanes x D/4 channel
 // quads: every chunk lane sums its chunks c = lane, lane+CL, ... (independent loads), then
 // the lanes are added in a fixed order, so the result does not depend on scheduling.
 // LOG2: partial maxima are in log2 units (scores scaled by sm_scale*log2(e)) and sums are
 // float; otherwise natural units and double sums (float mode).
-// FRAGS: some heads' partials are laid out by fragments (a template argument: its code and registers would cost
-// the plain form 0.3 us of its 4).
-template <int D, bool LOG2, bool FRAGS>
+// MIXED: heads with more than 64 query rows have partials laid out by fragments; their workgroups take those, a
+// fragment each (four chunks in flight, counts first: the plain form's registers and occupancy).
+template <int D, bool LOG2, bool MIXED>
 __global__ __launch_bounds__(256) void attn_merge_kernel(KvView kv, Shape sh, const int32_t* __restrict__ active_idx,
                                                          const int32_t* __restrict__ active_count,
                                                          const int32_t* __restrict__ sel_count, int cap, int nchunk,
@@ -342,14 +382,13 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(KvView kv, Shape sh, co
   __shared__ Acc lred[CL];
   __shared__ float wmax[CL];
   const int r = blockIdx.x, j = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
-  if constexpr (FRAGS) {   // heads with more than 64 rows, or every head (few_tile)
-    // (no counts prepared: the dense step, every row and every page)
-    const int M = min(mrows ? min(mrows[b * sh.Hkv + j], sh.rows_max) : sh.rows_max, part.rows);
-    if (few_tile == kManyRowStage || M > kUnionRows) {
-      __shared__ __attribute__((aligned(16))) float frag_lds[4 * (256 + 64)];
-      if (r / (D / 8 / fragments_per_block(nchunk)) * kPartialTile >= M) return;
-      const int U = ucount ? min(ucount[b * sh.Hkv + j], sh.max_pages) : seq_pages(kv, sh, b), pps = kManyRowStage / sh.g;
-      merge_fragments<D>(sh, active_idx, b, j, r, M, min(nchunk, (U + pps - 1) / pps), nchunk, part, o_p, lse_p, frag_lds);
+  if constexpr (MIXED) {
+    const int M = min(min(mrows[b * sh.Hkv + j], sh.rows_max), part.rows);
+    if (__builtin_expect(M > kUnionRows, 0)) {
+      __shared__ __attribute__((aligned(16))) float frag_lds[4 * kFragSlot];
+      if (r / (D / 8) * kPartialTile >= M) return;
+      const int U = min(ucount[b * sh.Hkv + j], sh.max_pages), pps = kManyRowStage / sh.g;
+      merge_fragments<D, 4, 4, 4, false>(sh, active_idx, b, j, r, M, min(nchunk, (U + pps - 1) / pps), 0, nchunk, part, o_p, lse_p, frag_lds);
       return;
     }
     if (r >= M) return;
@@ -358,7 +397,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(KvView kv, Shape sh, co
   // workgroup for every possible row: those look at the count first and leave, instead of
   // fetching partials nobody wrote (a block of 224 possible rows with 35 active ones would fetch
   // six times what it needs).
-  if (!rows_known) {
+  if (!MIXED && !rows_known) {
     const int M0 = mrows ? mrows[b * sh.Hkv + j] : (active_idx ? min(active_count[b], sh.B) : sh.B) * sh.G;
     if (r >= M0) return;
   }
@@ -499,21 +538,36 @@ hipError_t launch_attn_merge(hipStream_t st, const KvView& kv, const Shape& sh, 
   // rows_hint: an upper bound on the active rows per KV head the host happens to know (0: none);
   // rows past it get no workgroup (they would only fetch partials speculatively and exit)
   const int rows = rows_hint >= 1 && rows_hint < sh.rows_max ? rows_hint : sh.rows_max;
-  int gx = rows;
-  if (many_tile == kManyRowStage) {   // fragments: see merge_fragments; heads of at most 64 rows: a workgroup per row
-    gx = (rows + kPartialTile - 1) / kPartialTile * (sh.d / 8 / fragments_per_block(nchunk));
-    if (few_tile != kManyRowStage) gx = max(gx, min(rows, kUnionRows));
-  }
-  dim3 grid(gx, sh.Hkv, batch);
   const int32_t* uc = prep && !dense_step ? prep->ucount : nullptr;
   const int32_t* mr = prep && !dense_step ? prep->mrows : nullptr;
   const int known = rows_hint >= 1 || !active_idx;   // (no list of active tokens: every row exists)
-  auto kern = sh.d == 128 ? (!prep ? attn_merge_kernel<128, false, false>
-                             : many_tile == kManyRowStage ? attn_merge_kernel<128, true, true> : attn_merge_kernel<128, true, false>)
-                          : (!prep ? attn_merge_kernel<64, false, false>
-                             : many_tile == kManyRowStage ? attn_merge_kernel<64, true, true> : attn_merge_kernel<64, true, false>);
-  kern<<<grid, 256, 0, st>>>(kv, sh, active_idx, active_count, sel_count, cap, nchunk, uc, mr, part, o_p, lse_p, known, few_tile,
-                             many_tile);
+  const int tiles = (rows + kPartialTile - 1) / kPartialTile, frags = sh.d / 8;
+  if (few_tile == kManyRowStage) {   // every head's partials are laid out by fragments
+    auto launch = [&](auto kern, int per_tile, int waves) {
+      kern<<<dim3(tiles * per_tile, sh.Hkv, batch), 64 * waves, 0, st>>>(kv, sh, active_idx, nchunk, uc, mr, part, o_p, lse_p, known);
+    };
+#define LOSA_FRAGMENTS(W, PER, KB)                                                                                  \
+  launch(sh.d == 128 ? (dense_step ? attn_merge_fragments_kernel<128, W, PER, KB, true>                             \
+                                   : attn_merge_fragments_kernel<128, W, PER, KB, false>)                           \
+                     : (dense_step ? attn_merge_fragments_kernel<64, W, PER, KB, true>                              \
+                                   : attn_merge_fragments_kernel<64, W, PER, KB, false>), frags * PER / W, W)
+    // One or two batches of loads per wavefront, no more wavefronts than that takes (the chip starts one per 10
+    // cycles and die).  By chunks, this form / its neighbour: 2 (128 heads, 128 rows) 6.7 / 10.3 us; 4 5.5 / 7.0;
+    // 16 (16 heads, 256 rows) 7.5 / 10.8; 32 (8 heads) 8.2 / 8.5; 64 (4 heads, 224 rows) 7.0 / 7.2; 256 (1 head) 7.0 / 8.6.
+    if (nchunk <= 4) LOSA_FRAGMENTS(4, 1, 2);
+    else if (nchunk <= 16) LOSA_FRAGMENTS(4, 1, 8);
+    else if (nchunk <= 64) LOSA_FRAGMENTS(4, 4, 8);
+    else LOSA_FRAGMENTS(8, 8, 8);
+#undef LOSA_FRAGMENTS
+    return hipGetLastError();
+  }
+  const bool mixed = many_tile == kManyRowStage;
+  auto kern = sh.d == 128 ? (!prep ? attn_merge_kernel<128, false, false> : mixed ? attn_merge_kernel<128, true, true> : attn_merge_kernel<128, true, false>)
+                          : (!prep ? attn_merge_kernel<64, false, false> : mixed ? attn_merge_kernel<64, true, true> : attn_merge_kernel<64, true, false>);
+  // (mixed: an odd width.  Most of its workgroups leave at once, and with a multiple of 8 the ones that stay meet on a
+  // few of every die's compute units: 14 of 64 rows, 40 heads 6.8 us, of 65 5.0)
+  kern<<<dim3(mixed ? max(min(rows, kUnionRows), tiles * frags) | 1 : rows, sh.Hkv, batch), 256, 0, st>>>(
+      kv, sh, active_idx, active_count, sel_count, cap, nchunk, uc, mr, part, o_p, lse_p, known, few_tile, many_tile);
   return hipGetLastError();
 }
 

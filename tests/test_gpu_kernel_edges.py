@@ -59,6 +59,40 @@ def test_merge_of_partials_laid_out_by_fragments(workgroups):
         r.close()
 
 
+@pytest.mark.parametrize("chunks", [1, 2, 4, 5, 8, 9, 16, 17, 31, 64, 65, 100, 300])
+def test_merge_by_fragments_at_the_edges_of_its_forms(chunks):
+    """Chunk counts around the lines between the forms (4, 16, 64) and around what a form's wavefronts hold at a
+    time, next to sequences that leave most chunks unwritten.  The workspace starts as NaN: a slot nobody wrote must
+    not be looked at."""
+    w = workload(19, 4, 1, 64, 16, (64 * 600 + 5, 64 * 3, 1), 19)
+    r = Rig(w, tuning={L.LOSA_TUNE_ATTN_WORKGROUPS: 3 * chunks})
+    r.ctx.workspace.fill_(255)
+    try:
+        check_sparse_attn(r, 0, None, None, dense=True)
+        check_page_bounds(r)
+        run_steps_end_to_end(r, [1], orc.SEL_TOPK, 18.0, w.topk_pages)      # 72 rows: the counts come from the device
+    finally:
+        r.close()
+
+
+@pytest.mark.parametrize("workgroups", [4, 20, 72, 1024])
+@pytest.mark.parametrize("B,G,d,g", [(33, 4, 128, 16), (32, 8, 64, 32), (17, 5, 128, 32)])
+def test_merge_of_heads_with_few_and_many_rows_in_one_launch(B, G, d, g, workgroups):
+    """A count only the device knows: heads of up to 64 rows and of more in one launch, none active in one sequence."""
+    w = workload(B, G, 1, d, g, (64 * 33 + 1, 700, 64 * 20, 1500), B)
+    r = Rig(w, tuning={L.LOSA_TUNE_ATTN_WORKGROUPS: workgroups})
+    r.ctx.workspace.fill_(255)
+    try:
+        check_page_bounds(r)
+        rng = np.random.Generator(np.random.Philox(B + workgroups))
+        lists = {(b, 0): np.sort(rng.permutation(P)[:max(1, P - 2)]).astype(np.int32) for b, P in enumerate(w.pages_per_seq)}
+        for counts in ((64 // G, 64 // G + 1, B, 0), (B, 1, 64 // G + 2, B - 1)):
+            active = [np.sort(rng.permutation(B)[:n]).astype(np.int32) for n in counts]
+            check_sparse_attn(r, 1, active, lists)
+    finally:
+        r.close()
+
+
 @pytest.mark.parametrize("B,G,d,g,n,workgroups", [
     (8, 5, 128, 16, 3, 256),     # 15 rows: one short of a row block
     (8, 2, 64, 32, 8, 256),      # 16 rows, pages of two 16-token tiles
