@@ -196,7 +196,6 @@ Layout make_layout(const losa_config* c) {
   L.active_count = cv.take((size_t)c->max_batch * 4);
   L.scores = cv.take(heads * rows_max * c->max_pages_per_seq * 4);
   L.rowmaps = cv.take(heads * rows_max * words * 4);
-  L.union_bits = cv.take(heads * (size_t)union_words(c->max_pages_per_seq) * 4);
   L.tickets = cv.take(heads * 4);
   L.sel_pages = cv.take(heads * c->max_pages_per_seq * 4);
   L.sel_count = cv.take(heads * 4);
@@ -208,6 +207,7 @@ Layout make_layout(const losa_config* c) {
   L.ucount = cv.take(heads * 4);
   L.mrows = cv.take(heads * 4);
   L.seq_tickets = cv.take((size_t)c->max_batch * 4);
+  L.union_bits = cv.take(heads * (size_t)union_words(c->max_pages_per_seq) * 4);
   L.total = cv.off;
   return L;
 }
@@ -747,7 +747,7 @@ losa_status losa_step(losa_ctx* ctx, void* stream, const losa_kv* kv, int32_t st
   const bool union_counted = fuse_prepare && counted && rows_upper >= 1 && rows_upper <= 64 && ctx->union_in_attention;
   const bool union_on_device = fuse_prepare && !counted && ctx->sh.rows_max <= 256 && ctx->union_in_attention;
   const bool union_in_attn = union_counted || union_on_device;
-  const UnionInKernel uni{ctx->union_bits, sc, union_on_device};
+  const UnionInKernel uni{ctx->union_bits, sc, union_words(ctx->sh.max_pages), union_copy_words(msp), union_on_device};
   s = score_pages_impl(ctx, st, view, kv->batch, msp, q, ctx->active_idx, ctx->active_count, topk_pages, nullptr,
                        ctx->sel_pages, sc, cap, fuse_prepare, rows_upper, rank_in_scores ? &ranking : nullptr,
                        union_in_attn ? ctx->union_bits : nullptr);

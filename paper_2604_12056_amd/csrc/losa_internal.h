@@ -64,12 +64,31 @@ struct AttnPrepared {
 // head's row-tile count from the device (rows_on_device).
 constexpr int kUnionRows = 64;   // the most rows the split-pages shape serves
 struct UnionInKernel {
-  const uint32_t* bits;      // [heads][union_words()] union of the head's picks; NULL: use AttnPrepared::entries
+  const uint32_t* bits;      // [heads][union_words()] union of the head's picks, in copies; NULL: use AttnPrepared::entries
   int32_t* sel_count;        // [heads] out: pages in the union (written by the head's first workgroup)
+  int stride, copy_words;    // union_words(), union_copy_words()
   bool rows_on_device;       // host side only: launch the form that sizes itself by AttnPrepared::mrows
 };
-// 32-bit words of one (sequence, KV head) union bitmap: whole 16-byte pieces
-__host__ __device__ inline int union_words(int max_pages) { return ((max_pages + 31) / 32 + 3) & ~3; }
+// A head's union bitmap.  Up to 1024 pages it is kept in copies, row r in copy r mod their number, that fill
+// kUnionSpread words: the rows' atomics on one word come one after the other, and with a short prefix they all fall
+// on the same few words (2 x 378-728 tokens, 32 rows: selection 7.4 us with one copy, 6.3 with 16; where a row
+// does not OR at all, 6.3).  The attention kernel reads all of them with the four loads it has for 8192 pages.
+// Beyond, the words are many enough: at 2048 pages four copies cost 0.5 us more than they save (4 x 65536 tokens).
+constexpr int kUnionSpread = 256;
+constexpr int kMostCopiedWords = 32;
+// words of one copy, for the pages the launch was sized for (KvView::seq_page_limit)
+__host__ __device__ inline int union_copy_words(int pages) {
+  const int words = (pages + 31) / 32;
+  return words <= 16 ? 16 : words <= kMostCopiedWords ? kMostCopiedWords : (words + 3) & ~3;
+}
+__host__ __device__ inline int union_copies(int copy_words) {
+  return copy_words <= kMostCopiedWords ? kUnionSpread / copy_words : 1;
+}
+// words per head, whatever the launch
+__host__ __device__ inline int union_words(int max_pages) {
+  const int words = union_copy_words(max_pages);
+  return words > kUnionSpread ? words : kUnionSpread;
+}
 
 // ---- losa_api.hip
 // Sets `n` ints to zero with a small fill kernel (safe to record into a captured graph).

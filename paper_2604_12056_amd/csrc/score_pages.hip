@@ -25,12 +25,13 @@ struct ScoreAux {
   int32_t* sel_count;
   int32_t* ucount;   // nullable
   int32_t* mrows;    // nullable
-  uint32_t* union_bits;   // nullable: union bitmap per head, cleared here for the selection to OR into
-  int union_len;          // its words per head
+  uint32_t* union_bits;   // nullable: union bitmaps, cleared here for the selection to OR into
+  int union_stride;       // words per head ...
+  int union_len;          // ... of which this launch uses so many
   // every thread of one workgroup per head
   __device__ void clear_union(int head) const {
     if (union_bits)
-      for (int w = threadIdx.x; w < union_len; w += 256) union_bits[(size_t)head * union_len + w] = 0u;
+      for (int w = threadIdx.x; w < union_len; w += 256) union_bits[(size_t)head * union_stride + w] = 0u;
   }
   __device__ void reset(int head, int M) const {
     tickets[head] = 0;
@@ -383,7 +384,10 @@ struct SelectOut {
   const void* q;        // query tensor (for the gather into prep.q_act)
   const int32_t* active_idx;
   bool rows_known;      // the grid has exactly one workgroup per existing row (+ the gather workgroup)
-  uint32_t* union_bits; // non-NULL: heads with at most kUnionRows rows only OR their picks into this bitmap
+  // union_words() | words of a copy << 10 | (copies - 1) << 20; beside the pointer, so that it arrives with it: fetched
+  // where it is used, it costs a scalar round trip (0.3 us)
+  uint32_t union_shape;
+  uint32_t* union_bits; // non-NULL: heads with at most kUnionRows rows only OR their picks into a copy of this bitmap
                         // ([heads, union_words()], cleared by the scoring kernel): no hand-over, no list
 };
 
@@ -740,8 +744,9 @@ __global__ __launch_bounds__(NT) void select_pages_kernel(KvView kv, Shape sh, c
     uint32_t* myrow = out.rowmaps + ((size_t)head * sh.rows_max + r) * words;
     if (out.union_bits && M <= kUnionRows) {
       // read by the next launch; nothing waits for the atomics here (an OR has no order)
-      uint32_t* u = out.union_bits + (size_t)head * union_words(sh.max_pages);
-      for (int w = tid; w < min(words, WORDS); w += NT)
+      const int copy_words = (int)(out.union_shape >> 10) & 0x3FF;
+      uint32_t* u = out.union_bits + (size_t)head * (out.union_shape & 0x3FF) + (r & (int)(out.union_shape >> 20)) * copy_words;
+      for (int w = tid; w < min(copy_words, min(words, WORDS)); w += NT)
         if (rowbits[w]) __hip_atomic_fetch_or(&u[w], rowbits[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     } else {
       for (int w = tid; w < words; w += NT)
@@ -960,8 +965,9 @@ hipError_t launch_page_scores(hipStream_t st, int dtype, const KvView& kv, const
                               uint32_t* union_bits) {
   if (batch <= 0) return hipSuccess;
   if (union_bits && dtype != LOSA_BF16) return hipErrorInvalidValue;
+  const int copy_words = union_copy_words(max_seq_pages);
   ScoreAux aux{tickets, sel_count, prep ? prep->ucount : nullptr, prep ? prep->mrows : nullptr, union_bits,
-               union_words(sh.max_pages)};
+               union_words(sh.max_pages), union_copies(copy_words) * copy_words};
   RankArgs ra{nullptr, 0, 0, 0.f, nullptr, nullptr, nullptr};
   if (ranking) {
     if (dtype != LOSA_BF16 || sh.B > kRankTokens) return hipErrorInvalidValue;
@@ -1005,6 +1011,9 @@ hipError_t launch_select_pages(hipStream_t st, const KvView& kv, const Shape& sh
   if (union_bits && (!prep || topk_out)) return hipErrorInvalidValue;
   SelectOut out;
   out.union_bits = union_bits;
+  const int copy_words = union_copy_words(max_seq_pages);
+  static_assert(kMaxSelectPages / 32 < 1024, "union_shape holds 10 bits of words");
+  out.union_shape = (uint32_t)union_words(sh.max_pages) | (uint32_t)copy_words << 10 | (uint32_t)(union_copies(copy_words) - 1) << 20;
   out.topk_out = topk_out;
   out.sel_pages = sel_pages;
   out.sel_count = sel_count;

@@ -143,7 +143,8 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
   if constexpr (UNION) {
     // The four wavefronts share the fetch of the page table (8 KiB; once per wavefront it would cost the
     // compute unit four times the traffic): a quarter each, one barrier.
-    const int words = (sh.max_pages + 31) >> 5;
+    const bool copies = uni.copy_words <= kMostCopiedWords;
+    const int words = copies ? kUnionSpread : uni.copy_words;
     // the head's page table, written by the selection kernel at an address known here: its first
     // kTablePagesInLds entries go to LDS, so that resolving a page needs no dependent load
     // (pages beyond them are looked up in memory)
@@ -154,8 +155,9 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
       const int i4 = min(wave * (64 * TPW) + lane + 64 * k, max(sh.max_pages / 4 - 1, 0));   // clamped inside the head's table
       tabv[k] = reinterpret_cast<const u32x4v_t*>(ent)[i4];
     }
-    // the head's union bitmap: up to four words per lane in flight (8192 pages are one memory round trip)
-    const uint32_t* head_bits = uni.bits + (size_t)head * union_words(sh.max_pages);
+    // the head's union bitmap: up to four words per lane in flight (8192 pages are one memory round trip); copies of
+    // 16 or 32 words lie one behind the other and are ORed in the lanes
+    const uint32_t* head_bits = uni.bits + (size_t)head * uni.stride;
     constexpr int kGroupsInFlight = 4;
     uint32_t ub[kGroupsInFlight];
 #pragma unroll
@@ -165,8 +167,19 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
     const int P = seq_pages(kv, sh, b);
     u_words = (P + 31) >> 5;
     __syncthreads();
+    if (copies) {
+      uint32_t all = (ub[0] | ub[1]) | (ub[2] | ub[3]);
+      if (uni.copy_words == 16) {
+        all = across_rows(all, [](uint32_t x, uint32_t y) { return x | y; });
+      } else {
+        const auto sw = __builtin_amdgcn_permlane32_swap(all, all, false, false);
+        all = sw[0] | sw[1];
+      }
+      ub[0] = all;   // (lanes past the copy's words hold repeats: past u_words, so cleared below)
+    }
+    const int ranked = copies ? 64 : words;
     int total = 0;
-    for (int g0 = 0; g0 < words; g0 += 64 * kGroupsInFlight) {
+    for (int g0 = 0; g0 < ranked; g0 += 64 * kGroupsInFlight) {
       if (g0) {
 #pragma unroll
         for (int u = 0; u < kGroupsInFlight; ++u)
@@ -174,7 +187,7 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
       }
 #pragma unroll
       for (int u = 0; u < kGroupsInFlight; ++u) {
-        if (g0 + 64 * u >= words) break;   // uniform
+        if (g0 + 64 * u >= ranked) break;   // uniform
         const int w = g0 + 64 * u + lane;
         uint32_t acc = ub[u];
         // pages past the sequence's last one are never picked; the masks only keep a stale bitmap harmless

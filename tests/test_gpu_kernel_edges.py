@@ -8,6 +8,7 @@ import torch
 from oracle import losa_oracle as orc
 from paper_2604_12056_amd import binding as L
 from paper_2604_12056_amd import synth
+from paper_2604_12056_amd.device_inputs import config_of
 
 from parity_util import Rig, check_page_bounds, check_sparse_attn, run_steps_end_to_end
 
@@ -278,3 +279,28 @@ def test_float_mode_keeps_values_near_the_end_of_the_range(d, page):
             assert np.abs(lse_p.cpu().numpy().reshape(-1) - lse).max() <= 1e-4
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("page,limit,reserved", [
+    (16, 5, 5), (16, 512, 512),              # copies of 16 words, the last prefix for them ...
+    (16, 513, 513), (32, 1024, 1024),        # ... of 32 ...
+    (16, 1025, 1025), (16, 2048, 2048), (16, 2049, 2049),   # ... and one bitmap, no copies
+    (16, 40, 3000), (16, 600, 600 + 4096)])  # a context reserved for more pages than the call says it uses
+def test_union_at_the_edges_of_its_copies(page, limit, reserved):
+    """Every number of rows per copy (the rows of 1, 7 and 16 tokens, 4 heads each, over 16, 8 or 1 copies), the
+    count known to the host and to the device only; every word of the bitmap gets a pick (the budget is a third)."""
+    w = workload(16, 4, 1, 64, page, (limit * page - 3, max(1, limit // 3) * page + 1, 1), 16, topk=max(1, limit // 3), T=5)
+    r = Rig(w)
+    r.ctx.close()
+    cfg = config_of(w, max_topk_pages=w.max_pages)
+    cfg.max_pages_per_seq = reserved
+    r.ctx = L.losa_create(cfg, "cuda:0")
+    r.ctx.workspace.fill_(255)
+    try:
+        check_page_bounds(r)
+        run_steps_end_to_end(r, range(1), orc.SEL_TOPK, 1.0, w.topk_pages)
+        for t, n in ((1, 1.0), (2, 7.0), (3, 16.0)):
+            run_steps_end_to_end(r, [t], orc.SEL_TOPK, n, w.topk_pages)
+        run_steps_end_to_end(r, [4], orc.SEL_MASS, 0.5, w.topk_pages)
+    finally:
+        r.close()
