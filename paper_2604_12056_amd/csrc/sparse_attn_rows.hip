@@ -164,9 +164,11 @@ __device__ __forceinline__ void attn_rows_body(int nchunk, int row_group, int j,
     v_lds[i] = Img::kValBase + (tok / 32) * Img::kValBlock + ((ch / 32) * 4 + (tok & 31) / 8) * Img::kValStrip + (ch & 31) * 16;
   }
   // stage n of this workgroup -> registers.  A stage past the list's end is requested all the same (so that the
-  // number of loads in flight at every wait is a compile-time constant): its entries decode to page 0.
+  // number of loads in flight at every wait is a compile-time constant): its entries decode to page 0, of which
+  // every lane then reads the first 16 bytes (a workgroup has three such stages, however few it has of its own).
   auto gload = [&](Stage& s, int n) {
     const int slot = (n * PPS) & 63;
+    const uint32_t real = n < ns ? ~0u : 0u;
 #pragma unroll
     for (int k = 0; k < PPS; ++k) s.nv[k] = __builtin_amdgcn_readlane(pg_valid, slot + k);
 #pragma unroll
@@ -174,7 +176,7 @@ __device__ __forceinline__ void attn_rows_body(int nchunk, int row_group, int j,
       // scalar base address + one lane offset: no vector address arithmetic in the loop
       const int ph = __builtin_amdgcn_readlane(pg_phys, slot + (i * 512 + wave * 64) / PPP);
       const size_t at = ((size_t)ph * sh.Hkv + j) * (PPP * 16);
-      const uint32_t lane_off = (uint32_t)((i * 512 + tid) % PPP) * 16u;
+      const uint32_t lane_off = (uint32_t)((i * 512 + tid) % PPP) * 16u & real;
       const unsigned char* kp = reinterpret_cast<const unsigned char*>(kv.k_pages) + at;
       const unsigned char* vp = reinterpret_cast<const unsigned char*>(kv.v_pages) + at;
       s.k[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4v_t*>(kp + lane_off));
@@ -339,9 +341,11 @@ __device__ __forceinline__ void attn_rows_body(int nchunk, int row_group, int j,
   };
   // One stage: kf holds the keys of its first block on entry and those of the next stage's on exit.  The barrier
   // stands before the last value products: they cover the latency of the next stage's first reads, and
-  // whatever of the image is still read behind it is safe with three images.
+  // whatever of the image is still read behind it is safe with three images.  The workgroup's last stage has no
+  // next one to stage and to wait for (with a few pages it is also the first).
   bf16x8_t kf[KS];
-  auto compute = [&](int cur, int next, const int (&nv)[PPS], Stage& s, int n_request) {
+  auto compute = [&](auto last_c, int cur, int next, const int (&nv)[PPS], Stage& s, int n_request) {
+    constexpr bool LAST = decltype(last_c)::value;
     const unsigned char* kb = lds + cur + lane_k;
     const unsigned char* vb = lds + cur + lane_v;
     const unsigned char* kb_next = lds + next + lane_k;
@@ -356,7 +360,7 @@ __device__ __forceinline__ void attn_rows_body(int nchunk, int row_group, int j,
       u32x4v_t vf1[2][CB];
       score_products(kf, s0);
       read_keys(kf1, kb + Img::kKeyBlock);
-      lstore(s, next);
+      if constexpr (!LAST) lstore(s, next);
       if (!full) mask_tail(s0, 0, nv);
       score_products(kf1, s1);
       sum0 = numerators(s0, p0);
@@ -367,20 +371,24 @@ __device__ __forceinline__ void attn_rows_body(int nchunk, int row_group, int j,
       sum1 = numerators(s1, p1);
       read_values(vf1, vb + Img::kValBlock);
       settle(s1, p1, sum1);
-      __syncthreads();
+      if constexpr (!LAST) __syncthreads();
       value_products(vf1, p1);
-      read_keys(kf, kb_next);
-      gload(s, n_request);
+      if constexpr (!LAST) {
+        read_keys(kf, kb_next);
+        gload(s, n_request);
+      }
     } else {
       score_products(kf, s0);
       read_values(vf, vb);
-      lstore(s, next);
+      if constexpr (!LAST) lstore(s, next);
       if (!full) mask_tail(s0, 0, nv);
       sum0 = numerators(s0, p0);
       settle(s0, p0, sum0);
-      __syncthreads();
-      read_keys(kf, kb_next);
-      gload(s, n_request);
+      if constexpr (!LAST) {
+        __syncthreads();
+        read_keys(kf, kb_next);
+        gload(s, n_request);
+      }
       value_products(vf, p0);
     }
   };
@@ -417,7 +425,7 @@ __device__ __forceinline__ void attn_rows_body(int nchunk, int row_group, int j,
     clear_tail(s);
     entries_for(n + 1 + PD);
     if constexpr (decltype(with_rows)::value) {
-      compute(cur, next, nv_cur, s, n + 1 + PD);
+      compute(std::false_type{}, cur, next, nv_cur, s, n + 1 + PD);
     } else {   // staging only: this wavefront has no rows
       lstore(s, next);
       gload(s, n + 1 + PD);
@@ -430,18 +438,17 @@ __device__ __forceinline__ void attn_rows_body(int nchunk, int row_group, int j,
   };
   static_assert(PD == 2, "the loop below is unrolled over the register sets");
   if (has_rows) {
-    for (int n = 0;; n += PD) {
+    for (int n = 0; n + 1 < ns; n += PD) {
       iterate(std::true_type{}, st[1], n);
-      if (n + 1 >= ns) break;
+      if (n + 2 >= ns) break;
       iterate(std::true_type{}, st[0], n + 1);
-      if (n + 2 >= ns) break;
     }
+    compute(std::true_type{}, cur, next, nv_cur, st[0], 0);
   } else {
-    for (int n = 0;; n += PD) {
+    for (int n = 0; n + 1 < ns; n += PD) {
       iterate(std::false_type{}, st[1], n);
-      if (n + 1 >= ns) break;
-      iterate(std::false_type{}, st[0], n + 1);
       if (n + 2 >= ns) break;
+      iterate(std::false_type{}, st[0], n + 1);
     }
   }
 
@@ -462,7 +469,7 @@ __device__ __forceinline__ void attn_rows_body(int nchunk, int row_group, int j,
     // O lane-linear, 16 bytes per lane, then reference and sum per row
     static_assert(kImages * Img::kBytes >= 4 * (CB * 4 * 1024 + 2 * 32 * 4), "the hand-over does not fit the stage buffers");
     float* so = reinterpret_cast<float*>(lds) + row_wave * (CB * 4 * 256 + 64);
-    __syncthreads();   // (the last stage_tail reads an image nobody needs)
+    __syncthreads();   // (the last stage's image is read up to here)
     if (block0 && has_rows) {
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb)
