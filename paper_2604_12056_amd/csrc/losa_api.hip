@@ -369,7 +369,7 @@ losa_status sparse_attn_impl(losa_ctx* ctx, hipStream_t st, const KvView& kv, in
   const bool both_shapes = mfma && !hinted && ctx->sh.rows_max > 64 && ctx->sh.rows_max <= 256;
   // matrix-core kernel: up to 64 rows ride in one workgroup; more rows -> groups of 4 x 64 rows
   // (float mode: a workgroup per 16 rows)
-  const int row_groups = mfma ? (rows_upper <= 64 ? 1 : (ctx->sh.rows_max + 255) / 256) : (rows_upper + 15) / 16;
+  const int row_groups = mfma ? (rows_upper + 255) / 256 : (rows_upper + 15) / 16;
   // rows > 64 take the shared-stage kernel (unless switched off); it alone serves the launch when the host
   // knows that no head can have fewer, or when the two shapes do not go together
   const bool rows_kernel = mfma && ctx->shared_tiles && rows_upper > 64;

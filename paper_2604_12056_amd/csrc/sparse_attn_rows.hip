@@ -563,7 +563,7 @@ static hipError_t launch_rows(hipStream_t st, const KvView& kv, const Shape& sh,
     if (e != hipSuccess) return e;
     attr_set = true;
   }
-  const int row_groups = (sh.rows_max + kRowGroup - 1) / kRowGroup;
+  const int row_groups = (part.rows + kRowGroup - 1) / kRowGroup;   // part.rows: what the host knows the count cannot exceed
   const float scale_log2e = sh.sm_scale * 1.4426950408889634f;
   dim3 grid(nchunk, sh.Hkv * row_groups, batch);
   if (e0 && e1)   // events bound to this dispatch: they read the kernel's own begin and end

@@ -48,6 +48,19 @@ def test_many_row_kernel_at_the_edges_of_its_row_counts(B, G, d, g, n, half_valu
         r.close()
 
 
+@pytest.mark.parametrize("n", [10, 36, 37, 64])     # 70, 252 | 259, 448 rows: one row group | two
+def test_counted_rows_of_a_block_with_two_row_groups(n):
+    """64 tokens x 7 heads: the grid has the row groups the count needs, not those of the whole block."""
+    w = workload(64, 7, 1, 64, 16, (64 * 40 + 9, 700, 1), n)
+    r = Rig(w)
+    r.ctx.workspace.fill_(255)
+    try:
+        check_page_bounds(r)
+        run_steps_end_to_end(r, range(2), orc.SEL_TOPK, float(n), w.topk_pages)
+    finally:
+        r.close()
+
+
 @pytest.mark.parametrize("workgroups", [8, 9, 12, 64, 1024])
 def test_merge_of_partials_laid_out_by_fragments(workgroups):
     """Chunk counts around the line between the merge's two forms (up to 8 chunks, more), and more chunks than
