@@ -111,8 +111,11 @@ def _stream(stream) -> Optional[int]:
     global _current_raw_stream
     if _current_raw_stream is None:
         import torch
-        current_device, raw_stream = torch.cuda.current_device, torch._C._cuda_getCurrentRawStream
-        _current_raw_stream = lambda: raw_stream(current_device())
+        current_device, raw_stream = torch.cuda.current_device, getattr(torch._C, "_cuda_getCurrentRawStream", None)
+        if raw_stream is not None:
+            _current_raw_stream = lambda: raw_stream(current_device())
+        else:   # not part of torch's public interface: without it, the public way
+            _current_raw_stream = lambda: torch.cuda.current_stream().cuda_stream
     return _current_raw_stream() or None
 
 

@@ -134,3 +134,20 @@ def test_bench_refuses_more_than_one_gpu():
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True,
                        timeout=60)
     assert r.returncode == 2 and "one GPU" in r.stderr and r.stdout.strip() == ""
+
+
+@pytest.mark.parametrize("private_getter", [True, False])
+def test_the_current_stream_is_asked_for_at_every_call(monkeypatch, private_getter):
+    """With torch's private getter of a stream's handle and, where a torch does not have it, without."""
+    import torch
+    handles = iter((11, 12, 21, 0))
+    stream = type("Stream", (), {"cuda_stream": property(lambda self: next(handles))})()
+    monkeypatch.setattr(binding, "_current_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: 3)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: stream)
+    if private_getter:
+        monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda device: next(handles) if device == 3 else None, raising=False)
+    else:
+        monkeypatch.delattr(torch._C, "_cuda_getCurrentRawStream", raising=False)
+    assert [binding._stream(None), binding._stream(None), binding._stream(7), binding._stream(None)] == [11, 12, 7, 21]
+    assert binding._stream(None) is None and binding._stream(0) is None     # the default stream
