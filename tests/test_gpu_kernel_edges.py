@@ -152,6 +152,10 @@ def test_block_merge_at_the_edges_of_row_and_key_tiles(B, Hq, Hkv, d, batch):
                                         lse_p.numpy(), B)
     for got, want in zip((out, o_b, lse_b), ref):
         assert np.abs(got.cpu().numpy() - want).max() <= 2e-2
+    # Probabilities enter as a bfloat16 pair: high part truncated, remainder (below 2^-7 of it) rounded to 8 bits, so off
+    # by at most 2^-16 each, and an output by 2^-16 of the largest value; exponentials and sums in float add less than 2e-5.
+    for got, want in zip((out, o_b, lse_b), ref):
+        assert np.abs(got.cpu().numpy() - want).max() <= 2.0 ** -16 * float(v.float().abs().max()) + 2e-5
 
 
 @pytest.mark.parametrize("B", [16, 64])
