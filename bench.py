@@ -10,7 +10,7 @@ every step reads its pages from HBM rather than from the 256 MiB last-level cach
 
 Prints ONE JSON line.  `value` = microseconds per step per layer (lower is better), inputs
 resident in HBM.  `roofline` is for the dominant kernel (the split-K attention kernel, which in
-sparse steps also builds the union of the picked pages from the per-row bitmaps while it
+sparse steps also ranks the union of the picked pages, one bitmap per head, while it
 starts up): algorithmic bytes (K+V of the pages touched plus the active query rows; the
 split-K partials it writes are overhead and not counted) divided by the kernel's mean
 duration from HIP events bound to its dispatch, in further passes over the same steps (the

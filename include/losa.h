@@ -232,8 +232,9 @@ losa_status losa_block_merge(losa_ctx* ctx, void* stream, int32_t batch, const v
 
 /* Tuning switches of a context: how the launches are shaped, never what they compute: every
  * decision (active set, picked pages, unions) is the same for every setting, and so is every
- * output bit except under the last two switches, which change the rounding order of the attention
- * over more than 64 query rows per KV head (outputs stay inside the bounds stated for losa_sparse_attn).
+ * output bit except under the first switch, which changes how the prefix is split and so the order of
+ * the attention's sums, and the last two, which change the rounding of the attention over more
+ * than 64 query rows per KV head (outputs stay inside the bounds stated for losa_sparse_attn).
  * Each has a default chosen by measurement on MI355X; tests
  * use them to drive the code paths a workload of their size would not reach.  A value takes
  * effect with the next call on the context.
@@ -250,12 +251,13 @@ losa_status losa_block_merge(losa_ctx* ctx, void* stream, int32_t batch, const v
  *   LOSA_TUNE_SHARED_TILES      : 1 (default): above 64 query rows per KV head eight wavefronts share
  *                                 each key/value tile through LDS; 0: four independent wavefronts
  *   LOSA_TUNE_HALF_PRECISION_VALUES: 1 (default): in that shared-tile form the value product runs in
- *                                 half precision: probabilities rounded once to 11 significant bits
- *                                 (output error up to 2^-10 of the largest |v| a row attends to, in
- *                                 practice a tenth of that), values converted bfloat16 -> half, which
- *                                 is exact up to |v| = 65504 and saturates there; 0: probabilities as
- *                                 a bfloat16 pair (2^-16) and values in bfloat16's own range, at about
- *                                 a fifth more time.  Steps with up to 64 rows always take the pair. */
+ *                                 half precision: probabilities rounded once to 11 significant bits and
+ *                                 normalised with their rounded sum (output error up to 2^-11 of the
+ *                                 weighted mean distance of a row's values from its output; lse_p from the
+ *                                 unrounded sum), values converted bfloat16 -> half, which is exact up to
+ *                                 |v| = 65504 and saturates there; 0: probabilities as a bfloat16 pair
+ *                                 (2^-16) and values in bfloat16's own range, at a
+ *                                 tenth (128 rows) to a fifth (256) more time.  Steps with up to 64 rows always take the pair. */
 typedef enum {
   LOSA_TUNE_ATTN_WORKGROUPS = 0,
   LOSA_TUNE_SELECT_ROUND = 1,

@@ -482,7 +482,7 @@ losa_status losa_create(const losa_config* cfg, void* workspace, size_t workspac
   ctx->target_workgroups = kTargetWorkgroups;
   ctx->rank_in_scores = true;
   ctx->select_round = 0;
-  ctx->score_round = 5L * 256;   // about five scoring workgroups per CU are resident at once
+  ctx->score_round = 5L * 256;   // (four scoring workgroups per CU are resident at once; a quarter more start as those end)
   ctx->union_in_attention = true;
   ctx->shared_tiles = true;
   ctx->half_values = true;
@@ -740,7 +740,7 @@ losa_status losa_step(losa_ctx* ctx, void* stream, const losa_kv* kv, int32_t st
   const bool counted = mode == LOSA_SEL_TOPK || mode == LOSA_SEL_FRACTION;
   const int rows_upper = counted ? select_count(ctx, (int)mode, param) * ctx->sh.G : 0;
   // Up to 64 query rows per KV head: the attention workgroups build the union of the per-row picks
-  // themselves, and the selection kernel ends with the row bitmaps.  With a count only the device
+  // themselves, and the selection kernel ends with ORing them into the head's bitmap.  With a count only the device
   // knows, the selection kernel does so for the heads it finds with at most 64 rows, and the attention
   // launch for those heads takes their row-tile counts from the device; heads with more rows get the
   // union list and the many-row launch as before.

@@ -275,7 +275,7 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape 
   // each row once instead of once per wavefront.  A row is D bfloat16 plus 16 bytes of padding:
   // the 16 lanes that read the same 16-byte column of 16 consecutive rows then fall on
   // different banks.
-  constexpr int kRows = 64, VPR = D / 8, STRIDE = D * 2 + 16;   // bytes; 64 rows cover the usual active sets in one go and keep LDS small enough for 8 workgroups per CU
+  constexpr int kRows = 64, VPR = D / 8, STRIDE = D * 2 + 16;   // bytes; 64 rows cover the usual active sets in one go; with 128 channels 38 KiB of LDS, four workgroups per CU
   // Staged already split by sign (score = q+ . max + q- . min): the split is done once per
   // workgroup by the staging threads, not once per wavefront, tile and row tile.
   __shared__ __attribute__((aligned(16))) unsigned char qs[2][kRows * STRIDE];   // [0]: q+, [1]: q-

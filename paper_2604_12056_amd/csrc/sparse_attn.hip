@@ -17,8 +17,8 @@
 // Keys of the next 16 tokens are requested when the score products of the current ones have been issued, values
 // when the value products have: one register set each, and the latency lies under the other half.
 //
-// What bounds it: the float64 products; a register-only loop of them reaches 69 TFLOP/s, and the
-// wavefronts' own start and end.  42 rows x 4 KV heads over 0.9 of 8001 tokens: 25 us (10 of them products;
+// What bounds it: the float64 products (a register-only loop of them reaches 49 TFLOP/s) and the
+// wavefronts' own start and end.  42 rows x 4 KV heads over 0.9 of 8001 tokens: 25 us (14 of them products;
 // 108 us on the vector ALUs with keys and values staged through LDS).
 //
 // attn_merge combines the chunks of a row in chunk order with the log-sum-exp rule the paper uses to merge

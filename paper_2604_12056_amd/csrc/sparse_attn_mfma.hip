@@ -771,7 +771,7 @@ static hipError_t launch_dg(hipStream_t st, const KvView& kv, const Shape& sh, i
                                                               m_lo, m_hi, *uni);
     return hipGetLastError();
   }
-  if (uni && uni->bits) {   // the kernel builds the union from the row bitmaps itself
+  if (uni && uni->bits) {   // the kernel ranks the head's union bitmap itself
     if (rows_upper <= 16) return launch_one<D, GP, 1, true, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi, *uni);
     if (rows_upper <= 32) return launch_one<D, GP, 2, true, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi, *uni);
     if (rows_upper <= 48) return launch_one<D, GP, 3, true, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi, *uni);

@@ -20,14 +20,12 @@
 // of the second product, and its A operand is one 16-byte piece of a channel-major value page.
 //
 // What bounds it.  At 256 rows matrix products, exponentials, LDS traffic and the HBM stream each take time
-// that adds up (stream alone 170 us, arithmetic alone 233 us, both 315 us for 1.07 GB of keys and values): the
-// clock falls to about 1.9 GHz under this load, i.e. the chip is at its power limit, where a register-only loop
-// of these products reaches 1750 TFLOP/s.  At up to 128 rows it runs at the HBM stream (5 TB/s).  Scheduling
+// that adds up: of 545 thousand cycles for 256 rows over 4 x 65536 tokens the matrix cores are busy 0.48, the vector ALUs'
+// issue port 0.49, both at once 0.17.  At up to 128 rows it runs at the HBM stream (5 TB/s).  Scheduling
 // hints (interleaving products with vector instructions) and wavefront priorities were measured and
 // change nothing.  Whole dense step against the kernel on 16x16x32 products with LDS tiles of 32 tokens:
-// 4 x 65536 tokens, 8 KV heads, 256 rows 363 -> 327 us; 16 sequences of 8k-32k, 4 KV heads, 224 rows
-// 328 -> 243 us; 32768 tokens, 224 rows 42.9 -> 40.6 us; the sparse step of 128 rows over 0.68 of
-// 4 x 65536 tokens 229 -> 193 us.
+// 4 x 65536 tokens, 8 KV heads, 256 rows 363 -> 329 us; the sparse step of 128 rows over 0.68 of 4 x 65536
+// tokens 230 -> 189 us (both with the normaliser's own sum, 2 % of the kernel).
 //
 // Memory to LDS.  A stage's keys and values are fetched once per workgroup with perfectly linear 16-byte
 // streaming loads (a page-head tile is contiguous; without the streaming hint +5%), two stages ahead in
