@@ -366,9 +366,9 @@ __global__ __launch_bounds__(64 * WAVES) void attn_merge_fragments_kernel(KvView
 // the lanes are added in a fixed order, so the result does not depend on scheduling.
 // LOG2: partial maxima are in log2 units (scores scaled by sm_scale*log2(e)) and sums are
 // float; otherwise natural units and double sums (float mode).
-// MIXED: heads with more than 64 query rows have partials laid out by fragments; their workgroups take those, a
-// fragment each (four chunks in flight, counts first: the plain form's registers and occupancy).
-template <int D, bool LOG2, bool MIXED>
+// MIXED (0: no): heads with more than 64 query rows have partials laid out by fragments; their workgroups take those, MIXED
+// wavefronts each (four chunks in flight, counts first: the plain form's registers and occupancy).
+template <int D, bool LOG2, int MIXED>
 __global__ __launch_bounds__(256) void attn_merge_kernel(KvView kv, Shape sh, const int32_t* __restrict__ active_idx,
                                                          const int32_t* __restrict__ active_count,
                                                          const int32_t* __restrict__ sel_count, int cap, int nchunk,
@@ -386,9 +386,9 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(KvView kv, Shape sh, co
     const int M = min(min(mrows[b * sh.Hkv + j], sh.rows_max), part.rows);
     if (__builtin_expect(M > kUnionRows, 0)) {
       __shared__ __attribute__((aligned(16))) float frag_lds[4 * kFragSlot];
-      if (r / (D / 8) * kPartialTile >= M) return;
+      if (r / (D / 8 / (4 / MIXED)) * kPartialTile >= M) return;
       const int U = min(ucount[b * sh.Hkv + j], sh.max_pages), pps = kManyRowStage / sh.g;
-      merge_fragments<D, 4, 4, 4, false>(sh, active_idx, b, j, r, M, min(nchunk, (U + pps - 1) / pps), 0, nchunk, part, o_p, lse_p, frag_lds);
+      merge_fragments<D, 4, MIXED, 4, false>(sh, active_idx, b, j, r, M, min(nchunk, (U + pps - 1) / pps), 0, nchunk, part, o_p, lse_p, frag_lds);
       return;
     }
     if (r >= M) return;
@@ -561,12 +561,15 @@ hipError_t launch_attn_merge(hipStream_t st, const KvView& kv, const Shape& sh, 
 #undef LOSA_FRAGMENTS
     return hipGetLastError();
   }
-  const bool mixed = many_tile == kManyRowStage;
-  auto kern = sh.d == 128 ? (!prep ? attn_merge_kernel<128, false, false> : mixed ? attn_merge_kernel<128, true, true> : attn_merge_kernel<128, true, false>)
-                          : (!prep ? attn_merge_kernel<64, false, false> : mixed ? attn_merge_kernel<64, true, true> : attn_merge_kernel<64, true, false>);
+  // wavefronts per fragment in a mixed launch: with few chunks one, a quarter of the workgroups
+  const int mixed = many_tile != kManyRowStage ? 0 : nchunk <= 16 ? 1 : 4;
+  auto kern = sh.d == 128 ? (!prep ? attn_merge_kernel<128, false, 0> : mixed == 0 ? attn_merge_kernel<128, true, 0>
+                             : mixed == 1 ? attn_merge_kernel<128, true, 1> : attn_merge_kernel<128, true, 4>)
+                          : (!prep ? attn_merge_kernel<64, false, 0> : mixed == 0 ? attn_merge_kernel<64, true, 0>
+                             : mixed == 1 ? attn_merge_kernel<64, true, 1> : attn_merge_kernel<64, true, 4>);
   // (mixed: an odd width.  Most of its workgroups leave at once, and with a multiple of 8 the ones that stay meet on a
-  // few of every die's compute units: 14 of 64 rows, 40 heads 6.8 us, of 65 5.0)
-  kern<<<dim3(mixed ? max(min(rows, kUnionRows), tiles * frags) | 1 : rows, sh.Hkv, batch), 256, 0, st>>>(
+  // few of every die's compute units: 14 of 64 rows, 40 heads 6.8 us, of 65 5.4)
+  kern<<<dim3(mixed ? max(min(rows, kUnionRows), tiles * frags * mixed / 4) | 1 : rows, sh.Hkv, batch), 256, 0, st>>>(
       kv, sh, active_idx, active_count, sel_count, cap, nchunk, uc, mr, part, o_p, lse_p, known, few_tile, many_tile);
   return hipGetLastError();
 }
