@@ -456,6 +456,7 @@ losa_status losa_create(const losa_config* cfg, void* workspace, size_t workspac
   sh.Hq = cfg->num_q_heads;
   sh.Hkv = cfg->num_kv_heads;
   sh.G = sh.Hq / sh.Hkv;
+  sh.g_magic = sh.G > 1 ? (uint32_t)(((1ULL << 32) + sh.G - 1) / sh.G) : 0;
   sh.d = cfg->head_dim;
   sh.H = cfg->hidden_size;
   sh.g = cfg->page_size;

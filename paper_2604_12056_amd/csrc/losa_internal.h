@@ -27,7 +27,12 @@ struct Shape {
   int32_t rows_max;    // B * G: rows of one KV head when every token is active
   int32_t Hkv, Hq, G, d, H, g, B;
   float sm_scale;
+  uint32_t g_magic;    // ceil(2^32 / G), for row_token()
 };
+// r / G for a query row r of a KV head (r < 4096 and G <= 4096, so the reciprocal rounded up is exact).
+__device__ __forceinline__ int row_token(const Shape& sh, int r) {
+  return sh.G == 1 ? r : (int)__umulhi((uint32_t)r, sh.g_magic);
+}
 
 // Pages of sequence b that the kernels look at: those the page table lists, that hold at least
 // one of the sequence's tokens (a table may list pages reserved ahead of the tokens: their

@@ -174,42 +174,40 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape 
   // code for more) consecutive 64-page tiles: what it does before
   // the first product (ranking, query staging) is then paid once for all of them, and a
   // batch of many sequences still fits the machine in one round of workgroups.
-  const int bx = blockIdx.x * tpw, j = blockIdx.y, b = blockIdx.z;
+  const int bx = blockIdx.x * tpw, j = blockIdx.y, b = blockIdx.z, head = b * sh.Hkv + j;
   constexpr int KS = D / 32;
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6, l16 = lane & 15, qd = lane >> 4;
+  const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, qd = lane >> 4;
+  const bool ranked = ra.delta != nullptr;   // uniform over the launch
+  const bool small = sh.B <= 64;             // a lane per token: every wavefront holds the whole block's scores
+  // Everything that can be fetched before the active set is known is requested first, the locality scores ahead of
+  // all (their address needs kernel arguments only; behind the page counts they came 0.5 us later).
+  float my_delta = 0.f;
+  if (ranked) my_delta = ra.delta[(size_t)b * sh.B + min(small ? lane : tid, sh.B - 1)];
   const int base = kv.page_indptr[b];
   const int P = seq_pages(kv, sh, b);
   const int p0 = bx * 64 + wave * 16;
   __shared__ __attribute__((aligned(16))) float sdelta[kRankTokens];
   __shared__ int act_list[kRankTokens];
   __shared__ int rscan[17];
-  const bool ranked = ra.delta != nullptr;   // uniform over the launch
-  const bool writes_active = ranked && bx == 0 && j == 0;   // this workgroup publishes the active set
+  const bool first = bx == 0;                             // this workgroup leaves what belongs to the head
+  const bool writes_active = ranked && first && j == 0;   // ... and this one publishes the active set
+  auto tile_page = [&](int t) { return max(0, min((bx + t) * 64 + wave * 16 + l16, P - 1)); };
   auto tile_phys = [&](int t) {   // page whose metadata rows lane l16 feeds for tile t of this workgroup (clamped: always valid)
-    const int pg = max(0, min((bx + t) * 64 + wave * 16 + l16, P - 1));
-    int ph = P > 0 ? kv.page_indices[base + pg] : 0;
-    return (unsigned)ph < (unsigned)kv.num_pages ? ph : 0;
+    const int ph = P > 0 ? kv.page_indices[base + tile_page(t)] : 0;
+    return (unsigned)ph < (unsigned)kv.num_pages ? ph : -1;
   };
-  if (bx * 64 >= P && !writes_active) {                      // no pages here and nothing to publish
-    if (bx == 0) aux.clear_union(b * sh.Hkv + j);
-    if (bx == 0 && tid == 0) aux.reset(b * sh.Hkv + j, 0);   // (P == 0: nothing will be selected either)
-    return;
-  }
+  if (bx * 64 >= P && !first) return;   // no pages here
 
-  // Everything that can be fetched before the active set is known is requested first: the
-  // locality scores, then the metadata rows of this wavefront's pages (two dependent round
-  // trips: page table, then the rows), which then travel while the ranking runs.
-  float my_delta = 0.f;
-  if (ranked && tid < sh.B) my_delta = ra.delta[(size_t)b * sh.B + tid];
-  // A operands: metadata rows of page p0 + l16 (a valid page is read for lanes past P, never stored).
+  // Metadata rows of this wavefront's pages: two dependent round trips (page table, then the rows), which travel
+  // while the ranking runs.  A operands: rows of page p0 + l16 (a valid page is read for lanes past P, never stored).
   // The page ids of all of this workgroup's tiles are fetched at once.
   int physv[MAXT];
 #pragma unroll
   for (int t = 0; t < MAXT; ++t) physv[t] = t < tpw ? tile_phys(t) : 0;
   bf16x8_t amin[KS], amax[KS];
   auto load_meta = [&](int phys, bf16x8_t (&mn)[KS], bf16x8_t (&mx)[KS]) {
-    const bf16_t* mrow = (const bf16_t*)kv.meta + ((size_t)phys * sh.Hkv + j) * 2 * D;
+    const bf16_t* mrow = (const bf16_t*)kv.meta + ((size_t)max(phys, 0) * sh.Hkv + j) * 2 * D;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       mn[ks] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(mrow + ks * 32 + qd * 8));
@@ -219,15 +217,71 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape 
   load_meta(physv[0], amin, amax);
 
   int M;
-  if (ranked) {
+  int list_at = 0;   // where this wavefront's copy of the active list starts in act_list
+  if (ranked && small) {
+    // A lane per token.  The four wavefronts each compare every token with a quarter of the block, the score compared
+    // with held in a scalar register, and meet once, in LDS; from the ranks on every wavefront works for itself: the
+    // active set is a lane mask, a token's place in the list the number of lanes below it, and every wavefront keeps its
+    // own copy of the list, so that no further barrier is needed.  With a thread per token, the scores in LDS, a scan and
+    // four barriers the ranking of 32 tokens took 1.55 of the kernel's 7.1 us (2048 pages, 42 rows, 4 KV heads); the
+    // kernel now takes 5.7.
+    const int B = sh.B;
+    const float mine = lane < B ? my_delta : -INFINITY;   // the padding never outranks a token
+    int act = 0, rank = 0;
+    if (ra.mode != LOSA_SEL_THRESHOLD) {
+      const int per = (B + 3) >> 2, k0 = wave * per, k1 = min(k0 + per, B);
+      for (int k = k0; k < k1; ++k) {
+        const float dk = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(mine), k));
+        rank += (int)(dk > mine) | ((int)(dk == mine) & (int)(k < lane));   // bitwise on purpose: no branches
+      }
+      int* ranks = reinterpret_cast<int*>(sdelta);
+      ranks[wave * 64 + lane] = rank;
+      __syncthreads();
+      rank = (ranks[lane] + ranks[64 + lane]) + (ranks[128 + lane] + ranks[192 + lane]);
+    }
+    if (ra.mode == LOSA_SEL_MASS) {
+      // Cumulative-mass rule, as in the stand-alone kernel: the scores in descending order are summed in that order in
+      // float, here by all lanes at once: lane r adds the scores of ranks 0..r and zeros after them.  A token is in A if
+      // the sum before it stays below tau * total (and total and tau are positive).
+      float* sorted = reinterpret_cast<float*>(act_list) + wave * 64;   // (free until the list is written)
+      if (lane < B) sorted[rank] = mine;
+      wave_lds_fence();
+      const float at_rank = sorted[min(lane, B - 1)];
+      float prefix = 0.f;
+      for (int k = 0; k < B; ++k) {
+        const float dk = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(at_rank), k));
+        prefix += k <= lane ? dk : 0.f;
+      }
+      const float total = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(prefix), B - 1));
+      wave_lds_fence();
+      sorted[lane] = prefix;
+      wave_lds_fence();
+      act = (lane < B) & (total > 0.f) & (ra.tau > 0.f) & ((rank == 0) | (int)(sorted[max(rank - 1, 0)] < ra.tau * total));
+      wave_lds_fence();
+    } else {
+      act = (lane < B) & (ra.mode == LOSA_SEL_THRESHOLD ? (int)(mine > ra.tau) : (int)(rank < ra.n));
+    }
+    const unsigned long long set = __ballot(act);
+    const int n_act = __popcll(set);
+    const int pos = __builtin_amdgcn_mbcnt_hi((unsigned)(set >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)set, 0));
+    list_at = wave * 64;
+    if (act) act_list[list_at + pos] = lane;
+    wave_lds_fence();
+    if (writes_active && wave == 0) {
+      if (lane < B) ra.mask[(size_t)b * B + lane] = (uint8_t)act;
+      if (act) ra.active_idx[(size_t)b * B + pos] = lane;
+      if (lane >= n_act && lane < B) ra.active_idx[(size_t)b * B + lane] = -1;
+      if (lane == 0) ra.active_count[b] = n_act;
+    }
+    M = n_act * sh.G;
+  } else if (ranked) {
     const int B = sh.B;   // <= kRankTokens (checked by the launcher)
     sdelta[tid] = tid < B ? my_delta : -INFINITY;   // 256 threads, kRankTokens entries: the padding never outranks a token
     __syncthreads();
     int act = 0, rank = 0;
     if (tid < B && ra.mode != LOSA_SEL_THRESHOLD) {
-      // four scores per LDS read, reads independent of one another (a scalar loop pays one LDS
-      // latency per token)
-#pragma unroll 4
+      // four scores per LDS read
+#pragma unroll 1   // (unrolled, the compare masks of 16 scores spill scalar registers to scratch in every launch)
       for (int k = 0; k < B; k += 4) {
         const f32x4_t dk = *reinterpret_cast<const f32x4_t*>(&sdelta[k]);
 #pragma unroll
@@ -238,8 +292,6 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape 
     if (ra.mode == LOSA_SEL_MASS) {
       // Cumulative-mass rule, as in the stand-alone kernel: prefix sums of the scores in descending order, taken
       // in that order in float by one thread; a token is in A if the sums before it stay below tau * total.
-      // One pass with four scores per LDS read, a chain of adds, instead of two of an LDS read per token: step with 64 tokens
-      // 31.3 -> 31.0 us, 16 tokens 35.1 -> 34.9.
       __shared__ __attribute__((aligned(16))) float sorted[kRankTokens], prefix[kRankTokens];
       if (tid < B) sorted[rank] = my_delta;
       if (tid < ((4 - (B & 3)) & 3)) sorted[B + tid] = 0.f;
@@ -264,9 +316,9 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape 
   } else {
     M = min(active_count[b], sh.B) * sh.G;
   }
-  if (bx == 0) aux.clear_union(b * sh.Hkv + j);
-  if (bx == 0 && tid == 0) aux.reset(b * sh.Hkv + j, M);
-  if (bx * 64 >= P) return;   // whole workgroup (only the publishing one gets here without pages)
+  if (first) aux.clear_union(head);
+  if (first && tid == 0) aux.reset(head, M);
+  if (bx * 64 >= P) return;   // whole workgroup (only a head's first one gets here without pages)
   if (M <= 0) return;
 
   float* out_base = scores + ((size_t)b * sh.Hkv + j) * sh.rows_max * sh.max_pages;
@@ -295,28 +347,29 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape 
         if (staged) __syncthreads();   // everyone is done reading the previous chunk
         // staging: thread -> (row, 16-byte vector); token ids first, then all the row loads
         constexpr int PER = kRows * VPR / 256;
-        int tok[PER];
+        int tok[PER], grp[PER];
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
-          const int rr = min((tid + 256 * k) / VPR, nrows - 1);
-          tok[k] = ranked ? act_list[(r0 + rr) / sh.G] : active_idx[(size_t)b * sh.B + (r0 + rr) / sh.G];
+          const int r = r0 + min((tid + 256 * k) / VPR, nrows - 1), a = row_token(sh, r);
+          grp[k] = r - a * sh.G;
+          tok[k] = ranked ? act_list[list_at + a] : active_idx[(size_t)b * sh.B + a];
         }
         uint4 v[PER];
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
-          const int rr = min((tid + 256 * k) / VPR, nrows - 1), cv = (tid + 256 * k) % VPR;
+          const int cv = (tid + 256 * k) % VPR;
           const int tc = (unsigned)tok[k] < (unsigned)sh.B ? tok[k] : 0;
-          v[k] = reinterpret_cast<const uint4*>(q + (((size_t)b * sh.B + tc) * sh.Hq + j * sh.G + (r0 + rr) % sh.G) * D)[cv];
+          v[k] = reinterpret_cast<const uint4*>(q + (((size_t)b * sh.B + tc) * sh.Hq + j * sh.G + grp[k]) * D)[cv];
         }
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
           const int rr = (tid + 256 * k) / VPR, cv = (tid + 256 * k) % VPR;
           if (rr < nrows) {
-            // per 16-bit half: all-ones where the sign bit is set
             typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+            typedef int16_t i16x8_t __attribute__((ext_vector_type(8)));
             const uint32_t keep = (unsigned)tok[k] < (unsigned)sh.B ? 0xFFFFFFFFu : 0u;
             const u32x4_t x = u32x4_t{v[k].x, v[k].y, v[k].z, v[k].w} & keep;
-            const u32x4_t mk = ((x >> 15) & 0x00010001u) * 0xFFFFu;
+            const u32x4_t mk = __builtin_bit_cast(u32x4_t, __builtin_bit_cast(i16x8_t, x) >> 15);   // all-ones where the sign bit is set
             *reinterpret_cast<u32x4_t*>(qs[0] + rr * STRIDE + cv * 16) = x & ~mk;
             *reinterpret_cast<u32x4_t*>(qs[1] + rr * STRIDE + cv * 16) = x & mk;
           }

@@ -209,6 +209,42 @@ def test_cumulative_mass_at_the_edges_of_its_prefix_sums(B):
             r.close()
 
 
+@pytest.mark.parametrize("B", [1, 2, 3, 4, 5, 31, 32, 33, 63, 64, 65, 128, 255, 256])
+def test_active_set_of_a_step_at_the_edges_of_its_ranking(B):
+    """losa_step ranks the block in the scoring kernel: a lane per token up to 64 tokens, a thread per token beyond.
+    Scores are squares of small integers, full of ties, so the sets have to be equal; three query heads per KV head."""
+    rng, d, dev = np.random.Generator(np.random.Philox(B)), 64, "cuda:0"
+    v = rng.integers(0, 8, size=(3, B)).astype(np.float32)
+    v[2] = 0.0                                      # a sequence without any change
+    lens = torch.tensor([40, 200, 1], dtype=torch.int32, device=dev)
+    pages, Hq, Hkv, g = [3, 13, 1], 6, 2, 16
+    h = torch.from_numpy(np.repeat(v.reshape(-1, 1), Hq * d, axis=1)).to(dev, torch.bfloat16)
+    gen = torch.Generator(device=dev)
+    gen.manual_seed(B)
+    draw = lambda *shape: torch.randn(shape, generator=gen, device=dev).to(torch.bfloat16)
+    kv = L.PagedKV(draw(17, Hkv, g, d), draw(17, Hkv, d, g), draw(17, Hkv, 2, d),
+                   torch.tensor([0, 3, 16, 17], dtype=torch.int32, device=dev),
+                   torch.randperm(17, generator=gen, device=dev).to(torch.int32), lens, max_seq_pages=13)
+    ctx = L.losa_create(L.make_config(max_batch=3, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, hidden_size=Hq * d,
+                                      page_size=g, block_size=B, max_pages_per_seq=13, max_topk_pages=2), dev)
+    try:
+        L.losa_page_bounds(ctx, kv)
+        q = draw(3 * B, Hq, d)
+        o_p, lse_p = torch.zeros((3 * B, Hq, d), device=dev), torch.zeros((3 * B, Hq), device=dev)
+        mask = torch.zeros(3 * B, dtype=torch.uint8, device=dev)
+        for mode, param in ((orc.SEL_TOPK, 0.0), (orc.SEL_TOPK, 1.0), (orc.SEL_TOPK, float(B // 2)), (orc.SEL_TOPK, float(B)),
+                            (orc.SEL_FRACTION, 0.3), (orc.SEL_THRESHOLD, 8.0), (orc.SEL_THRESHOLD, -1.0),
+                            (orc.SEL_MASS, 0.0), (orc.SEL_MASS, 0.25), (orc.SEL_MASS, 0.75), (orc.SEL_MASS, 1.0)):
+            mask.fill_(9)
+            L.losa_step(ctx, kv, 1, h, torch.zeros_like(h), q, mode, param, 2, o_p, lse_p, mask)
+            got = mask.cpu().numpy().reshape(3, B)
+            for b in range(3):
+                A = orc.active_set(v[b] ** 2, mode, param)
+                assert np.array_equal(got[b], np.isin(np.arange(B), A).astype(np.uint8)), (b, mode, param)
+    finally:
+        ctx.close()
+
+
 @pytest.mark.parametrize("page", [16, 32])
 @pytest.mark.parametrize("B,G,d", [
     (13, 5, 128),     # 65 rows: two token groups
