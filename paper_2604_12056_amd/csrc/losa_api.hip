@@ -346,8 +346,8 @@ losa_status score_pages_impl(losa_ctx* ctx, hipStream_t st, const KvView& kv, in
   }
   if (e != hipSuccess) return hip_fail(ctx, "page_scores launch", e);
   StageTimer timer(ctx, st, LOSA_STAGE_TOPK);
-  e = launch_select_pages(st, kv, ctx->sh, batch, max_seq_pages, q, active_idx, active_count, ctx->scores, topk,
-                          topk_out, sel_pages, sel_count, cap, ctx->rowmaps, ctx->tickets, prep, rows_upper,
+  e = launch_select_pages(st, kv, ctx->sh, batch, max_seq_pages, active_count, ctx->scores, topk, topk_out,
+                          sel_pages, sel_count, cap, ctx->rowmaps, ctx->tickets, prep, rows_upper,
                           ctx->select_round, union_bits);
   if (e != hipSuccess) return hip_fail(ctx, "select_pages launch", e);
   return LOSA_OK;

@@ -39,6 +39,13 @@ __device__ __forceinline__ int dpp_move(int v) {   // lanes without a source, or
   return __builtin_amdgcn_update_dpp(0, v, CTRL, ROW_MASK, 0xF, false);
 }
 
+// the value of lane (l ^ X), X = 1 or 2: inside the quads of four lanes
+template <int X>
+__device__ __forceinline__ int dpp_quad_xor(int v) {
+  static_assert(X == 1 || X == 2, "inside a quad");
+  return __builtin_amdgcn_update_dpp(v, v, X == 1 ? 0xB1 : 0x4E, 0xF, 0xF, false);   // quad_perm [1,0,3,2] / [2,3,0,1]
+}
+
 // Combines the four rows once every lane of a row already holds that row's result.
 template <typename F>
 __device__ __forceinline__ uint32_t across_rows(uint32_t v, F op) {

@@ -17,14 +17,14 @@ namespace losa {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
-// What the scoring kernel leaves ready for the selection kernel that follows it: the ticket
-// counter of every (sequence, KV head) at zero, and - when no token is active, so that no
-// selection workgroup will run - empty results.
+// What the scoring kernel leaves ready for the launches that follow it: the ticket counter of every (sequence, KV
+// head) at zero, empty results when no token is active, so that no selection workgroup will run, and - inside
+// losa_step - what the attention kernel reads: row count, gathered query rows (the scoring workgroups hold them
+// anyway) and, where that kernel ranks the union itself, the head's page table with every page's token count.
 struct ScoreAux {
   int32_t* tickets;
   int32_t* sel_count;
-  int32_t* ucount;   // nullable
-  int32_t* mrows;    // nullable
+  AttnPrepared prep;      // (all NULL: nobody reads it)
   uint32_t* union_bits;   // nullable: union bitmaps, cleared here for the selection to OR into
   int union_stride;       // words per head ...
   int union_len;          // ... of which this launch uses so many
@@ -35,12 +35,10 @@ struct ScoreAux {
   }
   __device__ void reset(int head, int M) const {
     tickets[head] = 0;
+    if (prep.mrows) prep.mrows[head] = M;
     if (M <= 0) {
       sel_count[head] = 0;
-      if (ucount) {
-        ucount[head] = 0;
-        mrows[head] = 0;
-      }
+      if (prep.ucount) prep.ucount[head] = 0;
     }
   }
 };
@@ -202,6 +200,7 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape 
   // Metadata rows of this wavefront's pages: two dependent round trips (page table, then the rows), which travel
   // while the ranking runs.  A operands: rows of page p0 + l16 (a valid page is read for lanes past P, never stored).
   // The page ids of all of this workgroup's tiles are fetched at once.
+  const int tokens = kv.seq_lens[b];
   int physv[MAXT];
 #pragma unroll
   for (int t = 0; t < MAXT; ++t) physv[t] = t < tpw ? tile_phys(t) : 0;
@@ -327,6 +326,7 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape 
   // each row once instead of once per wavefront.  A row is D bfloat16 plus 16 bytes of padding:
   // the 16 lanes that read the same 16-byte column of 16 consecutive rows then fall on
   // different banks.
+  const bool table = aux.prep.entries && aux.union_bits && M <= kUnionRows;   // the attention kernel will want the page table
   constexpr int kRows = 64, VPR = D / 8, STRIDE = D * 2 + 16;   // bytes; 64 rows cover the usual active sets in one go; with 128 channels 38 KiB of LDS, four workgroups per CU
   // Staged already split by sign (score = q+ . max + q- . min): the split is done once per
   // workgroup by the staging threads, not once per wavefront, tile and row tile.
@@ -338,6 +338,10 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape 
     const int p0t = p0 + t * 64;
     const bool live = p0t < P;   // a wavefront without pages still helps staging and keeps the barriers
     const bool vec_ok = (sh.max_pages & 3) == 0 && p0t + 16 <= P;
+    if (table && qd == 0 && p0t + l16 < P) {
+      const int page = p0t + l16, nv = max(0, min(sh.g, tokens - page * sh.g));
+      aux.prep.entries[(size_t)head * sh.max_pages + page] = physv[t] >= 0 && physv[t] < (1 << kEntryShift) ? (physv[t] | (nv << kEntryShift)) : 0;
+    }
     // the next tile's metadata rows travel while this tile is scored
     bf16x8_t nmin[KS], nmax[KS];
     if (t + 1 < MAXT && t + 1 < tpw) load_meta(physv[t + 1 < MAXT ? t + 1 : t], nmin, nmax);
@@ -372,6 +376,8 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape 
             const u32x4_t mk = __builtin_bit_cast(u32x4_t, __builtin_bit_cast(i16x8_t, x) >> 15);   // all-ones where the sign bit is set
             *reinterpret_cast<u32x4_t*>(qs[0] + rr * STRIDE + cv * 16) = x & ~mk;
             *reinterpret_cast<u32x4_t*>(qs[1] + rr * STRIDE + cv * 16) = x & mk;
+            if (t == 0 && first && aux.prep.q_act)
+              *reinterpret_cast<u32x4_t*>(aux.prep.q_act + ((size_t)head * sh.rows_max + r0 + rr) * D + cv * 8) = x;
           }
         }
         __syncthreads();
@@ -422,10 +428,11 @@ __device__ __forceinline__ uint32_t order_key(float f) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 
-// Device-wide hand-over used by the selection kernel: every row's workgroup stores its pick
-// bitmap, then takes a ticket; the workgroup that draws the last ticket of a (sequence, KV
-// head) ORs the rows, compacts the union and builds what the attention kernel consumes.
-// (How the stores are made visible to that workgroup is described at the hand-over.)
+// What the selection kernel leaves behind: a union bitmap per (sequence, KV head) that its row workgroups OR their
+// picks into, or (LIST) the union as an ascending page list: every row's workgroup stores its pick bitmap,
+// then takes a ticket; the workgroup that draws the last ticket of a head ORs the rows, compacts
+// the union and builds what the attention kernel consumes.  (How the stores are made visible to that
+// workgroup is described at the hand-over.)
 struct SelectOut {
   int32_t* topk_out;    // nullable [batch, B, Hq, topk]
   int32_t* sel_pages;   // [batch, Hkv, cap] logical pages of the union, ascending
@@ -433,10 +440,9 @@ struct SelectOut {
   int cap;
   uint32_t* rowmaps;    // workspace [heads, rows_max, words]: pick bitmap of every query row
   int32_t* tickets;     // workspace [heads], zero on entry (zeroed by the scoring kernel), zero on exit
-  AttnPrepared prep;    // entries == NULL: do not build the attention inputs
-  const void* q;        // query tensor (for the gather into prep.q_act)
-  const int32_t* active_idx;
-  bool rows_known;      // the grid has exactly one workgroup per existing row (+ the gather workgroup)
+  int32_t* entries;     // nullable: the list as the attention kernel reads it (AttnPrepared::entries) ...
+  int32_t* ucount;      // ... and its length
+  bool rows_known;      // the grid has exactly one workgroup per existing row
   // union_words() | words of a copy << 10 | (copies - 1) << 20; beside the pointer, so that it arrives with it: fetched
   // where it is used, it costs a scalar round trip (0.3 us)
   uint32_t union_shape;
@@ -444,186 +450,173 @@ struct SelectOut {
                         // ([heads, union_words()], cleared by the scoring kernel): no hand-over, no list
 };
 
-// Inclusive suffix scan over 256 histogram buckets by one wavefront: lane l owns buckets
-// 255-4l .. 252-4l (descending).  Returns through LDS the bucket where the running count from
-// the top first reaches `need`, how many are still needed inside that bucket, and how many
-// keys the bucket holds.
-__device__ __forceinline__ void find_bucket_wave0(const uint32_t* hist, int need, uint32_t* s_bucket, int* s_need,
-                                                  int* s_count) {
-  const int lane = threadIdx.x;   // caller guarantees threadIdx.x < 64
-  int c[4], tot = 0;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    c[k] = (int)hist[255 - 4 * lane - k];
-    tot += c[k];
-  }
-  const int incl = wave_inclusive_scan(tot);
-  int above = incl - tot;   // keys in buckets owned by lower lanes (= higher buckets)
-  if (above < need && incl >= need) {
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      if (above < need && above + c[k] >= need) {
-        *s_bucket = (uint32_t)(255 - 4 * lane - k);
-        *s_need = need - above;
-        *s_count = c[k];
-      }
-      above += c[k];
-    }
-  }
-}
-
 // A bucket of at most this many keys is ranked directly instead of by further histogram passes.
-template <int E> struct RankMax { static constexpr int value = E >= 32 ? 256 : 64; };
+constexpr int kRankMax = 64, kRankBits = 6;
 
-// LDS state of radix_kth.  hist must be all zero when radix_kth is entered (the caller clears it
-// early; the first barrier inside radix_kth orders that clear before its first use).
-template <int E, int NT>
+// LDS state of radix_kth.  hist and cand must be all zero when radix_kth is entered (radix_clear, called early; the
+// first barrier inside radix_kth orders the clear before its first use).
+template <int NT>
 struct RadixLds {
-  uint32_t hist[256];
-  __attribute__((aligned(16))) uint32_t cand[RankMax<E>::value];
-  uint32_t bucket, lo[NT / 64], hi[NT / 64], kth;
-  int need, count, ncand;
+  // one bucket and one candidate slot per lane behind the real ones take what does not count: an address per lane is
+  // cheaper than a branch around the access
+  __attribute__((aligned(16))) uint32_t hist[256 + 64];
+  __attribute__((aligned(16))) uint32_t cand[kRankMax + 64];
+  __attribute__((aligned(16))) uint32_t lo[NT / 64], hi[NT / 64];
+  __attribute__((aligned(8))) uint32_t kth, next;
+  int ncand;
 };
+template <int NT>
+__device__ __forceinline__ void radix_clear(RadixLds<NT>& L) {
+  if (threadIdx.x < 256) L.hist[threadIdx.x] = 0u;
+  if (threadIdx.x < kRankMax) L.cand[threadIdx.x] = 0u;
+}
 
 // Radix select.  It runs on keys relative to the row's smallest key and starts at the highest
 // bit of the row's largest one (a block min/max finds both), so the first histogram is already
 // spread over many buckets instead of piling every key onto the few exponent patterns the
-// scores share.  As soon as the bucket that holds the K-th key has at most RankMax<E> keys,
-// those are copied to LDS and ranked against each other directly (one thread per candidate),
-// which replaces the remaining histogram passes.
+// scores share.  As soon as the bucket that holds the K-th key has at most kRankMax keys,
+// those are copied to LDS and ranked against each other directly, which replaces the remaining histogram passes.
+// Four barriers for a row that needs one histogram: extremes, histogram, candidates, K-th key.  What lies between
+// them is done by every wavefront for itself where that saves a hand-over (the bucket search), and spread over the
+// threads where it is long (a candidate is compared with the others by four threads).
 //
-// The K-th largest of the workgroup's keys (thread t holds key[0..nmine)), Kp < number of keys:
-// on return every key > prefix is among the Kp largest, and of the keys == prefix the first
-// `need` in page order are (all of them when ties_cut is false).  On return the keys have been
-// rebased (the row minimum subtracted); prefix is in the same units.  all: Kp covers every key,
-// nothing to find.  Every thread of the workgroup must call it.
+// The K-th largest of the workgroup's keys (thread t holds key[0..nmine)), Kp < number of keys: on return the Kp
+// largest are the keys >= kth, unless `cut`: then keys > kth are among them, and of the keys == kth, of which not all
+// are, the first ones in page order.  On return the keys have been rebased (the row minimum subtracted); kth is
+// in the same units.  Every thread of the workgroup must call it.
 template <int E, int NT>
-__device__ __forceinline__ void radix_kth(uint32_t (&key)[E], int nmine, int Kp, bool all, RadixLds<E, NT>& L,
-                                          uint32_t& prefix, int& need, bool& ties_cut) {
-  const int tid = threadIdx.x;
+__device__ __forceinline__ void radix_kth(uint32_t (&key)[E], int nmine, int Kp, RadixLds<NT>& L, uint32_t& kth, bool& cut) {
+  const int tid = threadIdx.x, lane = tid & 63;
   constexpr int NW = NT / 64;
-  uint32_t pmask = 0u;
-  prefix = 0u;
-  need = Kp;
-  ties_cut = true;   // false once it is known that every key equal to the K-th is picked
-  if (!all) {
-    // highest differing bit of the row's keys
-    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+  static_assert(NT >= 4 * kRankMax, "four threads per candidate");
+  uint32_t lo = 0xFFFFFFFFu, hi = 0u;
 #pragma unroll
-    for (int i = 0; i < E; ++i)
-      if (i < nmine) {
-        lo = min(lo, key[i]);
-        hi = max(hi, key[i]);
-      }
-    lo = wave_min_u32(lo);
-    hi = wave_max_u32(hi);
-    if ((tid & 63) == 0) {
-      L.lo[tid >> 6] = lo;
-      L.hi[tid >> 6] = hi;
+  for (int i = 0; i < E; ++i) {
+    lo = min(lo, i < nmine ? key[i] : 0xFFFFFFFFu);
+    hi = max(hi, i < nmine ? key[i] : 0u);
+  }
+  lo = wave_min_u32(lo);
+  hi = wave_max_u32(hi);
+  if (lane == 0) {
+    L.lo[tid >> 6] = lo;
+    L.hi[tid >> 6] = hi;
+  }
+  if (tid == 0) {
+    L.ncand = 0;
+    L.next = 0xFFFFFFFFu;
+  }
+  __syncthreads();
+  lo = L.lo[0];
+  hi = L.hi[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) {
+    lo = min(lo, L.lo[w]);
+    hi = max(hi, L.hi[w]);
+  }
+  // Keys are taken relative to the row minimum from here on (order is unchanged): the
+  // first digit then resolves the row's actual range into 128..256 buckets wherever that
+  // range lies, instead of splitting at whatever power of two happens to fall inside it.
+#pragma unroll
+  for (int i = 0; i < E; ++i) key[i] -= lo;   // entries past the row's pages are never looked at
+  hi = __builtin_amdgcn_readfirstlane(hi - lo);
+  kth = 0u;
+  cut = true;
+  if (hi == 0u) return;                        // every key is the same
+  const int hb = 31 - __clz((int)hi);          // no key has a bit above hb
+  uint32_t pmask = hb >= 31 ? 0u : ~((2u << hb) - 1u), prefix = 0u;
+  int need = Kp;
+  bool first_pass = true;   // the histogram was cleared by the caller (a barrier has passed since)
+  for (int shift = max(hb - 7, 0);; shift = max(shift - 8, 0)) {
+    if (!first_pass) {
+      __syncthreads();   // everyone has read the previous pass's histogram
+      if (tid < 256) L.hist[tid] = 0u;
+      __syncthreads();
     }
-    if (tid == 0) L.ncand = 0;
+    first_pass = false;
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      const bool in = (i < nmine) & ((key[i] & pmask) == prefix);
+      atomicAdd(&L.hist[in ? (key[i] >> shift) & 255u : 256u + lane], 1u);
+    }
     __syncthreads();
-    lo = L.lo[0];
-    hi = L.hi[0];
+    // Every wavefront finds the bucket where the running count from the top first reaches `need`: lane l owns buckets
+    // 255-4l .. 252-4l (descending), the lane that crosses tells the others.
+    const uint4 c4 = *reinterpret_cast<const uint4*>(&L.hist[252 - 4 * lane]);
+    const int c[4] = {(int)c4.w, (int)c4.z, (int)c4.y, (int)c4.x};
+    const int tot = (c[0] + c[1]) + (c[2] + c[3]);
+    const int incl = wave_inclusive_scan(tot);
+    int above = incl - tot;   // keys in buckets owned by lower lanes (= higher buckets)
+    int bucket = 255 - 4 * lane, size = c[0];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) {
-      lo = min(lo, L.lo[w]);
-      hi = max(hi, L.hi[w]);
+    for (int k = 1; k < 4; ++k) {   // step down while the bucket does not reach `need`
+      const bool below = above + size < need;
+      above += below ? size : 0;
+      bucket -= below;
+      size = below ? c[k] : size;
     }
-    // Keys are taken relative to the row minimum from here on (order is unchanged): the
-    // first digit then resolves the row's actual range into 128..256 buckets wherever that
-    // range lies, instead of splitting at whatever power of two happens to fall inside it.
+    const int at = __builtin_ctzll(__ballot(incl >= need));   // the last lane's count covers every key: never empty
+    const uint32_t found = (uint32_t)__builtin_amdgcn_readlane(bucket, at);
+    const int count = __builtin_amdgcn_readlane(size, at);
+    need -= __builtin_amdgcn_readlane(above, at);
+    // bits of the digit that lie above bit hb (only when hb < 7) are common to all keys
+    const uint32_t dmask = 0xFFu << shift;
+    prefix = (prefix & ~dmask) | (found << shift);
+    pmask |= dmask;
+    if (shift == 0) {
+      kth = prefix;
+      cut = count != need;
+      return;
+    }
+    if (count <= kRankMax) {
+      // The K-th key is the need-th largest of `count` candidates: rank them directly.  A candidate is the key's bits
+      // below the digit (at most 24) over its slot number, so no two are equal and one compare ranks them.
+      // They are packed wavefront by wavefront (one LDS atomic each); which slots equal keys get does not matter.
+      int mine_n = 0;
 #pragma unroll
-    for (int i = 0; i < E; ++i) key[i] -= lo;   // entries past the row's pages are never looked at
-    hi -= lo;
-    const uint32_t diff = hi;
-    if (diff != 0u) {
-      const int hb = 31 - __clz((int)diff);          // no key has a bit above hb
-      pmask = hb >= 31 ? 0u : ~((2u << hb) - 1u);
-      prefix = 0u;
-      bool first_pass = true;   // the histogram was cleared at the top (a barrier has passed since)
-      for (int shift = max(hb - 7, 0);; shift = max(shift - 8, 0)) {
-        if (!first_pass) {
-          if (tid < 256) L.hist[tid] = 0u;
-          __syncthreads();
-        }
-        first_pass = false;
+      for (int i = 0; i < E; ++i) mine_n += (int)(i < nmine) & (int)((key[i] & pmask) == prefix);
+      const int wincl = wave_inclusive_scan(mine_n);
+      int wbase = 0;
+      if (lane == 63) wbase = atomicAdd(&L.ncand, wincl);
+      wbase = __builtin_amdgcn_readlane(wbase, 63);
+      int put = wbase + wincl - mine_n;
 #pragma unroll
-        for (int i = 0; i < E; ++i)
-          if (i < nmine && (key[i] & pmask) == prefix) atomicAdd(&L.hist[(key[i] >> shift) & 255u], 1u);
-        __syncthreads();
-        if (tid < 64) find_bucket_wave0(L.hist, need, &L.bucket, &L.need, &L.count);
-        __syncthreads();
-        // bits of the digit that lie above bit hb (only when hb < 7) are common to all keys
-        const uint32_t dmask = 0xFFu << shift;
-        prefix = (prefix & ~dmask) | (L.bucket << shift);
-        pmask |= dmask;
-        need = L.need;
-        const int count = L.count;
-        if (shift == 0) {
-          ties_cut = count != need;
-          break;
-        }
-        if (count <= RankMax<E>::value) {
-          // the K-th key is the need-th largest of `count` candidates: rank them directly.
-          // Candidates are packed wavefront by wavefront (one LDS atomic each); their order
-          // in the array does not matter to the ranks.
-          int mine_n = 0;
-#pragma unroll
-          for (int i = 0; i < E; ++i) mine_n += (int)(i < nmine) & (int)((key[i] & pmask) == prefix);
-          const int incl = wave_inclusive_scan(mine_n);
-          int wbase = 0;
-          if ((tid & 63) == 63) wbase = atomicAdd(&L.ncand, incl);
-          wbase = __builtin_amdgcn_readlane(wbase, 63);
-          int at = wbase + incl - mine_n;
-#pragma unroll
-          for (int i = 0; i < E; ++i)
-            if (i < nmine && (key[i] & pmask) == prefix) L.cand[at++] = key[i];
-          // pad to a whole number of 16-candidate steps with keys that rank below everything
-          if (tid < 16 && count + tid < RankMax<E>::value) L.cand[count + tid] = 0u;
-          __syncthreads();
-          if (tid < count) {
-            const uint32_t mine = L.cand[tid];
-            int gt = 0, ge = 0;
-            for (int u = 0; u < count; u += 16) {
-              uint4 c4[4];
-#pragma unroll
-              for (int k = 0; k < 4; ++k) c4[k] = *reinterpret_cast<const uint4*>(&L.cand[u + 4 * k]);
-#pragma unroll
-              for (int k = 0; k < 4; ++k) {
-                gt += (c4[k].x > mine) + (c4[k].y > mine) + (c4[k].z > mine) + (c4[k].w > mine);
-                ge += (c4[k].x >= mine) + (c4[k].y >= mine) + (c4[k].z >= mine) + (c4[k].w >= mine);
-              }
-            }
-            // the padding keys (0) count as ">= mine" only for a key that is 0 itself
-            if (mine == 0u) ge -= ((count + 15) & ~15) - count;
-            if (gt < need && need <= ge) {   // every thread that holds the K-th value writes the same
-              L.kth = mine;
-              L.need = need - gt;
-              L.count = ge - gt;
-            }
-          }
-          __syncthreads();
-          prefix = L.kth;
-          pmask = 0xFFFFFFFFu;
-          need = L.need;
-          ties_cut = L.count != need;
-          break;
-        }
+      for (int i = 0; i < E; ++i) {
+        const int in = (int)(i < nmine) & (int)((key[i] & pmask) == prefix);
+        L.cand[in ? put : kRankMax + lane] = (key[i] & ~pmask) << kRankBits | (uint32_t)(put & (kRankMax - 1));
+        put += in;
       }
-    } else {
-      prefix = 0u;          // every key is the same: ties by page order
-      pmask = 0xFFFFFFFFu;
+      __syncthreads();
+      // thread -> a candidate and a quarter of those it is compared with (unused slots are 0: above none of them)
+      if (tid < 4 * kRankMax) {
+        const int which = tid >> 2, quarter = tid & 3;
+        const uint32_t mine = L.cand[which];
+        int rank = 0;
+#pragma unroll
+        for (int k = 0; k < kRankMax / 16; ++k) {
+          const uint4 o = *reinterpret_cast<const uint4*>(&L.cand[quarter * 4 + k * 16]);
+          rank += (int)(o.x > mine) + (int)(o.y > mine) + (int)(o.z > mine) + (int)(o.w > mine);
+        }
+        rank += dpp_quad_xor<1>(rank);
+        rank += dpp_quad_xor<2>(rank);
+        if (which < count && rank == need - 1) L.kth = mine >> kRankBits;
+        if (which < count && rank == need) L.next = mine >> kRankBits;
+      }
+      __syncthreads();
+      const uint32_t low = L.kth;
+      kth = prefix | low;
+      cut = L.next == low;   // the next one, not among the Kp, has the same key
+      return;
     }
-  } else {
-    __syncthreads();
   }
 }
 
 // Per-query top pages, register resident (thread t of NT owns the E consecutive pages
-// [t*E, t*E+E); P <= NT*E: 256 threads x 8 up to 2048 pages, 1024 threads x 8 or 16 beyond),
-// fused with the union and the hand-over described above.
-template <int E, int NT, bool MULTI>
+// [t*E, t*E+E); P <= NT*E: 256 threads x 8 up to 2048 pages, 512 up to 4096, 1024 threads x 8 or 16 beyond).
+// LIST: heads may need the union list (SelectOut).
+// 2048 pages, 42 rows x 4 heads: 5.3 -> 4.5 us (before: histogram and candidates behind branches, a candidate ranked by
+// one thread, picks through LDS); 4096 pages, 9.2 us with 1024 threads and 5.7 with 512.  The query rows and the page
+// table, which a workgroup of this launch per head used to gather, come from the scoring kernel.
+template <int E, int NT, bool MULTI, bool LIST>
 __global__ __launch_bounds__(NT) void select_pages_kernel(KvView kv, Shape sh, const int32_t* __restrict__ active_count,
                                                            const float* __restrict__ scores, int topk, SelectOut out,
                                                            int rpw) {
@@ -632,15 +625,13 @@ __global__ __launch_bounds__(NT) void select_pages_kernel(KvView kv, Shape sh, c
   // the machine in one round: a second round of workgroups costs more than a second row.
   // MULTI = false is the one-row form (rpw == 1) without the loop's register cost.
   constexpr int WORDS = NT * E / 32;
-  __shared__ RadixLds<E, NT> rl;
-  __shared__ uint32_t rowbits[WORDS];   // this row's picks
-  __shared__ uint32_t ubits[WORDS];     // union of the head's rows (used by the workgroup that builds it)
-  __shared__ int s_last;
+  constexpr int TPW = 32 / E;           // threads whose pages share a bitmap word
+  __shared__ RadixLds<NT> rl;
   __shared__ int scan[17];
   // A workgroup's rows are r_first, r_first + r_step, ...: dealt round-robin over the row workgroups, so
   // that when the grid was sized for more rows than exist (a count only the device knows) the rows
   // that do exist still spread over as many workgroups as possible.
-  const int r_step = MULTI ? (int)gridDim.x - 1 : 1;
+  const int r_step = MULTI ? (int)gridDim.x : 1;
   const int r_first = blockIdx.x, j = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
   const int head = b * sh.Hkv + j;
   const int p_first_all = tid * E;
@@ -667,70 +658,16 @@ __global__ __launch_bounds__(NT) void select_pages_kernel(KvView kv, Shape sh, c
     }
   };
   if (out.rows_known) load_row(raw, r_first);
-  const int n_act = min(active_count[b], sh.B);
-  const int M = n_act * sh.G;
-  const int base = kv.page_indptr[b];
+  const int M = min(active_count[b], sh.B) * sh.G;
   const int P = min(seq_pages(kv, sh, b), NT * E);   // (the launcher picks NT * E >= the page limit)
-  const int L = kv.seq_lens[b];
-
-  if (blockIdx.x == gridDim.x - 1) {
-    // The extra workgroup of every (sequence, head) gathers the head's active query rows into
-    // the dense buffer the attention kernel reads, off the path of the selection.  Indices are
-    // clamped so that every load can be issued before the one it depends on has been checked.
-    if (out.prep.entries == nullptr || M <= 0) return;
-    if (out.union_bits && M <= kUnionRows) {
-      // nobody builds the list here, who would otherwise publish the row count
-      if (tid == 0) out.prep.mrows[head] = M;
-      // ... and the head gets its page table in the form the attention kernel consumes (physical id
-      // and valid-token count of every logical page), at an address that kernel knows when it starts
-      int32_t* tab = out.prep.entries + (size_t)head * sh.max_pages;
-      for (int p0 = tid; p0 < P; p0 += NT * 4) {
-        int ph[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) ph[k] = kv.page_indices[base + min(p0 + NT * k, P - 1)];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int pg = p0 + NT * k;
-          if (pg < P) {
-            const int nv = max(0, min(sh.g, L - pg * sh.g));
-            tab[pg] = ((unsigned)ph[k] < (unsigned)kv.num_pages && ph[k] < (1 << kEntryShift)) ? (ph[k] | (nv << kEntryShift)) : 0;
-          }
-        }
-      }
-    }
-    constexpr int QV = 4;   // 16-byte vectors per thread per sweep
-    const int vpr = sh.d / 8;
-    const bf16_t* q = (const bf16_t*)out.q;
-    uint4* dst = reinterpret_cast<uint4*>(out.prep.q_act + (size_t)head * sh.rows_max * sh.d);
-    for (int v0 = tid; v0 < M * vpr; v0 += NT * QV) {
-      int tok[QV];
-#pragma unroll
-      for (int k = 0; k < QV; ++k) tok[k] = out.active_idx[(size_t)b * sh.B + min((v0 + NT * k) / vpr, M - 1) / sh.G];
-      uint4 qv[QV];
-#pragma unroll
-      for (int k = 0; k < QV; ++k) {
-        const int rr = min((v0 + NT * k) / vpr, M - 1), cv = (v0 + NT * k) % vpr;
-        const int tc = (unsigned)tok[k] < (unsigned)sh.B ? tok[k] : 0;
-        qv[k] = reinterpret_cast<const uint4*>(q + (((size_t)b * sh.B + tc) * sh.Hq + j * sh.G + rr % sh.G) * sh.d)[cv];
-      }
-#pragma unroll
-      for (int k = 0; k < QV; ++k)
-        if (v0 + NT * k < M * vpr)
-          dst[v0 + NT * k] = (unsigned)tok[k] < (unsigned)sh.B ? qv[k] : make_uint4(0u, 0u, 0u, 0u);
-    }
-    return;
-  }
   if (r_first >= M) return;
   if (!out.rows_known) load_row(raw, r_first);
   const int words = (sh.max_pages + 31) / 32;
   const int Kp = min(topk, P);
   const int nmine_all = max(0, min(E, P - p_first));   // pages of this thread that exist
+  const bool only_bits = !LIST || (out.union_bits && M <= kUnionRows);
   // LDS that must start at zero is cleared now, while the scores are still on their way
-  for (int w = tid; w < WORDS; w += NT) {
-    rowbits[w] = 0u;
-    ubits[w] = 0u;
-  }
-  if (tid < 256) rl.hist[tid] = 0u;
+  radix_clear(rl);
   const int r_end = MULTI ? M : r_first + 1;
 #pragma unroll 1
   for (int r = r_first; r < r_end; r += r_step) {
@@ -740,178 +677,183 @@ __global__ __launch_bounds__(NT) void select_pages_kernel(KvView kv, Shape sh, c
     int p_first_r = p_first_all, nmine_r = nmine_all;
     if constexpr (MULTI) asm volatile("" : "+v"(p_first_r), "+v"(nmine_r));
     const int p_first = p_first_r, nmine = nmine_r;
-    const int a = r / sh.G, h = j * sh.G + r % sh.G;
-    int32_t* tk = out.topk_out ? out.topk_out + (((size_t)b * sh.B + a) * sh.Hq + h) * topk : nullptr;
+    int32_t* tk = nullptr;
+    if constexpr (LIST) {
+      const int a = row_token(sh, r), h = j * sh.G + r - a * sh.G;
+      if (out.topk_out) tk = out.topk_out + (((size_t)b * sh.B + a) * sh.Hq + h) * topk;
+    }
     uint32_t key[E];
 #pragma unroll
     for (int i = 0; i < E; ++i) key[i] = i < nmine ? order_key(raw[i]) : 0u;
     if (r + r_step < r_end) load_row(raw, r + r_step);   // the next row's scores, on their way during this row's selection
 
-    const bool all = Kp >= P;
-    uint32_t prefix;
-    int need;
-    bool ties_cut;
-    radix_kth<E, NT>(key, nmine, Kp, all, rl, prefix, need, ties_cut);
-    // picks: keys above the K-th, plus the first `need` keys equal to it in page order.
-    // (Bitwise logic on purpose: the short-circuit forms compile to a branch per key.)
-    int my_eq = 0, my_gt = 0;
-    if (ties_cut || tk) {   // the counts feed the scans below and nothing else
-  #pragma unroll
+    // Picks: keys from the K-th up; where not all keys equal to it are picked, the first of them in page order.
+    const bool all = Kp >= P;   // (Kp covers every page: nothing to find)
+    uint32_t kth = 0u, bits = 0u;
+    bool cut = false;
+    if (!all) radix_kth<E, NT>(key, nmine, Kp, rl, kth, cut);
+    if (cut) {   // block-uniform: derives from LDS values every thread read
+      int my_gt = 0, my_eq = 0;
+#pragma unroll
       for (int i = 0; i < E; ++i) {
-        const int in = i < nmine;
-        my_gt += in & ((int)all | (int)(key[i] > prefix));
-        my_eq += in & (int)!all & (int)(key[i] == prefix);
+        my_gt += (int)(i < nmine) & (int)(key[i] > kth);
+        my_eq += (int)(i < nmine) & (int)(key[i] == kth);
       }
-    }
-    int tot_eq;
-    int eq_rank = 0;   // block-uniform branch: ties_cut derives from LDS values every thread read
-    if (ties_cut) eq_rank = block_exclusive_scan(my_eq, scan, &tot_eq);
-    int pos = 0, tot_sel = 0;
-    if (tk) pos = block_exclusive_scan(my_gt + (ties_cut ? max(0, min(my_eq, need - eq_rank)) : my_eq), scan, &tot_sel);
-    uint32_t bits[(E + 31) / 32];
-  #pragma unroll
-    for (int w = 0; w < (E + 31) / 32; ++w) bits[w] = 0u;
-  #pragma unroll
-    for (int i = 0; i < E; ++i) {
-      const int in = i < nmine;
-      const int eq = in & (int)!all & (int)(key[i] == prefix);
-      const int sel = (in & ((int)all | (int)(key[i] > prefix))) | (eq & ((int)!ties_cut | (int)(eq_rank < need)));
-      eq_rank += eq;
-      bits[i / 32] |= (uint32_t)sel << ((p_first + i) & 31);
-      if (tk && sel) tk[pos++] = p_first + i;
-    }
-    if (E >= 32) {
-  #pragma unroll
-      for (int w = 0; w < (E + 31) / 32; ++w) rowbits[p_first / 32 + w] = bits[w];   // this thread owns whole words
+      int gt_total, eq_total;
+      block_exclusive_scan(my_gt, scan, &gt_total);
+      int eq_rank = block_exclusive_scan(my_eq, scan, &eq_total);
+#pragma unroll
+      for (int i = 0; i < E; ++i) {
+        const int eq = key[i] == kth;
+        bits |= (uint32_t)((int)(key[i] > kth) | (eq & (int)(eq_rank < Kp - gt_total))) << i;
+        eq_rank += eq;   // (only the pages past the row's last come behind one that does not exist)
+      }
     } else {
-      if (bits[0]) atomicOr(&rowbits[p_first / 32], bits[0]);
+#pragma unroll
+      for (int i = E - 1; i >= 0; --i) bits = bits + bits + (uint32_t)(key[i] >= kth);
+      if (all) bits = ~0u;
     }
-    if (tk)
-      for (int k = tot_sel + tid; k < topk; k += NT) tk[k] = -1;
-    __syncthreads();
-    // ---- hand-over: the last row of this (sequence, head) builds the union.
-    // The row bitmap travels in agent-scope atomic stores (written through to memory, past the
-    // per-die L2 slices); ordering is "my stores have completed (wait count zero), then my
-    // ticket".  A full agent-scope fence would also work but writes back and invalidates whole
-    // L2 slices, once per workgroup.
-    uint32_t* myrow = out.rowmaps + ((size_t)head * sh.rows_max + r) * words;
-    if (out.union_bits && M <= kUnionRows) {
+    bits &= (1u << nmine) - 1u;   // nmine <= E <= 16
+    if (tk) {
+      int total;
+      int pos = block_exclusive_scan(__popc(bits), scan, &total);
+#pragma unroll
+      for (int i = 0; i < E; ++i)
+        if ((bits >> i) & 1u) tk[pos++] = p_first + i;
+      for (int k = total + tid; k < topk; k += NT) tk[k] = -1;
+    }
+    // the threads that share a word put it together with lane moves; the first of them writes it out
+    bits <<= p_first & 31;
+    bits |= (uint32_t)dpp_quad_xor<1>((int)bits);
+    if constexpr (TPW == 4) bits |= (uint32_t)dpp_quad_xor<2>((int)bits);
+    static_assert(TPW == 2 || TPW == 4, "a word's threads are lanes of one quad");
+    const int word = p_first >> 5;
+    const bool writes = tid % TPW == 0;
+    if (only_bits) {
       // read by the next launch; nothing waits for the atomics here (an OR has no order)
       const int copy_words = (int)(out.union_shape >> 10) & 0x3FF;
       uint32_t* u = out.union_bits + (size_t)head * (out.union_shape & 0x3FF) + (r & (int)(out.union_shape >> 20)) * copy_words;
-      for (int w = tid; w < min(copy_words, min(words, WORDS)); w += NT)
-        if (rowbits[w]) __hip_atomic_fetch_or(&u[w], rowbits[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-      for (int w = tid; w < words; w += NT)
-        __hip_atomic_store(&myrow[w], w < WORDS ? rowbits[w] : 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (writes && bits) __hip_atomic_fetch_or(&u[word], bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // (bits: a page < P)
+    } else if constexpr (LIST) {
+      // ---- hand-over: the last row of this (sequence, head) builds the union.
+      // The row bitmap travels in agent-scope atomic stores (written through to memory, past the
+      // per-die L2 slices); ordering is "my stores have completed (wait count zero), then my
+      // ticket".  A full agent-scope fence would also work but writes back and invalidates whole
+      // L2 slices, once per workgroup.
+      uint32_t* myrow = out.rowmaps + ((size_t)head * sh.rows_max + r) * words;
+      if (writes && word < words) __hip_atomic_store(&myrow[word], bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int w = WORDS + tid; w < words; w += NT) __hip_atomic_store(&myrow[w], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (r + r_step < r_end) {
-      // the row bitmap has been read out (the stores above take their data at issue): clear the
-      // LDS state of the next row; its first barrier (inside radix_kth) orders these writes
+      // clear the LDS state of the next row (this row's last reads of it lie behind the barrier); the next row's
+      // first barrier (inside radix_kth) orders these writes
       __syncthreads();
-      for (int w = tid; w < WORDS; w += NT) rowbits[w] = 0u;
-      if (tid < 256) rl.hist[tid] = 0u;
+      radix_clear(rl);
     }
   }
-  if (out.union_bits && M <= kUnionRows) return;
-  const int rows_done = (r_end - 1 - r_first) / r_step + 1;
-  __builtin_amdgcn_s_waitcnt(0);
-  __atomic_signal_fence(__ATOMIC_SEQ_CST);
-  __syncthreads();
-  // the ticket counts rows: the workgroup whose rows complete the head's M builds the union
-  if (tid == 0)
-    s_last = __hip_atomic_fetch_add(&out.tickets[head], rows_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + rows_done == M;
-  __syncthreads();
-  if (!s_last) return;
-  if (tid == 0) out.tickets[head] = 0;
-  // Union of the M row bitmaps -> ascending page list (+ page entries for the attention kernel).
-  // Pages are handled a thread each, kTailPages per thread: their physical ids are fetched
-  // before the bits are known, together with the row bitmaps, so the tail is one memory
-  // round trip.  A page's slot in the list is the popcount prefix of its bitmap word plus
-  // the set bits below it in the word: no serial walk, stores ascend with the thread id.
-  const int wordsP = (P + 31) / 32;
-  int32_t* sel = out.sel_pages + (size_t)head * out.cap;
-  int32_t* ent = out.prep.entries ? out.prep.entries + (size_t)head * sh.max_pages : nullptr;
-  __shared__ int wordbase[WORDS];
-  int phys[E];
-  if (ent) {
-#pragma unroll
-    for (int i = 0; i < E; ++i)   // (an empty sequence has no entry of its own in the page table)
-      phys[i] = P > 0 ? kv.page_indices[base + min(tid + NT * i, P - 1)] : 0;
-  }
-  const uint32_t* maps = out.rowmaps + (size_t)head * sh.rows_max * words;
-  {
-    // Thread t ORs bitmap word (t mod nw) of every `groups`-th row in registers, 16 independent
-    // loads at a time (a loop of load-then-use would pay one memory latency per iteration),
-    // and only the per-thread results meet in LDS.  Agent-scope atomic loads: they are served
-    // from the coherence point, not from a line this compute unit or its die's L2 holds.  The
-    // writers' stores went through to memory (agent scope) and had completed before their
-    // tickets were drawn, but the bitmap regions of two (sequence, head) pairs can share a
-    // cache line (rows * words * 4 need not be a multiple of the line), and the union
-    // workgroup of the other pair may have fetched that line while this pair's rows were
-    // still being written.
-    for (int w0 = 0; w0 < wordsP; w0 += NT) {
-      const int nw = min(NT, wordsP - w0);
-      const int groups = NT / nw;
-      const int ww = w0 + tid % nw, rg = tid / nw;
-      if (rg < groups) {
-        uint32_t acc = 0u;
-        for (int r0 = rg; r0 < M; r0 += groups * 16) {
-          uint32_t v[16];
-#pragma unroll
-          for (int k = 0; k < 16; ++k) {
-            const int rr = r0 + groups * k;
-            v[k] = __hip_atomic_load(&maps[(size_t)min(rr, M - 1) * words + ww], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          }
-#pragma unroll
-          for (int k = 0; k < 16; ++k) acc |= (r0 + groups * k < M) ? v[k] : 0u;
-        }
-        if (acc) atomicOr(&ubits[ww], acc);
-      }
-    }
-  }
-  __syncthreads();
-  int base_out = 0;
-  for (int w0 = 0; w0 < WORDS; w0 += NT) {   // exclusive popcount prefix per word
-    const int w = w0 + tid;
-    const int c = w < wordsP ? __popc(ubits[w]) : 0;
-    int total;
-    const int ex = block_exclusive_scan(c, scan, &total);
-    if (w < WORDS) wordbase[w] = base_out + ex;
-    base_out += total;
-  }
-  __syncthreads();
-  // Every load of this thread has landed by now; saying so keeps the stores below from each
-  // waiting for the one before it (loads and stores share one in-order counter).
-  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0) only
-  uint32_t wd[E];
-  int wb[E];
-#pragma unroll
-  for (int i = 0; i < E; ++i) {   // all LDS reads first: one latency, not one per page
-    wd[i] = ubits[(tid + NT * i) >> 5];
-    wb[i] = wordbase[(tid + NT * i) >> 5];
-  }
-#pragma unroll
-  for (int i = 0; i < E; ++i) {
-    const int page = tid + NT * i;
-    if (page < P && ((wd[i] >> (page & 31)) & 1u)) {
-      const int at = wb[i] + __popc(wd[i] & ((1u << (page & 31)) - 1u));
-      if (at < out.cap) {
-        sel[at] = page;
-        if (ent) {
-          const int nv = max(0, min(sh.g, L - page * sh.g));
-          const int ph = phys[i];
-          ent[at] = ((unsigned)ph < (unsigned)kv.num_pages && ph < (1 << kEntryShift)) ? (ph | (nv << kEntryShift)) : 0;
-        }
-      }
-    }
-  }
-  const int U = min(base_out, out.cap);
-  if (tid == 0) {
-    out.sel_count[head] = U;
+  if constexpr (LIST) {
+    if (only_bits) return;
+    const int rows_done = (r_end - 1 - r_first) / r_step + 1;
+    __shared__ int s_last;
+    __shared__ uint32_t ubits[WORDS];     // union of the head's rows
+    for (int w = tid; w < WORDS; w += NT) ubits[w] = 0u;
+    __builtin_amdgcn_s_waitcnt(0);
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __syncthreads();
+    // the ticket counts rows: the workgroup whose rows complete the head's M builds the union
+    if (tid == 0)
+      s_last = __hip_atomic_fetch_add(&out.tickets[head], rows_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + rows_done == M;
+    __syncthreads();
+    if (!s_last) return;
+    if (tid == 0) out.tickets[head] = 0;
+    // Union of the M row bitmaps -> ascending page list (+ page entries for the attention kernel).
+    // Pages are handled a thread each, E per thread: their physical ids are fetched
+    // before the bits are known, together with the row bitmaps, so the tail is one memory
+    // round trip.  A page's slot in the list is the popcount prefix of its bitmap word plus
+    // the set bits below it in the word: no serial walk, stores ascend with the thread id.
+    const int wordsP = (P + 31) / 32;
+    const int base = kv.page_indptr[b];
+    const int L = kv.seq_lens[b];
+    int32_t* sel = out.sel_pages + (size_t)head * out.cap;
+    int32_t* ent = out.entries ? out.entries + (size_t)head * sh.max_pages : nullptr;
+    __shared__ int wordbase[WORDS];
+    int phys[E];
     if (ent) {
-      out.prep.ucount[head] = U;
-      out.prep.mrows[head] = M;
+#pragma unroll
+      for (int i = 0; i < E; ++i)   // (an empty sequence has no entry of its own in the page table)
+        phys[i] = P > 0 ? kv.page_indices[base + min(tid + NT * i, P - 1)] : 0;
+    }
+    const uint32_t* maps = out.rowmaps + (size_t)head * sh.rows_max * words;
+    {
+      // Thread t ORs bitmap word (t mod nw) of every `groups`-th row in registers, 16 independent
+      // loads at a time (a loop of load-then-use would pay one memory latency per iteration),
+      // and only the per-thread results meet in LDS.  Agent-scope atomic loads: they are served
+      // from the coherence point, not from a line this compute unit or its die's L2 holds.  The
+      // writers' stores went through to memory (agent scope) and had completed before their
+      // tickets were drawn, but the bitmap regions of two (sequence, head) pairs can share a
+      // cache line (rows * words * 4 need not be a multiple of the line), and the union
+      // workgroup of the other pair may have fetched that line while this pair's rows were
+      // still being written.
+      for (int w0 = 0; w0 < wordsP; w0 += NT) {
+        const int nw = min(NT, wordsP - w0);
+        const int groups = NT / nw;
+        const int ww = w0 + tid % nw, rg = tid / nw;
+        if (rg < groups) {
+          uint32_t acc = 0u;
+          for (int r0 = rg; r0 < M; r0 += groups * 16) {
+            uint32_t v[16];
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+              const int rr = r0 + groups * k;
+              v[k] = __hip_atomic_load(&maps[(size_t)min(rr, M - 1) * words + ww], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+#pragma unroll
+            for (int k = 0; k < 16; ++k) acc |= (r0 + groups * k < M) ? v[k] : 0u;
+          }
+          if (acc) atomicOr(&ubits[ww], acc);
+        }
+      }
+    }
+    __syncthreads();
+    int base_out = 0;
+    for (int w0 = 0; w0 < WORDS; w0 += NT) {   // exclusive popcount prefix per word
+      const int w = w0 + tid;
+      const int c = w < wordsP ? __popc(ubits[w]) : 0;
+      int total;
+      const int ex = block_exclusive_scan(c, scan, &total);
+      if (w < WORDS) wordbase[w] = base_out + ex;
+      base_out += total;
+    }
+    __syncthreads();
+    // Every load of this thread has landed by now; saying so keeps the stores below from each
+    // waiting for the one before it (loads and stores share one in-order counter).
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0) only
+    uint32_t wd[E];
+    int wb[E];
+#pragma unroll
+    for (int i = 0; i < E; ++i) {   // all LDS reads first: one latency, not one per page
+      wd[i] = ubits[(tid + NT * i) >> 5];
+      wb[i] = wordbase[(tid + NT * i) >> 5];
+    }
+#pragma unroll
+    for (int i = 0; i < E; ++i) {
+      const int page = tid + NT * i;
+      if (page < P && ((wd[i] >> (page & 31)) & 1u)) {
+        const int at = wb[i] + __popc(wd[i] & ((1u << (page & 31)) - 1u));
+        if (at < out.cap) {
+          sel[at] = page;
+          if (ent) {
+            const int nv = max(0, min(sh.g, L - page * sh.g));
+            const int ph = phys[i];
+            ent[at] = ((unsigned)ph < (unsigned)kv.num_pages && ph < (1 << kEntryShift)) ? (ph | (nv << kEntryShift)) : 0;
+          }
+        }
+      }
+    }
+    const int U = min(base_out, out.cap);
+    if (tid == 0) {
+      out.sel_count[head] = U;
+      if (ent) out.ucount[head] = U;
     }
   }
 }
@@ -928,12 +870,12 @@ __global__ __launch_bounds__(NT) void shared_select_kernel(KvView kv, Shape sh, 
                                                             const float* __restrict__ scores, int topk,
                                                             int32_t* __restrict__ sel_pages,
                                                             int32_t* __restrict__ sel_count, int cap) {
-  __shared__ RadixLds<E, NT> rl;
+  __shared__ RadixLds<NT> rl;
   __shared__ int scan[17];
   const int j = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
   const int head = b * sh.Hkv + j;
   const int p_first = tid * E;
-  if (tid < 256) rl.hist[tid] = 0u;
+  radix_clear(rl);
   const int M = min(active_count[b], sh.B) * sh.G;
   const int P = min(seq_pages(kv, sh, b), NT * E);
   if (M <= 0 || P <= 0) {
@@ -977,30 +919,31 @@ __global__ __launch_bounds__(NT) void shared_select_kernel(KvView kv, Shape sh, 
 
   const int Kp = min(topk, P);
   const bool all = Kp >= P;
-  uint32_t prefix;
-  int need;
-  bool ties_cut;
-  radix_kth<E, NT>(key, nmine, Kp, all, rl, prefix, need, ties_cut);
+  uint32_t kth = 0u;
+  bool cut = false;
+  if (!all) radix_kth<E, NT>(key, nmine, Kp, rl, kth, cut);
 
   int my_eq = 0, my_gt = 0;
 #pragma unroll
   for (int i = 0; i < E; ++i) {
     const bool in = i < nmine;
-    my_gt += in && (all || key[i] > prefix);
-    my_eq += in && !all && key[i] == prefix;
+    my_gt += in && (all || key[i] > kth);
+    my_eq += in && !all && key[i] == kth;
   }
-  int tot_eq, eq_rank = 0;
-  if (ties_cut) eq_rank = block_exclusive_scan(my_eq, scan, &tot_eq);
-  const int mine = my_gt + (ties_cut ? max(0, min(my_eq, need - eq_rank)) : my_eq);
+  int tot_gt, tot_eq, eq_rank = 0;
+  block_exclusive_scan(my_gt, scan, &tot_gt);
+  const int need = Kp - tot_gt;   // keys equal to the K-th that are kept
+  if (cut) eq_rank = block_exclusive_scan(my_eq, scan, &tot_eq);
+  const int mine = my_gt + (cut ? max(0, min(my_eq, need - eq_rank)) : my_eq);
   int total;
   int pos = block_exclusive_scan(mine, scan, &total);
   int32_t* sel = sel_pages + (size_t)head * cap;
 #pragma unroll
   for (int i = 0; i < E; ++i) {
     const bool in = i < nmine;
-    bool take = in && (all || key[i] > prefix);
-    if (in && !all && key[i] == prefix) {
-      take = !ties_cut || eq_rank < need;
+    bool take = in && (all || key[i] > kth);
+    if (in && !all && key[i] == kth) {
+      take = !cut || eq_rank < need;
       ++eq_rank;
     }
     if (take) {
@@ -1019,7 +962,7 @@ hipError_t launch_page_scores(hipStream_t st, int dtype, const KvView& kv, const
   if (batch <= 0) return hipSuccess;
   if (union_bits && dtype != LOSA_BF16) return hipErrorInvalidValue;
   const int copy_words = union_copy_words(max_seq_pages);
-  ScoreAux aux{tickets, sel_count, prep ? prep->ucount : nullptr, prep ? prep->mrows : nullptr, union_bits,
+  ScoreAux aux{tickets, sel_count, prep ? *prep : AttnPrepared{nullptr, nullptr, nullptr, nullptr}, union_bits,
                union_words(sh.max_pages), union_copies(copy_words) * copy_words};
   RankArgs ra{nullptr, 0, 0, 0.f, nullptr, nullptr, nullptr};
   if (ranking) {
@@ -1056,9 +999,8 @@ hipError_t launch_page_scores(hipStream_t st, int dtype, const KvView& kv, const
 }
 
 hipError_t launch_select_pages(hipStream_t st, const KvView& kv, const Shape& sh, int batch, int max_seq_pages,
-                               const void* q, const int32_t* active_idx, const int32_t* active_count,
-                               const float* scores, int topk, int32_t* topk_out, int32_t* sel_pages,
-                               int32_t* sel_count, int cap, uint32_t* rowmaps, int32_t* tickets,
+                               const int32_t* active_count, const float* scores, int topk, int32_t* topk_out,
+                               int32_t* sel_pages, int32_t* sel_count, int cap, uint32_t* rowmaps, int32_t* tickets,
                                const AttnPrepared* prep, int rows_hint, long workgroups_per_round, uint32_t* union_bits) {
   if (batch <= 0) return hipSuccess;
   if (union_bits && (!prep || topk_out)) return hipErrorInvalidValue;
@@ -1073,13 +1015,15 @@ hipError_t launch_select_pages(hipStream_t st, const KvView& kv, const Shape& sh
   out.cap = cap;
   out.rowmaps = rowmaps;
   out.tickets = tickets;
-  out.prep = prep ? *prep : AttnPrepared{nullptr, nullptr, nullptr, nullptr};
-  out.q = q;
-  out.active_idx = active_idx;
+  out.entries = prep ? prep->entries : nullptr;
+  out.ucount = prep ? prep->ucount : nullptr;
   out.rows_known = rows_hint >= 1;
   // rows_hint: an upper bound on |A| * G the host happens to know (0: none); rows past it get no workgroup
   const int rows = rows_hint >= 1 && rows_hint < sh.rows_max ? rows_hint : sh.rows_max;
   const int pages = max_seq_pages < sh.max_pages ? max_seq_pages : sh.max_pages;
+  if (pages > kMaxSelectPages) return hipErrorInvalidValue;
+  // no head can have more rows than a union bitmap serves: the kernel without the list
+  const bool list = !union_bits || rows > kUnionRows;
   // One row per workgroup while the grid fits the machine in one round (seven 256-thread
   // workgroups per CU for the one-row form, five for the several-row form, by their register
   // counts; one 1024-thread workgroup); beyond that, up to four rows per workgroup.
@@ -1091,30 +1035,26 @@ hipError_t launch_select_pages(hipStream_t st, const KvView& kv, const Shape& sh
   // (a count the host does not know: the grid has a workgroup for every possible row, and those past
   // the count leave at once; sized as if a quarter of the rows existed, so that a typical active set
   // is not made to share workgroups for the sake of rows that are not there)
-  const long wgs = (long)(rows + 1) * sh.Hkv * batch / (out.rows_known ? 1 : 4);
+  const long wgs = (long)rows * sh.Hkv * batch / (out.rows_known ? 1 : 4);
   int rpw = wgs <= fit_one ? 1 : (int)((wgs + fit_many - 1) / fit_many);
   rpw = rpw < 1 ? 1 : (rpw > 4 ? 4 : rpw);
-  dim3 grid((rows + rpw - 1) / rpw + 1, sh.Hkv, batch);   // + the query-gather workgroup
+  dim3 grid((rows + rpw - 1) / rpw, sh.Hkv, batch);
   // Few keys per thread keep the unrolled code small (it has to come through the instruction
   // cache on every launch) and the loads contiguous: longer sequences get more threads, not
   // more keys per thread.
+#define LOSA_SELECT(E, NT)                                                                                                             \
+  (rpw == 1 ? (list ? select_pages_kernel<E, NT, false, true> : select_pages_kernel<E, NT, false, false>)                              \
+            : (list ? select_pages_kernel<E, NT, true, true> : select_pages_kernel<E, NT, true, false>))<<<grid, NT, 0, st>>>(          \
+      kv, sh, active_count, scores, topk, out, rpw)
   if (pages <= 256 * 8)
-    if (rpw == 1)
-      select_pages_kernel<8, 256, false><<<grid, 256, 0, st>>>(kv, sh, active_count, scores, topk, out, 1);
-    else
-      select_pages_kernel<8, 256, true><<<grid, 256, 0, st>>>(kv, sh, active_count, scores, topk, out, rpw);
+    LOSA_SELECT(8, 256);
+  else if (pages <= 512 * 8)
+    LOSA_SELECT(8, 512);
   else if (pages <= 1024 * 8)
-    if (rpw == 1)
-      select_pages_kernel<8, 1024, false><<<grid, 1024, 0, st>>>(kv, sh, active_count, scores, topk, out, 1);
-    else
-      select_pages_kernel<8, 1024, true><<<grid, 1024, 0, st>>>(kv, sh, active_count, scores, topk, out, rpw);
-  else if (pages <= kMaxSelectPages)
-    if (rpw == 1)
-      select_pages_kernel<16, 1024, false><<<grid, 1024, 0, st>>>(kv, sh, active_count, scores, topk, out, 1);
-    else
-      select_pages_kernel<16, 1024, true><<<grid, 1024, 0, st>>>(kv, sh, active_count, scores, topk, out, rpw);
+    LOSA_SELECT(8, 1024);
   else
-    return hipErrorInvalidValue;
+    LOSA_SELECT(16, 1024);
+#undef LOSA_SELECT
   return hipGetLastError();
 }
 

@@ -245,6 +245,53 @@ def test_active_set_of_a_step_at_the_edges_of_its_ranking(B):
         ctx.close()
 
 
+@pytest.mark.parametrize("P", [1, 7, 64, 255, 256, 2047, 2048, 2049, 4096, 4097, 8192, 8193, 16384])
+def test_selection_at_the_edges_of_its_digits_buckets_and_threads(P):
+    """Scores set one by one (a page's bounds are its value in one channel, the query is 1, -1 or 0 there): clusters that
+    overflow the bucket ranked directly, ladders of neighbouring floats that need every digit, few values, one value,
+    the whole float range, infinities.  Picks and unions have to be equal: larger score first, then smaller page."""
+    rng, d, B, g, dev = np.random.Generator(np.random.Philox(P)), 64, 4, 16, "cuda:0"
+    ladder = (np.float32(3.0).view(np.int32) + rng.integers(0, 3 * P, P)).astype(np.int32).view(np.float32)
+    wide = (rng.choice([-1.0, 1.0], P) * 10.0 ** rng.uniform(-30, 30, P)).astype(np.float32)
+    normal = (40 + 10 * rng.standard_normal(P)).astype(np.float32)
+    kinds = {"normal": normal, "wide": wide, "ladder": ladder,
+             "cluster": np.where(rng.random(P) < 0.3, 7 + 1e-4 * rng.random(P), 50 * rng.standard_normal(P)).astype(np.float32),
+             "few": rng.integers(-2, 3, P).astype(np.float32), "one": np.full(P, -1.5, np.float32),
+             "infinite": np.where(rng.random(P) < 0.1, rng.choice([-np.inf, np.inf], P), normal).astype(np.float32)}
+    page_ids = torch.from_numpy(rng.permutation(P).astype(np.int32)).to(dev)
+    one_page = torch.zeros((1, 1, g, d), device=dev)
+    meta = torch.zeros((P, 1, 2, d), device=dev)
+    kv = L.PagedKV(one_page.expand(P, 1, g, d), one_page.reshape(1, 1, d, g).expand(P, 1, d, g), meta,
+                   torch.tensor([0, P], dtype=torch.int32, device=dev), page_ids,
+                   torch.tensor([P * g - 3], dtype=torch.int32, device=dev), max_seq_pages=P)
+    ctx = L.losa_create(L.make_config(max_batch=1, num_q_heads=1, num_kv_heads=1, head_dim=d, hidden_size=d, page_size=g,
+                                      block_size=B, max_pages_per_seq=P, max_topk_pages=P, dtype=L.LOSA_F32), dev)
+    active, count = torch.arange(B, dtype=torch.int32, device=dev), torch.tensor([B], dtype=torch.int32, device=dev)
+    sel, cnt = torch.zeros((1, 1, P), dtype=torch.int32, device=dev), torch.zeros((1, 1), dtype=torch.int32, device=dev)
+    try:
+        for kind, value in kinds.items():
+            meta[page_ids.long(), 0, :, 0] = torch.from_numpy(value).to(dev)[:, None]
+            scale = np.array([1.0, -1.0, 2.0 if kind == "infinite" else 0.0, 1.0], np.float32)
+            q = torch.zeros((B, 1, d), device=dev)
+            q[:, 0, 0] = torch.from_numpy(scale).to(dev)
+            for K in sorted({1, min(2, P), min(65, P), max(1, P // 16), max(1, P - 1), P}):
+                tk = torch.full((1, B, 1, K), -7, dtype=torch.int32, device=dev)
+                L.losa_score_pages(ctx, kv, q, active, count, K, tk, sel, cnt, P)
+                torch.cuda.synchronize()
+                got = tk.cpu().numpy().reshape(B, K)
+                with np.errstate(over="ignore"):
+                    want = [np.sort(np.argsort(-(s * value), kind="stable")[:K]) for s in scale]
+                for r in range(B):
+                    assert np.array_equal(got[r], want[r]), (kind, K, r)
+                union = np.unique(np.concatenate(want))
+                assert int(cnt.item()) == len(union) and np.array_equal(sel.cpu().numpy().reshape(-1)[:len(union)], union), (kind, K)
+                L.losa_score_pages_shared(ctx, kv, q, active, torch.ones_like(count), K, sel, cnt, P)   # row 0 alone
+                torch.cuda.synchronize()
+                assert int(cnt.item()) == K and np.array_equal(sel.cpu().numpy().reshape(-1)[:K], want[0]), (kind, K, "shared")
+    finally:
+        ctx.close()
+
+
 @pytest.mark.parametrize("page", [16, 32])
 @pytest.mark.parametrize("B,G,d", [
     (13, 5, 128),     # 65 rows: two token groups
