@@ -87,7 +87,8 @@ struct losa_ctx {
   bool union_in_attention;  // sparse steps of up to 64 rows: the attention kernel builds the union
   bool shared_tiles;        // more than 64 rows: 8 wavefronts share each tile through LDS (else 4 independent ones)
   bool half_values;         // ... and their value product runs in half precision (else P as a bfloat16 pair)
-  AttnPrepared prep;
+  uint16_t* q_act;          // gathered query rows and ...
+  int32_t* entries;         // ... page tables as the attention kernel reads them beside a union bitmap
   char err[256];
   // measurement hooks
   bool profiling = false;
@@ -169,7 +170,7 @@ struct Carve {
 
 struct Layout {
   size_t delta, mask, active_idx, active_count, scores, rowmaps, union_bits, tickets, sel_pages, sel_count, po, pm, pl;
-  size_t entries, q_act, ucount, mrows, seq_tickets, total;
+  size_t entries, q_act, seq_tickets, total;
   long part_rows;   // capacity of the split-K partial buffers, in (work item, query row) pairs
 };
 
@@ -204,10 +205,8 @@ Layout make_layout(const losa_config* c) {
   L.pl = cv.take((size_t)L.part_rows * 4);
   L.entries = cv.take(heads * c->max_pages_per_seq * 4);
   L.q_act = cv.take(heads * rows_max * c->head_dim * 2);
-  L.ucount = cv.take(heads * 4);
-  L.mrows = cv.take(heads * 4);
   L.seq_tickets = cv.take((size_t)c->max_batch * 4);
-  L.union_bits = cv.take(heads * (size_t)union_words(c->max_pages_per_seq) * 4);
+  L.union_bits = cv.take(heads * (size_t)union_words(c->max_pages_per_seq, (int)rows_max) * 4);
   L.total = cv.off;
   return L;
 }
@@ -335,19 +334,18 @@ losa_status select_active_impl(losa_ctx* ctx, hipStream_t st, int batch, const v
 
 losa_status score_pages_impl(losa_ctx* ctx, hipStream_t st, const KvView& kv, int batch, int max_seq_pages,
                              const void* q, const int32_t* active_idx, const int32_t* active_count, int topk,
-                             int32_t* topk_out, int32_t* sel_pages, int32_t* sel_count, int cap, bool prepare_attn,
-                             int rows_upper, const InKernelRanking* ranking = nullptr, uint32_t* union_bits = nullptr) {
-  const AttnPrepared* prep = prepare_attn ? &ctx->prep : nullptr;
+                             int32_t* topk_out, int32_t* sel_pages, int32_t* sel_count, int cap, int rows_upper,
+                             const InKernelRanking* ranking = nullptr, uint32_t* union_bits = nullptr) {
   hipError_t e;
   {
     StageTimer timer(ctx, st, LOSA_STAGE_SCORE);
     e = launch_page_scores(st, ctx->cfg.dtype, kv, ctx->sh, batch, max_seq_pages, q, active_idx, active_count,
-                           ctx->scores, ctx->tickets, sel_count, prep, ranking, ctx->score_round, union_bits);
+                           ctx->scores, ctx->tickets, sel_count, ctx->entries, ctx->q_act, rows_upper, ranking, ctx->score_round, union_bits);
   }
   if (e != hipSuccess) return hip_fail(ctx, "page_scores launch", e);
   StageTimer timer(ctx, st, LOSA_STAGE_TOPK);
   e = launch_select_pages(st, kv, ctx->sh, batch, max_seq_pages, active_count, ctx->scores, topk, topk_out,
-                          sel_pages, sel_count, cap, ctx->rowmaps, ctx->tickets, prep, rows_upper,
+                          sel_pages, sel_count, cap, ctx->rowmaps, ctx->tickets, rows_upper,
                           ctx->select_round, union_bits);
   if (e != hipSuccess) return hip_fail(ctx, "select_pages launch", e);
   return LOSA_OK;
@@ -356,7 +354,7 @@ losa_status score_pages_impl(losa_ctx* ctx, hipStream_t st, const KvView& kv, in
 losa_status sparse_attn_impl(losa_ctx* ctx, hipStream_t st, const KvView& kv, int batch, int max_seq_pages,
                              const void* q, const int32_t* active_idx, const int32_t* active_count,
                              const int32_t* sel_pages, const int32_t* sel_count, int cap, int rows_upper,
-                             bool prepared, float* o_p, float* lse_p, const UnionInKernel* uni = nullptr) {
+                             float* o_p, float* lse_p, const UnionInKernel* uni = nullptr) {
   const int upper = sel_pages ? (cap < max_seq_pages ? cap : max_seq_pages) : max_seq_pages;
   const bool mfma = ctx->cfg.dtype == LOSA_BF16;
   if (!active_idx) rows_upper = ctx->sh.rows_max;   // every token is active: the count is known
@@ -392,14 +390,7 @@ losa_status sparse_attn_impl(losa_ctx* ctx, hipStream_t st, const KvView& kv, in
     nchunk = pairs < 64 ? 64 : pairs < nchunk ? pairs : nchunk;
   }
   hipError_t e;
-  // the dense step of the shared-stage kernel reads page table and queries where they are; everything else
-  // that is not prepared yet goes through attn_prepare
-  const bool dense_step = rows_kernel && !active_idx && !sel_pages;
-  if (mfma && !prepared && !dense_step) {
-    StageTimer timer(ctx, st, LOSA_STAGE_TOPK);
-    e = launch_attn_prepare(st, kv, ctx->sh, batch, q, active_idx, active_count, sel_pages, sel_count, cap, ctx->prep);
-    if (e != hipSuccess) return hip_fail(ctx, "attn_prepare launch", e);
-  }
+  const AttnInputs in{q, active_idx, active_count, uni ? nullptr : sel_pages, sel_count, cap};
   {
     StageTimer timer(ctx, st, LOSA_STAGE_ATTN, /*bind_to_dispatch=*/mfma && !both_shapes);
     if (!mfma) {
@@ -409,21 +400,19 @@ losa_status sparse_attn_impl(losa_ctx* ctx, hipStream_t st, const KvView& kv, in
       const hipEvent_t e0 = both_shapes ? nullptr : timer.start(), e1 = both_shapes ? nullptr : timer.stop();
       e = hipSuccess;
       if (both_shapes || !rows_kernel)
-        e = launch_attn_mfma(st, kv, ctx->sh, batch, ctx->prep, nchunk, both_shapes ? 64 : rows_upper, part, e0, e1, 0,
-                             both_shapes ? 64 : 0x7fffffff, uni);
+        e = launch_attn_mfma(st, kv, ctx->sh, batch, in, nchunk, both_shapes ? 64 : rows_upper, part, e0, e1, 0,
+                             both_shapes ? 64 : 0x7fffffff, !hinted && (both_shapes || ctx->sh.rows_max <= kSparseRows), uni);
       if (e == hipSuccess && rows_kernel)
-        e = launch_attn_rows(st, kv, ctx->sh, batch, ctx->prep, dense_step ? q : nullptr, nchunk, part, e0, e1, both_shapes ? 64 : 0,
-                             ctx->half_values);
+        e = launch_attn_rows(st, kv, ctx->sh, batch, in, nchunk, part, e0, e1, both_shapes ? 64 : 0,
+                             ctx->half_values, upper, uni);
       else if (e == hipSuccess && both_shapes)
-        e = launch_attn_mfma(st, kv, ctx->sh, batch, ctx->prep, nchunk, ctx->sh.rows_max, part, nullptr, nullptr, 64,
-                             0x7fffffff, nullptr);
+        e = launch_attn_mfma(st, kv, ctx->sh, batch, in, nchunk, ctx->sh.rows_max, part, nullptr, nullptr, 64,
+                             0x7fffffff);
     }
   }
   if (e != hipSuccess) return hip_fail(ctx, "attention launch", e);
   StageTimer timer(ctx, st, LOSA_STAGE_MERGE);
-  e = launch_attn_merge(st, kv, ctx->sh, batch, active_idx, active_count, sel_count, cap, nchunk,
-                        mfma ? &ctx->prep : nullptr, part, o_p, lse_p, hinted ? rows_upper : 0, few_tile,
-                        many_tile, dense_step);
+  e = launch_attn_merge(st, kv, ctx->sh, batch, in, mfma, nchunk, part, o_p, lse_p, hinted ? rows_upper : 0, few_tile, many_tile);
   if (e != hipSuccess) return hip_fail(ctx, "attn_merge launch", e);
   return LOSA_OK;
 }
@@ -487,10 +476,8 @@ losa_status losa_create(const losa_config* cfg, void* workspace, size_t workspac
   ctx->union_in_attention = true;
   ctx->shared_tiles = true;
   ctx->half_values = true;
-  ctx->prep.entries = (int32_t*)(base + L.entries);
-  ctx->prep.q_act = (uint16_t*)(base + L.q_act);
-  ctx->prep.ucount = (int32_t*)(base + L.ucount);
-  ctx->prep.mrows = (int32_t*)(base + L.mrows);
+  ctx->entries = (int32_t*)(base + L.entries);
+  ctx->q_act = (uint16_t*)(base + L.q_act);
   ctx->seq_tickets = (int32_t*)(base + L.seq_tickets);
   ctx->err[0] = 0;
   *out = ctx;
@@ -634,7 +621,7 @@ losa_status losa_score_pages(losa_ctx* ctx, void* stream, const losa_kv* kv, con
   const long need = worst < msp ? worst : msp;
   if (cap < need) return fail(ctx, LOSA_ERR_INVALID_ARG, "cap %d is below the union's worst case %ld", cap, need);
   return score_pages_impl(ctx, as_stream(stream), view_of(kv, msp), kv->batch, msp, q, active_idx, active_count,
-                          topk_pages, topk_out, sel_pages, sel_count, cap, /*prepare_attn=*/false, /*rows_upper=*/0);
+                          topk_pages, topk_out, sel_pages, sel_count, cap, /*rows_upper=*/0);
 }
 
 losa_status losa_score_pages_shared(losa_ctx* ctx, void* stream, const losa_kv* kv, const void* q,
@@ -657,7 +644,7 @@ losa_status losa_score_pages_shared(losa_ctx* ctx, void* stream, const losa_kv* 
   {
     StageTimer timer(ctx, st, LOSA_STAGE_SCORE);
     e = launch_page_scores(st, ctx->cfg.dtype, view, ctx->sh, kv->batch, msp, q, active_idx, active_count, ctx->scores,
-                           ctx->tickets, sel_count, nullptr, nullptr, ctx->score_round);
+                           ctx->tickets, sel_count, nullptr, nullptr, 0, nullptr, ctx->score_round);
   }
   if (e != hipSuccess) return hip_fail(ctx, "page_scores launch", e);
   StageTimer timer(ctx, st, LOSA_STAGE_TOPK);
@@ -681,7 +668,7 @@ losa_status losa_sparse_attn(losa_ctx* ctx, void* stream, const losa_kv* kv, con
     return fail(ctx, LOSA_ERR_INVALID_ARG, "sel_pages and sel_count must both be given or both be NULL");
   if (sel_pages && cap < 1) return fail(ctx, LOSA_ERR_INVALID_ARG, "cap must be >= 1");
   return sparse_attn_impl(ctx, as_stream(stream), view_of(kv, msp), kv->batch, msp, q, active_idx, active_count, sel_pages,
-                          sel_count, cap, /*rows_upper=*/0, /*prepared=*/false, (float*)o_p, lse_p);
+                          sel_count, cap, /*rows_upper=*/0, (float*)o_p, lse_p);
 }
 
 losa_status losa_block_merge(losa_ctx* ctx, void* stream, int32_t batch, const void* q, const void* k_b,
@@ -711,7 +698,7 @@ losa_status losa_step(losa_ctx* ctx, void* stream, const losa_kv* kv, int32_t st
   hipStream_t st = as_stream(stream);
   const KvView view = view_of(kv, msp);
   if (dense)
-    return sparse_attn_impl(ctx, st, view, kv->batch, msp, q, nullptr, nullptr, nullptr, nullptr, 0, 0, false,
+    return sparse_attn_impl(ctx, st, view, kv->batch, msp, q, nullptr, nullptr, nullptr, nullptr, 0, 0,
                             (float*)o_p, lse_p);
   if (!h_cur || !h_prev) return fail(ctx, LOSA_ERR_INVALID_ARG, "losa_step: h_cur / h_prev are NULL");
   if (topk_pages < 1 || topk_pages > ctx->cfg.max_topk_pages)
@@ -736,25 +723,24 @@ losa_status losa_step(losa_ctx* ctx, void* stream, const losa_kv* kv, int32_t st
     if (s != LOSA_OK) return s;
   }
   const int cap = ctx->sh.max_pages;
-  const bool fuse_prepare = ctx->cfg.dtype == LOSA_BF16;   // the selection kernel also builds the attention inputs
+  const bool bf16 = ctx->cfg.dtype == LOSA_BF16;
   // the host knows |A| in the top-n modes, so selection and attention can be shaped for n*G rows
   const bool counted = mode == LOSA_SEL_TOPK || mode == LOSA_SEL_FRACTION;
   const int rows_upper = counted ? select_count(ctx, (int)mode, param) * ctx->sh.G : 0;
-  // Up to 64 query rows per KV head: the attention workgroups build the union of the per-row picks
-  // themselves, and the selection kernel ends with ORing them into the head's bitmap.  With a count only the device
-  // knows, the selection kernel does so for the heads it finds with at most 64 rows, and the attention
-  // launch for those heads takes their row-tile counts from the device; heads with more rows get the
-  // union list and the many-row launch as before.
-  const bool union_counted = fuse_prepare && counted && rows_upper >= 1 && rows_upper <= 64 && ctx->union_in_attention;
-  const bool union_on_device = fuse_prepare && !counted && ctx->sh.rows_max <= 256 && ctx->union_in_attention;
-  const bool union_in_attn = union_counted || union_on_device;
-  const UnionInKernel uni{ctx->union_bits, sc, union_words(ctx->sh.max_pages), union_copy_words(msp), union_on_device};
+  // The attention workgroups build the union of the per-row picks themselves, and the selection kernel ends with ORing
+  // them into the head's bitmap (for more than 64 rows only the shared-stage kernel does).  With a count only
+  // the device knows the attention launches take their row-tile counts from the device.
+  const bool few_only = (counted ? rows_upper : ctx->sh.rows_max) <= kSparseRows;
+  const bool union_in_attn = bf16 && ctx->union_in_attention && (!counted || rows_upper >= 1) && (few_only || ctx->shared_tiles);
+  const int union_upper = counted ? rows_upper : ctx->sh.rows_max;
+  const UnionInKernel uni{ctx->union_bits, ctx->entries, ctx->q_act, sc, union_words(ctx->sh.max_pages, ctx->sh.rows_max),
+                          union_copy_words(msp), union_copies(union_copy_words(msp), union_upper)};
   s = score_pages_impl(ctx, st, view, kv->batch, msp, q, ctx->active_idx, ctx->active_count, topk_pages, nullptr,
-                       ctx->sel_pages, sc, cap, fuse_prepare, rows_upper, rank_in_scores ? &ranking : nullptr,
+                       ctx->sel_pages, sc, cap, rows_upper, rank_in_scores ? &ranking : nullptr,
                        union_in_attn ? ctx->union_bits : nullptr);
   if (s != LOSA_OK) return s;
   return sparse_attn_impl(ctx, st, view, kv->batch, msp, q, ctx->active_idx, ctx->active_count, ctx->sel_pages, sc,
-                          cap, rows_upper, fuse_prepare, (float*)o_p, lse_p, union_in_attn ? &uni : nullptr);
+                          cap, rows_upper, (float*)o_p, lse_p, union_in_attn ? &uni : nullptr);
 }
 
 }  // extern "C"

@@ -51,34 +51,40 @@ struct Partials {
   int rows;   // rows per item in this launch: an upper bound on the query rows of a KV head
 };
 
-// Prepared inputs of the matrix-core attention kernel, per (sequence, KV head) = `head`.
-constexpr int kEntryShift = 26;   // entry = physical page id | (valid tokens << 26)
-struct AttnPrepared {
-  int32_t* entries;   // [heads, max_pages]
-  uint16_t* q_act;    // [heads, rows_max, d] bfloat16: query rows of the active tokens, gathered
-  int32_t* ucount;    // [heads] entries in the list
-  int32_t* mrows;     // [heads] query rows (|A| * G)
+// What the attention kernels read besides keys and values.
+struct AttnInputs {
+  const void* q;                 // [batch*B, Hq, d]
+  const int32_t* active_idx;     // [batch, B] token of every active slot, active_count [batch]; both NULL: every token
+  const int32_t* active_count;
+  const int32_t* list;           // [heads, cap] logical pages, sel_count [heads] of them; NULL: every page, or the union below
+  const int32_t* sel_count;
+  int cap;
 };
-// The other way the matrix-core kernel can get its page list (sparse steps of losa_step with at
-// most 64 query rows per KV head): the selection workgroups OR their row's picks into one bitmap per
-// head, and every attention workgroup ranks that union and resolves its own pages itself while it
-// starts up.  That takes the selection kernel's serial tail (bitmap hand-over to one workgroup per
-// head, union, list) out of the chain of launches.  When the host does not know the row count
-// (threshold / cumulative-mass selection) the selection kernel decides per (sequence, KV head),
-// by the count it finds, which of the two forms it leaves, and the attention launch takes each
-// head's row-tile count from the device (rows_on_device).
+// Query rows of a KV head of sequence b.  (A load behind a branch would wait for what the branch tests and hold up what
+// follows: the address is chosen instead, any valid one where there is no count.)
+__device__ __forceinline__ int active_rows(const AttnInputs& in, const KvView& kv, const Shape& sh, int b) {
+  const int n = (in.active_count ? in.active_count : kv.seq_lens)[b];
+  return (in.active_count ? min(n, sh.B) : sh.B) * sh.G;
+}
+constexpr int kEntryShift = 26;   // entry = physical page id | (valid tokens << 26)
+// The other way the matrix-core kernels can get their pages (sparse steps of losa_step): the selection workgroups OR
+// their row's picks into one bitmap per head, and every attention workgroup ranks that union and resolves its own pages
+// itself while it starts up.  That takes the selection kernel's serial tail (bitmap hand-over to one
+// workgroup per head, union, list) out of the chain of launches.
 constexpr int kUnionRows = 64;   // the most rows the split-pages shape serves
 struct UnionInKernel {
-  const uint32_t* bits;      // [heads][union_words()] union of the head's picks, in copies; NULL: use AttnPrepared::entries
+  const uint32_t* bits;      // [heads][union_words()] union of the head's picks, in copies; NULL: no union
+  const int32_t* entries;    // [heads, max_pages] the head's page table as entries, by logical page
+  const uint16_t* q_act;     // [heads, rows_max, d] bfloat16: query rows of the active tokens, gathered
   int32_t* sel_count;        // [heads] out: pages in the union (written by the head's first workgroup)
-  int stride, copy_words;    // union_words(), union_copy_words()
-  bool rows_on_device;       // host side only: launch the form that sizes itself by AttnPrepared::mrows
+  int stride, copy_words, copies;   // union_words(), union_copy_words(), union_copies()
 };
-// A head's union bitmap.  Up to 1024 pages it is kept in copies, row r in copy r mod their number, that fill
-// kUnionSpread words: the rows' atomics on one word come one after the other, and with a short prefix they all fall
-// on the same few words (2 x 378-728 tokens, 32 rows: selection 7.4 us with one copy, 6.3 with 16; where a row
-// does not OR at all, 6.3).  The attention kernel reads all of them with the four loads it has for 8192 pages.
-// Beyond, the words are many enough: at 2048 pages four copies cost 0.5 us more than they save (4 x 65536 tokens).
+// A head's union bitmap.  The rows' atomics on one word come one after the other (34 ns each), so it is kept in copies.  Up
+// to 1024 pages, where all rows fall on the same few words, row r goes to copy r mod their number, and they fill
+// kUnionSpread words (2 x 378-728 tokens, 32 rows: selection 7.4 us with one copy, 6.3 with 16; where a row
+// does not OR at all, 6.3).  The split-pages kernel reads all of them with the four loads it has for 8192 pages.
+// Beyond, the words are many enough for that kernel's rows (at 2048 pages four copies cost 0.5 us more than they
+// save, 4 x 65536 tokens), and every further 64 rows get a copy of their own, up to eight.
 constexpr int kUnionSpread = 256;
 constexpr int kMostCopiedWords = 32;
 // words of one copy, for the pages the launch was sized for (KvView::seq_page_limit)
@@ -86,12 +92,15 @@ __host__ __device__ inline int union_copy_words(int pages) {
   const int words = (pages + 31) / 32;
   return words <= 16 ? 16 : words <= kMostCopiedWords ? kMostCopiedWords : (words + 3) & ~3;
 }
-__host__ __device__ inline int union_copies(int copy_words) {
-  return copy_words <= kMostCopiedWords ? kUnionSpread / copy_words : 1;
+// their number (a power of two) for heads of up to `rows` rows, and the shift that makes a row its copy
+__host__ __device__ inline int union_copies(int copy_words, int rows) {
+  if (copy_words <= kMostCopiedWords) return kUnionSpread / copy_words;
+  return rows <= kUnionRows ? 1 : rows <= 2 * kUnionRows ? 2 : rows <= 4 * kUnionRows ? 4 : 8;
 }
+__host__ __device__ inline int union_row_shift(int copy_words) { return copy_words <= kMostCopiedWords ? 0 : 6; }
 // words per head, whatever the launch
-__host__ __device__ inline int union_words(int max_pages) {
-  const int words = union_copy_words(max_pages);
+__host__ __device__ inline int union_words(int max_pages, int rows_max) {
+  const int copy_words = union_copy_words(max_pages), words = copy_words * union_copies(copy_words, rows_max);
   return words > kUnionSpread ? words : kUnionSpread;
 }
 
@@ -133,44 +142,38 @@ struct InKernelRanking {
 };
 hipError_t launch_page_scores(hipStream_t st, int dtype, const KvView& kv, const Shape& sh, int batch, int max_seq_pages,
                               const void* q, const int32_t* active_idx, const int32_t* active_count,
-                              float* scores, int32_t* tickets, int32_t* sel_count, const AttnPrepared* prep,
+                              float* scores, int32_t* tickets, int32_t* sel_count, int32_t* entries, uint16_t* q_act, int rows_upper,
                               const InKernelRanking* ranking, long workgroups_per_round, uint32_t* union_bits = nullptr);
 hipError_t launch_select_pages(hipStream_t st, const KvView& kv, const Shape& sh, int batch, int max_seq_pages,
                                const int32_t* active_count, const float* scores, int topk, int32_t* topk_out,
                                int32_t* sel_pages, int32_t* sel_count, int cap, uint32_t* rowmaps, int32_t* tickets,
-                               const AttnPrepared* prep, int rows_hint, long workgroups_per_round,
+                               int rows_hint, long workgroups_per_round,
                                uint32_t* union_bits = nullptr);
 
 // ---- sparse_attn.hip (float mode, merge) and sparse_attn_mfma.hip (bfloat16)
 // Tiles of a (sequence, KV head) page list are dealt round-robin to `nchunk` work items: tiles of 32 tokens
-// (bfloat16), single pages (float mode).  launch_attn_merge: prep != NULL means bfloat16 partials.
+// (bfloat16), single pages (float mode).  launch_attn_merge: bf16 means bfloat16 partials.
 hipError_t launch_attn_f32(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const void* q,
                            const int32_t* active_idx, const int32_t* active_count, const int32_t* sel_pages,
                            const int32_t* sel_count, int cap, int nchunk, const Partials& part);
-hipError_t launch_attn_prepare(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const void* q,
-                               const int32_t* active_idx, const int32_t* active_count, const int32_t* sel_pages,
-                               const int32_t* sel_count, int cap, const AttnPrepared& prep);
 // e0/e1 (both or neither): events bound to the dispatch itself, for exact kernel timing.
-hipError_t launch_attn_mfma(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnPrepared& prep,
+hipError_t launch_attn_mfma(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnInputs& in,
                             int nchunk, int rows_upper, const Partials& part, hipEvent_t e0, hipEvent_t e1,
                             int m_lo = 0, int m_hi = 0x7fffffff,   // serves (sequence, head) pairs with m_lo < rows <= m_hi
-                            const UnionInKernel* uni = nullptr);
+                            bool rows_on_device = false, const UnionInKernel* uni = nullptr);   // ... up to 64, counted on the device
 // sparse_attn_rows.hip: more than 64 query rows per KV head, eight wavefronts sharing stages of kManyRowStage
 // tokens through LDS; serves (sequence, head) pairs with more than m_lo rows.  Its partials are laid out by
 // fragments: per 32 rows (kPartialTile; part.rows is a multiple of it) and 8 channels, 64 lanes x 4 floats,
 // lane = row of the tile + 32 * (second half of the 8 channels).
 constexpr int kManyRowStage = 64;
 constexpr int kPartialTile = 32;
-// dense_query: the query tensor of a dense step, which needs no prepared inputs; NULL otherwise.
-hipError_t launch_attn_rows(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnPrepared& prep,
-                            const void* dense_query, int nchunk, const Partials& part, hipEvent_t e0, hipEvent_t e1, int m_lo, bool half_values);
+hipError_t launch_attn_rows(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnInputs& in, int nchunk,
+                            const Partials& part, hipEvent_t e0, hipEvent_t e1, int m_lo, bool half_values, int upper,
+                            const UnionInKernel* uni);   // upper: the most pages a head can have
 // few_tile / many_tile: tokens per tile that the partials of a head with at most / more than 64 query rows were
 // dealt in (they decide which of the nchunk work items exist); kManyRowStage: partials laid out by fragments.
-hipError_t launch_attn_merge(hipStream_t st, const KvView& kv, const Shape& sh, int batch,
-                             const int32_t* active_idx, const int32_t* active_count,
-                             const int32_t* sel_count, int cap, int nchunk, const AttnPrepared* prep,
-                             const Partials& part, float* o_p, float* lse_p, int rows_hint, int few_tile, int many_tile,
-                             bool dense_step);   // dense_step: no counts were prepared (launch_attn_rows with dense_query)
+hipError_t launch_attn_merge(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnInputs& in,
+                             bool bf16, int nchunk, const Partials& part, float* o_p, float* lse_p, int rows_hint, int few_tile, int many_tile);
 
 // ---- block_merge.hip
 hipError_t launch_block_merge(hipStream_t st, int dtype, const Shape& sh, int batch, const void* q, const void* k_b,

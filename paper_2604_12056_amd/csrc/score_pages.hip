@@ -18,13 +18,14 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 
 // What the scoring kernel leaves ready for the launches that follow it: the ticket counter of every (sequence, KV
-// head) at zero, empty results when no token is active, so that no selection workgroup will run, and - inside
-// losa_step - what the attention kernel reads: row count, gathered query rows (the scoring workgroups hold them
-// anyway) and, where that kernel ranks the union itself, the head's page table with every page's token count.
+// head) at zero, an empty result when no token is active, so that no selection workgroup will run, and, where the
+// attention kernel ranks the union itself, what that kernel wants at addresses it knows: the head's page table with
+// every page's token count, and the gathered query rows (the scoring workgroups hold them anyway).
 struct ScoreAux {
   int32_t* tickets;
   int32_t* sel_count;
-  AttnPrepared prep;      // (all NULL: nobody reads it)
+  int32_t* entries;       // nullable: [heads, max_pages] physical page | valid tokens << kEntryShift, by logical page
+  uint16_t* q_act;        // ... and [heads, rows_max, d]
   uint32_t* union_bits;   // nullable: union bitmaps, cleared here for the selection to OR into
   int union_stride;       // words per head ...
   int union_len;          // ... of which this launch uses so many
@@ -35,11 +36,7 @@ struct ScoreAux {
   }
   __device__ void reset(int head, int M) const {
     tickets[head] = 0;
-    if (prep.mrows) prep.mrows[head] = M;
-    if (M <= 0) {
-      sel_count[head] = 0;
-      if (prep.ucount) prep.ucount[head] = 0;
-    }
+    if (M <= 0) sel_count[head] = 0;
   }
 };
 
@@ -326,7 +323,7 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape 
   // each row once instead of once per wavefront.  A row is D bfloat16 plus 16 bytes of padding:
   // the 16 lanes that read the same 16-byte column of 16 consecutive rows then fall on
   // different banks.
-  const bool table = aux.prep.entries && aux.union_bits && M <= kUnionRows;   // the attention kernel will want the page table
+  const bool table = aux.entries && M <= kUnionRows;   // the attention kernel will want the page table
   constexpr int kRows = 64, VPR = D / 8, STRIDE = D * 2 + 16;   // bytes; 64 rows cover the usual active sets in one go; with 128 channels 38 KiB of LDS, four workgroups per CU
   // Staged already split by sign (score = q+ . max + q- . min): the split is done once per
   // workgroup by the staging threads, not once per wavefront, tile and row tile.
@@ -340,7 +337,7 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape 
     const bool vec_ok = (sh.max_pages & 3) == 0 && p0t + 16 <= P;
     if (table && qd == 0 && p0t + l16 < P) {
       const int page = p0t + l16, nv = max(0, min(sh.g, tokens - page * sh.g));
-      aux.prep.entries[(size_t)head * sh.max_pages + page] = physv[t] >= 0 && physv[t] < (1 << kEntryShift) ? (physv[t] | (nv << kEntryShift)) : 0;
+      aux.entries[(size_t)head * sh.max_pages + page] = physv[t] >= 0 && physv[t] < (1 << kEntryShift) ? (physv[t] | (nv << kEntryShift)) : 0;
     }
     // the next tile's metadata rows travel while this tile is scored
     bf16x8_t nmin[KS], nmax[KS];
@@ -376,8 +373,8 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape 
             const u32x4_t mk = __builtin_bit_cast(u32x4_t, __builtin_bit_cast(i16x8_t, x) >> 15);   // all-ones where the sign bit is set
             *reinterpret_cast<u32x4_t*>(qs[0] + rr * STRIDE + cv * 16) = x & ~mk;
             *reinterpret_cast<u32x4_t*>(qs[1] + rr * STRIDE + cv * 16) = x & mk;
-            if (t == 0 && first && aux.prep.q_act)
-              *reinterpret_cast<u32x4_t*>(aux.prep.q_act + ((size_t)head * sh.rows_max + r0 + rr) * D + cv * 8) = x;
+            if (t == 0 && first && table)
+              *reinterpret_cast<u32x4_t*>(aux.q_act + ((size_t)head * sh.rows_max + r0 + rr) * D + cv * 8) = x;
           }
         }
         __syncthreads();
@@ -431,7 +428,7 @@ __device__ __forceinline__ uint32_t order_key(float f) {
 // What the selection kernel leaves behind: a union bitmap per (sequence, KV head) that its row workgroups OR their
 // picks into, or (LIST) the union as an ascending page list: every row's workgroup stores its pick bitmap,
 // then takes a ticket; the workgroup that draws the last ticket of a head ORs the rows, compacts
-// the union and builds what the attention kernel consumes.  (How the stores are made visible to that
+// the union.  (How the stores are made visible to that
 // workgroup is described at the hand-over.)
 struct SelectOut {
   int32_t* topk_out;    // nullable [batch, B, Hq, topk]
@@ -440,13 +437,11 @@ struct SelectOut {
   int cap;
   uint32_t* rowmaps;    // workspace [heads, rows_max, words]: pick bitmap of every query row
   int32_t* tickets;     // workspace [heads], zero on entry (zeroed by the scoring kernel), zero on exit
-  int32_t* entries;     // nullable: the list as the attention kernel reads it (AttnPrepared::entries) ...
-  int32_t* ucount;      // ... and its length
   bool rows_known;      // the grid has exactly one workgroup per existing row
-  // union_words() | words of a copy << 10 | (copies - 1) << 20; beside the pointer, so that it arrives with it: fetched
-  // where it is used, it costs a scalar round trip (0.3 us)
-  uint32_t union_shape;
-  uint32_t* union_bits; // non-NULL: heads with at most kUnionRows rows only OR their picks into a copy of this bitmap
+  // union_words() | words of a copy << 16 and (copies - 1) | row shift << 8; beside the pointer, so that they arrive with
+  // it: fetched where they are used, they cost a scalar round trip (0.3 us)
+  uint32_t union_shape, union_rows;
+  uint32_t* union_bits; // non-NULL: rows only OR their picks into a copy of this bitmap
                         // ([heads, union_words()], cleared by the scoring kernel): no hand-over, no list
 };
 
@@ -612,7 +607,7 @@ __device__ __forceinline__ void radix_kth(uint32_t (&key)[E], int nmine, int Kp,
 
 // Per-query top pages, register resident (thread t of NT owns the E consecutive pages
 // [t*E, t*E+E); P <= NT*E: 256 threads x 8 up to 2048 pages, 512 up to 4096, 1024 threads x 8 or 16 beyond).
-// LIST: heads may need the union list (SelectOut).
+// LIST: the union list instead of a bitmap (SelectOut).
 // 2048 pages, 42 rows x 4 heads: 5.3 -> 4.5 us (before: histogram and candidates behind branches, a candidate ranked by
 // one thread, picks through LDS); 4096 pages, 9.2 us with 1024 threads and 5.7 with 512.  The query rows and the page
 // table, which a workgroup of this launch per head used to gather, come from the scoring kernel.
@@ -665,7 +660,6 @@ __global__ __launch_bounds__(NT) void select_pages_kernel(KvView kv, Shape sh, c
   const int words = (sh.max_pages + 31) / 32;
   const int Kp = min(topk, P);
   const int nmine_all = max(0, min(E, P - p_first));   // pages of this thread that exist
-  const bool only_bits = !LIST || (out.union_bits && M <= kUnionRows);
   // LDS that must start at zero is cleared now, while the scores are still on their way
   radix_clear(rl);
   const int r_end = MULTI ? M : r_first + 1;
@@ -729,12 +723,12 @@ __global__ __launch_bounds__(NT) void select_pages_kernel(KvView kv, Shape sh, c
     static_assert(TPW == 2 || TPW == 4, "a word's threads are lanes of one quad");
     const int word = p_first >> 5;
     const bool writes = tid % TPW == 0;
-    if (only_bits) {
+    if constexpr (!LIST) {
       // read by the next launch; nothing waits for the atomics here (an OR has no order)
-      const int copy_words = (int)(out.union_shape >> 10) & 0x3FF;
-      uint32_t* u = out.union_bits + (size_t)head * (out.union_shape & 0x3FF) + (r & (int)(out.union_shape >> 20)) * copy_words;
+      uint32_t* u = out.union_bits + (size_t)head * (out.union_shape & 0xFFFF) +
+                    ((r >> (out.union_rows >> 8)) & (int)(out.union_rows & 0xFF)) * (int)(out.union_shape >> 16);
       if (writes && bits) __hip_atomic_fetch_or(&u[word], bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // (bits: a page < P)
-    } else if constexpr (LIST) {
+    } else {
       // ---- hand-over: the last row of this (sequence, head) builds the union.
       // The row bitmap travels in agent-scope atomic stores (written through to memory, past the
       // per-die L2 slices); ordering is "my stores have completed (wait count zero), then my
@@ -752,7 +746,6 @@ __global__ __launch_bounds__(NT) void select_pages_kernel(KvView kv, Shape sh, c
     }
   }
   if constexpr (LIST) {
-    if (only_bits) return;
     const int rows_done = (r_end - 1 - r_first) / r_step + 1;
     __shared__ int s_last;
     __shared__ uint32_t ubits[WORDS];     // union of the head's rows
@@ -766,23 +759,12 @@ __global__ __launch_bounds__(NT) void select_pages_kernel(KvView kv, Shape sh, c
     __syncthreads();
     if (!s_last) return;
     if (tid == 0) out.tickets[head] = 0;
-    // Union of the M row bitmaps -> ascending page list (+ page entries for the attention kernel).
-    // Pages are handled a thread each, E per thread: their physical ids are fetched
-    // before the bits are known, together with the row bitmaps, so the tail is one memory
-    // round trip.  A page's slot in the list is the popcount prefix of its bitmap word plus
-    // the set bits below it in the word: no serial walk, stores ascend with the thread id.
+    // Union of the M row bitmaps -> ascending page list.
+    // Pages are handled a thread each, E per thread.  A page's slot in the list is the popcount prefix of its bitmap
+    // word plus the set bits below it in the word: no serial walk, stores ascend with the thread id.
     const int wordsP = (P + 31) / 32;
-    const int base = kv.page_indptr[b];
-    const int L = kv.seq_lens[b];
     int32_t* sel = out.sel_pages + (size_t)head * out.cap;
-    int32_t* ent = out.entries ? out.entries + (size_t)head * sh.max_pages : nullptr;
     __shared__ int wordbase[WORDS];
-    int phys[E];
-    if (ent) {
-#pragma unroll
-      for (int i = 0; i < E; ++i)   // (an empty sequence has no entry of its own in the page table)
-        phys[i] = P > 0 ? kv.page_indices[base + min(tid + NT * i, P - 1)] : 0;
-    }
     const uint32_t* maps = out.rowmaps + (size_t)head * sh.rows_max * words;
     {
       // Thread t ORs bitmap word (t mod nw) of every `groups`-th row in registers, 16 independent
@@ -840,21 +822,11 @@ __global__ __launch_bounds__(NT) void select_pages_kernel(KvView kv, Shape sh, c
       const int page = tid + NT * i;
       if (page < P && ((wd[i] >> (page & 31)) & 1u)) {
         const int at = wb[i] + __popc(wd[i] & ((1u << (page & 31)) - 1u));
-        if (at < out.cap) {
-          sel[at] = page;
-          if (ent) {
-            const int nv = max(0, min(sh.g, L - page * sh.g));
-            const int ph = phys[i];
-            ent[at] = ((unsigned)ph < (unsigned)kv.num_pages && ph < (1 << kEntryShift)) ? (ph | (nv << kEntryShift)) : 0;
-          }
-        }
+        if (at < out.cap) sel[at] = page;
       }
     }
     const int U = min(base_out, out.cap);
-    if (tid == 0) {
-      out.sel_count[head] = U;
-      if (ent) out.ucount[head] = U;
-    }
+    if (tid == 0) out.sel_count[head] = U;
   }
 }
 
@@ -957,13 +929,14 @@ __global__ __launch_bounds__(NT) void shared_select_kernel(KvView kv, Shape sh, 
 hipError_t launch_page_scores(hipStream_t st, int dtype, const KvView& kv, const Shape& sh, int batch,
                               int max_seq_pages, const void* q, const int32_t* active_idx,
                               const int32_t* active_count, float* scores, int32_t* tickets, int32_t* sel_count,
-                              const AttnPrepared* prep, const InKernelRanking* ranking, long workgroups_per_round,
+                              int32_t* entries, uint16_t* q_act, int rows_upper, const InKernelRanking* ranking, long workgroups_per_round,
                               uint32_t* union_bits) {
   if (batch <= 0) return hipSuccess;
   if (union_bits && dtype != LOSA_BF16) return hipErrorInvalidValue;
   const int copy_words = union_copy_words(max_seq_pages);
-  ScoreAux aux{tickets, sel_count, prep ? *prep : AttnPrepared{nullptr, nullptr, nullptr, nullptr}, union_bits,
-               union_words(sh.max_pages), union_copies(copy_words) * copy_words};
+  ScoreAux aux{tickets, sel_count, union_bits ? entries : nullptr, q_act, union_bits,
+               union_words(sh.max_pages, sh.rows_max),
+               union_copies(copy_words, rows_upper >= 1 && rows_upper < sh.rows_max ? rows_upper : sh.rows_max) * copy_words};
   RankArgs ra{nullptr, 0, 0, 0.f, nullptr, nullptr, nullptr};
   if (ranking) {
     if (dtype != LOSA_BF16 || sh.B > kRankTokens) return hipErrorInvalidValue;
@@ -1001,29 +974,26 @@ hipError_t launch_page_scores(hipStream_t st, int dtype, const KvView& kv, const
 hipError_t launch_select_pages(hipStream_t st, const KvView& kv, const Shape& sh, int batch, int max_seq_pages,
                                const int32_t* active_count, const float* scores, int topk, int32_t* topk_out,
                                int32_t* sel_pages, int32_t* sel_count, int cap, uint32_t* rowmaps, int32_t* tickets,
-                               const AttnPrepared* prep, int rows_hint, long workgroups_per_round, uint32_t* union_bits) {
+                               int rows_hint, long workgroups_per_round, uint32_t* union_bits) {
   if (batch <= 0) return hipSuccess;
-  if (union_bits && (!prep || topk_out)) return hipErrorInvalidValue;
+  if (union_bits && topk_out) return hipErrorInvalidValue;
   SelectOut out;
   out.union_bits = union_bits;
   const int copy_words = union_copy_words(max_seq_pages);
-  static_assert(kMaxSelectPages / 32 < 1024, "union_shape holds 10 bits of words");
-  out.union_shape = (uint32_t)union_words(sh.max_pages) | (uint32_t)copy_words << 10 | (uint32_t)(union_copies(copy_words) - 1) << 20;
   out.topk_out = topk_out;
   out.sel_pages = sel_pages;
   out.sel_count = sel_count;
   out.cap = cap;
   out.rowmaps = rowmaps;
   out.tickets = tickets;
-  out.entries = prep ? prep->entries : nullptr;
-  out.ucount = prep ? prep->ucount : nullptr;
   out.rows_known = rows_hint >= 1;
   // rows_hint: an upper bound on |A| * G the host happens to know (0: none); rows past it get no workgroup
   const int rows = rows_hint >= 1 && rows_hint < sh.rows_max ? rows_hint : sh.rows_max;
+  out.union_shape = (uint32_t)union_words(sh.max_pages, sh.rows_max) | (uint32_t)copy_words << 16;
+  out.union_rows = (uint32_t)(union_copies(copy_words, rows) - 1) | (uint32_t)union_row_shift(copy_words) << 8;
   const int pages = max_seq_pages < sh.max_pages ? max_seq_pages : sh.max_pages;
   if (pages > kMaxSelectPages) return hipErrorInvalidValue;
-  // no head can have more rows than a union bitmap serves: the kernel without the list
-  const bool list = !union_bits || rows > kUnionRows;
+  const bool list = !union_bits;
   // One row per workgroup while the grid fits the machine in one round (seven 256-thread
   // workgroups per CU for the one-row form, five for the several-row form, by their register
   // counts; one 1024-thread workgroup); beyond that, up to four rows per workgroup.

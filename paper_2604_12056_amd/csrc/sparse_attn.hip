@@ -342,22 +342,26 @@ __device__ __forceinline__ void merge_fragments(const Shape& sh, const int32_t* 
   if (frag == 0 && half == 0) lse_p[orow] = any ? (m + log2f(l)) * 0.6931471805599453f : -INFINITY;
 }
 
-// Every head's partials are laid out by fragments.  DENSE: no counts were prepared (every row, every page).
+// Pages the partials of a head were dealt from.
+__device__ __forceinline__ int merged_pages(const AttnInputs& in, const KvView& kv, const Shape& sh, int b, int head) {
+  const int listed = *(in.sel_count ? in.sel_count + head : kv.seq_lens + b);   // (not behind a branch where there is a count)
+  return in.sel_count ? min(min(listed, in.cap), sh.max_pages) : seq_pages(kv, sh, b);
+}
+
+// Every head's partials are laid out by fragments.  DENSE: every row, every page.
 template <int D, int WAVES, int PER, int KB, bool DENSE>
-__global__ __launch_bounds__(64 * WAVES) void attn_merge_fragments_kernel(KvView kv, Shape sh, const int32_t* __restrict__ active_idx,
-                                                                          int nchunk, const int32_t* __restrict__ ucount,
-                                                                          const int32_t* __restrict__ mrows, Partials part,
+__global__ __launch_bounds__(64 * WAVES) void attn_merge_fragments_kernel(KvView kv, Shape sh, AttnInputs in, int nchunk, Partials part,
                                                                           float* __restrict__ o_p, float* __restrict__ lse_p,
                                                                           int rows_known) {
   __shared__ __attribute__((aligned(16))) float lds[PER > 1 ? WAVES * kFragSlot : 4];
   const int j = blockIdx.y, b = blockIdx.z, head = b * sh.Hkv + j;
   const auto counts = [&](int& M, int& live) {
-    M = min(DENSE ? sh.rows_max : min(mrows[head], sh.rows_max), part.rows);
-    const int pages = DENSE ? seq_pages(kv, sh, b) : min(ucount[head], sh.max_pages), pps = kManyRowStage / sh.g;
+    M = min(DENSE ? sh.rows_max : min(active_rows(in, kv, sh, b), sh.rows_max), part.rows);
+    const int pages = DENSE ? seq_pages(kv, sh, b) : merged_pages(in, kv, sh, b, head), pps = kManyRowStage / sh.g;
     live = min(nchunk, (pages + pps - 1) / pps);
   };
-  if (!DENSE && !rows_known && (int)blockIdx.x / (D / 8 / (WAVES / PER)) * kPartialTile >= mrows[head]) return;   // surplus workgroup
-  merge_fragments<D, WAVES, PER, KB, true>(sh, DENSE ? nullptr : active_idx, b, j, blockIdx.x, 0, 0, counts, nchunk, part, o_p, lse_p, lds);
+  if (!DENSE && !rows_known && (int)blockIdx.x / (D / 8 / (WAVES / PER)) * kPartialTile >= active_rows(in, kv, sh, b)) return;   // surplus workgroup
+  merge_fragments<D, WAVES, PER, KB, true>(sh, DENSE ? nullptr : in.active_idx, b, j, blockIdx.x, 0, 0, counts, nchunk, part, o_p, lse_p, lds);
 }
 
 // Combine the chunk partials of one query row with the log-sum-exp rule, normalise, and
@@ -369,11 +373,7 @@ __global__ __launch_bounds__(64 * WAVES) void attn_merge_fragments_kernel(KvView
 // MIXED (0: no): heads with more than 64 query rows have partials laid out by fragments; their workgroups take those, MIXED
 // wavefronts each (four chunks in flight, counts first: the plain form's registers and occupancy).
 template <int D, bool LOG2, int MIXED>
-__global__ __launch_bounds__(256) void attn_merge_kernel(KvView kv, Shape sh, const int32_t* __restrict__ active_idx,
-                                                         const int32_t* __restrict__ active_count,
-                                                         const int32_t* __restrict__ sel_count, int cap, int nchunk,
-                                                         const int32_t* __restrict__ ucount,
-                                                         const int32_t* __restrict__ mrows, Partials part,
+__global__ __launch_bounds__(256) void attn_merge_kernel(KvView kv, Shape sh, AttnInputs in, int nchunk, Partials part,
                                                          float* __restrict__ o_p, float* __restrict__ lse_p,
                                                          int rows_known, int few_tile, int many_tile) {
   typedef typename std::conditional<LOG2, float, double>::type Acc;
@@ -383,12 +383,12 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(KvView kv, Shape sh, co
   __shared__ float wmax[CL];
   const int r = blockIdx.x, j = blockIdx.y, b = blockIdx.z, tid = threadIdx.x;
   if constexpr (MIXED) {
-    const int M = min(min(mrows[b * sh.Hkv + j], sh.rows_max), part.rows);
+    const int M = min(min(active_rows(in, kv, sh, b), sh.rows_max), part.rows);
     if (__builtin_expect(M > kUnionRows, 0)) {
       __shared__ __attribute__((aligned(16))) float frag_lds[4 * kFragSlot];
       if (r / (D / 8 / (4 / MIXED)) * kPartialTile >= M) return;
-      const int U = min(ucount[b * sh.Hkv + j], sh.max_pages), pps = kManyRowStage / sh.g;
-      merge_fragments<D, 4, MIXED, 4, false>(sh, active_idx, b, j, r, M, min(nchunk, (U + pps - 1) / pps), 0, nchunk, part, o_p, lse_p, frag_lds);
+      const int U = merged_pages(in, kv, sh, b, b * sh.Hkv + j), pps = kManyRowStage / sh.g;
+      merge_fragments<D, 4, MIXED, 4, false>(sh, in.active_idx, b, j, r, M, min(nchunk, (U + pps - 1) / pps), 0, nchunk, part, o_p, lse_p, frag_lds);
       return;
     }
     if (r >= M) return;
@@ -397,10 +397,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(KvView kv, Shape sh, co
   // workgroup for every possible row: those look at the count first and leave, instead of
   // fetching partials nobody wrote (a block of 224 possible rows with 35 active ones would fetch
   // six times what it needs).
-  if (!MIXED && !rows_known) {
-    const int M0 = mrows ? mrows[b * sh.Hkv + j] : (active_idx ? min(active_count[b], sh.B) : sh.B) * sh.G;
-    if (r >= M0) return;
-  }
+  if (!MIXED && !rows_known && r >= active_rows(in, kv, sh, b)) return;
   // The first KSPEC chunks of this thread are fetched before it is known how many chunks are
   // live (slots exist for all nchunk work items): together with the counts below this makes
   // the kernel one memory round trip deep instead of three.
@@ -420,16 +417,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(KvView kv, Shape sh, co
     }
   }
   // the token of this row, fetched alongside (its slot exists whatever the active count is)
-  const int tok_early = active_idx ? active_idx[(size_t)b * sh.B + min(r / sh.G, sh.B - 1)] : r / sh.G;
-  int M, U;
-  if (ucount) {   // prepared by the matrix-core path
-    M = min(mrows[b * sh.Hkv + j], sh.rows_max);
-    U = min(ucount[b * sh.Hkv + j], sh.max_pages);
-  } else {
-    M = (active_idx ? min(active_count[b], sh.B) : sh.B) * sh.G;
-    const int P = seq_pages(kv, sh, b);
-    U = sel_count ? min(sel_count[b * sh.Hkv + j], cap) : P;
-  }
+  const int tok_early = in.active_idx ? in.active_idx[(size_t)b * sh.B + min(r / sh.G, sh.B - 1)] : r / sh.G;
+  const int M = min(active_rows(in, kv, sh, b), sh.rows_max), U = merged_pages(in, kv, sh, b, b * sh.Hkv + j);
   if (r >= min(M, part.rows)) return;
   const int hg = r % sh.G;
   const int tok = tok_early;   // r < M <= B*G here, so the index above was not clamped
@@ -530,21 +519,18 @@ hipError_t launch_attn_f32(hipStream_t st, const KvView& kv, const Shape& sh, in
   return launch(st, kv, sh, batch, (const float*)q, active_idx, active_count, sel_pages, sel_count, cap, nchunk, part);
 }
 
-hipError_t launch_attn_merge(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const int32_t* active_idx,
-                             const int32_t* active_count, const int32_t* sel_count, int cap, int nchunk,
-                             const AttnPrepared* prep, const Partials& part, float* o_p, float* lse_p, int rows_hint,
-                             int few_tile, int many_tile, bool dense_step) {
+hipError_t launch_attn_merge(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnInputs& in,
+                             bool bf16, int nchunk, const Partials& part, float* o_p, float* lse_p, int rows_hint, int few_tile, int many_tile) {
   if (batch <= 0) return hipSuccess;
   // rows_hint: an upper bound on the active rows per KV head the host happens to know (0: none);
   // rows past it get no workgroup (they would only fetch partials speculatively and exit)
   const int rows = rows_hint >= 1 && rows_hint < sh.rows_max ? rows_hint : sh.rows_max;
-  const int32_t* uc = prep && !dense_step ? prep->ucount : nullptr;
-  const int32_t* mr = prep && !dense_step ? prep->mrows : nullptr;
-  const int known = rows_hint >= 1 || !active_idx;   // (no list of active tokens: every row exists)
+  const bool dense_step = !in.active_idx && !in.sel_count;
+  const int known = rows_hint >= 1 || !in.active_idx;   // (no list of active tokens: every row exists)
   const int tiles = (rows + kPartialTile - 1) / kPartialTile, frags = sh.d / 8;
   if (few_tile == kManyRowStage) {   // every head's partials are laid out by fragments
     auto launch = [&](auto kern, int per_tile, int waves) {
-      kern<<<dim3(tiles * per_tile, sh.Hkv, batch), 64 * waves, 0, st>>>(kv, sh, active_idx, nchunk, uc, mr, part, o_p, lse_p, known);
+      kern<<<dim3(tiles * per_tile, sh.Hkv, batch), 64 * waves, 0, st>>>(kv, sh, in, nchunk, part, o_p, lse_p, known);
     };
 #define LOSA_FRAGMENTS(W, PER, KB)                                                                                  \
   launch(sh.d == 128 ? (dense_step ? attn_merge_fragments_kernel<128, W, PER, KB, true>                             \
@@ -563,14 +549,14 @@ hipError_t launch_attn_merge(hipStream_t st, const KvView& kv, const Shape& sh, 
   }
   // wavefronts per fragment in a mixed launch: with few chunks one, a quarter of the workgroups
   const int mixed = many_tile != kManyRowStage ? 0 : nchunk <= 16 ? 1 : 4;
-  auto kern = sh.d == 128 ? (!prep ? attn_merge_kernel<128, false, 0> : mixed == 0 ? attn_merge_kernel<128, true, 0>
+  auto kern = sh.d == 128 ? (!bf16 ? attn_merge_kernel<128, false, 0> : mixed == 0 ? attn_merge_kernel<128, true, 0>
                              : mixed == 1 ? attn_merge_kernel<128, true, 1> : attn_merge_kernel<128, true, 4>)
-                          : (!prep ? attn_merge_kernel<64, false, 0> : mixed == 0 ? attn_merge_kernel<64, true, 0>
+                          : (!bf16 ? attn_merge_kernel<64, false, 0> : mixed == 0 ? attn_merge_kernel<64, true, 0>
                              : mixed == 1 ? attn_merge_kernel<64, true, 1> : attn_merge_kernel<64, true, 4>);
   // (mixed: an odd width.  Most of its workgroups leave at once, and with a multiple of 8 the ones that stay meet on a
   // few of every die's compute units: 14 of 64 rows, 40 heads 6.8 us, of 65 5.4)
   kern<<<dim3(mixed ? max(min(rows, kUnionRows), tiles * frags * mixed / 4) | 1 : rows, sh.Hkv, batch), 256, 0, st>>>(
-      kv, sh, active_idx, active_count, sel_count, cap, nchunk, uc, mr, part, o_p, lse_p, known, few_tile, many_tile);
+      kv, sh, in, nchunk, part, o_p, lse_p, known, few_tile, many_tile);
   return hipGetLastError();
 }
 

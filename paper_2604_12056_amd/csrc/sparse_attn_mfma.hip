@@ -71,29 +71,24 @@ struct MergeSlot {   // LDS image of one wavefront's state: O as [row tile][chan
   static constexpr int kFloats = kOFloats + 2 * R * 16;
 };
 
-// Inputs of the matrix-core kernel are *prepared* per (sequence, KV head) by whoever decided
-// the selection (the union kernel inside losa_step, or attn_prepare_kernel for the
-// stand-alone entry point and the dense initialisation):
-//   entries[i] = physical page id | (valid tokens << kEntryShift)   for the i-th page of the list
-//   q_act      = the query rows of the active tokens, gathered densely, [rows_max, d] bfloat16
-//   ucount     = number of list entries,  mrows = number of query rows (|A| * G)
-// so that a wavefront can issue its page-entry loads, its query loads and the two counts all
-// at once when it starts: the only dependent memory round trip left before key/value data
-// flows is entries -> pages.
-// UNION (split-pages shape only): there is no prepared page list.  The selection kernel left the
-// union of the head's picks as a bitmap and a copy of the head's page table (which the four wavefronts
-// bring to LDS together); every wavefront ranks the union with a popcount prefix sum (lane = bitmap
+// A wavefront resolves its pages itself: list entry (logical page) -> page table -> key and value pages, with the query rows
+// gathered by the active list beside it, everything that does not depend on what is still under way requested at once.
+// (A launch of its own that resolved the list and gathered the rows first took 3.5 us; the two dependent
+// round trips it saved here take 0.6.)
+// UNION (split-pages shape only): there is no page list.  The selection kernel left the
+// union of the head's picks as a bitmap, the scoring kernel the query rows and a copy of the head's page table (which the
+// four wavefronts bring to LDS together); every wavefront ranks the union with a popcount prefix sum (lane = bitmap
 // word), keeps words and ranks in LDS (in its own merge slot, which is idle until the combine), and finds
 // the pages of its own tiles by rank: a binary search over the word ranks, a 5-step search inside
 // the word, then the page's entry from the table in LDS (from memory for pages beyond the first
-// 2048).  That is more start-up work than with a prepared list (about 1.5 us at 2048 pages), in
+// 2048).  That is more start-up work than with a list (about 1.5 us at 2048 pages), in
 // exchange for the selection kernel's whole hand-over tail (about 4 us).
 constexpr int kMaxUnionWords = kMaxSelectPages / 32;
 constexpr int kTablePagesInLds = 2048;   // the first so many entries of a head's page table are kept in LDS
 // LDS of the split-pages shape, in floats: the four wavefronts' merge slots, then (UNION) the page table.
 constexpr int kUnionShared = kTablePagesInLds;
 template <int D, int GP, int R, bool SPLIT_PAGES, int NBUF, bool UNION = false>
-__device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, int nrbg, Shape sh, KvView kv, Partials part,
+__device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk, int nrbg, Shape sh, KvView kv, Partials part,
                                                float scale_log2e, int m_lo, int m_hi, UnionInKernel uni, float* lds) {
   static_assert(!UNION || SPLIT_PAGES, "the union is built in the kernel only in the split-pages shape");
   static_assert(!UNION || MergeSlot<D, R>::kFloats >= 2 * kMaxUnionWords, "the union's words and ranks do not fit a merge slot");
@@ -118,20 +113,34 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
   const int wstart = SPLIT_PAGES ? wave : 0, wstride = SPLIT_PAGES ? 4 : 1;
   const int tfirst = chunk + nchunk * wstart;   // first tile of this wavefront
   const int tstep = nchunk * wstride;           // distance between its tiles
-  const int32_t* ent = prep.entries + (size_t)head * sh.max_pages;
+  const int32_t* ent = UNION ? uni.entries + (size_t)head * sh.max_pages : nullptr;
 
   // ---- start-up.  What gates the kernel is when the first key/value load leaves, and that
   // needs only the counts and the page entries: they are fetched first, the exit tests follow,
   // and the query fragments are requested next but not waited for until after the first tiles
   // have been requested (they arrive long before the first tile does).
-  const int M_raw = prep.mrows[head];
+  [[maybe_unused]] int tok[R];   // token of row l16 of every row tile (clamped: a slot that exists)
+  if constexpr (!UNION) {
+#pragma unroll
+    for (int mt = 0; mt < R; ++mt) {
+      const int a = row_token(sh, min(rb * (R * 16) + mt * 16 + l16, sh.rows_max - 1));
+      tok[mt] = in.active_idx ? in.active_idx[(size_t)b * sh.B + a] : a;
+    }
+  }
+  auto list_position = [&](int first_local_tile) {
+    return ((long)tfirst + (long)(first_local_tile + lane / PPT) * tstep) * PPT + lane % PPT;
+  };
+  auto listed = [&](long lp) {   // logical page at a position of the list (inside the array whatever the list's length is)
+    return in.list ? in.list[(size_t)head * in.cap + min(lp, (long)in.cap - 1)] : (int)min(lp, (long)sh.max_pages);
+  };
+  [[maybe_unused]] int logical = 0;
+  if constexpr (!UNION) logical = listed(list_position(0));
+  const int M_raw = UNION ? min(in.active_count[b], sh.B) * sh.G : active_rows(in, kv, sh, b);
+  const int base = kv.page_indptr[b], P = seq_pages(kv, sh, b), tokens = kv.seq_lens[b];
   int U_raw;
   int pg_entry = 0;
-  auto fetch_entries = [&](int first_local_tile) {
-    if constexpr (!UNION) {
-      const long lp = ((long)tfirst + (long)(first_local_tile + lane / PPT) * tstep) * PPT + lane % PPT;
-      pg_entry = lp < sh.max_pages ? ent[lp] : 0;   // inside the array whatever U is; checked against U at use
-    }
+  [[maybe_unused]] auto fetch_entry = [&]() {   // of page `logical`: its id; page and id are checked when it is decoded
+    if (P > 0) pg_entry = kv.page_indices[base + max(0, min(logical, P - 1))];
   };
   // UNION: words and ranks of the head's union, in this wavefront's own merge slot; the page table behind the slots
   [[maybe_unused]] uint32_t* u_bits = reinterpret_cast<uint32_t*>(lds + (SPLIT_PAGES ? wave : 0) * kSlotStride);
@@ -164,7 +173,6 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
     for (int u = 0; u < kGroupsInFlight; ++u) ub[u] = 64 * u < words ? head_bits[min(64 * u + lane, words - 1)] : 0u;
 #pragma unroll
     for (int k = 0; k < TPW; ++k) reinterpret_cast<u32x4v_t*>(u_tab)[wave * (64 * TPW) + lane + 64 * k] = tabv[k];
-    const int P = seq_pages(kv, sh, b);
     u_words = (P + 31) >> 5;
     __syncthreads();
     if (copies) {
@@ -201,13 +209,10 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
       }
     }
     U_raw = total;
-    if (chunk == 0 && threadIdx.x == 0 && M_raw > 0) {   // for the merge kernel and the caller's diagnostics
-      prep.ucount[head] = total;
-      if (uni.sel_count) uni.sel_count[head] = total;
-    }
+    if (chunk == 0 && threadIdx.x == 0 && M_raw > 0) uni.sel_count[head] = total;   // for the merge kernel and the caller's diagnostics
   } else {
-    U_raw = prep.ucount[head];
-    fetch_entries(0);
+    U_raw = in.list ? min(in.sel_count[head], in.cap) : P;
+    fetch_entry();
   }
   const int U = min(U_raw, sh.max_pages);
   const int M = min(M_raw, min(sh.rows_max, part.rows));   // (rows past the partial stride have nowhere to go: the host sizes it from an upper bound)
@@ -222,13 +227,19 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
 
   bf16x8_t qf[R][KS];
   {
-    const bf16_t* qa = prep.q_act + (size_t)head * sh.rows_max * D;
 #pragma unroll
     for (int mt = 0; mt < R; ++mt) {
-      const int rg = min(rb * (R * 16) + mt * 16 + l16, sh.rows_max - 1);
+      const int r = min(rb * (R * 16) + mt * 16 + l16, sh.rows_max - 1);
+      const bf16_t* row;
+      if constexpr (UNION) {   // (gathered by the scoring kernel: the rows' tokens are one round trip less here)
+        row = uni.q_act + ((size_t)head * sh.rows_max + r) * D;
+      } else {
+        const int t = (unsigned)tok[mt] < (unsigned)sh.B ? tok[mt] : 0;
+        row = (const bf16_t*)in.q + (((size_t)b * sh.B + t) * sh.Hq + j * sh.G + (r - row_token(sh, r) * sh.G)) * D;
+      }
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks)
-        qf[mt][ks] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(qa + (size_t)rg * D + ks * 32 + qd * 8));
+        qf[mt][ks] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(row + ks * 32 + qd * 8));
     }
   }
   __builtin_amdgcn_sched_barrier(0);   // the query loads stay ahead of the tile loads below
@@ -248,7 +259,7 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
   // ---- decoded page entries of this wavefront's next 64 pages, one per lane
   int pg_phys = 0, pg_valid = 0;
   auto decode_entries = [&](int first_local_tile) {
-    const long lp = ((long)tfirst + (long)(first_local_tile + lane / PPT) * tstep) * PPT + lane % PPT;
+    const long lp = list_position(first_local_tile);
     if constexpr (UNION) {
       // the page of rank lp in the union: the last bitmap word whose rank is <= lp, then the
       // (lp - rank)-th set bit of that word; its physical id comes from the page table
@@ -277,11 +288,17 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
       const bool from_lds = page < tab_lds_pages;
       pg_entry = !want ? 0 : (from_lds ? u_tab[page] : ent[page]);
     }
-    const int e = lp < U ? pg_entry : 0;   // UNION: the entry of the page just found
-    const int ph = e & ((1 << kEntryShift) - 1);
-    const bool ok = (unsigned)ph < (unsigned)kv.num_pages;
+    int ph, nv;
+    if constexpr (UNION) {   // the entry of the page just found
+      ph = pg_entry & ((1 << kEntryShift) - 1);
+      nv = (int)((unsigned)pg_entry >> kEntryShift);
+    } else {
+      ph = (unsigned)logical < (unsigned)P ? pg_entry : -1;
+      nv = max(0, tokens - logical * GP);
+    }
+    const bool ok = lp < U && (unsigned)ph < (unsigned)kv.num_pages;
     pg_phys = ok ? ph : 0;
-    pg_valid = ok ? min(GP, (int)((unsigned)e >> kEntryShift)) : 0;
+    pg_valid = ok ? min(GP, nv) : 0;
   };
 
   // A 32-token tile is fed to the matrix core as two 16-row halves.  Row i of half h is token
@@ -484,10 +501,12 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
 #pragma unroll
   for (int k = 0; k < NBUF - 1; ++k) load_tile(tb[k], k, min(ntw, TPR));
   __builtin_amdgcn_sched_barrier(0);
-  // rows past M hold whatever the workspace held: make them zero queries (first wait for them)
+  // rows past M, and of tokens that do not exist: zero queries (first wait for them)
 #pragma unroll
   for (int mt = 0; mt < R; ++mt) {
-    const uint32_t keep = rb * (R * 16) + mt * 16 + l16 < M ? 0xFFFFFFFFu : 0u;
+    bool keep_row = rb * (R * 16) + mt * 16 + l16 < M;
+    if constexpr (!UNION) keep_row &= (unsigned)tok[mt] < (unsigned)sh.B;
+    const uint32_t keep = keep_row ? 0xFFFFFFFFu : 0u;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
       uint4 x = __builtin_bit_cast(uint4, qf[mt][ks]);
@@ -501,7 +520,10 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
   for (int nb = 0; nb < ntw; nb += TPR) {
     const int ne = min(ntw, nb + TPR);
     if (nb > 0) {
-      fetch_entries(nb);
+      if constexpr (!UNION) {
+        logical = listed(list_position(nb));
+        fetch_entry();
+      }
       decode_entries(nb);
 #pragma unroll
       for (int k = 0; k < NBUF - 1; ++k) load_tile(tb[k], nb + k, ne);
@@ -630,100 +652,39 @@ __device__ __forceinline__ void attn_mfma_body(AttnPrepared prep, int nchunk, in
 }
 
 template <int D, int GP, int R, bool SPLIT_PAGES, int NBUF, bool UNION = false>
-__global__ __launch_bounds__(256) void attn_mfma_kernel(AttnPrepared prep, int nchunk, int nrbg, Shape sh, KvView kv,
+__global__ __launch_bounds__(256) void attn_mfma_kernel(AttnInputs in, int nchunk, int nrbg, Shape sh, KvView kv,
                                                         Partials part, float scale_log2e, int m_lo, int m_hi,
                                                         UnionInKernel uni) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
-  attn_mfma_body<D, GP, R, SPLIT_PAGES, NBUF, UNION>(prep, nchunk, nrbg, sh, kv, part, scale_log2e,
+  attn_mfma_body<D, GP, R, SPLIT_PAGES, NBUF, UNION>(in, nchunk, nrbg, sh, kv, part, scale_log2e,
                                                                             m_lo, m_hi, uni, lds);
 }
 
-// The split-pages shape with the union built in the kernel, for launches whose row counts only the
-// device knows (threshold / cumulative-mass selection): every (sequence, KV head) runs the body
-// compiled for its own number of 16-row tiles, read from the count the selection kernel left, so a
+// The split-pages shape for launches whose row counts only the device knows (threshold / cumulative-mass selection, the
+// separate calls): every (sequence, KV head) runs the body
+// compiled for its own number of 16-row tiles, read from the count the selection left, so that a
 // head with a few active rows does not pay for the 64 the launch has to allow.  Heads with more than
-// 64 rows are not served here (m_hi).
-template <int D, int GP>
-__global__ __launch_bounds__(256) void attn_mfma_rows_kernel(AttnPrepared prep, int nchunk, Shape sh, KvView kv, Partials part,
+// 64 rows are not served here.
+template <int D, int GP, bool UNION>
+__global__ __launch_bounds__(256) void attn_mfma_rows_kernel(AttnInputs in, int nchunk, Shape sh, KvView kv, Partials part,
                                                              float scale_log2e, int m_lo, int m_hi, UnionInKernel uni) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
-  const int M = __builtin_amdgcn_readfirstlane(prep.mrows[blockIdx.z * sh.Hkv + blockIdx.y]);
+  const int M = active_rows(in, kv, sh, blockIdx.z);
   if (M <= 0 || M > kUnionRows) return;
   if (M <= 16)
-    attn_mfma_body<D, GP, 1, true, 2, true>(prep, nchunk, 1, sh, kv, part, scale_log2e, m_lo, m_hi, uni, lds);
+    attn_mfma_body<D, GP, 1, true, 2, UNION>(in, nchunk, 1, sh, kv, part, scale_log2e, m_lo, m_hi, uni, lds);
   else if (M <= 32)
-    attn_mfma_body<D, GP, 2, true, 2, true>(prep, nchunk, 1, sh, kv, part, scale_log2e, m_lo, m_hi, uni, lds);
+    attn_mfma_body<D, GP, 2, true, 2, UNION>(in, nchunk, 1, sh, kv, part, scale_log2e, m_lo, m_hi, uni, lds);
   else if (M <= 48)
-    attn_mfma_body<D, GP, 3, true, 2, true>(prep, nchunk, 1, sh, kv, part, scale_log2e, m_lo, m_hi, uni, lds);
+    attn_mfma_body<D, GP, 3, true, 2, UNION>(in, nchunk, 1, sh, kv, part, scale_log2e, m_lo, m_hi, uni, lds);
   else
-    attn_mfma_body<D, GP, 4, true, 2, true>(prep, nchunk, 1, sh, kv, part, scale_log2e, m_lo, m_hi, uni, lds);
-}
-
-// Builds the prepared inputs of attn_mfma_kernel when the selection kernel has not done so
-// (stand-alone losa_sparse_attn, and the dense initialisation): resolves the page list
-// (logical ids, or every page when sel_pages is NULL) to entries and gathers the query rows
-// of the active tokens (every token when active_idx is NULL).  kPrepSlices workgroups per
-// (sequence, KV head) share the work, so no thread walks a long chain of dependent loads.
-constexpr int kPrepSlices = 16;
-
-__global__ __launch_bounds__(256) void attn_prepare_kernel(KvView kv, Shape sh, const bf16_t* __restrict__ q,
-                                                           const int32_t* __restrict__ active_idx,
-                                                           const int32_t* __restrict__ active_count,
-                                                           const int32_t* __restrict__ sel_pages,
-                                                           const int32_t* __restrict__ sel_count, int cap,
-                                                           AttnPrepared prep) {
-  const int j = blockIdx.x, b = blockIdx.y;
-  const int gtid = blockIdx.z * 256 + threadIdx.x, gthreads = kPrepSlices * 256;
-  const int head = b * sh.Hkv + j;
-  const int base = kv.page_indptr[b];
-  const int P = seq_pages(kv, sh, b);
-  const int L = kv.seq_lens[b];
-  const int32_t* list = sel_pages ? sel_pages + (size_t)head * cap : nullptr;
-  const int U = max(0, min(list ? min(sel_count[head], cap) : P, sh.max_pages));
-  const int n_act = active_idx ? active_count[b] : sh.B;
-  int32_t* ent = prep.entries + (size_t)head * sh.max_pages;
-  for (int i = gtid; i < U; i += gthreads) {
-    const int logical = list ? list[i] : i;
-    int e = 0;
-    if ((unsigned)logical < (unsigned)P) {
-      const int ph = kv.page_indices[base + logical];
-      const int nv = max(0, min(sh.g, L - logical * sh.g));
-      if ((unsigned)ph < (unsigned)kv.num_pages && ph < (1 << kEntryShift)) e = ph | (nv << kEntryShift);
-    }
-    ent[i] = e;
-  }
-  const int M = max(0, min(n_act, sh.B)) * sh.G;
-  const int vpr = sh.d / 8;   // 16-byte vectors per query row
-  uint4* dst = reinterpret_cast<uint4*>(prep.q_act + (size_t)head * sh.rows_max * sh.d);
-  for (int v = gtid; v < M * vpr; v += gthreads) {
-    const int r = v / vpr, cv = v % vpr;
-    const int a = r / sh.G, hg = r % sh.G;
-    const int tok = active_idx ? active_idx[(size_t)b * sh.B + a] : a;
-    uint4 val = make_uint4(0u, 0u, 0u, 0u);
-    if ((unsigned)tok < (unsigned)sh.B)
-      val = reinterpret_cast<const uint4*>(q + (((size_t)b * sh.B + tok) * sh.Hq + j * sh.G + hg) * sh.d)[cv];
-    dst[v] = val;
-  }
-  if (gtid == 0) {
-    prep.ucount[head] = U;
-    prep.mrows[head] = M;
-  }
-}
-
-hipError_t launch_attn_prepare(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const void* q,
-                               const int32_t* active_idx, const int32_t* active_count, const int32_t* sel_pages,
-                               const int32_t* sel_count, int cap, const AttnPrepared& prep) {
-  if (batch <= 0) return hipSuccess;
-  dim3 grid(sh.Hkv, batch, kPrepSlices);
-  attn_prepare_kernel<<<grid, 256, 0, st>>>(kv, sh, (const bf16_t*)q, active_idx, active_count, sel_pages, sel_count,
-                                            cap, prep);
-  return hipGetLastError();
+    attn_mfma_body<D, GP, 4, true, 2, UNION>(in, nchunk, 1, sh, kv, part, scale_log2e, m_lo, m_hi, uni, lds);
 }
 
 template <int D, int GP, int R, bool SPLIT, bool UNION = false>
-static hipError_t launch_one(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnPrepared& prep,
+static hipError_t launch_one(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnInputs& in,
                              int nchunk, const Partials& part, hipEvent_t ev_start, hipEvent_t ev_stop, int m_lo,
-                             int m_hi, const UnionInKernel& uni = UnionInKernel{nullptr, nullptr}) {
+                             int m_hi, const UnionInKernel& uni = UnionInKernel{nullptr}) {
   const int nrbg = SPLIT ? 1 : (sh.rows_max + R * 64 - 1) / (R * 64);
   const size_t lds_bytes = SPLIT ? (4 * MergeSlot<D, R>::kFloats + (UNION ? kUnionShared : 0)) * sizeof(float)
                                  : 0;
@@ -745,56 +706,60 @@ static hipError_t launch_one(hipStream_t st, const KvView& kv, const Shape& sh, 
   const float scale_log2e = sh.sm_scale * 1.4426950408889634f;
   dim3 grid(nchunk, sh.Hkv * nrbg, batch);
   if (ev_start && ev_stop)   // events bound to this dispatch: they read the kernel's own begin and end
-    hipExtLaunchKernelGGL(kern, grid, dim3(256), (uint32_t)lds_bytes, st, ev_start, ev_stop, 0, prep, nchunk,
+    hipExtLaunchKernelGGL(kern, grid, dim3(256), (uint32_t)lds_bytes, st, ev_start, ev_stop, 0, in, nchunk,
                           nrbg, sh, kv, part, scale_log2e, m_lo, m_hi, uni);
   else
-    kern<<<grid, 256, lds_bytes, st>>>(prep, nchunk, nrbg, sh, kv, part, scale_log2e, m_lo, m_hi, uni);
+    kern<<<grid, 256, lds_bytes, st>>>(in, nchunk, nrbg, sh, kv, part, scale_log2e, m_lo, m_hi, uni);
   return hipGetLastError();
 }
 
+// rows_on_device: launch the form that takes every head's row-tile count from the device.
 // More than 64 rows: 4 independent wavefronts of 64 rows.
 template <int D, int GP>
-static hipError_t launch_dg(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnPrepared& prep,
+static hipError_t launch_dg(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnInputs& in,
                             int nchunk, int rows_upper, const Partials& part, hipEvent_t e0, hipEvent_t e1, int m_lo,
-                            int m_hi, const UnionInKernel* uni) {
-  if (uni && uni->bits && uni->rows_on_device) {   // ... and takes every head's row-tile count from the device
-    const size_t lds_bytes = (4 * MergeSlot<D, 4>::kFloats + kUnionShared) * sizeof(float);
-    auto kern = attn_mfma_rows_kernel<D, GP>;
-    static bool attr_set = false;   // per instantiation
-    if (lds_bytes > 48 * 1024 && !attr_set) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                         (int)lds_bytes);
-      if (e != hipSuccess) return e;
-      attr_set = true;
-    }
-    kern<<<dim3(nchunk, sh.Hkv, batch), 256, lds_bytes, st>>>(prep, nchunk, sh, kv, part, sh.sm_scale * 1.4426950408889634f,
-                                                              m_lo, m_hi, *uni);
-    return hipGetLastError();
+                            int m_hi, bool rows_on_device, const UnionInKernel* uni) {
+  if (rows_on_device) {
+    auto launch = [&](auto kern, size_t lds_bytes, bool& attr_set) -> hipError_t {
+      if (lds_bytes > 48 * 1024 && !attr_set) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)lds_bytes);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+      }
+      kern<<<dim3(nchunk, sh.Hkv, batch), 256, lds_bytes, st>>>(in, nchunk, sh, kv, part, sh.sm_scale * 1.4426950408889634f,
+                                                                m_lo, m_hi, uni ? *uni : UnionInKernel{nullptr});
+      return hipGetLastError();
+    };
+    constexpr size_t slots = 4 * MergeSlot<D, 4>::kFloats;
+    static bool with_union = false, with_list = false;   // (attribute set) per instantiation
+    return uni ? launch(attn_mfma_rows_kernel<D, GP, true>, (slots + kUnionShared) * sizeof(float), with_union)
+               : launch(attn_mfma_rows_kernel<D, GP, false>, slots * sizeof(float), with_list);
   }
   if (uni && uni->bits) {   // the kernel ranks the head's union bitmap itself
-    if (rows_upper <= 16) return launch_one<D, GP, 1, true, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi, *uni);
-    if (rows_upper <= 32) return launch_one<D, GP, 2, true, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi, *uni);
-    if (rows_upper <= 48) return launch_one<D, GP, 3, true, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi, *uni);
-    if (rows_upper <= 64) return launch_one<D, GP, 4, true, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi, *uni);
+    if (rows_upper <= 16) return launch_one<D, GP, 1, true, true>(st, kv, sh, batch, in, nchunk, part, e0, e1, m_lo, m_hi, *uni);
+    if (rows_upper <= 32) return launch_one<D, GP, 2, true, true>(st, kv, sh, batch, in, nchunk, part, e0, e1, m_lo, m_hi, *uni);
+    if (rows_upper <= 48) return launch_one<D, GP, 3, true, true>(st, kv, sh, batch, in, nchunk, part, e0, e1, m_lo, m_hi, *uni);
+    if (rows_upper <= 64) return launch_one<D, GP, 4, true, true>(st, kv, sh, batch, in, nchunk, part, e0, e1, m_lo, m_hi, *uni);
     return hipErrorInvalidValue;
   }
-  if (rows_upper <= 16) return launch_one<D, GP, 1, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi);
-  if (rows_upper <= 32) return launch_one<D, GP, 2, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi);
-  if (rows_upper <= 48) return launch_one<D, GP, 3, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi);
-  if (rows_upper <= 64) return launch_one<D, GP, 4, true>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi);
-  return launch_one<D, GP, 4, false>(st, kv, sh, batch, prep, nchunk, part, e0, e1, m_lo, m_hi);
+  if (rows_upper <= 16) return launch_one<D, GP, 1, true>(st, kv, sh, batch, in, nchunk, part, e0, e1, m_lo, m_hi);
+  if (rows_upper <= 32) return launch_one<D, GP, 2, true>(st, kv, sh, batch, in, nchunk, part, e0, e1, m_lo, m_hi);
+  if (rows_upper <= 48) return launch_one<D, GP, 3, true>(st, kv, sh, batch, in, nchunk, part, e0, e1, m_lo, m_hi);
+  if (rows_upper <= 64) return launch_one<D, GP, 4, true>(st, kv, sh, batch, in, nchunk, part, e0, e1, m_lo, m_hi);
+  return launch_one<D, GP, 4, false>(st, kv, sh, batch, in, nchunk, part, e0, e1, m_lo, m_hi);
 }
 
-hipError_t launch_attn_mfma(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnPrepared& prep,
+hipError_t launch_attn_mfma(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnInputs& in,
                             int nchunk, int rows_upper, const Partials& part, hipEvent_t e0, hipEvent_t e1, int m_lo,
-                            int m_hi, const UnionInKernel* uni) {
+                            int m_hi, bool rows_on_device, const UnionInKernel* uni) {
   if (batch <= 0 || nchunk <= 0) return hipSuccess;
   if (sh.d == 128) {
-    if (sh.g == 16) return launch_dg<128, 16>(st, kv, sh, batch, prep, nchunk, rows_upper, part, e0, e1, m_lo, m_hi, uni);
-    return launch_dg<128, 32>(st, kv, sh, batch, prep, nchunk, rows_upper, part, e0, e1, m_lo, m_hi, uni);
+    if (sh.g == 16) return launch_dg<128, 16>(st, kv, sh, batch, in, nchunk, rows_upper, part, e0, e1, m_lo, m_hi, rows_on_device, uni);
+    return launch_dg<128, 32>(st, kv, sh, batch, in, nchunk, rows_upper, part, e0, e1, m_lo, m_hi, rows_on_device, uni);
   }
-  if (sh.g == 16) return launch_dg<64, 16>(st, kv, sh, batch, prep, nchunk, rows_upper, part, e0, e1, m_lo, m_hi, uni);
-  return launch_dg<64, 32>(st, kv, sh, batch, prep, nchunk, rows_upper, part, e0, e1, m_lo, m_hi, uni);
+  if (sh.g == 16) return launch_dg<64, 16>(st, kv, sh, batch, in, nchunk, rows_upper, part, e0, e1, m_lo, m_hi, rows_on_device, uni);
+  return launch_dg<64, 32>(st, kv, sh, batch, in, nchunk, rows_upper, part, e0, e1, m_lo, m_hi, rows_on_device, uni);
 }
 
 }  // namespace losa

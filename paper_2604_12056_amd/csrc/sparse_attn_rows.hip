@@ -87,11 +87,14 @@ __device__ __forceinline__ uint32_t bf16_pair_to_half(uint32_t two_bf16) {
 //
 // TG token groups: with up to 128 rows four wavefronts hold all of them, and the other four take the
 // second 32-token block of every stage instead of idling; the two halves meet through LDS at the end.
-template <int D, int GP, bool HALF, int TG>
+// Where a workgroup's pages come from: the whole page table (the dense step), a list of logical pages, or the head's
+// union bitmap, out of which it has made its own list.
+enum class PageSource { all, list, own };
+
+template <int D, int GP, bool HALF, int TG, PageSource SRC>
 __device__ __forceinline__ void attn_rows_body(int nchunk, int row_group, int j, const Shape& sh,
-                                               const KvView& kv, const Partials& part, float scale_log2e, int M, int U,
-                                               const int32_t* list, int dense_tokens, const bf16_t* q, int first_entry,
-                                               unsigned char* lds) {
+                                               const KvView& kv, const Partials& part, float scale_log2e, int M, int U, int P,
+                                               const AttnInputs& in, const uint16_t* own, int logical, int entry, unsigned char* lds) {
   typedef StageImage<D, GP> Img;
   constexpr int KS = D / 16;            // k-steps of the score product
   constexpr int CB = D / 32;            // 32-channel blocks of the output
@@ -113,31 +116,48 @@ __device__ __forceinline__ void attn_rows_body(int nchunk, int row_group, int j,
   const int nstages_all = (U + PPS - 1) / PPS;
   const int ns = (nstages_all - 1 - chunk) / nchunk + 1;   // stages of this workgroup: chunk, chunk + nchunk, ... (chunk < nstages_all)
 
-  // list: the head's prepared entries or, for the dense step (dense_tokens >= 0), the sequence's page table
-  int next_entry = first_entry, pg_phys = 0, pg_valid = 0;
+  // Page entries, one per lane and batch of SPF stages: position in the list -> logical page -> page table, each step
+  // requested a stage before the next needs it.
+  int next_logical = logical, next_entry = entry, pg_phys = 0, pg_valid = 0;
+  const int32_t* table = kv.page_indices + kv.page_indptr[b];
+  const int tokens = kv.seq_lens[b];
   auto list_position = [&](int first_stage) {
     return ((long)chunk + (long)(first_stage + lane / PPS) * nchunk) * PPS + lane % PPS;
   };
-  auto fetch_entries = [&](int first_stage) {
-    const long lp = list_position(first_stage);
-    next_entry = lp < U ? list[lp] : 0;
+  [[maybe_unused]] auto fetch_logical = [&](int first_stage) {
+    if constexpr (SRC == PageSource::own)   // (the last stages of a batch may not exist: any page)
+      next_logical = own[min(first_stage + lane / PPS, ns - 1) * PPS + lane % PPS];
+    else
+      next_logical = in.list[(size_t)head * in.cap + min(list_position(first_stage), (long)in.cap - 1)];
+  };
+  auto fetch_entry = [&](int first_stage) {   // (an empty sequence has no entry of its own)
+    if constexpr (SRC == PageSource::all) {
+      const long lp = list_position(first_stage);
+      next_entry = lp < U ? table[lp] : 0;
+    } else {
+      if (P > 0) next_entry = table[max(0, min(next_logical, P - 1))];
+    }
   };
   auto decode_entries = [&](int first_stage) {
     const long lp = list_position(first_stage);
-    const bool dense = dense_tokens >= 0;
-    const int ph = dense ? next_entry : next_entry & ((1 << kEntryShift) - 1);
-    const int nv = dense ? (int)min((long)GP, (long)dense_tokens - lp * GP) : min(GP, (int)((unsigned)next_entry >> kEntryShift));
-    const bool ok = lp < U && (unsigned)ph < (unsigned)kv.num_pages;
-    pg_phys = ok ? ph : 0;
-    pg_valid = ok ? nv : 0;
+    bool ok = lp < U && (unsigned)next_entry < (unsigned)kv.num_pages;
+    if constexpr (SRC == PageSource::all) {
+      pg_valid = ok ? (int)min((long)GP, (long)tokens - lp * GP) : 0;
+    } else {
+      ok &= (unsigned)next_logical < (unsigned)P;
+      pg_valid = ok ? max(0, min(GP, tokens - next_logical * GP)) : 0;
+    }
+    pg_phys = ok ? next_entry : 0;
   };
 
   // queries: B operands, lane = row l32, channels 16*ks + 8*half ..
   bf16x8_t qf[KS];
+  bool known_row;
   {
-    const int row = min(r0 + l32, sh.rows_max - 1);
-    const bf16_t* qa = dense_tokens >= 0 ? q + (((size_t)b * sh.B + row / sh.G) * sh.Hq + j * sh.G + row % sh.G) * D
-                                         : q + ((size_t)head * sh.rows_max + row) * D;
+    const int row = min(r0 + l32, sh.rows_max - 1), a = row_token(sh, row);
+    const int tok = in.active_idx ? in.active_idx[(size_t)b * sh.B + a] : a;
+    known_row = r0 + l32 < M && (unsigned)tok < (unsigned)sh.B;
+    const bf16_t* qa = (const bf16_t*)in.q + (((size_t)b * sh.B + (known_row ? tok : 0)) * sh.Hq + j * sh.G + (row - a * sh.G)) * D;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
       qf[ks] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(qa + ks * 16 + half * 8));
@@ -394,16 +414,18 @@ __device__ __forceinline__ void attn_rows_body(int nchunk, int row_group, int j,
   decode_entries(0);
 #pragma unroll
   for (int k = 0; k < PD; ++k) gload(st[k], k);
-  // rows past M hold whatever the workspace held: make them zero queries
+  // rows past M, and of tokens that do not exist: zero queries
   {
-    const uint32_t keep = r0 + l32 < M ? 0xFFFFFFFFu : 0u;
+    const uint32_t keep = known_row ? 0xFFFFFFFFu : 0u;
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) qf[ks] = __builtin_bit_cast(bf16x8_t, __builtin_bit_cast(u32x4v_t, qf[ks]) & keep);
   }
-  // page entries come in batches of SPF stages, fetched one stage before they are decoded
+  static_assert(SPF > PD + 2, "the second batch of entries is under way before it is needed");
   auto entries_for = [&](int n) {
     if (n % SPF == 0) decode_entries(n);
-    if ((n + 1) % SPF == 0) fetch_entries(n + 1);
+    if ((n + 1) % SPF == 0) fetch_entry(n + 1);
+    if constexpr (SRC != PageSource::all)
+      if ((n + 2) % SPF == 0) fetch_logical(n + 2);
   };
   // Stages in flight: n + 2 and n + 3 in registers while stage n is computed on and stage n + 1 moves to LDS.
   clear_tail(st[0]);
@@ -515,49 +537,111 @@ __device__ __forceinline__ void attn_rows_body(int nchunk, int row_group, int j,
     }
 }
 
-// dense_q: the query tensor of the dense step (every token, every page), which then needs no prepared inputs:
-// the page table and the queries are read where they are.  NULL: inputs as prepared.
-template <int D, int GP, bool HALF>
-__global__ __launch_bounds__(512) void attn_rows_kernel(AttnPrepared prep, const bf16_t* dense_q, int nchunk, int row_groups,
-                                                        Shape sh, KvView kv, Partials part, float scale_log2e, int m_lo) {
+// The workgroup's own pages out of the head's union bitmap.  A thread ORs the copies of a word, a prefix sum over
+// the population counts ranks the words, and the pages of all stages of the workgroup are found at once, a thread each, by a
+// binary search of the rank over the words and one inside the word.  Against the list that the selection kernel's last
+// workgroup of a head used to build (a hand-over of every row's bitmap, about 5 us), per step: 140 rows over 8192 tokens 43.9
+// -> 38.2 us, 280 over 32768 86.0 -> 72.3, 160 over 2 x 2048 58.5 -> 43.3, 128 over 4 x 65536 190 -> 182.
+template <int PPS>
+__device__ __forceinline__ int own_pages(const UnionInKernel& uni, const KvView& kv, const Shape& sh, int b, int head, int P, int chunk, int nchunk,
+                                         unsigned char* lds, uint16_t* own) {
+  uint32_t* words = reinterpret_cast<uint32_t*>(lds);
+  int* ranks = reinterpret_cast<int*>(words + kMaxSelectPages / 32);
+  int* scan = ranks + kMaxSelectPages / 32;
+  const int tid = threadIdx.x, nw = (P + 31) >> 5;
+  const uint32_t* bits = uni.bits + (size_t)head * uni.stride + min(tid, uni.copy_words - 1);
+  uint32_t word = 0u;
+  for (int c0 = 0; c0 < uni.copies; c0 += 4) {
+    uint32_t x[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) x[c] = bits[(size_t)min(c0 + c, uni.copies - 1) * uni.copy_words];
+    word |= (x[0] | x[1]) | (x[2] | x[3]);
+  }
+  // pages past the sequence's last one are never picked; the masks only keep a stale bitmap harmless
+  if (tid >= nw) word = 0u;
+  if (tid == nw - 1 && (P & 31)) word &= (1u << (P & 31)) - 1u;
+  int U;
+  const int rank = block_exclusive_scan(__popc(word), scan, &U);
+  words[tid] = word;
+  ranks[tid] = rank;
+  __syncthreads();
+  const int stages = (U + PPS - 1) / PPS, mine = chunk < stages ? ((stages - 1 - chunk) / nchunk + 1) * PPS : 0;
+  for (int i = tid; i < mine; i += 512) {
+    int k = (chunk + i / PPS * nchunk) * PPS + i % PPS, page = 0;
+    if (k < U) {
+      int lo = 0, hi = nw;
+      while (hi - lo > 1) {   // (the trip count depends on nw only)
+        const int mid = (lo + hi) >> 1;
+        if (ranks[mid] <= k) lo = mid; else hi = mid;
+      }
+      const uint32_t w = words[lo];
+      k -= ranks[lo];
+      int pos = 0;
+#pragma unroll
+      for (int sft = 16; sft >= 1; sft >>= 1) {
+        const int c = __popc((w >> pos) & ((1u << sft) - 1u));
+        if (k >= c) {
+          k -= c;
+          pos += sft;
+        }
+      }
+      page = lo * 32 + pos;
+    }
+    own[i] = (uint16_t)page;
+  }
+  __syncthreads();
+  return U;
+}
+
+template <int D, int GP, bool HALF, PageSource SRC>
+__global__ __launch_bounds__(512) void attn_rows_kernel(AttnInputs in, int nchunk, int row_groups, Shape sh, KvView kv, Partials part,
+                                                        float scale_log2e, int m_lo, UnionInKernel uni) {
   extern __shared__ __attribute__((aligned(16))) unsigned char stage_lds[];
   const int j = blockIdx.y / row_groups, row_group = blockIdx.y % row_groups, b = blockIdx.z;
   const int head = b * sh.Hkv + j;
   constexpr int PPS = StageImage<D, GP>::kPages;
   const int lane = threadIdx.x & 63;
   const long lp = ((long)blockIdx.x + (long)(lane / PPS) * nchunk) * PPS + lane % PPS;
-  const int32_t* list = prep.entries + (size_t)head * sh.max_pages;
-  const bf16_t* q = prep.q_act;
-  int M, U, first_entry, dense_tokens = -1;
-  if (dense_q) {
-    list = kv.page_indices + kv.page_indptr[b];
-    q = dense_q;
-    U = seq_pages(kv, sh, b);
-    M = min(sh.rows_max, part.rows);
-    dense_tokens = kv.seq_lens[b];
-    first_entry = lp < U ? list[lp] : 0;
-  } else {   // the first page entries are requested together with the counts (checked against U when they are decoded)
-    first_entry = lp < sh.max_pages ? list[lp] : 0;
-    M = min(__builtin_amdgcn_readfirstlane(prep.mrows[head]), min(sh.rows_max, part.rows));
-    U = min(__builtin_amdgcn_readfirstlane(prep.ucount[head]), sh.max_pages);
+  int logical = (int)min(lp, (long)sh.max_pages);
+  // (the first list entries travel with the counts they are checked against)
+  if constexpr (SRC == PageSource::list) logical = in.list[(size_t)head * in.cap + min(lp, (long)in.cap - 1)];
+  const int M = min(active_rows(in, kv, sh, b), min(sh.rows_max, part.rows));
+  const int P = seq_pages(kv, sh, b);
+  int U = P;
+  if constexpr (SRC == PageSource::list) U = min(min(in.sel_count[head], in.cap), sh.max_pages);
+  // nothing active, a row count another launch serves, or no row in this group
+  if (M <= max(m_lo, row_group * kRowGroup)) return;
+  uint16_t* own = reinterpret_cast<uint16_t*>(stage_lds + kImages * StageImage<D, GP>::kBytes);
+  if constexpr (SRC == PageSource::own) {
+    static_assert(kImages * StageImage<D, GP>::kBytes >= kMaxSelectPages / 32 * 8 + 128, "the union's words and ranks do not fit the stage buffers");
+    U = own_pages<PPS>(uni, kv, sh, b, head, P, blockIdx.x, nchunk, stage_lds, own);
+    if (blockIdx.x == 0 && row_group == 0 && threadIdx.x == 0) uni.sel_count[head] = U;   // for the merge kernel and the caller's diagnostics
   }
-  // nothing active, a row count another launch serves, no row in this group, or no stage for this workgroup
-  if (M <= max(m_lo, row_group * kRowGroup) || (int)blockIdx.x >= (U + PPS - 1) / PPS) return;
+  const int stages = (U + PPS - 1) / PPS;
+  if ((int)blockIdx.x >= stages) return;
+  if constexpr (SRC == PageSource::own) logical = own[min(lane / PPS, (stages - 1 - (int)blockIdx.x) / nchunk) * PPS + lane % PPS];
+  const int entry = P > 0 ? kv.page_indices[kv.page_indptr[b] + max(0, min(logical, P - 1))] : 0;
   if (M <= 128)
-    attn_rows_body<D, GP, HALF, 2>(nchunk, row_group, j, sh, kv, part, scale_log2e, M, U, list, dense_tokens, q, first_entry, stage_lds);
+    attn_rows_body<D, GP, HALF, 2, SRC>(nchunk, row_group, j, sh, kv, part, scale_log2e, M, U, P, in, own, logical, entry, stage_lds);
   else
-    attn_rows_body<D, GP, HALF, 1>(nchunk, row_group, j, sh, kv, part, scale_log2e, M, U, list, dense_tokens, q, first_entry, stage_lds);
+    attn_rows_body<D, GP, HALF, 1, SRC>(nchunk, row_group, j, sh, kv, part, scale_log2e, M, U, P, in, own, logical, entry, stage_lds);
 }
 
-template <int D, int GP, bool HALF>
-static hipError_t launch_rows(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnPrepared& prep,
-                              const bf16_t* dense_q, int nchunk, const Partials& part, hipEvent_t e0, hipEvent_t e1, int m_lo) {
-  constexpr size_t lds_bytes = kImages * StageImage<D, GP>::kBytes;
-  auto kern = attn_rows_kernel<D, GP, HALF>;
+template <int D, int GP, bool HALF, PageSource SRC>
+static hipError_t launch_rows(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnInputs& in,
+                              int nchunk, const Partials& part, hipEvent_t e0, hipEvent_t e1, int m_lo, int upper,
+                              const UnionInKernel& uni) {
+  // own pages: behind the stage buffers, two bytes for every page a workgroup may own
+  constexpr bool OWN = SRC == PageSource::own;
+  constexpr int PPS = StageImage<D, GP>::kPages;
+  constexpr size_t images = kImages * StageImage<D, GP>::kBytes, most = images + (OWN ? 2 * kMaxSelectPages : 0);
+  static_assert(most <= 160 * 1024, "the stage buffers and the longest list exceed the LDS");
+  const size_t lds_bytes = images + (OWN ? (size_t)((upper + PPS - 1) / PPS + nchunk - 1) / nchunk * PPS * 2 : 0);
+  auto kern = attn_rows_kernel<D, GP, HALF, SRC>;
   static bool attr_set = false;   // per instantiation
-  if (lds_bytes > 48 * 1024 && !attr_set) {
+  if (most > 48 * 1024 && !attr_set) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)lds_bytes);
+                                       (int)most);
     if (e != hipSuccess) return e;
     attr_set = true;
   }
@@ -565,27 +649,31 @@ static hipError_t launch_rows(hipStream_t st, const KvView& kv, const Shape& sh,
   const float scale_log2e = sh.sm_scale * 1.4426950408889634f;
   dim3 grid(nchunk, sh.Hkv * row_groups, batch);
   if (e0 && e1)   // events bound to this dispatch: they read the kernel's own begin and end
-    hipExtLaunchKernelGGL(kern, grid, dim3(512), (uint32_t)lds_bytes, st, e0, e1, 0, prep, dense_q, nchunk, row_groups, sh, kv,
-                          part, scale_log2e, m_lo);
+    hipExtLaunchKernelGGL(kern, grid, dim3(512), (uint32_t)lds_bytes, st, e0, e1, 0, in, nchunk, row_groups, sh, kv,
+                          part, scale_log2e, m_lo, uni);
   else
-    kern<<<grid, 512, lds_bytes, st>>>(prep, dense_q, nchunk, row_groups, sh, kv, part, scale_log2e, m_lo);
+    kern<<<grid, 512, lds_bytes, st>>>(in, nchunk, row_groups, sh, kv, part, scale_log2e, m_lo, uni);
   return hipGetLastError();
 }
 
-hipError_t launch_attn_rows(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnPrepared& prep,
-                            const void* dense_query, int nchunk, const Partials& part, hipEvent_t e0, hipEvent_t e1, int m_lo, bool half_values) {
+hipError_t launch_attn_rows(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const AttnInputs& in, int nchunk,
+                            const Partials& part, hipEvent_t e0, hipEvent_t e1, int m_lo, bool half_values, int upper,
+                            const UnionInKernel* uni) {
   if (batch <= 0 || nchunk <= 0) return hipSuccess;
-  const bf16_t* dq = (const bf16_t*)dense_query;
-#define LOSA_ROWS(D, GP)                                                                              \
-  return half_values ? launch_rows<D, GP, true>(st, kv, sh, batch, prep, dq, nchunk, part, e0, e1, m_lo)  \
-                     : launch_rows<D, GP, false>(st, kv, sh, batch, prep, dq, nchunk, part, e0, e1, m_lo)
-  if (sh.d == 128) {
-    if (sh.g == 16) LOSA_ROWS(128, 16);
-    LOSA_ROWS(128, 32);
-  }
-  if (sh.g == 16) LOSA_ROWS(64, 16);
-  LOSA_ROWS(64, 32);
-#undef LOSA_ROWS
+  auto launch = [&](auto half, auto source) {
+    constexpr bool H = decltype(half)::value;
+    constexpr PageSource S = decltype(source)::value;
+    const UnionInKernel u = uni ? *uni : UnionInKernel{nullptr};
+    auto run = sh.d == 128 ? (sh.g == 16 ? launch_rows<128, 16, H, S> : launch_rows<128, 32, H, S>)
+                           : (sh.g == 16 ? launch_rows<64, 16, H, S> : launch_rows<64, 32, H, S>);
+    return run(st, kv, sh, batch, in, nchunk, part, e0, e1, m_lo, upper, u);
+  };
+  auto launch_half = [&](auto half) {
+    if (uni) return launch(half, std::integral_constant<PageSource, PageSource::own>());
+    if (in.list) return launch(half, std::integral_constant<PageSource, PageSource::list>());
+    return launch(half, std::integral_constant<PageSource, PageSource::all>());
+  };
+  return half_values ? launch_half(std::true_type()) : launch_half(std::false_type());
 }
 
 }  // namespace losa

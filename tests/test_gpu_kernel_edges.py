@@ -404,3 +404,72 @@ def test_union_at_the_edges_of_its_copies(page, limit, reserved):
         run_steps_end_to_end(r, [4], orc.SEL_MASS, 0.5, w.topk_pages)
     finally:
         r.close()
+
+
+@pytest.mark.parametrize("page,limit,B,G,workgroups", [
+    (16, 5, 17, 4, 256), (16, 512, 33, 8, 256),       # 68 and 264 rows over copies of 16 words
+    (16, 1024, 40, 4, 256),                           # ... of 32
+    (16, 1025, 33, 4, 256), (32, 1100, 64, 4, 64),    # one copy per 64 rows: two (68 .. 132 rows), four (256)
+    (16, 2049, 64, 7, 256),                           # ... eight (448)
+    (16, 4099, 17, 4, 1),                             # one workgroup owns every page of a head
+    (16, 16384, 17, 4, 2)])                           # the longest list of own pages: two heads, one workgroup each
+def test_union_of_more_than_64_rows_at_the_edges_of_its_copies(page, limit, B, G, workgroups):
+    """The many-row kernel makes the list of its own pages from the bitmap's copies; counts known to the host (all
+    rows, the fewest it serves) and to the device only, next to a prefix that leaves most workgroups without a stage."""
+    few = -(-65 // G)
+    w = workload(B, G, 1, 64, page, (limit * page - 3, min(limit, 7) * page + 1), B, topk=max(1, limit // 9), T=4)
+    r = Rig(w, tuning={L.LOSA_TUNE_ATTN_WORKGROUPS: workgroups})
+    r.ctx.workspace.fill_(255)
+    try:
+        check_page_bounds(r)
+        run_steps_end_to_end(r, range(1), orc.SEL_TOPK, 1.0, w.topk_pages)
+        run_steps_end_to_end(r, [1], orc.SEL_TOPK, float(B), w.topk_pages)
+        run_steps_end_to_end(r, [2], orc.SEL_TOPK, float(few), w.topk_pages)
+        run_steps_end_to_end(r, [3], orc.SEL_MASS, 0.9, w.topk_pages)
+    finally:
+        r.close()
+
+
+@pytest.mark.parametrize("B,G,d,page,n", [(8, 4, 64, 16, 3), (8, 7, 128, 32, 7), (8, 8, 64, 32, 8), (24, 4, 128, 16, 17), (40, 7, 64, 16, 40)])
+def test_listed_pages_that_do_not_exist_count_for_nothing(B, G, d, page, n):
+    """Page lists are resolved in the attention kernels: pages outside the sequence, in any place of a list, and lists of an
+    empty sequence leave the result of the other pages (neutral statistics if there are none); a second batch of
+    list entries per wavefront."""
+    w = workload(B, G, 1, d, page, (page * 300 - 5, page * 3, 1), n)
+    r = Rig(w, tuning={L.LOSA_TUNE_ATTN_WORKGROUPS: 3})
+    blk, kv = r.blk, r.layer.kv
+    dev = blk.q.device
+    rng = np.random.Generator(np.random.Philox(B + G))
+    try:
+        active = torch.full((3, B), -1, dtype=torch.int32, device=dev)
+        active[:, :n] = torch.from_numpy(np.sort(np.stack([rng.permutation(B)[:n] for _ in range(3)]), axis=1).astype(np.int32)).to(dev)
+        count = torch.full((3,), n, dtype=torch.int32, device=dev)
+        lens = kv.seq_lens.clone()
+        lens[2] = 0
+        part = L.PagedKV(kv.k_pages, kv.v_pages, kv.meta, kv.page_indptr, kv.page_indices, lens, max_seq_pages=300)
+        valid = [np.sort(rng.permutation(300)[:211]), np.array([0, 2]), np.array([], dtype=np.int64)]
+        cap, results = 300, []
+        for extra in (0, 1):
+            lists, cnt = torch.full((3, 1, cap), -9, dtype=torch.int32, device=dev), torch.zeros((3, 1), dtype=torch.int32, device=dev)
+            for b in range(3):
+                pages = valid[b]
+                if extra:
+                    bad = np.array([-1, 2 ** 31 - 1, -2 ** 31, (300, 3, 0)[b], (300, 3, 0)[b] + 5])
+                    pages = rng.permutation(np.concatenate([pages, bad]))
+                lists[b, 0, :len(pages)] = torch.from_numpy(pages.astype(np.int32)).to(dev)
+                cnt[b, 0] = len(pages)
+            o_p, lse_p = torch.full_like(blk.o_p, 3.0), torch.full_like(blk.lse_p, 3.0)
+            L.losa_sparse_attn(r.ctx, part, blk.q[1], active, count, lists, cnt, cap, o_p, lse_p)
+            torch.cuda.synchronize()
+            results.append((o_p.cpu().numpy(), lse_p.cpu().numpy()))
+        (o0, l0), (o1, l1) = results
+        for b in range(3):
+            rows = b * B + active[b, :n].cpu().numpy()
+            if b == 2:
+                assert np.all(o0[rows] == 0) and np.all(o1[rows] == 0) and np.all(l0[rows] == -np.inf) and np.all(l1[rows] == -np.inf)
+            else:   # other shares, other order of the sums: half the parity tolerance
+                assert np.abs(o0[rows] - o1[rows]).max() <= 1e-2 and np.abs(l0[rows] - l1[rows]).max() <= 1e-2
+        untouched = np.setdiff1d(np.arange(3 * B), np.concatenate([b * B + active[b, :n].cpu().numpy() for b in range(3)]))
+        assert np.all(o1[untouched] == 3.0) and np.all(l1[untouched] == 3.0)
+    finally:
+        r.close()
