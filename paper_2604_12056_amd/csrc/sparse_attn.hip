@@ -491,6 +491,79 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(KvView kv, Shape sh, At
   }
 }
 
+// The same for few chunks (nchunk <= KC): a wavefront takes 256 / D rows, a thread one channel quad of a row and all of its
+// chunks, with no LDS and no barrier.  The form above deals the chunks out to 1024 / D lanes per row, whether there are
+// that many or not, with eight loads each: with four chunks half of its threads have none and most loads are repeats.
+// Rows x heads, chunks, plain form / this: 64 x 128, 2 16.9 / 5.5 us; 63 x 64, 4 10.1 / 5.0; 35 x 64, 4 7.5 / 4.9; 64 x 32, 8
+// 6.8 / 4.9; 42 x 4, 8 the same.  With 11 or 12 chunks and few rows its threads' loads take longer than the plain form's
+// barriers (24 x 1 3.4 / 3.9).  A thread's products are rounded and added in chunk order, as the plain form's lanes
+// are, so the results are the same bits.
+// MIXED, as above: a workgroup of four wavefronts then, which takes fragments of the heads that have them (63 of 224 rows
+// x 64 heads, 4 chunks 10.3 / 5.1 us; 112 rows 6.6 / 6.3).
+constexpr int kFewChunks = 8;
+template <int D, int KC, bool MIXED>
+__global__ __launch_bounds__(64 * (MIXED ? 4 : 1)) void attn_merge_few_kernel(KvView kv, Shape sh, AttnInputs in, int nchunk, Partials part,
+                                                            float* __restrict__ o_p, float* __restrict__ lse_p,
+                                                            int rows_known, int few_tile, int many_tile) {
+  constexpr int C4 = D / 4, WAVES = MIXED ? 4 : 1;
+  const int tid = threadIdx.x, c4 = tid % C4, j = blockIdx.y, b = blockIdx.z;
+  const int r0 = blockIdx.x * (64 * WAVES / C4), r = r0 + tid / C4;
+  if constexpr (MIXED) {
+    const int M = min(min(active_rows(in, kv, sh, b), sh.rows_max), part.rows);
+    if (__builtin_expect(M > kUnionRows, 0)) {
+      if ((int)blockIdx.x / (D / 8 / WAVES) * kPartialTile >= M) return;
+      const int U = merged_pages(in, kv, sh, b, b * sh.Hkv + j), pps = kManyRowStage / sh.g;
+      merge_fragments<D, WAVES, 1, 4, false>(sh, in.active_idx, b, j, blockIdx.x, M, min(nchunk, (U + pps - 1) / pps), 0, nchunk, part, o_p, lse_p, nullptr);
+      return;
+    }
+    if (r0 >= M) return;
+  } else if (!rows_known && r0 >= active_rows(in, kv, sh, b)) {
+    return;   // surplus workgroup
+  }
+  float mk[KC], lk[KC];
+  f32x4v_t x[KC];
+#pragma unroll
+  for (int k = 0; k < KC; ++k) {   // before it is known how many chunks are live: slots exist for all of them
+    const size_t prow = (((size_t)b * sh.Hkv + j) * nchunk + min(k, nchunk - 1)) * part.rows + min(r, part.rows - 1);
+    mk[k] = part.m[prow];
+    lk[k] = part.l[prow];
+    x[k] = reinterpret_cast<const f32x4v_t*>(part.o + prow * D)[c4];
+  }
+  const int a = row_token(sh, min(r, sh.rows_max - 1));
+  const int tok = in.active_idx ? in.active_idx[(size_t)b * sh.B + a] : a;
+  const int M = min(min(active_rows(in, kv, sh, b), sh.rows_max), part.rows), U = merged_pages(in, kv, sh, b, b * sh.Hkv + j);
+  if (r >= M || (unsigned)tok >= (unsigned)sh.B) return;
+  const int ppt = (M <= kUnionRows ? few_tile : many_tile) / sh.g;
+  const int live = min(nchunk, (U + ppt - 1) / ppt);
+  float m_tot = -INFINITY;
+#pragma unroll
+  for (int k = 0; k < KC; ++k) {
+    if (k >= live) {   // not a chunk, or leftovers of earlier launches, NaN included
+      mk[k] = -INFINITY;
+      lk[k] = 0.f;
+      x[k] = (f32x4v_t){0.f, 0.f, 0.f, 0.f};
+    }
+    m_tot = fmaxf(m_tot, mk[k]);
+  }
+  const size_t orow = ((size_t)b * sh.B + tok) * sh.Hq + j * sh.G + (r - a * sh.G);
+  f32x4v_t o = {0.f, 0.f, 0.f, 0.f};
+  float l = 0.f;
+  if (!(m_tot > -1.0e29f)) {   // no valid token at all: the neutral element of the merge
+    reinterpret_cast<f32x4v_t*>(o_p + orow * D)[c4] = o;
+    if (c4 == 0) lse_p[orow] = -INFINITY;
+    return;
+  }
+#pragma unroll
+  for (int k = 0; k < KC; ++k) {
+#pragma clang fp contract(off)
+    const float w = exp2f(mk[k] - m_tot);
+    o += x[k] * w;
+    l += lk[k] * w;
+  }
+  reinterpret_cast<f32x4v_t*>(o_p + orow * D)[c4] = o / l;
+  if (c4 == 0) lse_p[orow] = (m_tot + log2f(l)) * 0.6931471805599453f;
+}
+
 template <int D, int GP>
 static hipError_t launch_f32(hipStream_t st, const KvView& kv, const Shape& sh, int batch, const float* q,
                              const int32_t* active_idx, const int32_t* active_count, const int32_t* sel_pages,
@@ -545,6 +618,17 @@ hipError_t launch_attn_merge(hipStream_t st, const KvView& kv, const Shape& sh, 
     else if (nchunk <= 64) LOSA_FRAGMENTS(4, 4, 8);
     else LOSA_FRAGMENTS(8, 8, 8);
 #undef LOSA_FRAGMENTS
+    return hipGetLastError();
+  }
+  if (bf16 && nchunk <= kFewChunks) {
+    const bool mixed = many_tile == kManyRowStage;
+    auto kern = mixed ? (sh.d == 128 ? (nchunk <= 4 ? attn_merge_few_kernel<128, 4, true> : attn_merge_few_kernel<128, 8, true>)
+                                     : (nchunk <= 4 ? attn_merge_few_kernel<64, 4, true> : attn_merge_few_kernel<64, 8, true>))
+                      : (sh.d == 128 ? (nchunk <= 4 ? attn_merge_few_kernel<128, 4, false> : attn_merge_few_kernel<128, 8, false>)
+                                     : (nchunk <= 4 ? attn_merge_few_kernel<64, 4, false> : attn_merge_few_kernel<64, 8, false>));
+    const int waves = mixed ? 4 : 1, per_wg = waves * 256 / sh.d, few = ((mixed ? min(rows, kUnionRows) : rows) + per_wg - 1) / per_wg;
+    kern<<<dim3(mixed ? max(few, tiles * frags / 4) | 1 : few, sh.Hkv, batch), 64 * waves, 0, st>>>(kv, sh, in, nchunk, part, o_p, lse_p,
+                                                                                                  known, few_tile, many_tile);
     return hipGetLastError();
   }
   // wavefronts per fragment in a mixed launch: with few chunks one, a quarter of the workgroups

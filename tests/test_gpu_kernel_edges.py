@@ -473,3 +473,24 @@ def test_listed_pages_that_do_not_exist_count_for_nothing(B, G, d, page, n):
         assert np.all(o1[untouched] == 3.0) and np.all(l1[untouched] == 3.0)
     finally:
         r.close()
+
+
+@pytest.mark.parametrize("B,G,d,page", [(9, 7, 128, 16), (16, 4, 64, 32), (33, 7, 64, 16), (40, 4, 128, 32)])
+@pytest.mark.parametrize("chunks", [1, 4, 5, 8, 9])
+def test_merge_of_few_chunks(B, G, d, page, chunks):
+    """Chunk counts at the edges of the merge's forms, next to a sequence with fewer chunks than the launch; counts known to
+    the host and to the device only, the latter up to 64 rows per head and with heads above and below them in one launch."""
+    few = 9 if G == 7 else 16   # the most tokens whose rows are at most 64
+    w = workload(B, G, 1, d, page, (page * 70 - 5, page * 2 + 1, 1), few, topk=40, T=6)
+    r = Rig(w, tuning={L.LOSA_TUNE_ATTN_WORKGROUPS: chunks * 3})
+    r.ctx.workspace.fill_(255)
+    try:
+        check_page_bounds(r)
+        run_steps_end_to_end(r, [0], orc.SEL_TOPK, 1.0, w.topk_pages)
+        run_steps_end_to_end(r, [1], orc.SEL_TOPK, float(few), w.topk_pages)
+        run_steps_end_to_end(r, [2], orc.SEL_TOPK, 1.0, w.topk_pages)
+        run_steps_end_to_end(r, [3], orc.SEL_MASS, 0.02, w.topk_pages)
+        run_steps_end_to_end(r, [4], orc.SEL_MASS, 0.5, w.topk_pages)
+        run_steps_end_to_end(r, [5], orc.SEL_MASS, 1.0, w.topk_pages)
+    finally:
+        r.close()
