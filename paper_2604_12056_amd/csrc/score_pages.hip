@@ -994,20 +994,20 @@ hipError_t launch_select_pages(hipStream_t st, const KvView& kv, const Shape& sh
   const int pages = max_seq_pages < sh.max_pages ? max_seq_pages : sh.max_pages;
   if (pages > kMaxSelectPages) return hipErrorInvalidValue;
   const bool list = !union_bits;
-  // One row per workgroup while the grid fits the machine in one round (seven 256-thread
-  // workgroups per CU for the one-row form, five for the several-row form, by their register
-  // counts; one 1024-thread workgroup); beyond that, up to four rows per workgroup.
-  const bool small = pages <= 256 * 8;
-  // (without the union hand-over at its end a workgroup is short enough that a grid somewhat past
-  // one round still beats two rows per workgroup: measured on 16 sequences of 36 rows x 4 heads)
-  const long fit_one = workgroups_per_round > 0 ? workgroups_per_round : (small ? (union_bits ? 10L : 7L) * 256 : 256L);
-  const long fit_many = workgroups_per_round > 0 ? workgroups_per_round : (small ? 5L * 256 : 256L);
-  // (a count the host does not know: the grid has a workgroup for every possible row, and those past
-  // the count leave at once; sized as if a quarter of the rows existed, so that a typical active set
-  // is not made to share workgroups for the sake of rows that are not there)
-  const long wgs = (long)rows * sh.Hkv * batch / (out.rows_known ? 1 : 4);
-  int rpw = wgs <= fit_one ? 1 : (int)((wgs + fit_many - 1) / fit_many);
-  rpw = rpw < 1 ? 1 : (rpw > 4 ? 4 : rpw);
+  // Query rows per workgroup: one per `round` workgroups of a grid with one row each.  A second row costs its selection
+  // once more, a further workgroup its start and, where it has no row, its leaving; how many workgroups outweigh a
+  // second row depends on the ending and on whether every row of the grid exists.
+  //   bitmaps, count known (1 / 2 / 4 rows, us): 3584 rows 13.4 / 13.7 / 16.7; 7680 26.9 / 27.1 / 28.9; 10240 31.0 / 29.7 / 29.8;
+  //     14336 40.7 / 39.6 / 39.1; 3584 of 4096 pages 22.4 / 25.8 / 27.5; 896 of 8192 pages 15.0 / 19.5 / 17.8
+  //   bitmaps, count on the device (1 / 2 / 4 / 8): 84 of 256 rows x 32 heads 10.0 / 9.4 / 8.8 / 9.4; 21 of 224 x 64 10.4 / 10.0 /
+  //     8.1 / 7.5; 35 of 224 x 8 5.0 / 4.9 / 5.1 / 7.1; 56 of 448 x 4, 8192 pages 8.7 / 7.9 / 7.0 / 6.9.  At most four: rows may all exist.
+  //   union list, whose workgroups draw tickets (1 / 2 / 4 / 8): 84 of 256 x 32 35.4 / 35.8 / 27.0 / 18.7; 70 of 224 x 64 43.1 / 43.8 /
+  //     36.1 / 22.7; 14 of 224 x 64 14.2 / 12.3 / 11.7 / 11.3; 35 of 224 x 8 9.6 / 9.9 / 10.0 / 10.0
+  const long wgs = (long)rows * sh.Hkv * batch;
+  const int threads = pages <= 256 * 8 ? 256 : pages <= 512 * 8 ? 512 : 1024;
+  const long round = (list ? 1024L : out.rows_known ? 5120L : 2048L) * 256 / threads;
+  const long want = workgroups_per_round > 0 ? (wgs + workgroups_per_round - 1) / workgroups_per_round : wgs / round;
+  const int rpw = (int)max(1L, min(want, list ? 8L : 4L));
   dim3 grid((rows + rpw - 1) / rpw, sh.Hkv, batch);
   // Few keys per thread keep the unrolled code small (it has to come through the instruction
   // cache on every launch) and the loads contiguous: longer sequences get more threads, not
