@@ -3,9 +3,8 @@
 //
 //   page_scores   s[b,j,r,p] = sum_c max(q_c*min_c, q_c*max_c)   r = a*G + hg over the active slots a
 //   select_pages  per row r: exact top-K by radix select on order-preserving keys (ties:
-//                 smaller page); the last row of a KV head to finish ORs the row bitmaps,
-//                 compacts the union into an ascending page list and, inside losa_step,
-//                 also builds the attention kernel's inputs
+//                 smaller page); picks go into a union bitmap per KV head, or, where the caller wants the
+//                 list, the last row of a head to finish ORs the row bitmaps and compacts them into one
 //
 // Everything that decides a set is integer work on float bit patterns: no float atomics,
 // so the outcome does not depend on scheduling.
