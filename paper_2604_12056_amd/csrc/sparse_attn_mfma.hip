@@ -727,8 +727,14 @@ static hipError_t launch_dg(hipStream_t st, const KvView& kv, const Shape& sh, i
         if (e != hipSuccess) return e;
         attr_set = true;
       }
-      kern<<<dim3(nchunk, sh.Hkv, batch), 256, lds_bytes, st>>>(in, nchunk, sh, kv, part, sh.sm_scale * 1.4426950408889634f,
-                                                                m_lo, m_hi, uni ? *uni : UnionInKernel{nullptr});
+      const dim3 grid(nchunk, sh.Hkv, batch);
+      const float scale_log2e = sh.sm_scale * 1.4426950408889634f;
+      const UnionInKernel u = uni ? *uni : UnionInKernel{nullptr};
+      if (e0 && e1)   // events bound to this dispatch, as in launch_one
+        hipExtLaunchKernelGGL(kern, grid, dim3(256), (uint32_t)lds_bytes, st, e0, e1, 0, in, nchunk, sh, kv, part, scale_log2e, m_lo,
+                              m_hi, u);
+      else
+        kern<<<grid, 256, lds_bytes, st>>>(in, nchunk, sh, kv, part, scale_log2e, m_lo, m_hi, u);
       return hipGetLastError();
     };
     constexpr size_t slots = 4 * MergeSlot<D, 4>::kFloats;
