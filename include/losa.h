@@ -61,7 +61,8 @@ typedef enum { LOSA_BF16 = 0, LOSA_F32 = 1 } losa_dtype;
  * MASS: tokens in descending score order until their running sum reaches param (in [0,1])
  * times the block's total score (the 50 % line of the paper's locality heat maps is
  * param = 0.5); nothing is selected when the total is zero or param is zero.
- * Ties: larger score first, then smaller token index. */
+ * Ties: larger score first, then smaller token index.  A score that is NaN ranks with infinity (and exceeds no
+ * threshold), so TOPK and FRACTION hold exactly n tokens whatever the states hold. */
 typedef enum {
   LOSA_SEL_TOPK = 0,
   LOSA_SEL_FRACTION = 1,

@@ -120,6 +120,11 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int* wave_tot, int* t
   return base + incl - v;
 }
 
+// A locality score as it is ranked: one that is no number (a hidden state that overflowed) ranks with infinity.  Ranks by
+// counting are then a permutation whatever the scores are, and a top-n selection holds n tokens, which is what the
+// launches behind it are sized for.  (A threshold compares the score itself.)
+__device__ __forceinline__ float ranked_score(float delta) { return delta == delta ? delta : INFINITY; }
+
 // Cumulative-mass rule.  `sorted`: B scores in descending order, zeros up to a multiple of four, 16-byte aligned;
 // prefix[k] = sorted[0] + ... + sorted[k], summed in that order by the one thread that calls this.
 __device__ __forceinline__ void sorted_prefix_sums(const float* sorted, float* prefix, int B) {

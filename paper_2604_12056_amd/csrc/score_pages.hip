@@ -221,7 +221,8 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape 
     // four barriers the ranking of 32 tokens took 1.55 of the kernel's 7.1 us (2048 pages, 42 rows, 4 KV heads); the
     // kernel now takes 5.7.
     const int B = sh.B;
-    const float mine = lane < B ? my_delta : -INFINITY;   // the padding never outranks a token
+    const float score = ra.mode == LOSA_SEL_THRESHOLD ? my_delta : ranked_score(my_delta);
+    const float mine = lane < B ? score : -INFINITY;   // the padding never outranks a token
     int act = 0, rank = 0;
     if (ra.mode != LOSA_SEL_THRESHOLD) {
       const int per = (B + 3) >> 2, k0 = wave * per, k1 = min(k0 + per, B);
@@ -271,6 +272,7 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape 
     M = n_act * sh.G;
   } else if (ranked) {
     const int B = sh.B;   // <= kRankTokens (checked by the launcher)
+    if (ra.mode != LOSA_SEL_THRESHOLD) my_delta = ranked_score(my_delta);
     sdelta[tid] = tid < B ? my_delta : -INFINITY;   // 256 threads, kRankTokens entries: the padding never outranks a token
     __syncthreads();
     int act = 0, rank = 0;

@@ -84,8 +84,10 @@ __global__ __launch_bounds__(256) void locality_select_kernel(const T* __restric
   if (!s_last) return;
   if (tid == 0) tickets[b] = 0;
   // ---- ranking by counting, B <= 1024: thread i handles tokens i, i+256, ...
-  for (int i = tid; i < B; i += 256)
-    sd[i] = __hip_atomic_load(&delta[(size_t)b * B + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int i = tid; i < B; i += 256) {
+    const float d = __hip_atomic_load(&delta[(size_t)b * B + i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    sd[i] = mode == LOSA_SEL_THRESHOLD ? d : ranked_score(d);
+  }
   __syncthreads();
   __shared__ __attribute__((aligned(16))) float sorted[1024], prefix[1024];   // cumulative-mass rule only
   if (mode == LOSA_SEL_MASS) {

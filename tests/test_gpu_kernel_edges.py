@@ -10,7 +10,7 @@ from paper_2604_12056_amd import binding as L
 from paper_2604_12056_amd import synth
 from paper_2604_12056_amd.device_inputs import config_of
 
-from parity_util import Rig, check_page_bounds, check_sparse_attn, run_steps_end_to_end
+from parity_util import Rig, check_page_bounds, check_sparse_attn, compare_state, gpu_union_of, oracle_selection, run_steps_end_to_end
 
 pytestmark = pytest.mark.gpu
 
@@ -243,6 +243,55 @@ def test_active_set_of_a_step_at_the_edges_of_its_ranking(B):
                 assert np.array_equal(got[b], np.isin(np.arange(B), A).astype(np.uint8)), (b, mode, param)
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("dtype,B,G", [("bf16", 9, 8), ("bf16", 16, 7), ("bf16", 33, 4), ("bf16", 64, 4), ("bf16", 65, 4), ("bf16", 256, 2),
+                                       ("f32", 24, 4)])
+def test_scores_that_are_no_number_rank_with_infinity(dtype, B, G):
+    """Several tokens whose change is NaN and one whose change is infinite: top-n selections hold exactly n tokens (64 query
+    rows per KV head at most, and fewer than there are such tokens), the steps attend for exactly those, over a
+    workspace that holds no page table of an earlier step."""
+    n = 64 // G if B * G > 64 else B // 2
+    rng = np.random.Generator(np.random.Philox(B * G))
+    odd = [np.sort(rng.permutation(B)[:min(B, n + 2)]), np.array([0, B - 1]), np.sort(rng.permutation(B)[:3])]
+
+    def poison(inp):
+        nan, inf = (0x7FC0, 0x7F80) if dtype == "bf16" else (np.nan, np.inf)
+        for b in range(3):
+            inp.h[1, b * B + odd[b], 5] = nan
+            inp.h[1, b * B + odd[b][-1], 5] = inf
+    w = workload(B, G, 1, 64, 16, (700, 33, 160), n, dtype=dtype)
+    r = Rig(w, mutate=poison)
+    blk = r.blk
+    r.ctx.workspace.fill_(255)
+    try:
+        check_page_bounds(r)
+        run_steps_end_to_end(r, [0], orc.SEL_TOPK, 1.0, w.topk_pages)
+        delta = orc.locality_score(r.inp.h[1], r.inp.h[0]).reshape(3, B)
+        assert all(np.isnan(delta[b, odd[b][:-1]]).all() and np.isposinf(delta[b, odd[b][-1]]) for b in range(3))
+        for mode, param in ((orc.SEL_TOPK, 1.0), (orc.SEL_TOPK, float(n)), (orc.SEL_FRACTION, n / B), (orc.SEL_TOPK, float(B)),
+                            (orc.SEL_THRESHOLD, 1e-3), (orc.SEL_MASS, 0.5)):
+            score = delta if mode == orc.SEL_THRESHOLD else np.where(np.isnan(delta), np.inf, delta)
+            want = [orc.active_set(score[b], mode, param) for b in range(3)]
+            before_o, before_l = blk.o_p.clone(), blk.lse_p.clone()
+            L.losa_step(r.ctx, r.layer.kv, 1, blk.h[1], blk.h[0], blk.q[1], mode, param, w.topk_pages, blk.o_p, blk.lse_p, blk.mask,
+                        blk.sel_count)
+            torch.cuda.synchronize()
+            mask, pages = blk.mask.cpu().numpy().reshape(3, B), blk.sel_count.cpu().numpy()
+            assert all(np.array_equal(np.nonzero(mask[b])[0], want[b]) for b in range(3)), (mode, param)
+            scores, picks, _ = oracle_selection(r, 1, want, w.topk_pages)
+            union, _ = gpu_union_of(r, 1, want, w.topk_pages, scores, picks)
+            assert all(pages[b, 0] == len(union[b, 0]) for b in range(3))
+            orc.losa_step(r.cache, 1, None, None, r.inp.q[1], mode, param, w.topk_pages, w.B, w.Hq, r.o_ref, r.L_ref,
+                          forced_active=want, forced_union=union)
+            compare_state(r, want, before_o, before_l)
+            for call in (lambda *out: L.losa_select_active(r.ctx, blk.h[1], blk.h[0], mode, param, *out),
+                         lambda *out: L.losa_select_active_static(r.ctx.cfg.dtype, 3, B, w.H, blk.h[1], blk.h[0], mode, param, *out)):
+                call(blk.delta, blk.mask, blk.active_idx, blk.active_count)
+                idx, count = blk.active_idx.cpu().numpy().reshape(3, B), blk.active_count.cpu().numpy()
+                assert all(np.array_equal(idx[b, :count[b]], want[b]) for b in range(3)), (mode, param)
+    finally:
+        r.close()
 
 
 @pytest.mark.parametrize("P", [1, 7, 64, 255, 256, 2047, 2048, 2049, 4096, 4097, 8192, 8193, 16384])
