@@ -73,6 +73,7 @@ def active_set(delta: np.ndarray, mode: int, param: float) -> np.ndarray:
     B = d32.shape[0]
     if mode == SEL_THRESHOLD:
         return np.nonzero(d32 > np.float32(param))[0].astype(np.int32)
+    d32 = np.where(np.isnan(d32), np.float32(np.inf), d32)   # no number: ranks with infinity
     order = sorted(range(B), key=lambda i: (-float(d32[i]), i))
     if mode == SEL_MASS:
         # Locality figures (threshold line): tokens in descending score order until their

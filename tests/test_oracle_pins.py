@@ -182,6 +182,17 @@ def test_active_set_cumulative_mass_rule():
             assert srt[:len(A) - 1].sum() < tau * d.sum() * (1 + 1e-6)
 
 
+def test_scores_that_are_no_number_rank_with_infinity():
+    """Stated in the interface: such a token ranks with infinity (ties to the smaller index) and exceeds no threshold."""
+    delta = np.array([0.5, np.nan, 3.0, np.inf, np.nan, 0.0])
+    assert orc.active_set(delta, orc.SEL_TOPK, 2).tolist() == [1, 3]
+    assert orc.active_set(delta, orc.SEL_TOPK, 4).tolist() == [1, 2, 3, 4]
+    assert orc.active_set(delta, orc.SEL_FRACTION, 1.0).tolist() == list(range(6))
+    assert orc.active_set(delta, orc.SEL_THRESHOLD, 1.0).tolist() == [2, 3]
+    assert orc.active_set(delta, orc.SEL_MASS, 0.5).tolist() == [1]
+    assert orc.active_set(delta, orc.SEL_MASS, 0.0).tolist() == []
+
+
 def test_active_set_brute_force():
     rng = np.random.default_rng(7)
     for _ in range(50):
