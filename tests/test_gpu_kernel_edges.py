@@ -8,7 +8,7 @@ import torch
 from oracle import losa_oracle as orc
 from paper_2604_12056_amd import binding as L
 from paper_2604_12056_amd import synth
-from paper_2604_12056_amd.device_inputs import config_of
+from paper_2604_12056_amd.device_inputs import config_of, to_host
 
 from parity_util import Rig, check_page_bounds, check_sparse_attn, compare_state, gpu_union_of, oracle_selection, run_steps_end_to_end
 
@@ -232,15 +232,28 @@ def test_active_set_of_a_step_at_the_edges_of_its_ranking(B):
         q = draw(3 * B, Hq, d)
         o_p, lse_p = torch.zeros((3 * B, Hq, d), device=dev), torch.zeros((3 * B, Hq), device=dev)
         mask = torch.zeros(3 * B, dtype=torch.uint8, device=dev)
+        order = [kv.page_indices[a:a + n].long() for a, n in ((0, 3), (3, 13), (16, 1))]
+        tokens = lambda x: [to_host(x[order[b]].transpose(1, 2).reshape(-1, Hkv, d)[:int(lens[b])]) for b in range(3)]
+        cache = orc.PrefixCache(tokens(kv.k_pages), tokens(kv.v_pages.transpose(2, 3)), g)
         for mode, param in ((orc.SEL_TOPK, 0.0), (orc.SEL_TOPK, 1.0), (orc.SEL_TOPK, float(B // 2)), (orc.SEL_TOPK, float(B)),
                             (orc.SEL_FRACTION, 0.3), (orc.SEL_THRESHOLD, 8.0), (orc.SEL_THRESHOLD, -1.0),
                             (orc.SEL_MASS, 0.0), (orc.SEL_MASS, 0.25), (orc.SEL_MASS, 0.75), (orc.SEL_MASS, 1.0)):
             mask.fill_(9)
+            o_p.fill_(7.0)
+            lse_p.fill_(7.0)
             L.losa_step(ctx, kv, 1, h, torch.zeros_like(h), q, mode, param, 2, o_p, lse_p, mask)
             got = mask.cpu().numpy().reshape(3, B)
+            want = [orc.active_set(v[b] ** 2, mode, param) for b in range(3)]
             for b in range(3):
-                A = orc.active_set(v[b] ** 2, mode, param)
-                assert np.array_equal(got[b], np.isin(np.arange(B), A).astype(np.uint8)), (b, mode, param)
+                assert np.array_equal(got[b], np.isin(np.arange(B), want[b]).astype(np.uint8)), (b, mode, param)
+            # the list, of which every wavefront of the scoring kernel holds a copy, is what the rest of the step goes by
+            o, lse = np.full((3 * B, Hq, d), 7.0), np.full((3 * B, Hq), 7.0)
+            orc.losa_step(cache, 1, None, None, to_host(q), mode, param, 2, B, Hq, o, lse, forced_active=want)
+            active = np.concatenate([b * B + want[b] for b in range(3)])
+            stable = np.setdiff1d(np.arange(3 * B), active)
+            got_o, got_l = o_p.cpu().numpy(), lse_p.cpu().numpy()
+            assert np.all(got_o[stable] == 7.0) and np.all(got_l[stable] == 7.0), (mode, param)
+            assert np.all(np.abs(got_o[active] - o[active]) <= 2e-2) and np.all(np.abs(got_l[active] - lse[active]) <= 2e-2), (mode, param)
     finally:
         ctx.close()
 
@@ -271,8 +284,7 @@ def test_scores_that_are_no_number_rank_with_infinity(dtype, B, G):
         assert all(np.isnan(delta[b, odd[b][:-1]]).all() and np.isposinf(delta[b, odd[b][-1]]) for b in range(3))
         for mode, param in ((orc.SEL_TOPK, 1.0), (orc.SEL_TOPK, float(n)), (orc.SEL_FRACTION, n / B), (orc.SEL_TOPK, float(B)),
                             (orc.SEL_THRESHOLD, 1e-3), (orc.SEL_MASS, 0.5)):
-            score = delta if mode == orc.SEL_THRESHOLD else np.where(np.isnan(delta), np.inf, delta)
-            want = [orc.active_set(score[b], mode, param) for b in range(3)]
+            want = [orc.active_set(delta[b], mode, param) for b in range(3)]
             before_o, before_l = blk.o_p.clone(), blk.lse_p.clone()
             L.losa_step(r.ctx, r.layer.kv, 1, blk.h[1], blk.h[0], blk.q[1], mode, param, w.topk_pages, blk.o_p, blk.lse_p, blk.mask,
                         blk.sel_count)
@@ -337,6 +349,99 @@ def test_selection_at_the_edges_of_its_digits_buckets_and_threads(P):
                 L.losa_score_pages_shared(ctx, kv, q, active, torch.ones_like(count), K, sel, cnt, P)   # row 0 alone
                 torch.cuda.synchronize()
                 assert int(cnt.item()) == K and np.array_equal(sel.cpu().numpy().reshape(-1)[:K], want[0]), (kind, K, "shared")
+    finally:
+        ctx.close()
+
+
+def rows_of_every_kind(rng, P, bf16):
+    """Page values of rows that a selection treats in different ways: one histogram, several, every digit, ties cut, one value."""
+    base, step, shift = (0x4040, 1, 16) if bf16 else (0x40400000, 3, 0)      # 3.0
+    spread = 100 if bf16 else step * P                                      # neighbouring numbers of the type
+    ladder = ((base + rng.integers(0, spread, P)) << shift).astype(np.uint32).view(np.float32)
+    rows = [(40 + 10 * rng.standard_normal(P)), np.full(P, -1.5), ladder, rng.integers(-2, 3, P),
+            np.where(rng.random(P) < 0.3, 7 + 1e-4 * rng.random(P), 50 * rng.standard_normal(P)),
+            rng.choice([-1.0, 1.0], P) * 10.0 ** rng.uniform(-30, 30, P), rng.standard_normal(P)]
+    return [torch.from_numpy(x.astype(np.float32)).to(torch.bfloat16 if bf16 else torch.float32).float().numpy() for x in rows]
+
+
+@pytest.mark.parametrize("P", [65, 2047, 2048, 2049, 4097, 8193, 16384])
+def test_selection_of_several_rows_per_workgroup_with_the_list(P):
+    """Rows of different kinds come one after the other in a workgroup, whose LDS state the next row starts from: up to eight
+    rows each (61 rows: eight workgroups, the last ones with one row less).  A row reads its kind's channel."""
+    rng, d, B, g, dev = np.random.Generator(np.random.Philox(P)), 64, 61, 16, "cuda:0"
+    kinds = rows_of_every_kind(rng, P, bf16=False)
+    kind_of = [(r // 8 + r) % len(kinds) for r in range(B)]       # changes along a workgroup's rows r, r + 8, r + 16, ...
+    sign = np.where(np.arange(B) % 3 == 2, -1.0, 1.0).astype(np.float32)
+    page_ids = torch.from_numpy(rng.permutation(P).astype(np.int32)).to(dev)
+    meta, one_page = torch.zeros((P, 1, 2, d), device=dev), torch.zeros((1, 1, g, d), device=dev)
+    for c, value in enumerate(kinds):
+        meta[page_ids.long(), 0, :, c] = torch.from_numpy(value).to(dev)[:, None]
+    q = torch.zeros((B, 1, d), device=dev)
+    q[torch.arange(B), 0, torch.tensor(kind_of)] = torch.from_numpy(sign).to(dev)
+    kv = L.PagedKV(one_page.expand(P, 1, g, d), one_page.reshape(1, 1, d, g).expand(P, 1, d, g), meta,
+                   torch.tensor([0, P], dtype=torch.int32, device=dev), page_ids,
+                   torch.tensor([P * g - 3], dtype=torch.int32, device=dev), max_seq_pages=P)
+    ctx = L.losa_create(L.make_config(max_batch=1, num_q_heads=1, num_kv_heads=1, head_dim=d, hidden_size=d, page_size=g,
+                                      block_size=B, max_pages_per_seq=P, max_topk_pages=P, dtype=L.LOSA_F32), dev)
+    active, count = torch.arange(B, dtype=torch.int32, device=dev), torch.zeros(1, dtype=torch.int32, device=dev)
+    sel, cnt = torch.zeros((1, 1, P), dtype=torch.int32, device=dev), torch.zeros((1, 1), dtype=torch.int32, device=dev)
+    try:
+        for rnd, n in ((1, B), (1, 9), (B // 2, B)):              # (the last: three rows each)
+            L.losa_set_tuning(ctx, L.LOSA_TUNE_SELECT_ROUND, rnd)
+            count.fill_(n)
+            for K in sorted({1, max(1, P // 16), P // 2, P - 1, P}):
+                tk = torch.full((1, B, 1, K), -7, dtype=torch.int32, device=dev)
+                L.losa_score_pages(ctx, kv, q, active, count, K, tk, sel, cnt, P)
+                torch.cuda.synchronize()
+                want = [np.sort(np.argsort(-(sign[r] * kinds[kind_of[r]]), kind="stable")[:K]) for r in range(n)]
+                got = tk.cpu().numpy().reshape(B, K)
+                for r in range(n):
+                    assert np.array_equal(got[r], want[r]), (rnd, n, K, r, kind_of[r])
+                union = np.unique(np.concatenate(want))
+                assert int(cnt.item()) == len(union) and np.array_equal(sel.cpu().numpy().reshape(-1)[:len(union)], union), (rnd, n, K)
+    finally:
+        ctx.close()
+
+
+@pytest.mark.parametrize("P,B,G", [(65, 17, 1), (2048, 17, 1), (2049, 17, 1), (4097, 61, 1), (16384, 17, 1),
+                                   (65, 61, 3), (2048, 61, 3), (4097, 61, 3), (8193, 61, 3)])
+def test_selection_of_several_rows_per_workgroup_with_the_bitmap(P, B, G):
+    """The same in losa_step, whose selection leaves a bitmap: up to four rows a workgroup, counts known to the host and to
+    the device only.  All keys are zero, so that every token of the union has the same weight, and a page's values are its
+    own signs in 64 channels: the sums, whole numbers, tell which pages the union holds."""
+    rng, d, g, dev = np.random.Generator(np.random.Philox(P + B)), 64, 16, "cuda:0"
+    kinds = rows_of_every_kind(rng, P, bf16=True)
+    page_ids = rng.permutation(P).astype(np.int32)
+    signs = rng.choice([-1.0, 1.0], (P, d)).astype(np.float32)              # by logical page
+    meta, v_pages = torch.zeros((P, 1, 2, d)), torch.zeros((P, 1, d, g))
+    for c, value in enumerate(kinds):
+        meta[page_ids, 0, :, c] = torch.from_numpy(value)[:, None]
+    v_pages[page_ids, 0] = torch.from_numpy(signs)[:, :, None]
+    kind_of = (np.arange(B * G) // 4 + np.arange(B * G)) % len(kinds)
+    q = torch.zeros((B * G, d))
+    q[torch.arange(B * G), torch.from_numpy(kind_of)] = 1.0
+    bf = lambda x: x.to(torch.bfloat16).to(dev)
+    kv = L.PagedKV(bf(torch.zeros((P, 1, g, d))), bf(v_pages), bf(meta), torch.tensor([0, P], dtype=torch.int32, device=dev),
+                   torch.from_numpy(page_ids).to(dev), torch.tensor([P * g], dtype=torch.int32, device=dev), max_seq_pages=P)
+    ctx = L.losa_create(L.make_config(max_batch=1, num_q_heads=G, num_kv_heads=1, head_dim=d, hidden_size=G * d, page_size=g,
+                                      block_size=B, max_pages_per_seq=P, max_topk_pages=P), dev)
+    ctx.workspace.fill_(255)
+    h = bf(torch.ones((B, G * d)))
+    o_p, lse_p = torch.zeros((B, G, d), device=dev), torch.zeros((B, G), device=dev)
+    mask, cnt = torch.zeros(B, dtype=torch.uint8, device=dev), torch.zeros((1, 1), dtype=torch.int32, device=dev)
+    try:
+        for rnd in (1, B * G // 2):
+            L.losa_set_tuning(ctx, L.LOSA_TUNE_SELECT_ROUND, rnd)
+            for mode, param, n in ((orc.SEL_TOPK, float(B), B), (orc.SEL_TOPK, 5.0, 5), (orc.SEL_THRESHOLD, 0.5, B)):
+                for K in sorted({1, max(1, P // 64), max(1, P // 8)}):
+                    L.losa_step(ctx, kv, 1, h, torch.zeros_like(h), bf(q).reshape(B, G, d), mode, param, K, o_p, lse_p, mask, cnt)
+                    torch.cuda.synchronize()
+                    union = np.unique(np.concatenate([np.argsort(-kinds[kind_of[r]], kind="stable")[:K] for r in range(n * G)]))
+                    assert int(mask.sum()) == n and int(cnt.item()) == len(union), (rnd, mode, n, K)
+                    total = signs[union].sum(axis=0)
+                    got = o_p.cpu().numpy()[:n].reshape(-1, d).astype(np.float64) * len(union)
+                    assert np.abs(got - total).max() <= 0.25, (rnd, mode, n, K)       # a page more, less or another: 1 or 2
+                    assert np.abs(lse_p.cpu().numpy()[:n] - np.log(len(union) * g)).max() <= 1e-4
     finally:
         ctx.close()
 
@@ -512,11 +617,14 @@ def test_listed_pages_that_do_not_exist_count_for_nothing(B, G, d, page, n):
             torch.cuda.synchronize()
             results.append((o_p.cpu().numpy(), lse_p.cpu().numpy()))
         (o0, l0), (o1, l1) = results
+        orc.losa_step(r.cache, 1, None, None, r.inp.q[1], 0, 0, 0, B, w.Hq, r.o_ref, r.L_ref,
+                      forced_active=[active[b, :n].cpu().numpy() for b in range(3)], forced_union={(b, 0): valid[b] for b in range(3)})
         for b in range(3):
             rows = b * B + active[b, :n].cpu().numpy()
             if b == 2:
                 assert np.all(o0[rows] == 0) and np.all(o1[rows] == 0) and np.all(l0[rows] == -np.inf) and np.all(l1[rows] == -np.inf)
             else:   # other shares, other order of the sums: half the parity tolerance
+                assert np.abs(o0[rows] - r.o_ref[rows]).max() <= 2e-2 and np.abs(l0[rows] - r.L_ref[rows]).max() <= 2e-2
                 assert np.abs(o0[rows] - o1[rows]).max() <= 1e-2 and np.abs(l0[rows] - l1[rows]).max() <= 1e-2
         untouched = np.setdiff1d(np.arange(3 * B), np.concatenate([b * B + active[b, :n].cpu().numpy() for b in range(3)]))
         assert np.all(o1[untouched] == 3.0) and np.all(l1[untouched] == 3.0)
