@@ -242,7 +242,8 @@ losa_status losa_block_merge(losa_ctx* ctx, void* stream, int32_t batch, const v
  *   LOSA_TUNE_ATTN_WORKGROUPS   : attention workgroups aimed at per launch (default 256: one per
  *                                 compute unit); 1..1024
  *   LOSA_TUNE_SELECT_ROUND      : selection workgroups counted as one round of the machine; a grid
- *                                 beyond it gives each workgroup up to eight query rows (0: default)
+ *                                 beyond it gives each workgroup up to four query rows, eight where the
+ *                                 union list is built (0: default)
  *   LOSA_TUNE_SCORE_ROUND       : the same for the scoring kernel (64-page tiles per workgroup); >= 1
  *   LOSA_TUNE_RANK_IN_SCORES    : 1 (default): inside losa_step the scoring kernel ranks the locality
  *                                 scores itself; 0: the locality kernel does, as in losa_select_active

@@ -84,7 +84,7 @@ struct losa_ctx {
   long select_round;        // selection workgroups per round (0: from the kernel's occupancy)
   long score_round;         // scoring workgroups the machine takes in one round
   bool rank_in_scores;      // losa_step lets the scoring kernel rank the locality scores
-  bool union_in_attention;  // sparse steps of up to 64 rows: the attention kernel builds the union
+  bool union_in_attention;  // sparse steps: the attention kernel builds the union (above 64 rows only with shared_tiles)
   bool shared_tiles;        // more than 64 rows: 8 wavefronts share each tile through LDS (else 4 independent ones)
   bool half_values;         // ... and their value product runs in half precision (else P as a bfloat16 pair)
   uint16_t* q_act;          // gathered query rows and ...

@@ -40,11 +40,12 @@ struct ScoreAux {
 };
 
 // In-kernel locality pruning (paper: Methodology, Locality Pruning): when `delta` is given,
-// every scoring workgroup ranks the block's locality scores itself (B <= kRankTokens, one
-// thread per token, ranking by counting as in the stand-alone kernel) instead of reading an
+// every scoring workgroup ranks the block's locality scores itself (B <= kRankTokens, ranking by
+// counting as in the stand-alone kernel) instead of reading an
 // active list some earlier launch produced, and the first workgroup of each sequence writes
 // mask / list / count out for the kernels that follow.  This replaces the hand-over at the end
-// of the locality kernel (store, wait, ticket, reload, rank) by B compares per thread here.
+// of the locality kernel (store, wait, ticket, reload, rank) by compares here: a quarter of the block per lane and
+// wavefront for blocks of up to 64 tokens, the whole block per thread beyond.
 constexpr int kRankTokens = 256;
 constexpr int kMaxTilesPerWg = 4;   // 64-page tiles one scoring workgroup may take
 struct RankArgs {
@@ -187,7 +188,7 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape 
   const bool first = bx == 0;                             // this workgroup leaves what belongs to the head
   const bool writes_active = ranked && first && j == 0;   // ... and this one publishes the active set
   auto tile_page = [&](int t) { return max(0, min((bx + t) * 64 + wave * 16 + l16, P - 1)); };
-  auto tile_phys = [&](int t) {   // page whose metadata rows lane l16 feeds for tile t of this workgroup (clamped: always valid)
+  auto tile_phys = [&](int t) {   // page whose metadata rows lane l16 feeds for tile t of this workgroup; -1: outside the pool
     const int ph = P > 0 ? kv.page_indices[base + tile_page(t)] : 0;
     return (unsigned)ph < (unsigned)kv.num_pages ? ph : -1;
   };
@@ -438,7 +439,7 @@ struct SelectOut {
   int cap;
   uint32_t* rowmaps;    // workspace [heads, rows_max, words]: pick bitmap of every query row
   int32_t* tickets;     // workspace [heads], zero on entry (zeroed by the scoring kernel), zero on exit
-  bool rows_known;      // the grid has exactly one workgroup per existing row
+  bool rows_known;      // every row of the grid exists (all workgroups have rows to select for)
   // union_words() | words of a copy << 16 and (copies - 1) | row shift << 8; beside the pointer, so that they arrive with
   // it: fetched where they are used, they cost a scalar round trip (0.3 us)
   uint32_t union_shape, union_rows;
@@ -617,8 +618,8 @@ __global__ __launch_bounds__(NT) void select_pages_kernel(KvView kv, Shape sh, c
                                                            const float* __restrict__ scores, int topk, SelectOut out,
                                                            int rpw) {
   // A workgroup selects for up to rpw query rows, one after the other (the next row's
-  // scores travel while the current row is selected).  rpw is 1 unless the grid would not fit
-  // the machine in one round: a second round of workgroups costs more than a second row.
+  // scores travel while the current row is selected).  rpw is 1 until further workgroups cost more than further
+  // rows (launch_select_pages says where).
   // MULTI = false is the one-row form (rpw == 1) without the loop's register cost.
   constexpr int WORDS = NT * E / 32;
   constexpr int TPW = 32 / E;           // threads whose pages share a bitmap word
@@ -1003,7 +1004,9 @@ hipError_t launch_select_pages(hipStream_t st, const KvView& kv, const Shape& sh
   //   bitmaps, count on the device (1 / 2 / 4 / 8): 84 of 256 rows x 32 heads 10.0 / 9.4 / 8.8 / 9.4; 21 of 224 x 64 10.4 / 10.0 /
   //     8.1 / 7.5; 35 of 224 x 8 5.0 / 4.9 / 5.1 / 7.1; 56 of 448 x 4, 8192 pages 8.7 / 7.9 / 7.0 / 6.9.  At most four: rows may all exist.
   //   union list, whose workgroups draw tickets (1 / 2 / 4 / 8): 84 of 256 x 32 35.4 / 35.8 / 27.0 / 18.7; 70 of 224 x 64 43.1 / 43.8 /
-  //     36.1 / 22.7; 14 of 224 x 64 14.2 / 12.3 / 11.7 / 11.3; 35 of 224 x 8 9.6 / 9.9 / 10.0 / 10.0
+  //     36.1 / 22.7; 14 of 224 x 64 14.2 / 12.3 / 11.7 / 11.3; 35 of 224 x 8 9.6 / 9.9 / 10.0 / 10.0.  Every row there, scoring
+  //     included: 224 x 64 196 / 130 / 105 / 103; 256 x 32 125 / 83 / 66 / 62; 224 x 16 66 / 49 / 41 / 44; 256 x 8 44.8 / 35.0 / 33.4 / 39.4;
+  //     224 x 4 28.9 / 26.3 / 28.3 / 36.4; 64 x 32 of 4096 pages 51.7 / 46.0 / 42.5 / 47.7; 224 x 8 of 8192 75 / 69 / 65 / 62
   const long wgs = (long)rows * sh.Hkv * batch;
   const int threads = pages <= 256 * 8 ? 256 : pages <= 512 * 8 ? 512 : 1024;
   const long round = (list ? 1024L : out.rows_known ? 5120L : 2048L) * 256 / threads;

@@ -154,7 +154,7 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
     // compute unit four times the traffic): a quarter each, one barrier.
     const bool copies = uni.copy_words <= kMostCopiedWords;
     const int words = copies ? kUnionSpread : uni.copy_words;
-    // the head's page table, written by the selection kernel at an address known here: its first
+    // the head's page table, written by the scoring kernel at an address known here: its first
     // kTablePagesInLds entries go to LDS, so that resolving a page needs no dependent load
     // (pages beyond them are looked up in memory)
     constexpr int TPW = kTablePagesInLds / 4 / 256;   // 16-byte pieces per lane per wavefront

@@ -75,6 +75,10 @@ __device__ __forceinline__ uint32_t bf16_pair_to_half(uint32_t two_bf16) {
   return __builtin_bit_cast(uint32_t, h);
 }
 
+// Where a workgroup's pages come from: the whole page table (the dense step), a list of logical pages, or the head's
+// union bitmap, out of which it has made its own list.
+enum class PageSource { all, list, own };
+
 // HALF: the value product runs in half precision.  Values are converted bfloat16 -> half while they are
 // staged (exact for 2^-14 <= |v| <= 65504, truncated towards zero below that range and held at +-65504
 // above it), the numerators enter as ONE half-precision operand (11 significant bits, round to nearest).
@@ -87,10 +91,6 @@ __device__ __forceinline__ uint32_t bf16_pair_to_half(uint32_t two_bf16) {
 //
 // TG token groups: with up to 128 rows four wavefronts hold all of them, and the other four take the
 // second 32-token block of every stage instead of idling; the two halves meet through LDS at the end.
-// Where a workgroup's pages come from: the whole page table (the dense step), a list of logical pages, or the head's
-// union bitmap, out of which it has made its own list.
-enum class PageSource { all, list, own };
-
 template <int D, int GP, bool HALF, int TG, PageSource SRC>
 __device__ __forceinline__ void attn_rows_body(int nchunk, int row_group, int j, const Shape& sh,
                                                const KvView& kv, const Partials& part, float scale_log2e, int M, int U, int P,

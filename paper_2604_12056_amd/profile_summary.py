@@ -25,6 +25,7 @@ import sys
 
 
 def _short(name: str) -> str:
+    name = re.sub(r"\([\w:]+\)(?=\d)", "", name)   # an enumerator as a template argument: (Type)1
     name = re.sub(r"\(.*", "", name)
     return name.replace("void ", "").strip()
 

@@ -55,3 +55,19 @@ def test_counters_reports_means_and_busy_fractions(tmp_path):
     assert float(lines["matrix-core busy / duration"]) == 0.4
     assert float(lines["vector-ALU issue busy / duration"]) == 0.6
     assert "launches 2" in r.stdout
+
+
+def test_trace_keeps_forms_apart_that_differ_in_an_enumerator(tmp_path):
+    """A template argument of an enumerated type is printed in parentheses, which do not end the kernel's name."""
+    with open(tmp_path / "x_kernel_trace.csv", "w", newline="") as f:
+        w = csv.DictWriter(f, fieldnames=["Kernel_Name", "Start_Timestamp", "End_Timestamp"])
+        w.writeheader()
+        for source, us in ((0, 7), (2, 5), (2, 3)):
+            w.writerow({"Kernel_Name": f"void losa::attn_rows_kernel<128, 16, true, (losa::PageSource){source}>(losa::AttnInputs, int)",
+                        "Start_Timestamp": 1000, "End_Timestamp": 1000 + 1000 * us})
+    r = subprocess.run([sys.executable, "-m", "paper_2604_12056_amd.profile_summary", "trace", str(tmp_path)], capture_output=True,
+                       text=True, cwd=ROOT)
+    assert r.returncode == 0, r.stderr
+    rows = {l[:78].strip(): l[78:].split() for l in r.stdout.splitlines()[1:]}
+    assert rows["losa::attn_rows_kernel<128, 16, true, 0>"][:2] == ["1", "7.00"]
+    assert rows["losa::attn_rows_kernel<128, 16, true, 2>"][:2] == ["2", "4.00"]
