@@ -324,7 +324,12 @@ losa_status select_active_impl(losa_ctx* ctx, hipStream_t st, int batch, const v
   if (!ctx->seq_tickets_clean) {   // first use: the ticket counters must start at zero; the kernel leaves them so
     e = launch_zero_ints(st, ctx->seq_tickets, ctx->cfg.max_batch);
     if (e != hipSuccess) return hip_fail(ctx, "ticket clear launch", e);
-    ctx->seq_tickets_clean = true;
+    // (a fill that is only recorded into a graph has cleared nothing for the calls made before the graph's first replay)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capture) == hipSuccess)
+      ctx->seq_tickets_clean = capture == hipStreamCaptureStatusNone;
+    else
+      (void)hipGetLastError();   // not to be found by the next launch's check
   }
   e = launch_locality_select(st, ctx->cfg.dtype, h_cur, h_prev, batch, B, ctx->sh.H, mode, n, tau, delta, mask,
                              active_idx, active_count, ctx->seq_tickets);

@@ -100,3 +100,39 @@ def test_graph_replay_c1_full_size():
 def test_graph_replay_float_mode():
     w = synth.config(0, dtype="f32").replace(T=3, name="C0-f32")
     _replay_and_compare(w, orc.SEL_TOPK, float(w.n_active))
+
+
+def test_first_call_of_a_context_recorded_into_a_graph():
+    """The ranking's ticket counters are cleared by a context's first call.  Recorded into a graph that has not been replayed yet,
+    that call has cleared nothing: an eager call before the first replay, and replays around more eager calls, give the
+    same active sets.  (Another context has loaded the kernels, which does not belong into a capture.)"""
+    w = SMALL
+    rig = Rig(w)
+    fresh = Rig(w)
+    fresh.ctx.workspace.fill_(255)
+
+    def select(r, n):
+        L.losa_select_active(r.ctx, r.blk.h[1], r.blk.h[0], orc.SEL_TOPK, float(n), r.blk.delta, r.blk.mask, r.blk.active_idx,
+                             r.blk.active_count)
+
+    def outputs(r):
+        torch.cuda.synchronize()
+        return [x.cpu().numpy().copy() for x in (r.blk.delta, r.blk.mask, r.blk.active_idx, r.blk.active_count)]
+
+    try:
+        want = {}
+        for n in (4, 6):
+            select(rig, n)
+            want[n] = outputs(rig)
+            assert want[n][3].tolist() == [n] * w.batch
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            select(fresh, 6)
+        for call, n in ((lambda: select(fresh, 4), 4), (g.replay, 6), (g.replay, 6), (lambda: select(fresh, 4), 4), (g.replay, 6)):
+            for x in (fresh.blk.delta, fresh.blk.mask, fresh.blk.active_idx, fresh.blk.active_count):
+                x.fill_(7)
+            call()
+            assert all(np.array_equal(a, b) for a, b in zip(outputs(fresh), want[n]))
+    finally:
+        rig.close()
+        fresh.close()
