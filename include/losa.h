@@ -243,7 +243,8 @@ losa_status losa_block_merge(losa_ctx* ctx, void* stream, int32_t batch, const v
  *                                 compute unit); 1..1024
  *   LOSA_TUNE_SELECT_ROUND      : selection workgroups counted as one round of the machine; a grid
  *                                 beyond it gives each workgroup up to four query rows, eight where the
- *                                 union list is built (0: default)
+ *                                 union list is built (0: default).  While it is set, short prefixes are
+ *                                 scored and selected in two launches too, not in one
  *   LOSA_TUNE_SCORE_ROUND       : the same for the scoring kernel (64-page tiles per workgroup); >= 1
  *   LOSA_TUNE_RANK_IN_SCORES    : 1 (default): inside losa_step the scoring kernel ranks the locality
  *                                 scores itself; 0: the locality kernel does, as in losa_select_active
@@ -274,7 +275,8 @@ losa_status losa_set_tuning(losa_ctx* ctx, losa_tuning knob, int64_t value);
 /* Measurement hooks (the paper's latency breakdown names four components: criticality
  * estimation, locality pruning, cache management, attention computation; cache management
  * costs nothing here because reuse is "do not write").  While enabled, every launch made
- * through this context is bracketed by HIP events on its stream.
+ * through this context is bracketed by HIP events on its stream, and every stage has a launch of
+ * its own (where short prefixes are otherwise scored and selected in one, with the same results).
  *   losa_profile_enable : enable != 0 creates the events (host objects), 0 releases them.
  *   losa_profile_read   : waits for the recorded events, adds up the elapsed milliseconds and
  *                         the launch count per stage into the two host arrays of

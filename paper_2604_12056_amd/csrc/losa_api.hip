@@ -716,17 +716,8 @@ losa_status losa_step(losa_ctx* ctx, void* stream, const losa_kv* kv, int32_t st
   // of the step's chain of dependent launches.
   InKernelRanking ranking{ctx->delta, (int)mode, 0, 0.f, mk, ctx->active_idx, ctx->active_count};
   const bool rank_in_scores = ctx->rank_in_scores && ctx->cfg.dtype == LOSA_BF16 && ctx->sh.B <= 256;
-  if (rank_in_scores) {
-    s = parse_select(ctx, (int)mode, param, &ranking.n, &ranking.tau);
-    if (s != LOSA_OK) return s;
-    StageTimer timer(ctx, st, LOSA_STAGE_LOCALITY);
-    hipError_t e = launch_locality_delta(st, ctx->cfg.dtype, h_cur, h_prev, kv->batch, ctx->sh.B, ctx->sh.H, ctx->delta);
-    if (e != hipSuccess) return hip_fail(ctx, "locality_delta launch", e);
-  } else {
-    s = select_active_impl(ctx, st, kv->batch, h_cur, h_prev, (int)mode, param, ctx->delta, mk, ctx->active_idx,
-                           ctx->active_count);
-    if (s != LOSA_OK) return s;
-  }
+  s = parse_select(ctx, (int)mode, param, &ranking.n, &ranking.tau);
+  if (s != LOSA_OK) return s;
   const int cap = ctx->sh.max_pages;
   const bool bf16 = ctx->cfg.dtype == LOSA_BF16;
   // the host knows |A| in the top-n modes, so selection and attention can be shaped for n*G rows
@@ -740,9 +731,31 @@ losa_status losa_step(losa_ctx* ctx, void* stream, const losa_kv* kv, int32_t st
   const int union_upper = counted ? rows_upper : ctx->sh.rows_max;
   const UnionInKernel uni{ctx->union_bits, ctx->entries, ctx->q_act, sc, union_words(ctx->sh.max_pages, ctx->sh.rows_max),
                           union_copy_words(msp), union_copies(union_copy_words(msp), union_upper)};
-  s = score_pages_impl(ctx, st, view, kv->batch, msp, q, ctx->active_idx, ctx->active_count, topk_pages, nullptr,
-                       ctx->sel_pages, sc, cap, rows_upper, rank_in_scores ? &ranking : nullptr,
-                       union_in_attn ? ctx->union_bits : nullptr);
+  // Short prefixes: scoring and selection in one launch.  (Not while stages are timed, which takes a launch for each, nor where
+  // the caller shapes the selection's grid.)
+  const bool picked = rank_in_scores && union_in_attn && !ctx->profiling && ctx->select_round == 0 &&
+                      pick_pages_serves(ctx->sh, kv->batch, msp, union_upper, counted);
+  if (rank_in_scores) {
+    const bool takes_hidden = picked && pick_takes_hidden(ctx->sh);
+    if (!takes_hidden) {
+      StageTimer timer(ctx, st, LOSA_STAGE_LOCALITY);
+      hipError_t e = launch_locality_delta(st, ctx->cfg.dtype, h_cur, h_prev, kv->batch, ctx->sh.B, ctx->sh.H, ctx->delta);
+      if (e != hipSuccess) return hip_fail(ctx, "locality_delta launch", e);
+    }
+    if (picked) {
+      hipError_t e = launch_pick_pages(st, view, ctx->sh, kv->batch, msp, q, takes_hidden ? h_cur : nullptr, takes_hidden ? h_prev : nullptr,
+                                       union_upper, topk_pages, ctx->tickets, sc, ctx->entries, ctx->q_act, ranking, ctx->union_bits);
+      if (e != hipSuccess) return hip_fail(ctx, "pick_pages launch", e);
+    }
+  } else {
+    s = select_active_impl(ctx, st, kv->batch, h_cur, h_prev, (int)mode, param, ctx->delta, mk, ctx->active_idx,
+                           ctx->active_count);
+    if (s != LOSA_OK) return s;
+  }
+  if (!picked)
+    s = score_pages_impl(ctx, st, view, kv->batch, msp, q, ctx->active_idx, ctx->active_count, topk_pages, nullptr,
+                         ctx->sel_pages, sc, cap, rows_upper, rank_in_scores ? &ranking : nullptr,
+                         union_in_attn ? ctx->union_bits : nullptr);
   if (s != LOSA_OK) return s;
   return sparse_attn_impl(ctx, st, view, kv->batch, msp, q, ctx->active_idx, ctx->active_count, ctx->sel_pages, sc,
                           cap, rows_upper, (float*)o_p, lse_p, union_in_attn ? &uni : nullptr);

@@ -150,6 +150,18 @@ hipError_t launch_select_pages(hipStream_t st, const KvView& kv, const Shape& sh
                                int rows_hint, long workgroups_per_round,
                                uint32_t* union_bits = nullptr);
 
+// Scoring and selection of short prefixes in one launch, which also takes the locality scores' place where a hidden state is short.
+// pick_pages_serves: whether it takes a step of `rows` active rows per KV head (rows_known; else up to that many).  It ranks as `ranking` says (delta is read only
+// without h_cur / h_prev) and leaves what the scoring kernel would for the attention, and the union bitmap complete.
+constexpr int kPickPages = 512;      // pages per sequence
+constexpr int kPickRows = 16;        // query rows per workgroup
+constexpr int kPickMostRows = 256;   // ... and per KV head: a copy of the union bitmap for each 16
+bool pick_pages_serves(const Shape& sh, int batch, int max_seq_pages, int rows, bool rows_known);
+inline bool pick_takes_hidden(const Shape& sh) { return sh.H <= 512; }
+hipError_t launch_pick_pages(hipStream_t st, const KvView& kv, const Shape& sh, int batch, int max_seq_pages, const void* q, const void* h_cur,
+                             const void* h_prev, int rows, int topk, int32_t* tickets, int32_t* sel_count, int32_t* entries, uint16_t* q_act,
+                             const InKernelRanking& ranking, uint32_t* union_bits);
+
 // ---- sparse_attn.hip (float mode, merge) and sparse_attn_mfma.hip (bfloat16)
 // Tiles of a (sequence, KV head) page list are dealt round-robin to `nchunk` work items: tiles of 32 tokens
 // (bfloat16), single pages (float mode).  launch_attn_merge: bf16 means bfloat16 partials.

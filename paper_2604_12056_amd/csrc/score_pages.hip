@@ -57,6 +57,52 @@ struct RankArgs {
   int32_t* active_count;
 };
 
+// Active set of a block of up to 64 tokens, a lane per token, by every wavefront of a workgroup of NW: 1 in the lanes of its
+// tokens.  The wavefronts each compare every token with their share of the block, the score compared
+// with held in a scalar register, and meet once, in LDS; from the ranks on every wavefront works for itself: the
+// active set is a lane mask, a token's place in the list the number of lanes below it, and every wavefront keeps its
+// own copy of the list, so that no further barrier is needed.  With a thread per token, the scores in LDS, a scan and
+// four barriers the ranking of 32 tokens took 1.55 of the scoring kernel's 7.1 us (2048 pages, 42 rows, 4 KV heads); that
+// kernel now takes 5.7.
+// ranks: NW * 64 ints of LDS; sorted: 64 floats for this wavefront alone.
+template <int NW>
+__device__ __forceinline__ int rank_small(const RankArgs& ra, int B, float my_delta, int lane, int wave, int* ranks, float* sorted) {
+  const float score = ra.mode == LOSA_SEL_THRESHOLD ? my_delta : ranked_score(my_delta);
+  const float mine = lane < B ? score : -INFINITY;   // the padding never outranks a token
+  int rank = 0;
+  if (ra.mode != LOSA_SEL_THRESHOLD) {
+    const int per = (B + NW - 1) / NW, k0 = wave * per, k1 = min(k0 + per, B);
+    for (int k = k0; k < k1; ++k) {
+      const float dk = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(mine), k));
+      rank += (int)(dk > mine) | ((int)(dk == mine) & (int)(k < lane));   // bitwise on purpose: no branches
+    }
+    ranks[wave * 64 + lane] = rank;
+    __syncthreads();
+    rank = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) rank += ranks[w * 64 + lane];
+  }
+  if (ra.mode != LOSA_SEL_MASS) return (lane < B) & (ra.mode == LOSA_SEL_THRESHOLD ? (int)(mine > ra.tau) : (int)(rank < ra.n));
+  // Cumulative-mass rule, as in the stand-alone kernel: the scores in descending order are summed in that order in
+  // float, here by all lanes at once: lane r adds the scores of ranks 0..r and zeros after them.  A token is in A if
+  // the sum before it stays below tau * total (and total and tau are positive).
+  if (lane < B) sorted[rank] = mine;
+  wave_lds_fence();
+  const float at_rank = sorted[min(lane, B - 1)];
+  float prefix = 0.f;
+  for (int k = 0; k < B; ++k) {
+    const float dk = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(at_rank), k));
+    prefix += k <= lane ? dk : 0.f;
+  }
+  const float total = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(prefix), B - 1));
+  wave_lds_fence();
+  sorted[lane] = prefix;
+  wave_lds_fence();
+  const int act = (lane < B) & (total > 0.f) & (ra.tau > 0.f) & ((rank == 0) | (int)(sorted[max(rank - 1, 0)] < ra.tau * total));
+  wave_lds_fence();
+  return act;
+}
+
 // Float mode.  A workgroup takes 8 pages and all rows of a KV head, a thread one page and two rows at a time,
 // four channels per step out of LDS; the terms of a score are added in channel order.  With 8 pages per
 // workgroup a prefix of a few thousand tokens fills the chip (with 32, a quarter of it); the two rows
@@ -215,49 +261,9 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape 
   int M;
   int list_at = 0;   // where this wavefront's copy of the active list starts in act_list
   if (ranked && small) {
-    // A lane per token.  The four wavefronts each compare every token with a quarter of the block, the score compared
-    // with held in a scalar register, and meet once, in LDS; from the ranks on every wavefront works for itself: the
-    // active set is a lane mask, a token's place in the list the number of lanes below it, and every wavefront keeps its
-    // own copy of the list, so that no further barrier is needed.  With a thread per token, the scores in LDS, a scan and
-    // four barriers the ranking of 32 tokens took 1.55 of the kernel's 7.1 us (2048 pages, 42 rows, 4 KV heads); the
-    // kernel now takes 5.7.
     const int B = sh.B;
-    const float score = ra.mode == LOSA_SEL_THRESHOLD ? my_delta : ranked_score(my_delta);
-    const float mine = lane < B ? score : -INFINITY;   // the padding never outranks a token
-    int act = 0, rank = 0;
-    if (ra.mode != LOSA_SEL_THRESHOLD) {
-      const int per = (B + 3) >> 2, k0 = wave * per, k1 = min(k0 + per, B);
-      for (int k = k0; k < k1; ++k) {
-        const float dk = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(mine), k));
-        rank += (int)(dk > mine) | ((int)(dk == mine) & (int)(k < lane));   // bitwise on purpose: no branches
-      }
-      int* ranks = reinterpret_cast<int*>(sdelta);
-      ranks[wave * 64 + lane] = rank;
-      __syncthreads();
-      rank = (ranks[lane] + ranks[64 + lane]) + (ranks[128 + lane] + ranks[192 + lane]);
-    }
-    if (ra.mode == LOSA_SEL_MASS) {
-      // Cumulative-mass rule, as in the stand-alone kernel: the scores in descending order are summed in that order in
-      // float, here by all lanes at once: lane r adds the scores of ranks 0..r and zeros after them.  A token is in A if
-      // the sum before it stays below tau * total (and total and tau are positive).
-      float* sorted = reinterpret_cast<float*>(act_list) + wave * 64;   // (free until the list is written)
-      if (lane < B) sorted[rank] = mine;
-      wave_lds_fence();
-      const float at_rank = sorted[min(lane, B - 1)];
-      float prefix = 0.f;
-      for (int k = 0; k < B; ++k) {
-        const float dk = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(at_rank), k));
-        prefix += k <= lane ? dk : 0.f;
-      }
-      const float total = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(prefix), B - 1));
-      wave_lds_fence();
-      sorted[lane] = prefix;
-      wave_lds_fence();
-      act = (lane < B) & (total > 0.f) & (ra.tau > 0.f) & ((rank == 0) | (int)(sorted[max(rank - 1, 0)] < ra.tau * total));
-      wave_lds_fence();
-    } else {
-      act = (lane < B) & (ra.mode == LOSA_SEL_THRESHOLD ? (int)(mine > ra.tau) : (int)(rank < ra.n));
-    }
+    const int act = rank_small<4>(ra, B, my_delta, lane, wave, reinterpret_cast<int*>(sdelta),
+                                  reinterpret_cast<float*>(act_list) + wave * 64);   // (free until the list is written)
     const unsigned long long set = __ballot(act);
     const int n_act = __popcll(set);
     const int pos = __builtin_amdgcn_mbcnt_hi((unsigned)(set >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)set, 0));
@@ -928,6 +934,211 @@ __global__ __launch_bounds__(NT) void shared_select_kernel(KvView kv, Shape sh, 
   if (tid == 0) sel_count[head] = min(total, cap);
 }
 
+// Scoring and selection in one launch, for prefixes of up to kPickPages pages.  A workgroup of 16 wavefronts takes 16 query
+// rows of a KV head and every page of the sequence: it ranks the locality scores (as the scoring kernel does), scores
+// all pages for its rows on the matrix cores, a wavefront per 16 pages, leaves the scores in LDS and selects a row per
+// wavefront out of them.  No score matrix in memory, one launch less, and no atomics: the rows' union is put
+// together in LDS and stored as the copy of the head's bitmap that belongs to the 16 rows.
+// A step of 42 rows x 4 heads over 128 pages 24.2 -> 22.1 us, of 128 rows x 128 heads 98 -> 78, with the locality scores (8 rows x 1 head,
+// 64 channels) 18.3 -> 16.3; where the line to the separate launches lies stands at pick_pages_serves.
+// What bounds it: the dependent round trips (locality scores; query rows beside page ids and metadata rows) and, as pages
+// grow, one compute unit taking all of a head's metadata (256 KiB at 512 pages and 128 channels), which is why longer
+// prefixes keep the two launches.
+// A row is selected by one wavefront without LDS: page 64*i + lane is key i of a lane; the K-th key is found bit by bit
+// from the highest in which the row's keys differ from its smallest, the count of keys that reach the candidate coming from scalar
+// population counts of the compares, until exactly K keys do (some 12 of up to 32 steps); the compares' lane masks then are the
+// row's bitmap as it stands.
+// The locality scores too, for hidden states of up to 64 16-byte pieces (`hid` given): a wavefront per token, sums in the order
+// of the locality kernel's, whose three other wavefronts have nothing then.
+struct PickHidden {
+  const bf16_t* cur;    // [batch*B, H], NULL: the locality scores are given
+  const bf16_t* prev;
+};
+template <int D, int TPW>   // TPW: 16-page tiles per wavefront
+__global__ __launch_bounds__(1024) void pick_pages_kernel(KvView kv, Shape sh, const bf16_t* __restrict__ q, ScoreAux aux,
+                                                          RankArgs ra, PickHidden hid, int topk) {
+  constexpr int NW = 16, KS = D / 32, VPR = D / 8, STRIDE = D * 2 + 16;
+  constexpr int NP = NW * 16 * TPW, ROW = NP + 4;   // pages; floats per row of scores in LDS (the writes of 16 rows spread over the banks)
+  constexpr int E = NP / 64, COPY = 16;             // keys per lane; words of a copy of the union bitmap
+  static_assert(NP / 32 <= COPY && kUnionSpread / COPY * kPickRows == kPickMostRows, "a copy of the bitmap holds a row's, and there is one for every 16 rows");
+  __shared__ __attribute__((aligned(16))) float sc[kPickRows * ROW];
+  __shared__ __attribute__((aligned(16))) unsigned char qs[2][kPickRows * STRIDE];   // [0]: q+, [1]: q-
+  __shared__ int ranks[NW * 64], act_list[NW * 64];
+  __shared__ float sdelta[64];
+  __shared__ uint32_t uw[COPY];
+  const int rt = blockIdx.x, j = blockIdx.y, b = blockIdx.z, head = b * sh.Hkv + j, r0 = rt * kPickRows;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, qd = lane >> 4;
+  const int B = sh.B;   // <= 64 (checked by the launcher)
+  float my_delta = 0.f;
+  uint4 hx[4], hy[4];
+  const int nvec = sh.H / 8;
+  if (hid.cur) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const size_t at = ((size_t)b * B + min(wave + NW * k, B - 1)) * nvec + min(lane, nvec - 1);
+      hx[k] = reinterpret_cast<const uint4*>(hid.cur)[at];
+      hy[k] = reinterpret_cast<const uint4*>(hid.prev)[at];
+    }
+  } else {
+    my_delta = ra.delta[(size_t)b * B + min(lane, B - 1)];
+  }
+  const int base = kv.page_indptr[b], P = min(seq_pages(kv, sh, b), NP), tokens = kv.seq_lens[b];
+  int phys[TPW];
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) {   // the page whose metadata rows lane l16 feeds; -1: outside the pool
+    const int ph = P > 0 ? kv.page_indices[base + max(0, min((wave + NW * t) * 16 + l16, P - 1))] : 0;
+    phys[t] = (unsigned)ph < (unsigned)kv.num_pages ? ph : -1;
+  }
+  bf16x8_t amin[TPW][KS], amax[TPW][KS];
+#pragma unroll
+  for (int t = 0; t < TPW; ++t) {
+    if ((wave + NW * t) * 16 >= P) break;   // uniform over the wavefront
+    const bf16_t* mrow = (const bf16_t*)kv.meta + ((size_t)max(phys[t], 0) * sh.Hkv + j) * 2 * D;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      amin[t][ks] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(mrow + ks * 32 + qd * 8));
+      amax[t][ks] = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4*>(mrow + D + ks * 32 + qd * 8));
+    }
+  }
+  if (tid < COPY) uw[tid] = 0u;
+  if (hid.cur) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      float fx[8], fy[8], part = 0.f;
+      widen16(hx[k], fx, bf16_t());
+      widen16(hy[k], fy, bf16_t());
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float df = fx[e] - fy[e];
+        part = fmaf(df, df, part);
+      }
+      const float sum = wave_sum(lane < nvec ? part : 0.f);
+      if (lane == 0 && wave + NW * k < B) sdelta[wave + NW * k] = sum / (float)sh.H;
+    }
+    __syncthreads();
+    my_delta = sdelta[min(lane, B - 1)];
+  }
+
+  // ---- active set; every wavefront holds it as a lane mask and keeps a list of its own
+  int* list = act_list + wave * 64;
+  const int act = rank_small<NW>(ra, B, my_delta, lane, wave, ranks, reinterpret_cast<float*>(list));
+  const unsigned long long set = __ballot(act);
+  const int n_act = __popcll(set), M = n_act * sh.G;
+  const int pos = __builtin_amdgcn_mbcnt_hi((unsigned)(set >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)set, 0));
+  if (act) list[pos] = lane;
+  wave_lds_fence();
+  if (rt == 0 && j == 0 && wave == 0) {
+    if (lane < B) ra.mask[(size_t)b * B + lane] = (uint8_t)act;
+    if (act) ra.active_idx[(size_t)b * B + pos] = lane;
+    if (lane >= n_act && lane < B) ra.active_idx[(size_t)b * B + lane] = -1;
+    if (lane == 0) ra.active_count[b] = n_act;
+  }
+  if (rt == 0 && tid == 0) aux.reset(head, M);
+  const int nrows = min(kPickRows, M - r0);   // (of this workgroup; none: zero copies)
+  const bool table = M <= kUnionRows;         // the attention kernel will want the page table and the rows
+
+  if (nrows > 0 && P > 0) {   // uniform over the workgroup
+    if (tid < kPickRows * VPR) {
+      const int rr = tid / VPR, cv = tid % VPR, r = r0 + min(rr, nrows - 1), a = row_token(sh, r);
+      const uint4 v = reinterpret_cast<const uint4*>(q + (((size_t)b * B + list[a]) * sh.Hq + j * sh.G + (r - a * sh.G)) * D)[cv];
+      typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+      typedef int16_t i16x8_t __attribute__((ext_vector_type(8)));
+      const u32x4_t x = {v.x, v.y, v.z, v.w};
+      const u32x4_t mk = __builtin_bit_cast(u32x4_t, __builtin_bit_cast(i16x8_t, x) >> 15);   // all-ones where the sign bit is set
+      *reinterpret_cast<u32x4_t*>(qs[0] + rr * STRIDE + cv * 16) = x & ~mk;
+      *reinterpret_cast<u32x4_t*>(qs[1] + rr * STRIDE + cv * 16) = x & mk;
+      if (table && rr < nrows) *reinterpret_cast<u32x4_t*>(aux.q_act + ((size_t)head * sh.rows_max + r) * D + cv * 8) = x;
+    }
+    if (rt == 0 && table && qd == 0) {
+#pragma unroll
+      for (int t = 0; t < TPW; ++t) {
+        const int page = (wave + NW * t) * 16 + l16, nv = max(0, min(sh.g, tokens - page * sh.g));
+        if (page < P)
+          aux.entries[(size_t)head * sh.max_pages + page] = phys[t] >= 0 && phys[t] < (1 << kEntryShift) ? (phys[t] | (nv << kEntryShift)) : 0;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < TPW; ++t) {
+      const int p0 = (wave + NW * t) * 16;
+      if (p0 >= P) break;   // uniform over the wavefront
+      f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) {   // (the same products in the same order as the scoring kernel's: the same bits)
+        const uint4 qpos = *reinterpret_cast<const uint4*>(qs[0] + l16 * STRIDE + ks * 64 + qd * 16);
+        const uint4 qneg = *reinterpret_cast<const uint4*>(qs[1] + l16 * STRIDE + ks * 64 + qd * 16);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(amax[t][ks], __builtin_bit_cast(bf16x8_t, qpos), acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(amin[t][ks], __builtin_bit_cast(bf16x8_t, qneg), acc, 0, 0, 0);
+      }
+      *reinterpret_cast<f32x4_t*>(&sc[l16 * ROW + p0 + 4 * qd]) = acc;   // pages p0 + 4*qd .. of row l16
+    }
+    __syncthreads();
+    if (wave < nrows) {
+      uint32_t key[E], lo = 0xFFFFFFFFu, hi = 0u;
+#pragma unroll
+      for (int i = 0; i < E; ++i) {
+        const bool in = 64 * i + lane < P;
+        const uint32_t kx = order_key(sc[wave * ROW + min(64 * i + lane, P - 1)]);   // (a page that exists: no bits of earlier use)
+        key[i] = kx;
+        lo = min(lo, kx);
+        hi = max(hi, in ? kx : 0u);
+      }
+      lo = __builtin_amdgcn_readfirstlane(wave_min_u32(lo));
+      hi = __builtin_amdgcn_readfirstlane(wave_max_u32(hi)) - lo;
+#pragma unroll
+      for (int i = 0; i < E; ++i) key[i] = 64 * i + lane < P ? key[i] - lo : 0u;   // (no candidate is 0: never counted)
+      const int Kp = min(topk, P);
+      uint32_t kth = 0u;
+      int reach = P;   // keys >= kth
+      if (Kp < P && hi) {
+        for (uint32_t bit = 1u << (31 - __clz((int)hi)); bit; bit >>= 1) {
+          const uint32_t cand = kth | bit;
+          int n = 0;
+#pragma unroll
+          for (int i = 0; i < E; ++i) n += __popcll(__ballot(key[i] >= cand));
+          if (n >= Kp) {
+            kth = cand;
+            reach = n;
+            if (n == Kp) break;
+          }
+        }
+      }
+      int need = 0;   // keys equal to the K-th that are picked, the first ones in page order (looked at only if not all are)
+      const bool cut = reach > Kp;
+      if (cut) {
+        int gt = 0;
+#pragma unroll
+        for (int i = 0; i < E; ++i) gt += __popcll(__ballot(key[i] > kth));
+        need = Kp - gt;
+      }
+      uint32_t mine = 0u;   // word `lane` of the row's bitmap
+#pragma unroll
+      for (int i = 0; i < E; ++i) {
+        const bool in = 64 * i + lane < P;
+        unsigned long long pick;
+        if (cut) {
+          const bool eq = in & (key[i] == kth);
+          const unsigned long long eqs = __ballot(eq);
+          const int before = __builtin_amdgcn_mbcnt_hi((unsigned)(eqs >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)eqs, 0));
+          pick = __ballot((in & (key[i] > kth)) | (eq & (before < need)));
+          need -= __popcll(eqs);   // (below zero: nothing further)
+        } else {
+          pick = __ballot(in & (key[i] >= kth));
+        }
+        mine = lane == 2 * i ? (uint32_t)pick : lane == 2 * i + 1 ? (uint32_t)(pick >> 32) : mine;
+      }
+      if (lane < 2 * E && mine) atomicOr(&uw[lane], mine);
+    }
+    __syncthreads();
+  }
+  // copy rt of the head's bitmap, and zeros for those that no workgroup has rows for
+  if (tid < kUnionSpread) {
+    const int copy = tid / COPY, tiles = gridDim.x;
+    if (copy == rt || (copy >= tiles && copy % tiles == rt))
+      aux.union_bits[(size_t)head * aux.union_stride + tid] = copy == rt && nrows > 0 && P > 0 ? uw[tid % COPY] : 0u;
+  }
+}
+
 hipError_t launch_page_scores(hipStream_t st, int dtype, const KvView& kv, const Shape& sh, int batch,
                               int max_seq_pages, const void* q, const int32_t* active_idx,
                               const int32_t* active_count, float* scores, int32_t* tickets, int32_t* sel_count,
@@ -970,6 +1181,41 @@ hipError_t launch_page_scores(hipStream_t st, int dtype, const KvView& kv, const
     (sh.d == 128 ? page_scores_f32_kernel<128> : page_scores_f32_kernel<64>)<<<grid, 256, 0, st>>>(
         kv, sh, (const float*)q, active_idx, active_count, scores, aux);
   }
+  return hipGetLastError();
+}
+
+// Whether one launch scores and selects.  It saves a launch and the score matrix's way through memory (2 us, and more the more
+// rows there are); it costs what a compute unit needs for all of a head's metadata (the separate scoring spreads the
+// pages over the chip), which the number of its workgroups does not change until the chip is full.  Separate launches / this, a step
+// in us, by pages and workgroups (heads x 16-row tiles; 128 channels):
+//   128 pages, 12 24.2 / 22.1; 320 52.5 / 46.4; 1024 98.0 / 78.1    192, 12 24.3 / 23.1
+//   256, 8 21.4 / 21.8; 12 24.6 / 24.6; 36 36.1 / 32.8; 44 35.4 / 35.3; 64 34.1 / 32.3; 96 36.5 / 34.1; 576 85.6 / 79.2; 2048 201 / 168
+//   375, 48 34.5 / 36.7; 96 42.0 / 42.0; 128 71.7 / 69.3; 192 61.8 / 57.6
+//   512, 64 51.7 / 55.2; 96 45.9 / 48.4; 128 50.3 / 51.4; 144 57.8 / 57.8; 192 69.0 / 67.4; 512 96.1 / 90.9
+//   (64 channels) 256, 1 17.1 / 15.0; 16 18.9 / 16.7    512, 2 20.3 / 22.0; 32 23.8 / 24.9
+// Where only the device knows the count, the grid has workgroups for rows that do not exist, each holding a compute unit for a start:
+//   64 pages, 56 23.4 / 21.1    128, 56 24.2 / 23.0; 896 41.6 / 47.1    192, 56 24.6 / 24.7    256, 448 38.5 / 41.5
+bool pick_pages_serves(const Shape& sh, int batch, int max_seq_pages, int rows, bool rows_known) {
+  const int tiles = (rows + kPickRows - 1) / kPickRows;
+  if (sh.B > 64 || max_seq_pages > kPickPages || tiles * kPickRows > kPickMostRows) return false;
+  const long workgroups = (long)tiles * sh.Hkv * batch;
+  if (!rows_known) return max_seq_pages <= 128 && workgroups <= 256;
+  return (long)max_seq_pages * sh.d <= 192 * 128 || workgroups >= (max_seq_pages <= 256 ? 32 : 144);
+}
+
+hipError_t launch_pick_pages(hipStream_t st, const KvView& kv, const Shape& sh, int batch, int max_seq_pages, const void* q, const void* h_cur,
+                             const void* h_prev, int rows, int topk, int32_t* tickets, int32_t* sel_count, int32_t* entries, uint16_t* q_act,
+                             const InKernelRanking& ranking, uint32_t* union_bits) {
+  if (batch <= 0) return hipSuccess;
+  if (sh.B > 64 || max_seq_pages > kPickPages || rows > kPickMostRows || (h_cur && !pick_takes_hidden(sh)))
+    return hipErrorInvalidValue;
+  const ScoreAux aux{tickets, sel_count, entries, q_act, union_bits, union_words(sh.max_pages, sh.rows_max), 0};
+  const RankArgs ra{ranking.delta, ranking.mode, ranking.n, ranking.tau, ranking.mask, ranking.active_idx, ranking.active_count};
+  const PickHidden hid{(const bf16_t*)h_cur, (const bf16_t*)h_prev};
+  const dim3 grid((rows + kPickRows - 1) / kPickRows, sh.Hkv, batch);
+  auto kern = sh.d == 128 ? (max_seq_pages <= 256 ? pick_pages_kernel<128, 1> : pick_pages_kernel<128, 2>)
+                          : (max_seq_pages <= 256 ? pick_pages_kernel<64, 1> : pick_pages_kernel<64, 2>);
+  kern<<<grid, 1024, 0, st>>>(kv, sh, (const bf16_t*)q, aux, ra, hid, topk);
   return hipGetLastError();
 }
 

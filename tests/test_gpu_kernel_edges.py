@@ -651,3 +651,63 @@ def test_merge_of_few_chunks(B, G, d, page, chunks):
         run_steps_end_to_end(r, [5], orc.SEL_MASS, 1.0, w.topk_pages)
     finally:
         r.close()
+
+
+@pytest.mark.parametrize("B,G,H", [(1, 1, 64), (17, 1, 520), (33, 3, 512), (64, 4, 256)])   # up to 256 rows; hidden states taken in the launch up to 512
+@pytest.mark.parametrize("P", [1, 15, 64, 65, 255, 256, 257, 512])
+def test_scoring_and_selection_in_one_launch(P, B, G, H):
+    """Short prefixes: a launch that scores and selects (and scores the tokens, where hidden states are short) against numpy's picks and,
+    bit for bit, against the separate launches.  Rows, values and sums as in the test of the bitmap above; two sequences."""
+    rng, d, g, dev = np.random.Generator(np.random.Philox(P + B)), 64, 16, "cuda:0"
+    lens = [P * g - 5, max(1, P * g // 3)]
+    pages = [(n + g - 1) // g for n in lens]
+    total = sum(pages)
+    kinds = [rows_of_every_kind(rng, p, bf16=True) for p in pages]
+    page_ids = rng.permutation(total).astype(np.int32)
+    signs = rng.choice([-1.0, 1.0], (total, d)).astype(np.float32)              # by logical page, one sequence behind the other
+    meta, v_pages = torch.zeros((total, 1, 2, d)), torch.zeros((total, 1, d, g))
+    for b, first in enumerate((0, pages[0])):
+        for c, value in enumerate(kinds[b]):
+            meta[page_ids[first:first + pages[b]], 0, :, c] = torch.from_numpy(value)[:, None]
+    v_pages[page_ids, 0] = torch.from_numpy(signs)[:, :, None]
+    kind_of = (np.arange(B * G) // 4 + np.arange(B * G)) % len(kinds[0])
+    q = torch.zeros((2, B * G, d))
+    q[:, torch.arange(B * G), torch.from_numpy(kind_of)] = 1.0
+    bf = lambda x: x.to(torch.bfloat16).to(dev)
+    kv = L.PagedKV(bf(torch.zeros((total, 1, g, d))), bf(v_pages), bf(meta), torch.tensor([0, pages[0], total], dtype=torch.int32, device=dev),
+                   torch.from_numpy(page_ids).to(dev), torch.tensor(lens, dtype=torch.int32, device=dev), max_seq_pages=P)
+    ctx = L.losa_create(L.make_config(max_batch=2, num_q_heads=G, num_kv_heads=1, head_dim=d, hidden_size=H, page_size=g,
+                                      block_size=B, max_pages_per_seq=P, max_topk_pages=P), dev)
+    ctx.workspace.fill_(255)
+    h = bf(torch.from_numpy((1.0 + rng.permutation(2 * B).astype(np.float32) / 64)[:, None].repeat(H, 1)))    # Delta = its square: no ties
+    order = np.argsort(-to_host(h.float()).reshape(2, B, H)[:, :, 0], axis=1, kind="stable")
+    out = lambda: (torch.zeros((2 * B, G, d), device=dev), torch.zeros((2 * B, G), device=dev),
+                   torch.zeros(2 * B, dtype=torch.uint8, device=dev), torch.zeros((2, 1), dtype=torch.int32, device=dev))
+    try:
+        for mode, param, n in ((orc.SEL_TOPK, float(B), B), (orc.SEL_TOPK, (B + 2) // 3, (B + 2) // 3), (orc.SEL_THRESHOLD, 0.5, B),
+                               (orc.SEL_THRESHOLD, 1e9, 0), (orc.SEL_MASS, 0.4, None)):
+            for K in sorted({1, max(1, P // 8), max(1, P - 1), P}):
+                got, separate = out(), out()
+                for o, rnd in ((got, 0), (separate, 1 << 30)):
+                    L.losa_set_tuning(ctx, L.LOSA_TUNE_SELECT_ROUND, rnd)
+                    L.losa_step(ctx, kv, 1, h, torch.zeros_like(h), bf(q).reshape(2 * B, G, d), mode, float(param), K, *o)
+                torch.cuda.synchronize()
+                assert all(torch.equal(x, y) for x, y in zip(got, separate)), (mode, n, K)
+                o_p, lse_p, mask, cnt = (x.cpu().numpy() for x in got)
+                for b, first in enumerate((0, pages[0])):
+                    active = np.flatnonzero(mask[b * B:(b + 1) * B])
+                    assert n is None or set(active) == set(order[b, :n]), (mode, n, K)
+                    if not len(active):
+                        assert cnt[b, 0] == 0
+                        continue
+                    rows = np.concatenate([(np.arange(len(active) * G))])     # row r is the r-th of the active tokens' heads
+                    picks = [np.argsort(-kinds[b][kind_of[active[r // G] * G + r % G]], kind="stable")[:K] for r in rows]
+                    union = np.unique(np.concatenate(picks))
+                    assert cnt[b, 0] == len(union), (mode, n, K, b)
+                    last = lens[b] - (pages[b] - 1) * g                          # tokens of the last page
+                    weight = np.where(union == pages[b] - 1, last, g).astype(np.float64)
+                    want = (signs[first + union] * weight[:, None]).sum(axis=0) / weight.sum()
+                    err = np.abs(o_p[b * B + active].reshape(-1, d) - want).max()
+                    assert err * weight.sum() <= 0.25 * min(last, g), (mode, n, K, b)
+    finally:
+        ctx.close()
