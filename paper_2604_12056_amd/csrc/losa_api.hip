@@ -80,7 +80,8 @@ struct losa_ctx {
   int32_t* sel_count;
   Partials part;
   long part_rows;           // capacity of the partial buffers in (work item, row) pairs
-  long target_workgroups;   // attention workgroups aimed at per launch
+  long target_workgroups;   // attention workgroups aimed at per launch ...
+  bool shares_set = false;  // ... by the caller: no rule on the shares' sizes beside it
   long select_round;        // selection workgroups per round (0: from the kernel's occupancy)
   long score_round;         // scoring workgroups the machine takes in one round
   bool rank_in_scores;      // losa_step lets the scoring kernel rank the locality scores
@@ -101,6 +102,7 @@ namespace {
 
 constexpr long kTargetItems = 1024;       // most split-K work items a sparse step may be given
 constexpr long kTargetWorkgroups = 256;   // attention workgroups aimed at per launch: one per CU
+constexpr long kMergedShares = 64;        // shares of a row that the merge kernel takes in one go (128 channels)
 constexpr long kFloatGroups = 2;          // float-mode workgroups per bfloat16 attention workgroup aimed at: two fit a CU
 constexpr int kSparseRows = 64;           // query rows per KV head up to which the split-pages work shape is used
 
@@ -270,13 +272,24 @@ losa_status hip_fail(losa_ctx* ctx, const char* what, hipError_t e) {
 
 // Number of equal shares a (sequence, KV head) page list of at most `upper` pages is split into,
 // when every work item holds `part_stride` rows of partials and tiles hold `tile` tokens.
-int pick_nchunk(const losa_ctx* ctx, int batch, int upper, long target, int row_groups, int part_stride, int tile) {
+// split_pages (the kernel whose four wavefronts deal a share's tiles out): a tile for each of them rather than more
+// shares, and no more shares than the merge takes in one go; more leave wavefronts without a tile and cost the merge loads.
+// A share per tile (at most 256 workgroups) / per four tiles, a step in us: 1 head of 64 channels, 2048 tokens 16.3 / 16.2, 8192 22.1 / 20.3,
+// 16384 22.6 / 18.9; 4 heads of 128 channels, 2048 22.4 / 21.2, 4096 25.0 / 23.8, 4 x 1024 23.4 / 22.2 (per eight: 25.1, 22.7, 23.2).
+// 256 shares / 128, 1 head of 64 channels: 65536 tokens 26.8 / 21.1, 131072 28.8 / 23.3; 256 / 64, 1 head of 128 channels: 131072
+// 50.1 / 35.1; 128 / 64, 2 heads: 41.5 / 37.6.
+int pick_nchunk(const losa_ctx* ctx, int batch, int upper, long target, int row_groups, int part_stride, int tile, bool split_pages) {
   const long heads = (long)batch * ctx->sh.Hkv;
   const long tiles = (upper + (tile / ctx->sh.g) - 1) / (tile / ctx->sh.g);
   long want = target / (heads * row_groups);
   const long fit = ctx->part_rows / (heads * part_stride);
   if (want > fit) want = fit;
   if (want > tiles) want = tiles;
+  if (split_pages && !ctx->shares_set) {
+    const long full = (tiles + 3) / 4, merged = kMergedShares * 128 / ctx->sh.d;
+    if (want > full) want = full;
+    if (want > merged) want = merged;
+  }
   if (want < 1) want = 1;
   return (int)want;
 }
@@ -384,7 +397,7 @@ losa_status sparse_attn_impl(losa_ctx* ctx, hipStream_t st, const KvView& kv, in
   const int many_tile = !mfma ? ctx->sh.g : rows_kernel ? kManyRowStage : 32;
   const int few_tile = !mfma ? ctx->sh.g : rows_kernel && !both_shapes ? kManyRowStage : 32;
   int nchunk = pick_nchunk(ctx, batch, upper, ctx->target_workgroups * (mfma ? 1 : kFloatGroups), row_groups, part.rows,
-                           few_tile);
+                           few_tile, mfma && few_tile == 32 && rows_upper <= 64);
   // float mode: workgroups of the same share and different row blocks are nchunk apart in the grid; a multiple of
   // the die count (8) puts them on one die, so that its L2 serves all but the first
   if (!mfma && nchunk >= 8) nchunk &= ~7;
@@ -502,6 +515,7 @@ losa_status losa_set_tuning(losa_ctx* ctx, losa_tuning knob, int64_t value) {
       if (value < 1 || value > kTargetItems)
         return fail(ctx, LOSA_ERR_INVALID_ARG, "attention workgroups must be in 1..%ld", kTargetItems);
       ctx->target_workgroups = (long)value;
+      ctx->shares_set = true;
       return LOSA_OK;
     case LOSA_TUNE_SELECT_ROUND:
       if (value < 0) return fail(ctx, LOSA_ERR_INVALID_ARG, "selection round must be >= 0");
