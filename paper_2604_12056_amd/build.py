@@ -18,6 +18,8 @@ HIPCC_FLAGS = [
     # matrix-core accumulators in ordinary vector registers: the online-softmax rescale is plain
     # vector arithmetic on them, and the accumulator-register form costs a copy in and out per tile
     "-mllvm", "-amdgpu-mfma-vgpr-form=1",
+    # leading plain kernel arguments arrive in scalar registers instead of through a load (see KvView)
+    "-mllvm", "-amdgpu-kernarg-preload-count=16",
     "-Wall", "-Wno-unused-command-line-argument",
 ]
 

@@ -148,12 +148,17 @@ typedef __attribute__((ext_vector_type(4))) float bm_f32x4_t;
 typedef __attribute__((ext_vector_type(8))) float bm_f32x8_t;
 
 template <int D, int NTILE, int CW>
-__global__ __launch_bounds__(128 * NTILE) void block_merge_mfma_kernel(Shape sh, const bf16_t* __restrict__ q,
+__global__ __launch_bounds__(128 * NTILE) void block_merge_mfma_kernel(const bf16_t* __restrict__ q,
                                                                const bf16_t* __restrict__ k_b,
                                                                const bf16_t* __restrict__ v_b,
+                                                               int block, int q_heads, int kv_heads, int group,
                                                                const float* __restrict__ o_p,
-                                                               const float* __restrict__ lse_p, float* __restrict__ out,
+                                                               const float* __restrict__ lse_p, Shape sh, float* __restrict__ out,
                                                                float* __restrict__ o_b, float* __restrict__ lse_b) {
+  sh.B = block;   // (leading arguments: see KvView)
+  sh.Hq = q_heads;
+  sh.Hkv = kv_heads;
+  sh.G = group;
   constexpr int KS = D / 32, NT = CW / 16, PAIRS = 16 * NTILE;   // PAIRS: token pairs of the block's tiles
   constexpr int THREADS = 128 * NTILE, ITEMS = PAIRS * (CW / 8), PER = (ITEMS + THREADS - 1) / THREADS;   // (token pair, 8 channels) to stage; per thread
   __shared__ __attribute__((aligned(16))) uint32_t vT[CW][PAIRS + 4];   // [channel][token pair]; rows stay 16-byte aligned
@@ -315,7 +320,8 @@ hipError_t launch_block_merge(hipStream_t st, int dtype, const Shape& sh, int ba
                                     : (sh.B <= 32 ? (spread ? block_merge_mfma_kernel<64, 1, kSpreadChannels> : block_merge_mfma_kernel<64, 1, 64>)
                                                   : (spread ? block_merge_mfma_kernel<64, 2, kSpreadChannels> : block_merge_mfma_kernel<64, 2, 64>));
     const dim3 mgrid(sh.Hq, batch, spread ? sh.d / kSpreadChannels : 1);
-    kernel<<<mgrid, sh.B <= 32 ? 128 : 256, 0, st>>>(sh, (const bf16_t*)q, (const bf16_t*)k_b, (const bf16_t*)v_b, o_p, lse_p, out, o_b, lse_b);
+    kernel<<<mgrid, sh.B <= 32 ? 128 : 256, 0, st>>>((const bf16_t*)q, (const bf16_t*)k_b, (const bf16_t*)v_b, sh.B, sh.Hq, sh.Hkv, sh.G, o_p, lse_p, sh,
+                                                     out, o_b, lse_b);
     return hipGetLastError();
   }
   dim3 grid((sh.B + 31) / 32, sh.Hq, batch);

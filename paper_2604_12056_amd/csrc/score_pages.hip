@@ -206,11 +206,16 @@ __global__ __launch_bounds__(256) void page_scores_f32_kernel(KvView kv, Shape s
 // the B operands are the sign-split query fragments.  Output leaves the matrix core as 4
 // consecutive pages per lane and query row: one 16-byte store.
 template <int D, int MAXT>
-__global__ __launch_bounds__(256) void page_scores_mfma_kernel(KvView kv, Shape sh, const bf16_t* __restrict__ q,
+__global__ __launch_bounds__(256) void page_scores_mfma_kernel(const float* delta, const int32_t* page_indptr, const int32_t* seq_lens, int block,
+                                                               KvView kv, Shape sh, const bf16_t* __restrict__ q,
                                                                const int32_t* __restrict__ active_idx,
                                                                const int32_t* __restrict__ active_count,
                                                                float* __restrict__ scores, ScoreAux aux, RankArgs ra,
                                                                int tpw) {
+  ra.delta = delta;   // (leading arguments: see KvView)
+  kv.page_indptr = page_indptr;
+  kv.seq_lens = seq_lens;
+  sh.B = block;
   // A workgroup scores tpw (<= MAXT, a template argument so that the one-tile form carries no
   // code for more) consecutive 64-page tiles: what it does before
   // the first product (ranking, query staging) is then paid once for all of them, and a
@@ -445,7 +450,6 @@ struct SelectOut {
   int cap;
   uint32_t* rowmaps;    // workspace [heads, rows_max, words]: pick bitmap of every query row
   int32_t* tickets;     // workspace [heads], zero on entry (zeroed by the scoring kernel), zero on exit
-  bool rows_known;      // every row of the grid exists (all workgroups have rows to select for)
   // union_words() | words of a copy << 16 and (copies - 1) | row shift << 8; beside the pointer, so that they arrive with
   // it: fetched where they are used, they cost a scalar round trip (0.3 us)
   uint32_t union_shape, union_rows;
@@ -620,9 +624,14 @@ __device__ __forceinline__ void radix_kth(uint32_t (&key)[E], int nmine, int Kp,
 // one thread, picks through LDS); 4096 pages, 9.2 us with 1024 threads and 5.7 with 512.  The query rows and the page
 // table, which a workgroup of this launch per head used to gather, come from the scoring kernel.
 template <int E, int NT, bool MULTI, bool LIST>
-__global__ __launch_bounds__(NT) void select_pages_kernel(KvView kv, Shape sh, const int32_t* __restrict__ active_count,
-                                                           const float* __restrict__ scores, int topk, SelectOut out,
-                                                           int rpw) {
+__global__ __launch_bounds__(NT) void select_pages_kernel(const float* __restrict__ scores, const int32_t* __restrict__ active_count,
+                                                           const int32_t* page_indptr, const int32_t* seq_lens, int kv_heads, int rows_max,
+                                                           int max_pages, int rows_known, KvView kv, Shape sh, int topk, SelectOut out, int rpw) {
+  kv.page_indptr = page_indptr;   // (leading arguments: see KvView)
+  kv.seq_lens = seq_lens;
+  sh.Hkv = kv_heads;
+  sh.rows_max = rows_max;
+  sh.max_pages = max_pages;
   // A workgroup selects for up to rpw query rows, one after the other (the next row's
   // scores travel while the current row is selected).  rpw is 1 until further workgroups cost more than further
   // rows (launch_select_pages says where).
@@ -639,7 +648,7 @@ __global__ __launch_bounds__(NT) void select_pages_kernel(KvView kv, Shape sh, c
   const int head = b * sh.Hkv + j;
   const int p_first_all = tid * E;
   const int p_first = p_first_all;
-  // When the host knows the row count (every workgroup of the grid has a row), the row's
+  // When the host knows the row count (rows_known: every workgroup of the grid has a row), the row's
   // scores are fetched before anything else: the address depends on kernel arguments only,
   // so these loads travel together with the loads of the counts below (entries past the
   // sequence's pages are masked later).  Otherwise they wait until the row is known to exist.
@@ -660,11 +669,11 @@ __global__ __launch_bounds__(NT) void select_pages_kernel(KvView kv, Shape sh, c
       for (int i = 0; i < E; ++i) dst[i] = row[min(p_first + i, sh.max_pages - 1)];
     }
   };
-  if (out.rows_known) load_row(raw, r_first);
+  if (rows_known) load_row(raw, r_first);
   const int M = min(active_count[b], sh.B) * sh.G;
   const int P = min(seq_pages(kv, sh, b), NT * E);   // (the launcher picks NT * E >= the page limit)
   if (r_first >= M) return;
-  if (!out.rows_known) load_row(raw, r_first);
+  if (!rows_known) load_row(raw, r_first);
   const int words = (sh.max_pages + 31) / 32;
   const int Kp = min(topk, P);
   const int nmine_all = max(0, min(E, P - p_first));   // pages of this thread that exist
@@ -948,15 +957,17 @@ __global__ __launch_bounds__(NT) void shared_select_kernel(KvView kv, Shape sh, 
 // from the highest in which the row's keys differ from its smallest, the count of keys that reach the candidate coming from scalar
 // population counts of the compares, until exactly K keys do (some 12 of up to 32 steps); the compares' lane masks then are the
 // row's bitmap as it stands.
-// The locality scores too, for hidden states of up to 64 16-byte pieces (`hid` given): a wavefront per token, sums in the order
+// The locality scores too, for hidden states of up to 64 16-byte pieces (h_cur given): a wavefront per token, sums in the order
 // of the locality kernel's, whose three other wavefronts have nothing then.
-struct PickHidden {
-  const bf16_t* cur;    // [batch*B, H], NULL: the locality scores are given
-  const bf16_t* prev;
-};
 template <int D, int TPW>   // TPW: 16-page tiles per wavefront
-__global__ __launch_bounds__(1024) void pick_pages_kernel(KvView kv, Shape sh, const bf16_t* __restrict__ q, ScoreAux aux,
-                                                          RankArgs ra, PickHidden hid, int topk) {
+__global__ __launch_bounds__(1024) void pick_pages_kernel(const float* delta, const bf16_t* h_cur, const bf16_t* h_prev, const int32_t* page_indptr,
+                                                          const int32_t* seq_lens, int block, int hidden, KvView kv, Shape sh,
+                                                          const bf16_t* __restrict__ q, ScoreAux aux, RankArgs ra, int topk) {
+  ra.delta = delta;   // (leading arguments: see KvView)
+  kv.page_indptr = page_indptr;
+  kv.seq_lens = seq_lens;
+  sh.B = block;
+  sh.H = hidden;
   constexpr int NW = 16, KS = D / 32, VPR = D / 8, STRIDE = D * 2 + 16;
   constexpr int NP = NW * 16 * TPW, ROW = NP + 4;   // pages; floats per row of scores in LDS (the writes of 16 rows spread over the banks)
   constexpr int E = NP / 64, COPY = 16;             // keys per lane; words of a copy of the union bitmap
@@ -972,12 +983,12 @@ __global__ __launch_bounds__(1024) void pick_pages_kernel(KvView kv, Shape sh, c
   float my_delta = 0.f;
   uint4 hx[4], hy[4];
   const int nvec = sh.H / 8;
-  if (hid.cur) {
+  if (h_cur) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const size_t at = ((size_t)b * B + min(wave + NW * k, B - 1)) * nvec + min(lane, nvec - 1);
-      hx[k] = reinterpret_cast<const uint4*>(hid.cur)[at];
-      hy[k] = reinterpret_cast<const uint4*>(hid.prev)[at];
+      hx[k] = reinterpret_cast<const uint4*>(h_cur)[at];
+      hy[k] = reinterpret_cast<const uint4*>(h_prev)[at];
     }
   } else {
     my_delta = ra.delta[(size_t)b * B + min(lane, B - 1)];
@@ -1001,7 +1012,7 @@ __global__ __launch_bounds__(1024) void pick_pages_kernel(KvView kv, Shape sh, c
     }
   }
   if (tid < COPY) uw[tid] = 0u;
-  if (hid.cur) {
+  if (h_cur) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       float fx[8], fy[8], part = 0.f;
@@ -1168,14 +1179,14 @@ hipError_t launch_page_scores(hipStream_t st, int dtype, const KvView& kv, const
     dim3 mgrid((unsigned)((tiles + tpw - 1) / tpw), sh.Hkv, batch);
     if (sh.d == 128) {
       if (tpw == 1)
-        page_scores_mfma_kernel<128, 1><<<mgrid, 256, 0, st>>>(kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, 1);
+        page_scores_mfma_kernel<128, 1><<<mgrid, 256, 0, st>>>(ra.delta, kv.page_indptr, kv.seq_lens, sh.B, kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, 1);
       else
-        page_scores_mfma_kernel<128, kMaxTilesPerWg><<<mgrid, 256, 0, st>>>(kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, tpw);
+        page_scores_mfma_kernel<128, kMaxTilesPerWg><<<mgrid, 256, 0, st>>>(ra.delta, kv.page_indptr, kv.seq_lens, sh.B, kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, tpw);
     } else {
       if (tpw == 1)
-        page_scores_mfma_kernel<64, 1><<<mgrid, 256, 0, st>>>(kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, 1);
+        page_scores_mfma_kernel<64, 1><<<mgrid, 256, 0, st>>>(ra.delta, kv.page_indptr, kv.seq_lens, sh.B, kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, 1);
       else
-        page_scores_mfma_kernel<64, kMaxTilesPerWg><<<mgrid, 256, 0, st>>>(kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, tpw);
+        page_scores_mfma_kernel<64, kMaxTilesPerWg><<<mgrid, 256, 0, st>>>(ra.delta, kv.page_indptr, kv.seq_lens, sh.B, kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, tpw);
     }
   } else {
     (sh.d == 128 ? page_scores_f32_kernel<128> : page_scores_f32_kernel<64>)<<<grid, 256, 0, st>>>(
@@ -1211,11 +1222,11 @@ hipError_t launch_pick_pages(hipStream_t st, const KvView& kv, const Shape& sh, 
     return hipErrorInvalidValue;
   const ScoreAux aux{tickets, sel_count, entries, q_act, union_bits, union_words(sh.max_pages, sh.rows_max), 0};
   const RankArgs ra{ranking.delta, ranking.mode, ranking.n, ranking.tau, ranking.mask, ranking.active_idx, ranking.active_count};
-  const PickHidden hid{(const bf16_t*)h_cur, (const bf16_t*)h_prev};
   const dim3 grid((rows + kPickRows - 1) / kPickRows, sh.Hkv, batch);
   auto kern = sh.d == 128 ? (max_seq_pages <= 256 ? pick_pages_kernel<128, 1> : pick_pages_kernel<128, 2>)
                           : (max_seq_pages <= 256 ? pick_pages_kernel<64, 1> : pick_pages_kernel<64, 2>);
-  kern<<<grid, 1024, 0, st>>>(kv, sh, (const bf16_t*)q, aux, ra, hid, topk);
+  kern<<<grid, 1024, 0, st>>>(ra.delta, (const bf16_t*)h_cur, (const bf16_t*)h_prev, kv.page_indptr, kv.seq_lens, sh.B, sh.H, kv, sh,
+                              (const bf16_t*)q, aux, ra, topk);
   return hipGetLastError();
 }
 
@@ -1234,7 +1245,7 @@ hipError_t launch_select_pages(hipStream_t st, const KvView& kv, const Shape& sh
   out.cap = cap;
   out.rowmaps = rowmaps;
   out.tickets = tickets;
-  out.rows_known = rows_hint >= 1;
+  const bool rows_known = rows_hint >= 1;
   // rows_hint: an upper bound on |A| * G the host happens to know (0: none); rows past it get no workgroup
   const int rows = rows_hint >= 1 && rows_hint < sh.rows_max ? rows_hint : sh.rows_max;
   out.union_shape = (uint32_t)union_words(sh.max_pages, sh.rows_max) | (uint32_t)copy_words << 16;
@@ -1255,7 +1266,7 @@ hipError_t launch_select_pages(hipStream_t st, const KvView& kv, const Shape& sh
   //     224 x 4 28.9 / 26.3 / 28.3 / 36.4; 64 x 32 of 4096 pages 51.7 / 46.0 / 42.5 / 47.7; 224 x 8 of 8192 75 / 69 / 65 / 62
   const long wgs = (long)rows * sh.Hkv * batch;
   const int threads = pages <= 256 * 8 ? 256 : pages <= 512 * 8 ? 512 : 1024;
-  const long round = (list ? 1024L : out.rows_known ? 5120L : 2048L) * 256 / threads;
+  const long round = (list ? 1024L : rows_known ? 5120L : 2048L) * 256 / threads;
   const long want = workgroups_per_round > 0 ? (wgs + workgroups_per_round - 1) / workgroups_per_round : wgs / round;
   const int rpw = (int)max(1L, min(want, list ? 8L : 4L));
   dim3 grid((rows + rpw - 1) / rpw, sh.Hkv, batch);
@@ -1265,7 +1276,7 @@ hipError_t launch_select_pages(hipStream_t st, const KvView& kv, const Shape& sh
 #define LOSA_SELECT(E, NT)                                                                                                             \
   (rpw == 1 ? (list ? select_pages_kernel<E, NT, false, true> : select_pages_kernel<E, NT, false, false>)                              \
             : (list ? select_pages_kernel<E, NT, true, true> : select_pages_kernel<E, NT, true, false>))<<<grid, NT, 0, st>>>(          \
-      kv, sh, active_count, scores, topk, out, rpw)
+      scores, active_count, kv.page_indptr, kv.seq_lens, sh.Hkv, sh.rows_max, sh.max_pages, rows_known, kv, sh, topk, out, rpw)
   if (pages <= 256 * 8)
     LOSA_SELECT(8, 256);
   else if (pages <= 512 * 8)

@@ -651,11 +651,37 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
   }
 }
 
+// The leading arguments (see KvView) put where the code reads them: union bitmap, entries and words per head; or list,
+// counts and capacity.
+template <bool UNION>
+__device__ __forceinline__ void take_leading(const void* first, const int32_t* second, const int32_t* active_count, const int32_t* page_indptr,
+                                             const int32_t* seq_lens, int stride, int copy_words, int max_pages, int kv_heads, AttnInputs& in,
+                                             Shape& sh, KvView& kv, UnionInKernel& uni) {
+  in.active_count = active_count;
+  kv.page_indptr = page_indptr;
+  kv.seq_lens = seq_lens;
+  sh.max_pages = max_pages;
+  sh.Hkv = kv_heads;
+  if constexpr (UNION) {
+    uni.bits = static_cast<const uint32_t*>(first);
+    uni.entries = second;
+    uni.stride = stride;
+    uni.copy_words = copy_words;
+  } else {
+    in.list = static_cast<const int32_t*>(first);
+    in.sel_count = second;
+    in.cap = stride;
+  }
+}
+
 template <int D, int GP, int R, bool SPLIT_PAGES, int NBUF, bool UNION = false>
-__global__ __launch_bounds__(256) void attn_mfma_kernel(AttnInputs in, int nchunk, int nrbg, Shape sh, KvView kv,
+__global__ __launch_bounds__(256) void attn_mfma_kernel(const void* first, const int32_t* second, const int32_t* active_count, const int32_t* page_indptr, const int32_t* seq_lens,
+                                                        int stride, int copy_words, int max_pages, int kv_heads, AttnInputs in,
+                                                        int nchunk, int nrbg, Shape sh, KvView kv,
                                                         Partials part, float scale_log2e, int m_lo, int m_hi,
                                                         UnionInKernel uni) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
+  take_leading<UNION>(first, second, active_count, page_indptr, seq_lens, stride, copy_words, max_pages, kv_heads, in, sh, kv, uni);
   attn_mfma_body<D, GP, R, SPLIT_PAGES, NBUF, UNION>(in, nchunk, nrbg, sh, kv, part, scale_log2e,
                                                                             m_lo, m_hi, uni, lds);
 }
@@ -666,9 +692,12 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(AttnInputs in, int nchun
 // head with a few active rows does not pay for the 64 the launch has to allow.  Heads with more than
 // 64 rows are not served here.
 template <int D, int GP, bool UNION>
-__global__ __launch_bounds__(256) void attn_mfma_rows_kernel(AttnInputs in, int nchunk, Shape sh, KvView kv, Partials part,
+__global__ __launch_bounds__(256) void attn_mfma_rows_kernel(const void* first, const int32_t* second, const int32_t* active_count, const int32_t* page_indptr, const int32_t* seq_lens,
+                                                             int stride, int copy_words, int max_pages, int kv_heads, AttnInputs in,
+                                                             int nchunk, Shape sh, KvView kv, Partials part,
                                                              float scale_log2e, int m_lo, int m_hi, UnionInKernel uni) {
   extern __shared__ __attribute__((aligned(16))) float lds[];
+  take_leading<UNION>(first, second, active_count, page_indptr, seq_lens, stride, copy_words, max_pages, kv_heads, in, sh, kv, uni);
   const int M = active_rows(in, kv, sh, blockIdx.z);
   if (M <= 0 || M > kUnionRows) return;
   if (M <= 16)
@@ -706,10 +735,12 @@ static hipError_t launch_one(hipStream_t st, const KvView& kv, const Shape& sh, 
   const float scale_log2e = sh.sm_scale * 1.4426950408889634f;
   dim3 grid(nchunk, sh.Hkv * nrbg, batch);
   if (ev_start && ev_stop)   // events bound to this dispatch: they read the kernel's own begin and end
-    hipExtLaunchKernelGGL(kern, grid, dim3(256), (uint32_t)lds_bytes, st, ev_start, ev_stop, 0, in, nchunk,
+    hipExtLaunchKernelGGL(kern, grid, dim3(256), (uint32_t)lds_bytes, st, ev_start, ev_stop, 0, UNION ? (const void*)uni.bits : in.list, UNION ? uni.entries : in.sel_count, in.active_count, kv.page_indptr, kv.seq_lens,
+                          UNION ? uni.stride : in.cap, uni.copy_words, sh.max_pages, sh.Hkv, in, nchunk,
                           nrbg, sh, kv, part, scale_log2e, m_lo, m_hi, uni);
   else
-    kern<<<grid, 256, lds_bytes, st>>>(in, nchunk, nrbg, sh, kv, part, scale_log2e, m_lo, m_hi, uni);
+    kern<<<grid, 256, lds_bytes, st>>>(UNION ? (const void*)uni.bits : in.list, UNION ? uni.entries : in.sel_count, in.active_count, kv.page_indptr, kv.seq_lens,
+                          UNION ? uni.stride : in.cap, uni.copy_words, sh.max_pages, sh.Hkv, in, nchunk, nrbg, sh, kv, part, scale_log2e, m_lo, m_hi, uni);
   return hipGetLastError();
 }
 
@@ -731,10 +762,12 @@ static hipError_t launch_dg(hipStream_t st, const KvView& kv, const Shape& sh, i
       const float scale_log2e = sh.sm_scale * 1.4426950408889634f;
       const UnionInKernel u = uni ? *uni : UnionInKernel{nullptr};
       if (e0 && e1)   // events bound to this dispatch, as in launch_one
-        hipExtLaunchKernelGGL(kern, grid, dim3(256), (uint32_t)lds_bytes, st, e0, e1, 0, in, nchunk, sh, kv, part, scale_log2e, m_lo,
+        hipExtLaunchKernelGGL(kern, grid, dim3(256), (uint32_t)lds_bytes, st, e0, e1, 0, uni ? (const void*)u.bits : in.list, uni ? u.entries : in.sel_count, in.active_count, kv.page_indptr, kv.seq_lens,
+                              uni ? u.stride : in.cap, u.copy_words, sh.max_pages, sh.Hkv, in, nchunk, sh, kv, part, scale_log2e, m_lo,
                               m_hi, u);
       else
-        kern<<<grid, 256, lds_bytes, st>>>(in, nchunk, sh, kv, part, scale_log2e, m_lo, m_hi, u);
+        kern<<<grid, 256, lds_bytes, st>>>(uni ? (const void*)u.bits : in.list, uni ? u.entries : in.sel_count, in.active_count, kv.page_indptr, kv.seq_lens,
+                              uni ? u.stride : in.cap, u.copy_words, sh.max_pages, sh.Hkv, in, nchunk, sh, kv, part, scale_log2e, m_lo, m_hi, u);
       return hipGetLastError();
     };
     constexpr size_t slots = 4 * MergeSlot<D, 4>::kFloats;
