@@ -79,10 +79,13 @@ struct MergeSlot {   // LDS image of one wavefront's state: O as [row tile][chan
 // union of the head's picks as a bitmap, the scoring kernel the query rows and a copy of the head's page table (which the
 // four wavefronts bring to LDS together); every wavefront ranks the union with a popcount prefix sum (lane = bitmap
 // word), keeps words and ranks in LDS (in its own merge slot, which is idle until the combine), and finds
-// the pages of its own tiles by rank: a binary search over the word ranks, a 5-step search inside
+// the pages of its own tiles by rank: a four-way search over the word ranks, a 5-step search inside
 // the word, then the page's entry from the table in LDS (from memory for pages beyond the first
 // 2048).  That is more start-up work than with a list (about 1.5 us at 2048 pages), in
 // exchange for the selection kernel's whole hand-over tail (about 4 us).
+// By stamps (42 rows x 4 heads, 0.72 of 2048 pages; 2.45 GHz): a wavefront has its bitmap after 1550 cycles, its first pages after
+// 3900, has asked for its first tile after 7400 (a compute unit takes some 22 bytes of requests a cycle), has it after 12700,
+// takes 2700 to 3800 cycles a tile, the combine and the stores 4900; cached keys and values take 2 us off the step, no more.
 constexpr int kMaxUnionWords = kMaxSelectPages / 32;
 constexpr int kTablePagesInLds = 2048;   // the first so many entries of a head's page table are kept in LDS
 // LDS of the split-pages shape, in floats: the four wavefronts' merge slots, then (UNION) the page table.
@@ -174,6 +177,10 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
 #pragma unroll
     for (int k = 0; k < TPW; ++k) reinterpret_cast<u32x4v_t*>(u_tab)[wave * (64 * TPW) + lane + 64 * k] = tabv[k];
     u_words = (P + 31) >> 5;
+    // Kernel arguments that the way to the first tile needs, all fetched by now: fetched where they are used, each group
+    // of them is a scalar round trip there.
+    asm volatile("" ::"s"(nchunk), "s"(sh.rows_max), "s"(part.rows), "s"(kv.num_pages), "s"(kv.k_pages), "s"(kv.v_pages), "s"(uni.q_act),
+                 "s"(uni.sel_count), "s"(m_lo), "s"(m_hi), "s"(sh.B), "s"(sh.G));
     __syncthreads();
     if (copies) {
       uint32_t all = (ub[0] | ub[1]) | (ub[2] | ub[3]);
@@ -209,7 +216,6 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
       }
     }
     U_raw = total;
-    if (chunk == 0 && threadIdx.x == 0 && M_raw > 0) uni.sel_count[head] = total;   // for the merge kernel and the caller's diagnostics
   } else {
     U_raw = in.list ? min(in.sel_count[head], in.cap) : P;
     fetch_entry();
@@ -222,7 +228,16 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
   // fourth: this launch only serves row counts in (m_lo, m_hi] (the host may not know the count
   // and then launches both work shapes, each taking its own range)
   const bool has_rows = SPLIT_PAGES || rb * (R * 16) < M;
-  if ((M <= 0) | (chunk >= ntiles) | !has_rows | (M <= m_lo) | (M > m_hi)) return;
+  // the union's size, for the merge kernel and the caller's diagnostics: stored at the end, as the wait for a page entry out of
+  // memory would be one for this store too
+  [[maybe_unused]] auto leave_count = [&]() {
+    if constexpr (UNION)
+      if (chunk == 0 && threadIdx.x == 0 && M_raw > 0) uni.sel_count[head] = U_raw;
+  };
+  if ((M <= 0) | (chunk >= ntiles) | !has_rows | (M <= m_lo) | (M > m_hi)) {
+    leave_count();
+    return;
+  }
   const int ntw = tfirst < ntiles ? (ntiles - 1 - tfirst) / tstep + 1 : 0;   // this wavefront's tiles
 
   bf16x8_t qf[R][KS];
@@ -266,10 +281,16 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
       int page = 0;
       const bool want = lp < U;
       if (want) {
-        int lo = 0, hi = u_words, k = (int)lp;
-        while (hi - lo > 1) {   // (the trip count depends on u_words only: uniform over the wavefront)
-          const int mid = (lo + hi) >> 1;
-          if (u_base[mid] <= k) lo = mid; else hi = mid;
+        int lo = 0, k = (int)lp;
+        // four ways a step (three LDS reads at once): 3 steps for 64 words; the trip count is uniform over the wavefront
+        for (int step = u_words <= 64 ? 16 : u_words <= 256 ? 64 : 256; step; step >>= 2) {
+          int below = 0;
+#pragma unroll
+          for (int i = 1; i < 4; ++i) {
+            const int at = lo + i * step;
+            below += (int)(at < u_words) & (int)(u_base[min(at, u_words - 1)] <= k);
+          }
+          lo += below * step;
         }
         const uint32_t word = u_bits[lo];
         k -= u_base[lo];
@@ -375,7 +396,7 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
   };
 
   // softmax update and value products of a tile whose scores are given
-  auto softmax_values = [&](Tile& t, f32x4_t (&sc)[R][2]) {
+  auto softmax_values = [&](Tile& t, f32x4_t (&sc)[R][2], bool first) {
     // valid tokens among this lane's 8 (tile tokens 8*qd .. 8*qd+7)
     int lane_valid;
     bool full;
@@ -426,6 +447,7 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
       any_up |= tm[mt] > up_thr[mt];
     }
     if (__any(any_up)) {
+      float al[R];
 #pragma unroll
       for (int mt = 0; mt < R; ++mt) {
         const float m_cand = max_over_lane_groups(tm[mt]) * scale_log2e;
@@ -434,8 +456,13 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
         m_run[mt] = up ? m_cand : m_run[mt];
         up_thr[mt] = (m_run[mt] + kLag) * inv_scale_log2e;
         l_run[mt] *= alpha;
+        al[mt] = alpha;
+      }
+      if (!first) {   // (a wavefront's first tile always gets here, with nothing accumulated yet)
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) o[mt][nt] *= alpha;
+        for (int mt = 0; mt < R; ++mt)
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) o[mt][nt] *= al[mt];
       }
     }
     // ---- phase 3: numerators as a bfloat16 pair, value products.
@@ -485,10 +512,10 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
       __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);   // 3 VALU
     }
   };
-  auto compute_tile = [&](Tile& t) {
+  auto compute_tile = [&](Tile& t, bool first) {
     f32x4_t sc[R][2];
     score_products(t.k, sc);
-    softmax_values(t, sc);
+    softmax_values(t, sc, first);
   };
 
   // ---- main loop: NBUF tile buffers in registers, NBUF-1 tiles of lookahead (how many: see
@@ -532,11 +559,12 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
 #pragma unroll
       for (int k = 0; k < NBUF; ++k) {
         load_tile(tb[(k + NBUF - 1) % NBUF], n + k + NBUF - 1, ne);
-        if (n + k < ne) compute_tile(tb[k]);
+        if (n + k < ne) compute_tile(tb[k], n + k == 0);
       }
     }
   }
 
+  leave_count();
   // each lane summed its own tokens; rows are spread over the 4 lane groups
 #pragma unroll
   for (int mt = 0; mt < R; ++mt) l_run[mt] = sum_over_lane_groups(l_run[mt]);
