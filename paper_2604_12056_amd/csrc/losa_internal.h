@@ -48,6 +48,20 @@ __device__ __forceinline__ int seq_pages(const KvView& kv, const Shape& sh, int 
   return max(0, min(min(listed, filled), min(sh.max_pages, kv.seq_page_limit)));
 }
 
+// The same with what else is read of the page table, in one scalar round trip: the empty asm keeps the three loads ahead of
+// whatever tests one of them (not a volatile one: loads behind that are vector loads).  (Kernel arguments and counts are kept together the same way: left alone, each is fetched
+// where it is used, and a kernel of a few microseconds walked through four to six scalar round trips one after the other.)
+struct Sequence {
+  int base, tokens, pages;   // first entry of the page table, prefix length, seq_pages()
+};
+__device__ __forceinline__ Sequence sequence(const KvView& kv, const Shape& sh, int b) {
+  int base = __builtin_amdgcn_readfirstlane(kv.page_indptr[b]), end = __builtin_amdgcn_readfirstlane(kv.page_indptr[b + 1]);
+  int tokens = __builtin_amdgcn_readfirstlane(kv.seq_lens[b]);
+  asm("" : "+s"(base), "+s"(end), "+s"(tokens) : "s"(sh.g), "s"(sh.max_pages), "s"(kv.seq_page_limit));
+  const int filled = (tokens + sh.g - 1) >> (sh.g == 16 ? 4 : 5);
+  return {base, tokens, max(0, min(min(end - base, filled), min(sh.max_pages, kv.seq_page_limit)))};
+}
+
 // Split-K partials of the attention: item = ((b*Hkv + j)*nchunk + c), row r < rows.
 struct Partials {
   float* o;   // [items, rows, d]   un-normalised sum_t exp(s_t - m) v_t

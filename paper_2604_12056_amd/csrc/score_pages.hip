@@ -206,7 +206,9 @@ __global__ __launch_bounds__(256) void page_scores_f32_kernel(KvView kv, Shape s
 // the B operands are the sign-split query fragments.  Output leaves the matrix core as 4
 // consecutive pages per lane and query row: one 16-byte store.
 template <int D, int MAXT>
-__global__ __launch_bounds__(256) void page_scores_mfma_kernel(const float* delta, const int32_t* page_indptr, const int32_t* seq_lens, int block,
+__global__ __launch_bounds__(256) void page_scores_mfma_kernel(const float* delta, const int32_t* page_indptr, const int32_t* seq_lens,
+                                                               const int32_t* page_indices, void* meta, int block, int kv_heads, int num_pages,
+                                                               int max_pages,
                                                                KvView kv, Shape sh, const bf16_t* __restrict__ q,
                                                                const int32_t* __restrict__ active_idx,
                                                                const int32_t* __restrict__ active_count,
@@ -215,7 +217,12 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(const float* delt
   ra.delta = delta;   // (leading arguments: see KvView)
   kv.page_indptr = page_indptr;
   kv.seq_lens = seq_lens;
+  kv.page_indices = page_indices;
+  kv.meta = meta;
+  kv.num_pages = num_pages;
   sh.B = block;
+  sh.Hkv = kv_heads;
+  sh.max_pages = max_pages;
   // A workgroup scores tpw (<= MAXT, a template argument so that the one-tile form carries no
   // code for more) consecutive 64-page tiles: what it does before
   // the first product (ranking, query staging) is then paid once for all of them, and a
@@ -230,8 +237,8 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(const float* delt
   // all (their address needs kernel arguments only; behind the page counts they came 0.5 us later).
   float my_delta = 0.f;
   if (ranked) my_delta = ra.delta[(size_t)b * sh.B + min(small ? lane : tid, sh.B - 1)];
-  const int base = kv.page_indptr[b];
-  const int P = seq_pages(kv, sh, b);
+  const Sequence seq = sequence(kv, sh, b);
+  const int base = seq.base, P = seq.pages, tokens = seq.tokens;
   const int p0 = bx * 64 + wave * 16;
   __shared__ __attribute__((aligned(16))) float sdelta[kRankTokens];
   __shared__ int act_list[kRankTokens];
@@ -248,7 +255,6 @@ __global__ __launch_bounds__(256) void page_scores_mfma_kernel(const float* delt
   // Metadata rows of this wavefront's pages: two dependent round trips (page table, then the rows), which travel
   // while the ranking runs.  A operands: rows of page p0 + l16 (a valid page is read for lanes past P, never stored).
   // The page ids of all of this workgroup's tiles are fetched at once.
-  const int tokens = kv.seq_lens[b];
   int physv[MAXT];
 #pragma unroll
   for (int t = 0; t < MAXT; ++t) physv[t] = t < tpw ? tile_phys(t) : 0;
@@ -670,8 +676,11 @@ __global__ __launch_bounds__(NT) void select_pages_kernel(const float* __restric
     }
   };
   if (rows_known) load_row(raw, r_first);
-  const int M = min(active_count[b], sh.B) * sh.G;
-  const int P = min(seq_pages(kv, sh, b), NT * E);   // (the launcher picks NT * E >= the page limit)
+  int n_act = active_count[b];
+  const Sequence seq = sequence(kv, sh, b);
+  asm("" : "+s"(n_act) : "s"(seq.tokens), "s"(sh.B), "s"(sh.G), "s"(topk), "s"(out.union_bits), "s"(out.union_shape), "s"(out.union_rows));   // (see Sequence)
+  const int P = min(seq.pages, NT * E);   // (the launcher picks NT * E >= the page limit)
+  const int M = min(n_act, sh.B) * sh.G;
   if (r_first >= M) return;
   if (!rows_known) load_row(raw, r_first);
   const int words = (sh.max_pages + 31) / 32;
@@ -993,7 +1002,9 @@ __global__ __launch_bounds__(1024) void pick_pages_kernel(const float* delta, co
   } else {
     my_delta = ra.delta[(size_t)b * B + min(lane, B - 1)];
   }
-  const int base = kv.page_indptr[b], P = min(seq_pages(kv, sh, b), NP), tokens = kv.seq_lens[b];
+  Sequence seq = sequence(kv, sh, b);
+  asm("" : "+s"(seq.base) : "s"(kv.page_indices), "s"(kv.meta), "s"(kv.num_pages), "s"(sh.Hkv));   // (see Sequence)
+  const int base = seq.base, P = min(seq.pages, NP), tokens = seq.tokens;
   int phys[TPW];
 #pragma unroll
   for (int t = 0; t < TPW; ++t) {   // the page whose metadata rows lane l16 feeds; -1: outside the pool
@@ -1179,14 +1190,14 @@ hipError_t launch_page_scores(hipStream_t st, int dtype, const KvView& kv, const
     dim3 mgrid((unsigned)((tiles + tpw - 1) / tpw), sh.Hkv, batch);
     if (sh.d == 128) {
       if (tpw == 1)
-        page_scores_mfma_kernel<128, 1><<<mgrid, 256, 0, st>>>(ra.delta, kv.page_indptr, kv.seq_lens, sh.B, kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, 1);
+        page_scores_mfma_kernel<128, 1><<<mgrid, 256, 0, st>>>(ra.delta, kv.page_indptr, kv.seq_lens, kv.page_indices, kv.meta, sh.B, sh.Hkv, kv.num_pages, sh.max_pages, kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, 1);
       else
-        page_scores_mfma_kernel<128, kMaxTilesPerWg><<<mgrid, 256, 0, st>>>(ra.delta, kv.page_indptr, kv.seq_lens, sh.B, kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, tpw);
+        page_scores_mfma_kernel<128, kMaxTilesPerWg><<<mgrid, 256, 0, st>>>(ra.delta, kv.page_indptr, kv.seq_lens, kv.page_indices, kv.meta, sh.B, sh.Hkv, kv.num_pages, sh.max_pages, kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, tpw);
     } else {
       if (tpw == 1)
-        page_scores_mfma_kernel<64, 1><<<mgrid, 256, 0, st>>>(ra.delta, kv.page_indptr, kv.seq_lens, sh.B, kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, 1);
+        page_scores_mfma_kernel<64, 1><<<mgrid, 256, 0, st>>>(ra.delta, kv.page_indptr, kv.seq_lens, kv.page_indices, kv.meta, sh.B, sh.Hkv, kv.num_pages, sh.max_pages, kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, 1);
       else
-        page_scores_mfma_kernel<64, kMaxTilesPerWg><<<mgrid, 256, 0, st>>>(ra.delta, kv.page_indptr, kv.seq_lens, sh.B, kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, tpw);
+        page_scores_mfma_kernel<64, kMaxTilesPerWg><<<mgrid, 256, 0, st>>>(ra.delta, kv.page_indptr, kv.seq_lens, kv.page_indices, kv.meta, sh.B, sh.Hkv, kv.num_pages, sh.max_pages, kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, tpw);
     }
   } else {
     (sh.d == 128 ? page_scores_f32_kernel<128> : page_scores_f32_kernel<64>)<<<grid, 256, 0, st>>>(

@@ -356,16 +356,18 @@ __device__ __forceinline__ void take_leading(const float* pm, const float* pl, c
 
 // Pages the partials of a head were dealt from.
 __device__ __forceinline__ int merged_pages(const AttnInputs& in, const KvView& kv, const Shape& sh, int b, int head) {
-  const int listed = *(in.sel_count ? in.sel_count + head : kv.seq_lens + b);   // (not behind a branch where there is a count)
-  return in.sel_count ? min(min(listed, in.cap), sh.max_pages) : seq_pages(kv, sh, b);
+  int listed = __builtin_amdgcn_readfirstlane(*(in.sel_count ? in.sel_count + head : kv.seq_lens + b));   // (not behind a branch where there is a count)
+  const Sequence seq = sequence(kv, sh, b);
+  asm("" : "+s"(listed) : "s"(seq.tokens), "s"(in.cap));   // (see Sequence)
+  const int all = seq.pages;
+  return in.sel_count ? min(min(listed, in.cap), sh.max_pages) : all;
 }
 
 // Every head's partials are laid out by fragments.  DENSE: every row, every page.
 template <int D, int WAVES, int PER, int KB, bool DENSE>
 __global__ __launch_bounds__(64 * WAVES) void attn_merge_fragments_kernel(const float* pm, const float* pl, const float* po, const int32_t* active_count, const int32_t* sel_count,
-                                                                    int part_rows, int nchunk, int kv_heads, KvView kv, Shape sh, AttnInputs in, Partials part,
-                                                                          float* __restrict__ o_p, float* __restrict__ lse_p,
-                                                                          int rows_known) {
+                                                                    int part_rows, int nchunk, int kv_heads, int rows_known, KvView kv, Shape sh, AttnInputs in, Partials part,
+                                                                          float* __restrict__ o_p, float* __restrict__ lse_p) {
   __shared__ __attribute__((aligned(16))) float lds[PER > 1 ? WAVES * kFragSlot : 4];
   take_leading(pm, pl, po, active_count, sel_count, part_rows, kv_heads, in, sh, part);
   const int j = blockIdx.y, b = blockIdx.z, head = b * sh.Hkv + j;
@@ -388,9 +390,8 @@ __global__ __launch_bounds__(64 * WAVES) void attn_merge_fragments_kernel(const 
 // wavefronts each (four chunks in flight, counts first: the plain form's registers and occupancy).
 template <int D, bool LOG2, int MIXED>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const float* pm, const float* pl, const float* po, const int32_t* active_count, const int32_t* sel_count,
-                                                         int part_rows, int nchunk, int kv_heads, KvView kv, Shape sh, AttnInputs in, Partials part,
-                                                         float* __restrict__ o_p, float* __restrict__ lse_p,
-                                                         int rows_known, int few_tile, int many_tile) {
+                                                         int part_rows, int nchunk, int kv_heads, int rows_known, KvView kv, Shape sh, AttnInputs in, Partials part,
+                                                         float* __restrict__ o_p, float* __restrict__ lse_p, int few_tile, int many_tile) {
   typedef typename std::conditional<LOG2, float, double>::type Acc;
   take_leading(pm, pl, po, active_count, sel_count, part_rows, kv_heads, in, sh, part);
   constexpr int C4 = D / 4, CL = 256 / C4;
@@ -432,11 +433,14 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* pm, const 
       po_s[k] = reinterpret_cast<const float4*>(part.o + prow * D)[c4];
     }
   }
+  __builtin_amdgcn_sched_barrier(0);   // nothing is fetched or waited for ahead of them
   // the token of this row, fetched alongside (its slot exists whatever the active count is)
-  const int tok_early = in.active_idx ? in.active_idx[(size_t)b * sh.B + min(r / sh.G, sh.B - 1)] : r / sh.G;
+  const int a = row_token(sh, min(r, sh.rows_max - 1));
+  const int tok_listed = *(in.active_idx ? in.active_idx + (size_t)b * sh.B + a : kv.seq_lens + b);   // (no branch around a load)
   const int M = min(active_rows(in, kv, sh, b), sh.rows_max), U = merged_pages(in, kv, sh, b, b * sh.Hkv + j);
+  const int tok_early = in.active_idx ? tok_listed : a;
   if (r >= min(M, part.rows)) return;
-  const int hg = r % sh.G;
+  const int hg = r - a * sh.G;
   const int tok = tok_early;   // r < M <= B*G here, so the index above was not clamped
   if ((unsigned)tok >= (unsigned)sh.B) return;
   const int ppt = (M <= kUnionRows ? few_tile : many_tile) / sh.g;
@@ -519,9 +523,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* pm, const 
 constexpr int kFewChunks = 8;
 template <int D, int KC, bool MIXED>
 __global__ __launch_bounds__(64 * (MIXED ? 4 : 1)) void attn_merge_few_kernel(const float* pm, const float* pl, const float* po, const int32_t* active_count, const int32_t* sel_count,
-                                                            int part_rows, int nchunk, int kv_heads, KvView kv, Shape sh, AttnInputs in, Partials part,
-                                                            float* __restrict__ o_p, float* __restrict__ lse_p,
-                                                            int rows_known, int few_tile, int many_tile) {
+                                                            int part_rows, int nchunk, int kv_heads, int rows_known, KvView kv, Shape sh, AttnInputs in, Partials part,
+                                                            float* __restrict__ o_p, float* __restrict__ lse_p, int few_tile, int many_tile) {
   constexpr int C4 = D / 4, WAVES = MIXED ? 4 : 1;
   take_leading(pm, pl, po, active_count, sel_count, part_rows, kv_heads, in, sh, part);
   const int tid = threadIdx.x, c4 = tid % C4, j = blockIdx.y, b = blockIdx.z;
@@ -547,8 +550,10 @@ __global__ __launch_bounds__(64 * (MIXED ? 4 : 1)) void attn_merge_few_kernel(co
     lk[k] = part.l[prow];
     x[k] = reinterpret_cast<const f32x4v_t*>(part.o + prow * D)[c4];
   }
+  __builtin_amdgcn_sched_barrier(0);   // nothing is fetched or waited for ahead of them
   const int a = row_token(sh, min(r, sh.rows_max - 1));
-  const int tok = in.active_idx ? in.active_idx[(size_t)b * sh.B + a] : a;
+  const int tok_listed = *(in.active_idx ? in.active_idx + (size_t)b * sh.B + a : kv.seq_lens + b);   // (no branch around a load)
+  const int tok = in.active_idx ? tok_listed : a;
   const int M = min(min(active_rows(in, kv, sh, b), sh.rows_max), part.rows), U = merged_pages(in, kv, sh, b, b * sh.Hkv + j);
   if (r >= M || (unsigned)tok >= (unsigned)sh.B) return;
   const int ppt = (M <= kUnionRows ? few_tile : many_tile) / sh.g;
@@ -621,7 +626,7 @@ hipError_t launch_attn_merge(hipStream_t st, const KvView& kv, const Shape& sh, 
   const int tiles = (rows + kPartialTile - 1) / kPartialTile, frags = sh.d / 8;
   if (few_tile == kManyRowStage) {   // every head's partials are laid out by fragments
     auto launch = [&](auto kern, int per_tile, int waves) {
-      kern<<<dim3(tiles * per_tile, sh.Hkv, batch), 64 * waves, 0, st>>>(part.m, part.l, part.o, in.active_count, in.sel_count, part.rows, nchunk, sh.Hkv, kv, sh, in, part, o_p, lse_p, known);
+      kern<<<dim3(tiles * per_tile, sh.Hkv, batch), 64 * waves, 0, st>>>(part.m, part.l, part.o, in.active_count, in.sel_count, part.rows, nchunk, sh.Hkv, known, kv, sh, in, part, o_p, lse_p);
     };
 #define LOSA_FRAGMENTS(W, PER, KB)                                                                                  \
   launch(sh.d == 128 ? (dense_step ? attn_merge_fragments_kernel<128, W, PER, KB, true>                             \
@@ -645,8 +650,8 @@ hipError_t launch_attn_merge(hipStream_t st, const KvView& kv, const Shape& sh, 
                       : (sh.d == 128 ? (nchunk <= 4 ? attn_merge_few_kernel<128, 4, false> : attn_merge_few_kernel<128, 8, false>)
                                      : (nchunk <= 4 ? attn_merge_few_kernel<64, 4, false> : attn_merge_few_kernel<64, 8, false>));
     const int waves = mixed ? 4 : 1, per_wg = waves * 256 / sh.d, few = ((mixed ? min(rows, kUnionRows) : rows) + per_wg - 1) / per_wg;
-    kern<<<dim3(mixed ? max(few, tiles * frags / 4) | 1 : few, sh.Hkv, batch), 64 * waves, 0, st>>>(part.m, part.l, part.o, in.active_count, in.sel_count, part.rows, nchunk, sh.Hkv, kv, sh, in, part, o_p, lse_p,
-                                                                                                  known, few_tile, many_tile);
+    kern<<<dim3(mixed ? max(few, tiles * frags / 4) | 1 : few, sh.Hkv, batch), 64 * waves, 0, st>>>(part.m, part.l, part.o, in.active_count, in.sel_count, part.rows, nchunk, sh.Hkv, known, kv, sh, in, part, o_p, lse_p,
+                                                                                                  few_tile, many_tile);
     return hipGetLastError();
   }
   // wavefronts per fragment in a mixed launch: with few chunks one, a quarter of the workgroups
@@ -658,7 +663,7 @@ hipError_t launch_attn_merge(hipStream_t st, const KvView& kv, const Shape& sh, 
   // (mixed: an odd width.  Most of its workgroups leave at once, and with a multiple of 8 the ones that stay meet on a
   // few of every die's compute units: 14 of 64 rows, 40 heads 6.8 us, of 65 5.4)
   kern<<<dim3(mixed ? max(min(rows, kUnionRows), tiles * frags * mixed / 4) | 1 : rows, sh.Hkv, batch), 256, 0, st>>>(
-      part.m, part.l, part.o, in.active_count, in.sel_count, part.rows, nchunk, sh.Hkv, kv, sh, in, part, o_p, lse_p, known, few_tile, many_tile);
+      part.m, part.l, part.o, in.active_count, in.sel_count, part.rows, nchunk, sh.Hkv, known, kv, sh, in, part, o_p, lse_p, few_tile, many_tile);
   return hipGetLastError();
 }
 

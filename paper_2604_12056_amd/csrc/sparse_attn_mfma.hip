@@ -139,7 +139,8 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
   [[maybe_unused]] int logical = 0;
   if constexpr (!UNION) logical = listed(list_position(0));
   const int M_raw = UNION ? min(in.active_count[b], sh.B) * sh.G : active_rows(in, kv, sh, b);
-  const int base = kv.page_indptr[b], P = seq_pages(kv, sh, b), tokens = kv.seq_lens[b];
+  const Sequence seq = sequence(kv, sh, b);
+  const int base = seq.base, P = seq.pages, tokens = seq.tokens;
   int U_raw;
   int pg_entry = 0;
   [[maybe_unused]] auto fetch_entry = [&]() {   // of page `logical`: its id; page and id are checked when it is decoded

@@ -621,7 +621,7 @@ __global__ __launch_bounds__(512) void attn_rows_kernel(const void* first, const
   // (the first list entries travel with the counts they are checked against)
   if constexpr (SRC == PageSource::list) logical = in.list[(size_t)head * in.cap + min(lp, (long)in.cap - 1)];
   const int M = min(active_rows(in, kv, sh, b), min(sh.rows_max, part.rows));
-  const int P = seq_pages(kv, sh, b);
+  const int P = sequence(kv, sh, b).pages;
   int U = P;
   if constexpr (SRC == PageSource::list) U = min(min(in.sel_count[head], in.cap), sh.max_pages);
   // nothing active, a row count another launch serves, or no row in this group
