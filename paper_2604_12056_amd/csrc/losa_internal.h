@@ -30,7 +30,8 @@ struct KvView {
 struct Shape {
   int32_t max_pages;   // row stride of the score matrix / bitmap sizing (config.max_pages_per_seq)
   int32_t rows_max;    // B * G: rows of one KV head when every token is active
-  int32_t Hkv, Hq, G, d, H, g, B;
+  int32_t g;           // (beside the two above, which are fetched with it)
+  int32_t Hkv, Hq, G, d, H, B;
   float sm_scale;
   uint32_t g_magic;    // ceil(2^32 / G), for row_token()
 };

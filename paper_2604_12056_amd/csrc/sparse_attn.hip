@@ -343,15 +343,16 @@ __device__ __forceinline__ void merge_fragments(const Shape& sh, const int32_t* 
 }
 
 // The leading arguments of the merge kernels (see KvView) put where the code reads them.
-__device__ __forceinline__ void take_leading(const float* pm, const float* pl, const float* po, const int32_t* active_count, const int32_t* sel_count,
-                                             int part_rows, int kv_heads, AttnInputs& in, Shape& sh, Partials& part) {
+__device__ __forceinline__ void take_leading(const float* pm, const float* pl, const float* po, const int32_t* active_count,
+                                             int part_rows, int kv_heads, int group, int block, AttnInputs& in, Shape& sh, Partials& part) {
   part.m = const_cast<float*>(pm);
   part.l = const_cast<float*>(pl);
   part.o = const_cast<float*>(po);
   part.rows = part_rows;
   in.active_count = active_count;
-  in.sel_count = sel_count;
   sh.Hkv = kv_heads;
+  sh.G = group;
+  sh.B = block;
 }
 
 // Pages the partials of a head were dealt from.
@@ -365,11 +366,11 @@ __device__ __forceinline__ int merged_pages(const AttnInputs& in, const KvView& 
 
 // Every head's partials are laid out by fragments.  DENSE: every row, every page.
 template <int D, int WAVES, int PER, int KB, bool DENSE>
-__global__ __launch_bounds__(64 * WAVES) void attn_merge_fragments_kernel(const float* pm, const float* pl, const float* po, const int32_t* active_count, const int32_t* sel_count,
-                                                                    int part_rows, int nchunk, int kv_heads, int rows_known, KvView kv, Shape sh, AttnInputs in, Partials part,
+__global__ __launch_bounds__(64 * WAVES) void attn_merge_fragments_kernel(const float* pm, const float* pl, const float* po, const int32_t* active_count,
+                                                                    int part_rows, int nchunk, int kv_heads, int rows_known, int group, int block, KvView kv, Shape sh, AttnInputs in, Partials part,
                                                                           float* __restrict__ o_p, float* __restrict__ lse_p) {
   __shared__ __attribute__((aligned(16))) float lds[PER > 1 ? WAVES * kFragSlot : 4];
-  take_leading(pm, pl, po, active_count, sel_count, part_rows, kv_heads, in, sh, part);
+  take_leading(pm, pl, po, active_count, part_rows, kv_heads, group, block, in, sh, part);
   const int j = blockIdx.y, b = blockIdx.z, head = b * sh.Hkv + j;
   const auto counts = [&](int& M, int& live) {
     M = min(DENSE ? sh.rows_max : min(active_rows(in, kv, sh, b), sh.rows_max), part.rows);
@@ -389,11 +390,11 @@ __global__ __launch_bounds__(64 * WAVES) void attn_merge_fragments_kernel(const 
 // MIXED (0: no): heads with more than 64 query rows have partials laid out by fragments; their workgroups take those, MIXED
 // wavefronts each (four chunks in flight, counts first: the plain form's registers and occupancy).
 template <int D, bool LOG2, int MIXED>
-__global__ __launch_bounds__(256) void attn_merge_kernel(const float* pm, const float* pl, const float* po, const int32_t* active_count, const int32_t* sel_count,
-                                                         int part_rows, int nchunk, int kv_heads, int rows_known, KvView kv, Shape sh, AttnInputs in, Partials part,
+__global__ __launch_bounds__(256) void attn_merge_kernel(const float* pm, const float* pl, const float* po, const int32_t* active_count,
+                                                         int part_rows, int nchunk, int kv_heads, int rows_known, int group, int block, KvView kv, Shape sh, AttnInputs in, Partials part,
                                                          float* __restrict__ o_p, float* __restrict__ lse_p, int few_tile, int many_tile) {
   typedef typename std::conditional<LOG2, float, double>::type Acc;
-  take_leading(pm, pl, po, active_count, sel_count, part_rows, kv_heads, in, sh, part);
+  take_leading(pm, pl, po, active_count, part_rows, kv_heads, group, block, in, sh, part);
   constexpr int C4 = D / 4, CL = 256 / C4;
   __shared__ __attribute__((aligned(16))) Acc red[CL][D];
   __shared__ Acc lred[CL];
@@ -423,14 +424,14 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* pm, const 
   float4 po_s[KSPEC];
   {
     const int cl = tid / C4, c4 = tid % C4;
-    const size_t item0 = ((size_t)b * sh.Hkv + j) * nchunk;
+    const uint32_t item0 = (uint32_t)(b * sh.Hkv + j) * nchunk;   // (rows of partials are counted in 32 bits: fewer than the bytes of them)
 #pragma unroll
     for (int k = 0; k < KSPEC; ++k) {
       const int c = min(cl + CL * k, nchunk - 1);
-      const size_t prow = (item0 + c) * part.rows + r;
+      const uint32_t prow = (item0 + c) * part.rows + r;
       pm_s[k] = part.m[prow];
       pl_s[k] = part.l[prow];
-      po_s[k] = reinterpret_cast<const float4*>(part.o + prow * D)[c4];
+      po_s[k] = reinterpret_cast<const float4*>(part.o + (size_t)prow * D)[c4];
     }
   }
   __builtin_amdgcn_sched_barrier(0);   // nothing is fetched or waited for ahead of them
@@ -522,11 +523,11 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* pm, const 
 // x 64 heads, 4 chunks 10.3 / 5.1 us; 112 rows 6.6 / 6.3).
 constexpr int kFewChunks = 8;
 template <int D, int KC, bool MIXED>
-__global__ __launch_bounds__(64 * (MIXED ? 4 : 1)) void attn_merge_few_kernel(const float* pm, const float* pl, const float* po, const int32_t* active_count, const int32_t* sel_count,
-                                                            int part_rows, int nchunk, int kv_heads, int rows_known, KvView kv, Shape sh, AttnInputs in, Partials part,
+__global__ __launch_bounds__(64 * (MIXED ? 4 : 1)) void attn_merge_few_kernel(const float* pm, const float* pl, const float* po, const int32_t* active_count,
+                                                            int part_rows, int nchunk, int kv_heads, int rows_known, int group, int block, KvView kv, Shape sh, AttnInputs in, Partials part,
                                                             float* __restrict__ o_p, float* __restrict__ lse_p, int few_tile, int many_tile) {
   constexpr int C4 = D / 4, WAVES = MIXED ? 4 : 1;
-  take_leading(pm, pl, po, active_count, sel_count, part_rows, kv_heads, in, sh, part);
+  take_leading(pm, pl, po, active_count, part_rows, kv_heads, group, block, in, sh, part);
   const int tid = threadIdx.x, c4 = tid % C4, j = blockIdx.y, b = blockIdx.z;
   const int r0 = blockIdx.x * (64 * WAVES / C4), r = r0 + tid / C4;
   if constexpr (MIXED) {
@@ -545,10 +546,10 @@ __global__ __launch_bounds__(64 * (MIXED ? 4 : 1)) void attn_merge_few_kernel(co
   f32x4v_t x[KC];
 #pragma unroll
   for (int k = 0; k < KC; ++k) {   // before it is known how many chunks are live: slots exist for all of them
-    const size_t prow = (((size_t)b * sh.Hkv + j) * nchunk + min(k, nchunk - 1)) * part.rows + min(r, part.rows - 1);
+    const uint32_t prow = ((uint32_t)(b * sh.Hkv + j) * nchunk + min(k, nchunk - 1)) * part.rows + min(r, part.rows - 1);   // (32 bits hold it)
     mk[k] = part.m[prow];
     lk[k] = part.l[prow];
-    x[k] = reinterpret_cast<const f32x4v_t*>(part.o + prow * D)[c4];
+    x[k] = reinterpret_cast<const f32x4v_t*>(part.o + (size_t)prow * D)[c4];
   }
   __builtin_amdgcn_sched_barrier(0);   // nothing is fetched or waited for ahead of them
   const int a = row_token(sh, min(r, sh.rows_max - 1));
@@ -626,7 +627,7 @@ hipError_t launch_attn_merge(hipStream_t st, const KvView& kv, const Shape& sh, 
   const int tiles = (rows + kPartialTile - 1) / kPartialTile, frags = sh.d / 8;
   if (few_tile == kManyRowStage) {   // every head's partials are laid out by fragments
     auto launch = [&](auto kern, int per_tile, int waves) {
-      kern<<<dim3(tiles * per_tile, sh.Hkv, batch), 64 * waves, 0, st>>>(part.m, part.l, part.o, in.active_count, in.sel_count, part.rows, nchunk, sh.Hkv, known, kv, sh, in, part, o_p, lse_p);
+      kern<<<dim3(tiles * per_tile, sh.Hkv, batch), 64 * waves, 0, st>>>(part.m, part.l, part.o, in.active_count, part.rows, nchunk, sh.Hkv, known, sh.G, sh.B, kv, sh, in, part, o_p, lse_p);
     };
 #define LOSA_FRAGMENTS(W, PER, KB)                                                                                  \
   launch(sh.d == 128 ? (dense_step ? attn_merge_fragments_kernel<128, W, PER, KB, true>                             \
@@ -650,7 +651,7 @@ hipError_t launch_attn_merge(hipStream_t st, const KvView& kv, const Shape& sh, 
                       : (sh.d == 128 ? (nchunk <= 4 ? attn_merge_few_kernel<128, 4, false> : attn_merge_few_kernel<128, 8, false>)
                                      : (nchunk <= 4 ? attn_merge_few_kernel<64, 4, false> : attn_merge_few_kernel<64, 8, false>));
     const int waves = mixed ? 4 : 1, per_wg = waves * 256 / sh.d, few = ((mixed ? min(rows, kUnionRows) : rows) + per_wg - 1) / per_wg;
-    kern<<<dim3(mixed ? max(few, tiles * frags / 4) | 1 : few, sh.Hkv, batch), 64 * waves, 0, st>>>(part.m, part.l, part.o, in.active_count, in.sel_count, part.rows, nchunk, sh.Hkv, known, kv, sh, in, part, o_p, lse_p,
+    kern<<<dim3(mixed ? max(few, tiles * frags / 4) | 1 : few, sh.Hkv, batch), 64 * waves, 0, st>>>(part.m, part.l, part.o, in.active_count, part.rows, nchunk, sh.Hkv, known, sh.G, sh.B, kv, sh, in, part, o_p, lse_p,
                                                                                                   few_tile, many_tile);
     return hipGetLastError();
   }
@@ -663,7 +664,7 @@ hipError_t launch_attn_merge(hipStream_t st, const KvView& kv, const Shape& sh, 
   // (mixed: an odd width.  Most of its workgroups leave at once, and with a multiple of 8 the ones that stay meet on a
   // few of every die's compute units: 14 of 64 rows, 40 heads 6.8 us, of 65 5.4)
   kern<<<dim3(mixed ? max(min(rows, kUnionRows), tiles * frags * mixed / 4) | 1 : rows, sh.Hkv, batch), 256, 0, st>>>(
-      part.m, part.l, part.o, in.active_count, in.sel_count, part.rows, nchunk, sh.Hkv, known, kv, sh, in, part, o_p, lse_p, few_tile, many_tile);
+      part.m, part.l, part.o, in.active_count, part.rows, nchunk, sh.Hkv, known, sh.G, sh.B, kv, sh, in, part, o_p, lse_p, few_tile, many_tile);
   return hipGetLastError();
 }
 
