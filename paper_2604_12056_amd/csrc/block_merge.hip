@@ -202,6 +202,7 @@ __global__ __launch_bounds__(128 * NTILE) void block_merge_mfma_kernel(const bf1
   bm_f32x4_t op[NT];
 #pragma unroll
   for (int nt = 0; nt < NT; ++nt) op[nt] = *reinterpret_cast<const bm_f32x4_t*>(o_p + orow_early * D + c0 + nt * 16 + 4 * qd);
+  __builtin_amdgcn_sched_barrier(0);   // all loads leave before the first is waited for (left alone, the values' wait for the keys)
 
   const float scale_log2e = sh.sm_scale * 1.4426950408889634f;
   float s[NTILE][8];
