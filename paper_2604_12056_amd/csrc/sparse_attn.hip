@@ -364,6 +364,19 @@ __device__ __forceinline__ int merged_pages(const AttnInputs& in, const KvView& 
   return in.sel_count ? min(min(listed, in.cap), sh.max_pages) : all;
 }
 
+// Query rows of a KV head (up to what partials hold) and the pages they were dealt, from one scalar round trip.
+struct RowsPages {
+  int rows, pages;
+};
+__device__ __forceinline__ RowsPages rows_and_pages(const AttnInputs& in, const KvView& kv, const Shape& sh, const Partials& part, int b, int head) {
+  int n = __builtin_amdgcn_readfirstlane((in.active_count ? in.active_count : kv.seq_lens)[b]);
+  int listed = __builtin_amdgcn_readfirstlane(*(in.sel_count ? in.sel_count + head : kv.seq_lens + b));
+  const Sequence seq = sequence(kv, sh, b);
+  asm("" : "+s"(n), "+s"(listed) : "s"(seq.tokens));   // (see Sequence)
+  return {min(min((in.active_count ? min(n, sh.B) : sh.B) * sh.G, sh.rows_max), part.rows),
+          in.sel_count ? min(min(listed, in.cap), sh.max_pages) : seq.pages};
+}
+
 // Every head's partials are laid out by fragments.  DENSE: every row, every page.
 template <int D, int WAVES, int PER, int KB, bool DENSE>
 __global__ __launch_bounds__(64 * WAVES) void attn_merge_fragments_kernel(const float* pm, const float* pl, const float* po, const int32_t* active_count,
@@ -373,8 +386,9 @@ __global__ __launch_bounds__(64 * WAVES) void attn_merge_fragments_kernel(const 
   take_leading(pm, pl, po, active_count, part_rows, kv_heads, group, block, in, sh, part);
   const int j = blockIdx.y, b = blockIdx.z, head = b * sh.Hkv + j;
   const auto counts = [&](int& M, int& live) {
-    M = min(DENSE ? sh.rows_max : min(active_rows(in, kv, sh, b), sh.rows_max), part.rows);
-    const int pages = DENSE ? seq_pages(kv, sh, b) : merged_pages(in, kv, sh, b, head), pps = kManyRowStage / sh.g;
+    const RowsPages rp = rows_and_pages(in, kv, sh, part, b, head);
+    M = DENSE ? min(sh.rows_max, part.rows) : rp.rows;
+    const int pages = DENSE ? sequence(kv, sh, b).pages : rp.pages, pps = kManyRowStage / sh.g;
     live = min(nchunk, (pages + pps - 1) / pps);
   };
   if (!DENSE && !rows_known && (int)blockIdx.x / (D / 8 / (WAVES / PER)) * kPartialTile >= active_rows(in, kv, sh, b)) return;   // surplus workgroup
@@ -436,11 +450,15 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* pm, const 
   }
   __builtin_amdgcn_sched_barrier(0);   // nothing is fetched or waited for ahead of them
   // the token of this row, fetched alongside (its slot exists whatever the active count is)
-  const int a = row_token(sh, min(r, sh.rows_max - 1));
+  int row = min(r, sh.rows_max - 1);
+  asm("" : "+s"(row) : "s"(kv.page_indptr), "s"(kv.seq_lens), "s"(in.sel_count), "s"(in.cap), "s"(in.active_idx), "s"(sh.g_magic), "s"(few_tile),
+      "s"(many_tile), "s"(o_p), "s"(lse_p));   // (see Sequence)
+  const int a = row_token(sh, row);
   const int tok_listed = *(in.active_idx ? in.active_idx + (size_t)b * sh.B + a : kv.seq_lens + b);   // (no branch around a load)
-  const int M = min(active_rows(in, kv, sh, b), sh.rows_max), U = merged_pages(in, kv, sh, b, b * sh.Hkv + j);
+  const RowsPages rp = rows_and_pages(in, kv, sh, part, b, b * sh.Hkv + j);
+  const int M = rp.rows, U = rp.pages;
   const int tok_early = in.active_idx ? tok_listed : a;
-  if (r >= min(M, part.rows)) return;
+  if (r >= M) return;
   const int hg = r - a * sh.G;
   const int tok = tok_early;   // r < M <= B*G here, so the index above was not clamped
   if ((unsigned)tok >= (unsigned)sh.B) return;
@@ -552,10 +570,14 @@ __global__ __launch_bounds__(64 * (MIXED ? 4 : 1)) void attn_merge_few_kernel(co
     x[k] = reinterpret_cast<const f32x4v_t*>(part.o + (size_t)prow * D)[c4];
   }
   __builtin_amdgcn_sched_barrier(0);   // nothing is fetched or waited for ahead of them
-  const int a = row_token(sh, min(r, sh.rows_max - 1));
+  int last_row = sh.rows_max - 1;
+  asm("" : "+s"(last_row) : "s"(kv.page_indptr), "s"(kv.seq_lens), "s"(in.sel_count), "s"(in.cap), "s"(in.active_idx), "s"(sh.g_magic), "s"(few_tile),
+      "s"(many_tile), "s"(o_p), "s"(lse_p));   // (see Sequence)
+  const int a = row_token(sh, min(r, last_row));
   const int tok_listed = *(in.active_idx ? in.active_idx + (size_t)b * sh.B + a : kv.seq_lens + b);   // (no branch around a load)
   const int tok = in.active_idx ? tok_listed : a;
-  const int M = min(min(active_rows(in, kv, sh, b), sh.rows_max), part.rows), U = merged_pages(in, kv, sh, b, b * sh.Hkv + j);
+  const RowsPages rp = rows_and_pages(in, kv, sh, part, b, b * sh.Hkv + j);
+  const int M = rp.rows, U = rp.pages;
   if (r >= M || (unsigned)tok >= (unsigned)sh.B) return;
   const int ppt = (M <= kUnionRows ? few_tile : many_tile) / sh.g;
   const int live = min(nchunk, (U + ppt - 1) / ppt);

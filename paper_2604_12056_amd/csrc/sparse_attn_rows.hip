@@ -93,7 +93,7 @@ enum class PageSource { all, list, own };
 // second 32-token block of every stage instead of idling; the two halves meet through LDS at the end.
 template <int D, int GP, bool HALF, int TG, PageSource SRC>
 __device__ __forceinline__ void attn_rows_body(int nchunk, int row_group, int j, const Shape& sh,
-                                               const KvView& kv, const Partials& part, float scale_log2e, int M, int U, int P,
+                                               const KvView& kv, const Partials& part, float scale_log2e, int M, int U, const Sequence& seq,
                                                const AttnInputs& in, const uint16_t* own, int logical, int entry, unsigned char* lds) {
   typedef StageImage<D, GP> Img;
   constexpr int KS = D / 16;            // k-steps of the score product
@@ -119,8 +119,8 @@ __device__ __forceinline__ void attn_rows_body(int nchunk, int row_group, int j,
   // Page entries, one per lane and batch of SPF stages: position in the list -> logical page -> page table, each step
   // requested a stage before the next needs it.
   int next_logical = logical, next_entry = entry, pg_phys = 0, pg_valid = 0;
-  const int32_t* table = kv.page_indices + kv.page_indptr[b];
-  const int tokens = kv.seq_lens[b];
+  const int32_t* table = kv.page_indices + seq.base;
+  const int tokens = seq.tokens, P = seq.pages;
   auto list_position = [&](int first_stage) {
     return ((long)chunk + (long)(first_stage + lane / PPS) * nchunk) * PPS + lane % PPS;
   };
@@ -620,10 +620,15 @@ __global__ __launch_bounds__(512) void attn_rows_kernel(const void* first, const
   int logical = (int)min(lp, (long)sh.max_pages);
   // (the first list entries travel with the counts they are checked against)
   if constexpr (SRC == PageSource::list) logical = in.list[(size_t)head * in.cap + min(lp, (long)in.cap - 1)];
-  const int M = min(active_rows(in, kv, sh, b), min(sh.rows_max, part.rows));
-  const int P = sequence(kv, sh, b).pages;
+  int n = __builtin_amdgcn_readfirstlane((in.active_count ? in.active_count : kv.seq_lens)[b]), listed = 0;
+  if constexpr (SRC == PageSource::list) listed = __builtin_amdgcn_readfirstlane(in.sel_count[head]);
+  const Sequence seq = sequence(kv, sh, b);
+  asm("" : "+s"(n), "+s"(listed) : "s"(seq.tokens), "s"(kv.page_indices), "s"(kv.k_pages), "s"(kv.v_pages), "s"(kv.num_pages), "s"(in.q),
+      "s"(in.active_idx), "s"(sh.G), "s"(sh.g_magic), "s"(sh.B), "s"(part.rows), "s"(m_lo));   // (see Sequence)
+  const int M = min((in.active_count ? min(n, sh.B) : sh.B) * sh.G, min(sh.rows_max, part.rows));
+  const int P = seq.pages;
   int U = P;
-  if constexpr (SRC == PageSource::list) U = min(min(in.sel_count[head], in.cap), sh.max_pages);
+  if constexpr (SRC == PageSource::list) U = min(min(listed, in.cap), sh.max_pages);
   // nothing active, a row count another launch serves, or no row in this group
   if (M <= max(m_lo, row_group * kRowGroup)) return;
   uint16_t* own = reinterpret_cast<uint16_t*>(stage_lds + kImages * StageImage<D, GP>::kBytes);
@@ -635,11 +640,11 @@ __global__ __launch_bounds__(512) void attn_rows_kernel(const void* first, const
   const int stages = (U + PPS - 1) / PPS;
   if ((int)blockIdx.x >= stages) return;
   if constexpr (SRC == PageSource::own) logical = own[min(lane / PPS, (stages - 1 - (int)blockIdx.x) / nchunk) * PPS + lane % PPS];
-  const int entry = P > 0 ? kv.page_indices[kv.page_indptr[b] + max(0, min(logical, P - 1))] : 0;
+  const int entry = P > 0 ? kv.page_indices[seq.base + max(0, min(logical, P - 1))] : 0;
   if (M <= 128)
-    attn_rows_body<D, GP, HALF, 2, SRC>(nchunk, row_group, j, sh, kv, part, scale_log2e, M, U, P, in, own, logical, entry, stage_lds);
+    attn_rows_body<D, GP, HALF, 2, SRC>(nchunk, row_group, j, sh, kv, part, scale_log2e, M, U, seq, in, own, logical, entry, stage_lds);
   else
-    attn_rows_body<D, GP, HALF, 1, SRC>(nchunk, row_group, j, sh, kv, part, scale_log2e, M, U, P, in, own, logical, entry, stage_lds);
+    attn_rows_body<D, GP, HALF, 1, SRC>(nchunk, row_group, j, sh, kv, part, scale_log2e, M, U, seq, in, own, logical, entry, stage_lds);
 }
 
 template <int D, int GP, bool HALF, PageSource SRC>
