@@ -131,10 +131,10 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
     }
   }
   auto list_position = [&](int first_local_tile) {
-    return ((long)tfirst + (long)(first_local_tile + lane / PPT) * tstep) * PPT + lane % PPT;
+    return (tfirst + (first_local_tile + lane / PPT) * tstep) * PPT + lane % PPT;   // (below 64 x 4096 past a list of 16384)
   };
-  auto listed = [&](long lp) {   // logical page at a position of the list (inside the array whatever the list's length is)
-    return in.list ? in.list[(size_t)head * in.cap + min(lp, (long)in.cap - 1)] : (int)min(lp, (long)sh.max_pages);
+  auto listed = [&](int lp) {   // logical page at a position of the list (inside the array whatever the list's length is)
+    return in.list ? in.list[(size_t)head * in.cap + min(lp, in.cap - 1)] : min(lp, sh.max_pages);
   };
   [[maybe_unused]] int logical = 0;
   if constexpr (!UNION) logical = listed(list_position(0));
@@ -275,14 +275,14 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
   // ---- decoded page entries of this wavefront's next 64 pages, one per lane
   int pg_phys = 0, pg_valid = 0;
   auto decode_entries = [&](int first_local_tile) {
-    const long lp = list_position(first_local_tile);
+    const int lp = list_position(first_local_tile);
     if constexpr (UNION) {
       // the page of rank lp in the union: the last bitmap word whose rank is <= lp, then the
       // (lp - rank)-th set bit of that word; its physical id comes from the page table
       int page = 0;
       const bool want = lp < U;
       if (want) {
-        int lo = 0, k = (int)lp;
+        int lo = 0, k = lp;
         // four ways a step (three LDS reads at once): 3 steps for 64 words; the trip count is uniform over the wavefront
         for (int step = u_words <= 64 ? 16 : u_words <= 256 ? 64 : 256; step; step >>= 2) {
           int below = 0;
@@ -570,7 +570,7 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
 #pragma unroll
   for (int mt = 0; mt < R; ++mt) l_run[mt] = sum_over_lane_groups(l_run[mt]);
 
-  const size_t item = ((size_t)head * nchunk + chunk);
+  const uint32_t item = (uint32_t)head * nchunk + chunk;   // (32 bits hold the rows of all partials)
   if (SPLIT_PAGES) {
     // ---- one-round combine of the 4 wavefronts: wavefront w owns channel tiles {w*NTW ..} of
     // the partial.  Everyone publishes (ref, sum) and the O tiles it does NOT own in LDS (its
@@ -630,7 +630,7 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
         }
         const int rg = mt * 16 + l16;
         if (rg < M) {
-          const size_t prow = item * part.rows + rg;
+          const uint32_t prow = item * part.rows + rg;
           if (W == 0 && qd == 0) {
             // (streaming stores: the partials are read once, by the next launch; leaving them out of the
             // caches' write-back at the kernel's end measured 0.3 us per step at 48 MB launches)
@@ -642,7 +642,7 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
             f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int w = 0; w < 4; ++w) acc += ov[mt][k][w] * wgt[w];
-            __builtin_nontemporal_store(acc, reinterpret_cast<f32x4_t*>(part.o + prow * D + (W * NTW + k) * 16 + qd * 4));
+            __builtin_nontemporal_store(acc, reinterpret_cast<f32x4_t*>(part.o + (size_t)prow * D + (W * NTW + k) * 16 + qd * 4));
           }
         }
       }
@@ -668,14 +668,14 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
   for (int mt = 0; mt < R; ++mt) {
     const int rg = rb * (R * 16) + mt * 16 + l16;
     if (rg < M) {
-      const size_t prow = item * part.rows + rg;
+      const uint32_t prow = item * part.rows + rg;
       if (qd == 0) {
         part.m[prow] = m_run[mt];
         part.l[prow] = l_run[mt];
       }
 #pragma unroll
       for (int nt = 0; nt < NT; ++nt)
-        *reinterpret_cast<f32x4_t*>(part.o + prow * D + nt * 16 + qd * 4) = o[mt][nt];
+        *reinterpret_cast<f32x4_t*>(part.o + (size_t)prow * D + nt * 16 + qd * 4) = o[mt][nt];
     }
   }
 }
