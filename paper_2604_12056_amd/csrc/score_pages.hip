@@ -130,34 +130,43 @@ __global__ __launch_bounds__(256) void page_scores_f32_kernel(KvView kv, Shape s
   int tok[QV];
   auto load_tokens = [&](int r0) {
 #pragma unroll
-    for (int k = 0; k < QV; ++k) tok[k] = active_idx[(size_t)b * sh.B + min((r0 + (tid + 256 * k) / VPR) / sh.G, sh.B - 1)];
+    for (int k = 0; k < QV; ++k) tok[k] = active_idx[(size_t)b * sh.B + row_token(sh, min(r0 + (tid + 256 * k) / VPR, sh.rows_max - 1))];
   };
   auto load_queries = [&](int r0) {
 #pragma unroll
     for (int k = 0; k < QV; ++k) {
-      const int r = r0 + (tid + 256 * k) / VPR, cv = (tid + 256 * k) % VPR;
+      const int r = min(r0 + (tid + 256 * k) / VPR, sh.rows_max - 1), cv = (tid + 256 * k) % VPR;
       const int tc = (unsigned)tok[k] < (unsigned)sh.B ? tok[k] : 0;
-      qv[k] = reinterpret_cast<const float4*>(q + (((size_t)b * sh.B + tc) * sh.Hq + j * sh.G + r % sh.G) * D)[cv];
+      qv[k] = reinterpret_cast<const float4*>(q + (((size_t)b * sh.B + tc) * sh.Hq + j * sh.G + (r - row_token(sh, r) * sh.G)) * D)[cv];
     }
   };
   load_tokens(0);
-  const int base = kv.page_indptr[b];
-  const int P = seq_pages(kv, sh, b);
-  const int n = min(active_count[b], sh.B);
-  const int M = n * sh.G;
-  if (blockIdx.x == 0 && tid == 0) aux.reset(b * sh.Hkv + j, M);
-  if (p0 >= P) return;
-  if (M <= 0) return;
-  load_queries(0);
+  int n = __builtin_amdgcn_readfirstlane(active_count[b]);
+  const Sequence seq = sequence(kv, sh, b);
+  asm("" : "+s"(n) : "s"(seq.tokens), "s"(kv.page_indices), "s"(kv.meta), "s"(kv.num_pages), "s"(sh.Hkv), "s"(sh.B), "s"(sh.G), "s"(q));   // (see Sequence)
+  const int base = seq.base, P = seq.pages, M = min(n, sh.B) * sh.G;
+  if (p0 >= P || M <= 0) {
+    if (blockIdx.x == 0 && tid == 0) aux.reset(b * sh.Hkv + j, M);
+    return;
+  }
   int phys[MV];
 #pragma unroll
   for (int k = 0; k < MV; ++k) phys[k] = kv.page_indices[base + min(p0 + (tid + 256 * k) / (2 * VPR), P - 1)];
+  load_queries(0);
+  __builtin_amdgcn_sched_barrier(0);
+  if (blockIdx.x == 0 && tid == 0) aux.reset(b * sh.Hkv + j, M);   // (behind the loads: a wait for one of them would be one for this store)
+  float4 mv[MV];   // all requested before the first is waited for
+#pragma unroll
+  for (int k = 0; k < MV; ++k) {
+    const int v = tid + 256 * k, rem = v % (2 * VPR), which = rem / VPR, cv = rem % VPR;
+    const bool ok = (unsigned)phys[k] < (unsigned)kv.num_pages;
+    mv[k] = reinterpret_cast<const float4*>((const float*)kv.meta + (((size_t)(ok ? phys[k] : 0) * sh.Hkv + j) * 2 + which) * D)[cv];
+  }
 #pragma unroll
   for (int k = 0; k < MV; ++k) {
     const int v = tid + 256 * k, pg = v / (2 * VPR), rem = v % (2 * VPR), which = rem / VPR, cv = rem % VPR;
     const bool ok = (unsigned)phys[k] < (unsigned)kv.num_pages;
-    const float4 f = reinterpret_cast<const float4*>((const float*)kv.meta + (((size_t)(ok ? phys[k] : 0) * sh.Hkv + j) * 2 + which) * D)[cv];
-    *reinterpret_cast<float4*>(which ? &mx[pg][cv * 4] : &mn[pg][cv * 4]) = ok ? f : make_float4(0.f, 0.f, 0.f, 0.f);
+    *reinterpret_cast<float4*>(which ? &mx[pg][cv * 4] : &mn[pg][cv * 4]) = ok ? mv[k] : make_float4(0.f, 0.f, 0.f, 0.f);
   }
 
   const int pg = tid % PT, rs = tid / PT;   // rows rs and rs + 32 of the staged ones
