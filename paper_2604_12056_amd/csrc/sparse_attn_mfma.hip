@@ -127,24 +127,34 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
 #pragma unroll
     for (int mt = 0; mt < R; ++mt) {
       const int a = row_token(sh, min(rb * (R * 16) + mt * 16 + l16, sh.rows_max - 1));
-      tok[mt] = in.active_idx ? in.active_idx[(size_t)b * sh.B + a] : a;
+      const int at = *(in.active_idx ? in.active_idx + (size_t)b * sh.B + a : kv.seq_lens + b);   // (no branch around a load: what
+      tok[mt] = in.active_idx ? at : a;                                                            // joins behind one waits for it)
     }
   }
   auto list_position = [&](int first_local_tile) {
     return (tfirst + (first_local_tile + lane / PPT) * tstep) * PPT + lane % PPT;   // (below 64 x 4096 past a list of 16384)
   };
   auto listed = [&](int lp) {   // logical page at a position of the list (inside the array whatever the list's length is)
-    return in.list ? in.list[(size_t)head * in.cap + min(lp, in.cap - 1)] : min(lp, sh.max_pages);
+    const int at = *(in.list ? in.list + (size_t)head * in.cap + min(lp, in.cap - 1) : kv.seq_lens + b);
+    return in.list ? at : min(lp, sh.max_pages);
   };
   [[maybe_unused]] int logical = 0;
   if constexpr (!UNION) logical = listed(list_position(0));
-  const int M_raw = UNION ? min(in.active_count[b], sh.B) * sh.G : active_rows(in, kv, sh, b);
+  // counts, the sequence and (lists; the union has its own place) the arguments that the way to the first tile needs: see Sequence
+  int n_act = __builtin_amdgcn_readfirstlane((in.active_count ? in.active_count : kv.seq_lens)[b]), n_listed = 0;
+  if constexpr (!UNION) n_listed = __builtin_amdgcn_readfirstlane(*(in.list ? in.sel_count + head : kv.seq_lens + b));
   const Sequence seq = sequence(kv, sh, b);
+  if constexpr (UNION)
+    asm("" : "+s"(n_act) : "s"(seq.tokens));
+  else
+    asm("" : "+s"(n_act), "+s"(n_listed) : "s"(seq.tokens), "s"(kv.page_indices), "s"(kv.num_pages), "s"(kv.k_pages), "s"(kv.v_pages), "s"(in.q),
+        "s"(sh.rows_max), "s"(part.rows), "s"(sh.Hq), "s"(m_lo), "s"(m_hi));
+  const int M_raw = (in.active_count ? min(n_act, sh.B) : sh.B) * sh.G;
   const int base = seq.base, P = seq.pages, tokens = seq.tokens;
   int U_raw;
   int pg_entry = 0;
   [[maybe_unused]] auto fetch_entry = [&]() {   // of page `logical`: its id; page and id are checked when it is decoded
-    if (P > 0) pg_entry = kv.page_indices[base + max(0, min(logical, P - 1))];
+    pg_entry = *(P > 0 ? kv.page_indices + base + max(0, min(logical, P - 1)) : kv.seq_lens + b);   // (an empty sequence has none)
   };
   // UNION: words and ranks of the head's union, in this wavefront's own merge slot; the page table behind the slots
   [[maybe_unused]] uint32_t* u_bits = reinterpret_cast<uint32_t*>(lds + (SPLIT_PAGES ? wave : 0) * kSlotStride);
@@ -218,7 +228,7 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
     }
     U_raw = total;
   } else {
-    U_raw = in.list ? min(in.sel_count[head], in.cap) : P;
+    U_raw = in.list ? min(n_listed, in.cap) : P;
     fetch_entry();
   }
   const int U = min(U_raw, sh.max_pages);
