@@ -3,6 +3,7 @@ validation reports errors without touching a GPU."""
 import ctypes as C
 import os
 import re
+import struct
 
 import pytest
 
@@ -30,6 +31,41 @@ def test_every_declared_symbol_is_exported(lib):
     assert set(names) == set(binding.EXPORTS)
     for n in names:
         assert getattr(lib, n) is not None
+
+
+def _kernels_of(path):
+    """{kernel: its metadata} of the library's device code: every bundle's code objects, their notes named "AMDGPU"."""
+    msgpack, kernels = pytest.importorskip("msgpack"), {}
+    data = open(path, "rb").read()
+    for at in (m.start() for m in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", data)):
+        entry = at + 32
+        for _ in range(int.from_bytes(data[at + 24:at + 32], "little")):
+            offset, size, name = struct.unpack_from("<QQQ", data, entry)
+            triple = data[entry + 24:entry + 24 + name]
+            entry += 24 + name
+            if not triple.startswith(b"hip"):
+                continue
+            elf = data[at + offset:at + offset + size]
+            headers, = struct.unpack_from("<Q", elf, 32)
+            each, count = struct.unpack_from("<HH", elf, 54)
+            for header in (headers + i * each for i in range(count)):
+                kind, _, note, _, _, length = struct.unpack_from("<IIQQQQ", elf, header)
+                end = note + length
+                while kind == 4 and note < end:      # PT_NOTE
+                    name_bytes, text_bytes, note_kind = struct.unpack_from("<III", elf, note)
+                    text = note + 12 + (name_bytes + 3 & ~3)
+                    if note_kind == 32 and elf[note + 12:note + 18] == b"AMDGPU":
+                        meta = msgpack.unpackb(elf[text:text + text_bytes], strict_map_key=False)
+                        kernels.update((k[".name"], k) for k in meta["amdhsa.kernels"])
+                    note = text + (text_bytes + 3 & ~3)
+    return kernels
+
+
+def test_no_kernel_needs_scratch_memory(lib):
+    """A register file that is one or two registers short costs every launch of a kernel its scratch memory."""
+    kernels = _kernels_of(binding.LIB_PATH)
+    assert len(kernels) > 100
+    assert not {n: k[".private_segment_fixed_size"] for n, k in kernels.items() if k[".private_segment_fixed_size"]}
 
 
 def _cfg(**kw):
