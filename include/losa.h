@@ -239,8 +239,9 @@ losa_status losa_block_merge(losa_ctx* ctx, void* stream, int32_t batch, const v
  * Each has a default chosen by measurement on MI355X; tests
  * use them to drive the code paths a workload of their size would not reach.  A value takes
  * effect with the next call on the context.
- *   LOSA_TUNE_ATTN_WORKGROUPS   : attention workgroups aimed at per launch (default 256: one per
- *                                 compute unit); 1..1024
+ *   LOSA_TUNE_ATTN_WORKGROUPS   : attention workgroups aimed at per launch; 1..1024 (default 256: one per
+ *                                 compute unit, and up to 64 query rows per KV head fewer where a prefix
+ *                                 does not pay for so many; any other number is aimed at as it is)
  *   LOSA_TUNE_SELECT_ROUND      : selection workgroups counted as one round of the machine; a grid
  *                                 beyond it gives each workgroup up to four query rows, eight where the
  *                                 union list is built (0: default).  While it is set, short prefixes are

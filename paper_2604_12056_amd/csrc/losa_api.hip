@@ -81,7 +81,7 @@ struct losa_ctx {
   Partials part;
   long part_rows;           // capacity of the partial buffers in (work item, row) pairs
   long target_workgroups;   // attention workgroups aimed at per launch ...
-  bool shares_set = false;  // ... by the caller: no rule on the shares' sizes beside it
+  bool shares_set = false;  // ... other than by default: no rule on the shares' sizes beside it
   long select_round;        // selection workgroups per round (0: from the kernel's occupancy)
   long score_round;         // scoring workgroups the machine takes in one round
   bool rank_in_scores;      // losa_step lets the scoring kernel rank the locality scores
@@ -515,7 +515,7 @@ losa_status losa_set_tuning(losa_ctx* ctx, losa_tuning knob, int64_t value) {
       if (value < 1 || value > kTargetItems)
         return fail(ctx, LOSA_ERR_INVALID_ARG, "attention workgroups must be in 1..%ld", kTargetItems);
       ctx->target_workgroups = (long)value;
-      ctx->shares_set = true;
+      ctx->shares_set = value != kTargetWorkgroups;
       return LOSA_OK;
     case LOSA_TUNE_SELECT_ROUND:
       if (value < 0) return fail(ctx, LOSA_ERR_INVALID_ARG, "selection round must be >= 0");

@@ -47,6 +47,26 @@ class Rig:
         self.ctx.close()
 
 
+def workspace_parts(ctx) -> dict:
+    """{name: bytes of the workspace (a view)} as losa_create carves it: which buffers a call wrote tells which launches it made."""
+    c = ctx.cfg
+    G, heads, tokens = c.num_q_heads // c.num_kv_heads, c.max_batch * c.num_kv_heads, c.max_batch * c.block_size
+    rows, pages = c.block_size * G, c.max_pages_per_seq
+    part_rows = max(1024 * min(rows, 64), max(heads, 256) * ((rows + 31) // 32 * 32))
+    copy_words = 16 if pages <= 512 else 32 if pages <= 1024 else ((pages + 31) // 32 + 3) // 4 * 4
+    copies = 256 // copy_words if copy_words <= 32 else 1 if rows <= 64 else 2 if rows <= 128 else 4 if rows <= 256 else 8
+    sizes = {"delta": tokens * 4, "mask": tokens, "active_idx": tokens * 4, "active_count": c.max_batch * 4, "scores": heads * rows * pages * 4,
+             "rowmaps": heads * rows * ((pages + 31) // 32) * 4, "tickets": heads * 4, "sel_pages": heads * pages * 4, "sel_count": heads * 4,
+             "partial_o": part_rows * c.head_dim * 4, "partial_m": part_rows * 4, "partial_l": part_rows * 4, "entries": heads * pages * 4,
+             "q_act": heads * rows * c.head_dim * 2, "seq_tickets": c.max_batch * 4, "union_bits": heads * max(256, copy_words * copies) * 4}
+    assert sum(-(-n // 256) * 256 for n in sizes.values()) == L.losa_workspace_bytes(c), "the library carves its workspace in another way"
+    at, parts = (-ctx.workspace.data_ptr()) % 256, {}
+    for name, n in sizes.items():
+        parts[name] = ctx.workspace[at:at + n]
+        at += -(-n // 256) * 256
+    return parts
+
+
 def check_near_tie_sets(got: set, want: set, value64, K_eff: int, what: str) -> int:
     """Two picked sets may differ only in items whose float64 value is within NEAR_TIE of the
     K-th largest.  Returns the number of differing items."""

@@ -10,7 +10,8 @@ from paper_2604_12056_amd import binding as L
 from paper_2604_12056_amd import synth
 from paper_2604_12056_amd.device_inputs import config_of, to_host
 
-from parity_util import Rig, check_page_bounds, check_sparse_attn, compare_state, gpu_union_of, oracle_selection, run_steps_end_to_end
+from parity_util import (Rig, check_page_bounds, check_sparse_attn, compare_state, gpu_union_of, oracle_selection, run_steps_end_to_end,
+                         workspace_parts)
 
 pytestmark = pytest.mark.gpu
 
@@ -711,3 +712,45 @@ def test_scoring_and_selection_in_one_launch(P, B, G, H):
                     assert err * weight.sum() <= 0.25 * min(last, g), (mode, n, K, b)
     finally:
         ctx.close()
+
+
+class OnePagePrefix:
+    """One sequence whose pages are all the same few, for launches over prefixes of any length: the values of a physical page are its
+    number, so a dense step's output is known."""
+
+    def __init__(self, tokens, B, G, Hkv, d, g):
+        ints, self.heads, self.rows = (lambda *x: torch.tensor(x, dtype=torch.int32, device="cuda")), Hkv, B * G
+        P = -(-tokens // g)
+        ids = torch.arange(P, dtype=torch.int32, device="cuda") % 7
+        v = torch.arange(7, device="cuda", dtype=torch.bfloat16)[:, None, None, None].expand(7, Hkv, d, g).contiguous()
+        zeros = lambda *shape: torch.zeros(shape, device="cuda", dtype=torch.bfloat16)
+        self.kv = L.PagedKV(zeros(7, Hkv, g, d), v, zeros(7, Hkv, 2, d), ints(0, P), ids, ints(tokens), max_seq_pages=P)
+        self.ctx = L.losa_create(L.make_config(max_batch=1, num_q_heads=Hkv * G, num_kv_heads=Hkv, head_dim=d, hidden_size=64, page_size=g,
+                                               block_size=B, max_pages_per_seq=P, max_topk_pages=1), "cuda:0")
+        weights = torch.full((P,), float(g), dtype=torch.float64, device="cuda")
+        weights[-1] = tokens - (P - 1) * g
+        self.mean, self.tokens = float((ids.double() * weights).sum() / tokens), tokens
+        self.q, self.o_p = zeros(B, Hkv * G, d), torch.zeros((B, Hkv * G, d), device="cuda")
+        self.lse_p = torch.zeros((B, Hkv * G), device="cuda")
+
+    def dense_shares(self):
+        """Shares that the dense step's page list was split into: work items whose partials were written."""
+        self.ctx.workspace.fill_(255)
+        L.losa_step(self.ctx, self.kv, 0, None, None, self.q, orc.SEL_TOPK, 1.0, 1, self.o_p, self.lse_p)
+        torch.cuda.synchronize()
+        assert float((self.o_p - self.mean).abs().max()) <= 1e-3 and float((self.lse_p - np.log(self.tokens)).abs().max()) <= 1e-4
+        written = int((workspace_parts(self.ctx)["partial_m"].view(torch.int32) != -1).sum())
+        assert written % (self.heads * self.rows) == 0
+        return written // (self.heads * self.rows)
+
+
+def test_attention_workgroups_can_be_set_back_to_their_default():
+    """A context whose number of workgroups was changed and set back splits a prefix as one that was never touched."""
+    r = OnePagePrefix(16384, 16, 4, 1, 128, 16)
+    try:
+        default = r.dense_shares()
+        for value, shares in ((100, 100), (256, default), (1, 1), (1024, 512), (256, default)):     # 512 tiles of 32 tokens
+            L.losa_set_tuning(r.ctx, L.LOSA_TUNE_ATTN_WORKGROUPS, value)
+            assert r.dense_shares() == shares, value
+    finally:
+        r.ctx.close()
