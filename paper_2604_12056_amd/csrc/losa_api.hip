@@ -278,20 +278,33 @@ losa_status hip_fail(losa_ctx* ctx, const char* what, hipError_t e) {
 // 16384 22.6 / 18.9; 4 heads of 128 channels, 2048 22.4 / 21.2, 4096 25.0 / 23.8, 4 x 1024 23.4 / 22.2 (per eight: 25.1, 22.7, 23.2).
 // 256 shares / 128, 1 head of 64 channels: 65536 tokens 26.8 / 21.1, 131072 28.8 / 23.3; 256 / 64, 1 head of 128 channels: 131072
 // 50.1 / 35.1; 128 / 64, 2 heads: 41.5 / 37.6.
-int pick_nchunk(const losa_ctx* ctx, int batch, int upper, long target, int row_groups, int part_stride, int tile, bool split_pages) {
+// More shares than that where what is read pays for their merge: 2 * sqrt(tiles) of them, about the best number from 1024 tiles on (time ~
+// a * tiles / shares + b * shares).  `pages` is how many the list probably holds.  256 shares / 64 / this many, 1 head of 128
+// channels, 64 rows, every page: 131072 tokens 39.8 / 40.2 / 33.7, 262144 49.0 / 69.2 / 46.4, 524288 68.2 / 125.7 / 67.1; a step of
+// 42 rows with an eighth of the pages each, 131072 50.7 / 48.3 / 43.5, 524288 80.8 / 123 / 80.0.
+int pick_nchunk(const losa_ctx* ctx, int batch, int upper, long target, int row_groups, int part_stride, int tile, bool split_pages, long pages) {
   const long heads = (long)batch * ctx->sh.Hkv;
-  const long tiles = (upper + (tile / ctx->sh.g) - 1) / (tile / ctx->sh.g);
+  const int per_tile = tile / ctx->sh.g;
+  const long tiles = (upper + per_tile - 1) / per_tile;
   long want = target / (heads * row_groups);
   const long fit = ctx->part_rows / (heads * part_stride);
   if (want > fit) want = fit;
   if (want > tiles) want = tiles;
   if (split_pages && !ctx->shares_set) {
-    const long full = (tiles + 3) / 4, merged = kMergedShares * 128 / ctx->sh.d;
+    const long full = (tiles + 3) / 4, paid = (long)(2.f * sqrtf((float)(pages < upper ? pages : upper) / (float)per_tile));
+    const long merged = kMergedShares * 128 / ctx->sh.d;
     if (want > full) want = full;
-    if (want > merged) want = merged;
+    if (want > merged) want = paid < merged ? merged : paid < want ? paid : want;
   }
   if (want < 1) want = 1;
   return (int)want;
+}
+
+// Pages that the union of `rows` rows' picks of `topk` pages each probably holds.  Rows of a head pick alike: as if some
+// 3.1 * sqrt(rows) of them picked pages of their own (0.18 to 0.97 of all pages with 16 to 128 rows, to 0.04).
+long union_pages(int rows, int topk) {
+  const float apart = 3.1f * sqrtf((float)rows);
+  return (long)((apart < (float)rows ? apart : (float)rows) * (float)topk) + 1;
 }
 
 // |A| for the top-n modes (TOPK, FRACTION); the caller has validated param.
@@ -372,7 +385,7 @@ losa_status score_pages_impl(losa_ctx* ctx, hipStream_t st, const KvView& kv, in
 losa_status sparse_attn_impl(losa_ctx* ctx, hipStream_t st, const KvView& kv, int batch, int max_seq_pages,
                              const void* q, const int32_t* active_idx, const int32_t* active_count,
                              const int32_t* sel_pages, const int32_t* sel_count, int cap, int rows_upper,
-                             float* o_p, float* lse_p, const UnionInKernel* uni = nullptr) {
+                             float* o_p, float* lse_p, const UnionInKernel* uni = nullptr, int topk = 0) {
   const int upper = sel_pages ? (cap < max_seq_pages ? cap : max_seq_pages) : max_seq_pages;
   const bool mfma = ctx->cfg.dtype == LOSA_BF16;
   if (!active_idx) rows_upper = ctx->sh.rows_max;   // every token is active: the count is known
@@ -397,7 +410,8 @@ losa_status sparse_attn_impl(losa_ctx* ctx, hipStream_t st, const KvView& kv, in
   const int many_tile = !mfma ? ctx->sh.g : rows_kernel ? kManyRowStage : 32;
   const int few_tile = !mfma ? ctx->sh.g : rows_kernel && !both_shapes ? kManyRowStage : 32;
   int nchunk = pick_nchunk(ctx, batch, upper, ctx->target_workgroups * (mfma ? 1 : kFloatGroups), row_groups, part.rows,
-                           few_tile, mfma && few_tile == 32 && rows_upper <= 64);
+                           few_tile, mfma && few_tile == 32 && rows_upper <= 64,
+                           topk > 0 ? union_pages(rows_upper, topk) : upper);   // topk: of the rows, 0: every page of a list, or every page
   // float mode: workgroups of the same share and different row blocks are nchunk apart in the grid; a multiple of
   // the die count (8) puts them on one die, so that its L2 serves all but the first
   if (!mfma && nchunk >= 8) nchunk &= ~7;
@@ -772,7 +786,7 @@ losa_status losa_step(losa_ctx* ctx, void* stream, const losa_kv* kv, int32_t st
                          union_in_attn ? ctx->union_bits : nullptr);
   if (s != LOSA_OK) return s;
   return sparse_attn_impl(ctx, st, view, kv->batch, msp, q, ctx->active_idx, ctx->active_count, ctx->sel_pages, sc,
-                          cap, rows_upper, (float*)o_p, lse_p, union_in_attn ? &uni : nullptr);
+                          cap, rows_upper, (float*)o_p, lse_p, union_in_attn ? &uni : nullptr, topk_pages);
 }
 
 }  // extern "C"

@@ -754,3 +754,15 @@ def test_attention_workgroups_can_be_set_back_to_their_default():
             assert r.dense_shares() == shares, value
     finally:
         r.ctx.close()
+
+
+@pytest.mark.parametrize("tokens,Hkv,d,g,shares", [
+    (32768, 1, 128, 16, 64), (32768, 1, 64, 16, 128),          # what the merge takes in one go
+    (131072, 1, 128, 16, 128), (524288, 1, 128, 32, 256),      # 4096 and 16384 tiles: 2 * sqrt(tiles)
+    (524288, 2, 128, 32, 128), (524288, 1, 64, 32, 256)])      # ... at most a workgroup per compute unit
+def test_long_prefixes_of_few_heads_fill_the_chip(tokens, Hkv, d, g, shares):
+    r = OnePagePrefix(tokens, 16, 4, Hkv, d, g)
+    try:
+        assert r.dense_shares() == shares
+    finally:
+        r.ctx.close()
