@@ -6,6 +6,7 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <algorithm>
 #include <new>
 #include <vector>
 
@@ -103,6 +104,7 @@ namespace {
 constexpr long kTargetItems = 1024;       // most split-K work items a sparse step may be given
 constexpr long kTargetWorkgroups = 256;   // attention workgroups aimed at per launch: one per CU
 constexpr long kMergedShares = 64;        // shares of a row that the merge kernel takes in one go (128 channels)
+constexpr long kFewPartials = 4096;       // rows of partials in all that a launch may have for a share per two tiles
 constexpr long kFloatGroups = 2;          // float-mode workgroups per bfloat16 attention workgroup aimed at: two fit a CU
 constexpr int kSparseRows = 64;           // query rows per KV head up to which the split-pages work shape is used
 
@@ -278,6 +280,10 @@ losa_status hip_fail(losa_ctx* ctx, const char* what, hipError_t e) {
 // 16384 22.6 / 18.9; 4 heads of 128 channels, 2048 22.4 / 21.2, 4096 25.0 / 23.8, 4 x 1024 23.4 / 22.2 (per eight: 25.1, 22.7, 23.2).
 // 256 shares / 128, 1 head of 64 channels: 65536 tokens 26.8 / 21.1, 131072 28.8 / 23.3; 256 / 64, 1 head of 128 channels: 131072
 // 50.1 / 35.1; 128 / 64, 2 heads: 41.5 / 37.6.
+// With 128 channels two tiles, while the launch has few partials to merge (kFewPartials rows): there the wavefronts' own tiles take longer
+// than the merge of shares twice as many.  A share per tile / four / two, every page, 16 rows: 1 head, 1024 tokens 7.2 / 7.8 / 7.3, 2048 7.5 /
+// 8.0 / 7.4; 4 heads, 1024 7.5 / 8.0 / 7.4, 8 heads 8.1 / 8.2 / 7.7; 32 rows, 1 head, 1024 8.5 / 9.1 / 8.7; 8 heads, 4096 - / 10.0 / 10.5;
+// 64 rows, 1 head, 1024 11.6 / 12.1 / 11.6, 4 heads, 2048 14.7 / 12.7 / 13.3.
 // More shares than that where what is read pays for their merge: 2 * sqrt(tiles) of them, about the best number from 1024 tiles on (time ~
 // a * tiles / shares + b * shares).  `pages` is how many the list probably holds.  256 shares / 64 / this many, 1 head of 128
 // channels, 64 rows, every page: 131072 tokens 39.8 / 40.2 / 33.7, 262144 49.0 / 69.2 / 46.4, 524288 68.2 / 125.7 / 67.1; a step of
@@ -291,7 +297,9 @@ int pick_nchunk(const losa_ctx* ctx, int batch, int upper, long target, int row_
   if (want > fit) want = fit;
   if (want > tiles) want = tiles;
   if (split_pages && !ctx->shares_set) {
-    const long full = (tiles + 3) / 4, paid = (long)(2.f * sqrtf((float)(pages < upper ? pages : upper) / (float)per_tile));
+    long full = (tiles + 3) / 4;
+    if (ctx->sh.d == 128) full = std::max(full, std::min((tiles + 1) / 2, kFewPartials / (heads * part_stride)));
+    const long paid = (long)(2.f * sqrtf((float)(pages < upper ? pages : upper) / (float)per_tile));
     const long merged = kMergedShares * 128 / ctx->sh.d;
     if (want > full) want = full;
     if (want > merged) want = paid < merged ? merged : paid < want ? paid : want;

@@ -766,3 +766,14 @@ def test_long_prefixes_of_few_heads_fill_the_chip(tokens, Hkv, d, g, shares):
         assert r.dense_shares() == shares
     finally:
         r.ctx.close()
+
+
+@pytest.mark.parametrize("tokens,G,Hkv,d,shares", [
+    (100, 1, 1, 128, 2), (1024, 1, 1, 128, 16), (1024, 1, 8, 128, 16), (1024, 4, 4, 128, 16),   # two tiles of 32 tokens a share ...
+    (2048, 4, 4, 128, 16), (1024, 4, 8, 128, 8), (1024, 1, 1, 64, 8)])   # ... four where 4096 rows of partials are passed, and with 64 channels
+def test_short_prefixes_are_split_into_shares_of_two_or_four_tiles(tokens, G, Hkv, d, shares):
+    r = OnePagePrefix(tokens, 16, G, Hkv, d, 16)
+    try:
+        assert r.dense_shares() == shares
+    finally:
+        r.ctx.close()
