@@ -715,23 +715,24 @@ def test_scoring_and_selection_in_one_launch(P, B, G, H):
 
 
 class OnePagePrefix:
-    """One sequence whose pages are all the same few, for launches over prefixes of any length: the values of a physical page are its
+    """Sequences whose pages are all the same few, for launches over prefixes of any length: the values of a physical page are its
     number, so a dense step's output is known."""
 
-    def __init__(self, tokens, B, G, Hkv, d, g):
+    def __init__(self, tokens, B, G, Hkv, d, g, batch=1):
         ints, self.heads, self.rows = (lambda *x: torch.tensor(x, dtype=torch.int32, device="cuda")), Hkv, B * G
         P = -(-tokens // g)
         ids = torch.arange(P, dtype=torch.int32, device="cuda") % 7
         v = torch.arange(7, device="cuda", dtype=torch.bfloat16)[:, None, None, None].expand(7, Hkv, d, g).contiguous()
         zeros = lambda *shape: torch.zeros(shape, device="cuda", dtype=torch.bfloat16)
-        self.kv = L.PagedKV(zeros(7, Hkv, g, d), v, zeros(7, Hkv, 2, d), ints(0, P), ids, ints(tokens), max_seq_pages=P)
-        self.ctx = L.losa_create(L.make_config(max_batch=1, num_q_heads=Hkv * G, num_kv_heads=Hkv, head_dim=d, hidden_size=64, page_size=g,
-                                               block_size=B, max_pages_per_seq=P, max_topk_pages=1), "cuda:0")
+        self.kv = L.PagedKV(zeros(7, Hkv, g, d), v, zeros(7, Hkv, 2, d), ints(*range(0, (batch + 1) * P, P)), ids.repeat(batch), ints(*[tokens] * batch),
+                            max_seq_pages=P)
+        self.ctx = L.losa_create(L.make_config(max_batch=batch, num_q_heads=Hkv * G, num_kv_heads=Hkv, head_dim=d, hidden_size=64, page_size=g,
+                                               block_size=B, max_pages_per_seq=P, max_topk_pages=P), "cuda:0")
         weights = torch.full((P,), float(g), dtype=torch.float64, device="cuda")
         weights[-1] = tokens - (P - 1) * g
         self.mean, self.tokens = float((ids.double() * weights).sum() / tokens), tokens
-        self.q, self.o_p = zeros(B, Hkv * G, d), torch.zeros((B, Hkv * G, d), device="cuda")
-        self.lse_p = torch.zeros((B, Hkv * G), device="cuda")
+        self.q, self.o_p = zeros(batch * B, Hkv * G, d), torch.zeros((batch * B, Hkv * G, d), device="cuda")
+        self.lse_p, self.h = torch.zeros((batch * B, Hkv * G), device="cuda"), (zeros(batch * B, 64) + 1, zeros(batch * B, 64))
 
     def dense_shares(self):
         """Shares that the dense step's page list was split into: work items whose partials were written."""
@@ -775,5 +776,36 @@ def test_short_prefixes_are_split_into_shares_of_two_or_four_tiles(tokens, G, Hk
     r = OnePagePrefix(tokens, 16, G, Hkv, d, 16)
     try:
         assert r.dense_shares() == shares
+    finally:
+        r.ctx.close()
+
+
+def scored_in_one_launch(ctx, step):
+    """Whether the step that `step` makes scores and selects in one launch, which keeps no score matrix in memory.  (The scores of
+    pages that exist are no NaN of all ones.)"""
+    ctx.workspace.fill_(255)
+    step()
+    torch.cuda.synchronize()
+    return bool((workspace_parts(ctx)["scores"].view(torch.int32) == -1).all())
+
+
+@pytest.mark.parametrize("P,d,Hkv,batch,n,one", [   # 7 query heads per KV head
+    (100, 128, 1, 1, 2, True), (160, 128, 4, 1, 2, True), (161, 128, 4, 1, 2, False),    # 14 rows, few workgroups
+    (192, 128, 4, 1, 3, True), (193, 128, 4, 1, 3, False),                               # two tiles of rows
+    (256, 128, 8, 4, 2, False), (256, 128, 8, 5, 2, True),                               # 32 and 40 workgroups
+    (256, 64, 1, 1, 2, True), (257, 64, 1, 1, 2, False), (384, 64, 4, 1, 8, False),      # 64 channels: up to 256 pages ...
+    (320, 64, 8, 8, 2, True), (322, 64, 8, 8, 2, False), (384, 64, 8, 16, 2, True),      # ... with 64, and with 128 workgroups
+    (320, 64, 1, 1, 16, False), (320, 64, 1, 1, 17, True), (384, 64, 1, 4, 17, False), (384, 64, 1, 5, 17, True),   # ... with eight tiles of rows
+    (512, 128, 8, 3, 13, True), (512, 128, 8, 6, 13, False), (288, 128, 8, 6, 13, True), (512, 128, 8, 16, 8, True), (513, 128, 8, 16, 8, False)])
+def test_which_prefixes_are_scored_and_selected_in_one_launch(P, d, Hkv, batch, n, one):
+    r = OnePagePrefix(16 * P - 5, 32, 7, Hkv, d, 16, batch)
+    count, K = torch.zeros((batch, Hkv), dtype=torch.int32, device="cuda"), P // 3
+    try:
+        assert one == scored_in_one_launch(r.ctx, lambda: L.losa_step(r.ctx, r.kv, 1, *r.h, r.q, orc.SEL_TOPK, float(n), K, r.o_p, r.lse_p,
+                                                                      None, count))
+        assert bool((count == K).all())                      # every page scores the same: the first ones
+        mean = float((torch.arange(K) % 7).double().mean())
+        o_p = r.o_p.reshape(batch, 32, -1)
+        assert float((o_p[:, :n] - mean).abs().max()) <= 1e-2 and float(o_p[:, n:].abs().max()) == 0.0
     finally:
         r.ctx.close()
