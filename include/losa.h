@@ -246,7 +246,8 @@ losa_status losa_block_merge(losa_ctx* ctx, void* stream, int32_t batch, const v
  *                                 beyond it gives each workgroup up to four query rows, eight where the
  *                                 union list is built (0: default).  While it is set, short prefixes are
  *                                 scored and selected in two launches too, not in one
- *   LOSA_TUNE_SCORE_ROUND       : the same for the scoring kernel (64-page tiles per workgroup); >= 1
+ *   LOSA_TUNE_SCORE_ROUND       : the same for the scoring kernel (64-page tiles per workgroup); >= 1 (default
+ *                                 1280).  Any other number keeps short prefixes in two launches as well
  *   LOSA_TUNE_RANK_IN_SCORES    : 1 (default): inside losa_step the scoring kernel ranks the locality
  *                                 scores itself; 0: the locality kernel does, as in losa_select_active
  *   LOSA_TUNE_UNION_IN_ATTENTION: 1 (default): the union of a KV head's picked pages is built in the

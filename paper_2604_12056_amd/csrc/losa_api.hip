@@ -106,6 +106,7 @@ constexpr long kTargetWorkgroups = 256;   // attention workgroups aimed at per l
 constexpr long kMergedShares = 64;        // shares of a row that the merge kernel takes in one go (128 channels)
 constexpr long kFewPartials = 4096;       // rows of partials in all that a launch may have for a share per two tiles
 constexpr long kFloatGroups = 2;          // float-mode workgroups per bfloat16 attention workgroup aimed at: two fit a CU
+constexpr long kScoreRound = 5L * 256;    // scoring workgroups counted as one round: four per CU are resident, a quarter more start as those end
 constexpr int kSparseRows = 64;           // query rows per KV head up to which the split-pages work shape is used
 
 thread_local char g_create_err[256] = "";
@@ -512,7 +513,7 @@ losa_status losa_create(const losa_config* cfg, void* workspace, size_t workspac
   ctx->target_workgroups = kTargetWorkgroups;
   ctx->rank_in_scores = true;
   ctx->select_round = 0;
-  ctx->score_round = 5L * 256;   // (four scoring workgroups per CU are resident at once; a quarter more start as those end)
+  ctx->score_round = kScoreRound;
   ctx->union_in_attention = true;
   ctx->shared_tiles = true;
   ctx->half_values = true;
@@ -768,8 +769,8 @@ losa_status losa_step(losa_ctx* ctx, void* stream, const losa_kv* kv, int32_t st
   const UnionInKernel uni{ctx->union_bits, ctx->entries, ctx->q_act, sc, union_words(ctx->sh.max_pages, ctx->sh.rows_max),
                           union_copy_words(msp), union_copies(union_copy_words(msp), union_upper)};
   // Short prefixes: scoring and selection in one launch.  (Not while stages are timed, which takes a launch for each, nor where
-  // the caller shapes the selection's grid.)
-  const bool picked = rank_in_scores && union_in_attn && !ctx->profiling && ctx->select_round == 0 &&
+  // the caller shapes the grid of either.)
+  const bool picked = rank_in_scores && union_in_attn && !ctx->profiling && ctx->select_round == 0 && ctx->score_round == kScoreRound &&
                       pick_pages_serves(ctx->sh, kv->batch, msp, union_upper, counted);
   if (rank_in_scores) {
     const bool takes_hidden = picked && pick_takes_hidden(ctx->sh);

@@ -809,3 +809,19 @@ def test_which_prefixes_are_scored_and_selected_in_one_launch(P, d, Hkv, batch, 
         assert float((o_p[:, :n] - mean).abs().max()) <= 1e-2 and float(o_p[:, n:].abs().max()) == 0.0
     finally:
         r.ctx.close()
+
+
+def test_a_step_whose_grids_are_shaped_scores_and_selects_in_two_launches():
+    """Each switch that shapes or names one of the two launches brings them back, and its default the one launch."""
+    r = OnePagePrefix(64 * 16, 32, 7, 4, 128, 16)
+    try:
+        one = lambda: scored_in_one_launch(r.ctx, lambda: L.losa_step(r.ctx, r.kv, 1, *r.h, r.q, orc.SEL_TOPK, 6.0, 9, r.o_p, r.lse_p))
+        assert one()
+        for knob, value, default in ((L.LOSA_TUNE_SELECT_ROUND, 100, 0), (L.LOSA_TUNE_SCORE_ROUND, 1, 1280), (L.LOSA_TUNE_SCORE_ROUND, 1 << 30, 1280),
+                                     (L.LOSA_TUNE_RANK_IN_SCORES, 0, 1), (L.LOSA_TUNE_UNION_IN_ATTENTION, 0, 1)):
+            L.losa_set_tuning(r.ctx, knob, value)
+            assert not one(), (knob, value)
+            L.losa_set_tuning(r.ctx, knob, default)
+            assert one(), (knob, default)
+    finally:
+        r.ctx.close()
