@@ -210,9 +210,11 @@ def test_cumulative_mass_at_the_edges_of_its_prefix_sums(B):
             r.close()
 
 
-@pytest.mark.parametrize("B", [1, 2, 3, 4, 5, 31, 32, 33, 63, 64, 65, 128, 255, 256])
-def test_active_set_of_a_step_at_the_edges_of_its_ranking(B):
-    """losa_step ranks the block in the scoring kernel: a lane per token up to 64 tokens, a thread per token beyond.
+@pytest.mark.parametrize("B,select_round", [(B, 0) for B in (1, 2, 3, 4, 5, 31, 32, 33, 63, 64, 65, 128, 255, 256)] +
+                         [(B, 1 << 30) for B in (1, 2, 3, 4, 5, 31, 32, 33, 63, 64)])
+def test_active_set_of_a_step_at_the_edges_of_its_ranking(B, select_round):
+    """losa_step ranks the block where it scores: a lane per token up to 64 tokens, by the sixteen wavefronts of the launch that also
+    selects or, with the selection's grid set, by the four of the scoring kernel; a thread per token beyond, in the scoring kernel.
     Scores are squares of small integers, full of ties, so the sets have to be equal; three query heads per KV head."""
     rng, d, dev = np.random.Generator(np.random.Philox(B)), 64, "cuda:0"
     v = rng.integers(0, 8, size=(3, B)).astype(np.float32)
@@ -228,6 +230,7 @@ def test_active_set_of_a_step_at_the_edges_of_its_ranking(B):
                    torch.randperm(17, generator=gen, device=dev).to(torch.int32), lens, max_seq_pages=13)
     ctx = L.losa_create(L.make_config(max_batch=3, num_q_heads=Hq, num_kv_heads=Hkv, head_dim=d, hidden_size=Hq * d,
                                       page_size=g, block_size=B, max_pages_per_seq=13, max_topk_pages=2), dev)
+    L.losa_set_tuning(ctx, L.LOSA_TUNE_SELECT_ROUND, select_round)
     try:
         L.losa_page_bounds(ctx, kv)
         q = draw(3 * B, Hq, d)
@@ -242,12 +245,13 @@ def test_active_set_of_a_step_at_the_edges_of_its_ranking(B):
             mask.fill_(9)
             o_p.fill_(7.0)
             lse_p.fill_(7.0)
-            L.losa_step(ctx, kv, 1, h, torch.zeros_like(h), q, mode, param, 2, o_p, lse_p, mask)
+            one = scored_in_one_launch(ctx, lambda: L.losa_step(ctx, kv, 1, h, torch.zeros_like(h), q, mode, param, 2, o_p, lse_p, mask))
+            assert not mask.any() or one == (B <= 64 and not select_round)
             got = mask.cpu().numpy().reshape(3, B)
             want = [orc.active_set(v[b] ** 2, mode, param) for b in range(3)]
             for b in range(3):
                 assert np.array_equal(got[b], np.isin(np.arange(B), want[b]).astype(np.uint8)), (b, mode, param)
-            # the list, of which every wavefront of the scoring kernel holds a copy, is what the rest of the step goes by
+            # the list, of which every wavefront that ranks holds a copy, is what the rest of the step goes by
             o, lse = np.full((3 * B, Hq, d), 7.0), np.full((3 * B, Hq), 7.0)
             orc.losa_step(cache, 1, None, None, to_host(q), mode, param, 2, B, Hq, o, lse, forced_active=want)
             active = np.concatenate([b * B + want[b] for b in range(3)])
@@ -259,9 +263,10 @@ def test_active_set_of_a_step_at_the_edges_of_its_ranking(B):
         ctx.close()
 
 
-@pytest.mark.parametrize("dtype,B,G", [("bf16", 9, 8), ("bf16", 16, 7), ("bf16", 33, 4), ("bf16", 64, 4), ("bf16", 65, 4), ("bf16", 256, 2),
-                                       ("f32", 24, 4)])
-def test_scores_that_are_no_number_rank_with_infinity(dtype, B, G):
+@pytest.mark.parametrize("dtype,B,G,select_round", [("bf16", 9, 8, 0), ("bf16", 16, 7, 0), ("bf16", 33, 4, 0), ("bf16", 64, 4, 0), ("bf16", 65, 4, 0),
+                                                    ("bf16", 256, 2, 0), ("f32", 24, 4, 0), ("bf16", 9, 8, 1 << 30), ("bf16", 33, 4, 1 << 30),
+                                                    ("bf16", 64, 4, 1 << 30)])     # (set: ranked in the scoring kernel, see above)
+def test_scores_that_are_no_number_rank_with_infinity(dtype, B, G, select_round):
     """Several tokens whose change is NaN and one whose change is infinite: top-n selections hold exactly n tokens (64 query
     rows per KV head at most, and fewer than there are such tokens), the steps attend for exactly those, over a
     workspace that holds no page table of an earlier step."""
@@ -275,7 +280,7 @@ def test_scores_that_are_no_number_rank_with_infinity(dtype, B, G):
             inp.h[1, b * B + odd[b], 5] = nan
             inp.h[1, b * B + odd[b][-1], 5] = inf
     w = workload(B, G, 1, 64, 16, (700, 33, 160), n, dtype=dtype)
-    r = Rig(w, mutate=poison)
+    r = Rig(w, mutate=poison, tuning={L.LOSA_TUNE_SELECT_ROUND: select_round})
     blk = r.blk
     r.ctx.workspace.fill_(255)
     try:
@@ -654,62 +659,84 @@ def test_merge_of_few_chunks(B, G, d, page, chunks):
         r.close()
 
 
-@pytest.mark.parametrize("B,G,H", [(1, 1, 64), (17, 1, 520), (33, 3, 512), (64, 4, 256)])   # up to 256 rows; hidden states taken in the launch up to 512
-@pytest.mark.parametrize("P", [1, 15, 64, 65, 255, 256, 257, 512])
-def test_scoring_and_selection_in_one_launch(P, B, G, H):
+def scored_in_one_launch(ctx, step):
+    """Whether the step that `step` makes scores and selects in one launch, which keeps no score matrix in memory.  (The scores of
+    pages that exist are no NaN of all ones.)"""
+    ctx.workspace.fill_(255)
+    step()
+    torch.cuda.synchronize()
+    return bool((workspace_parts(ctx)["scores"].view(torch.int32) == -1).all())
+
+
+ONE_LAUNCH = [(P, 64, 1, 16, B, G, H) for P in (1, 15, 64, 65, 255, 256)        # hidden states are taken in the launch up to 512
+              for B, G, H in ((1, 1, 64), (17, 1, 520), (33, 3, 512), (64, 4, 256))]
+ONE_LAUNCH += [(P, d, 8, g, 64, 4, H) for P, d, g, H in (                       # two tiles of pages per wavefront: 256 and 144 workgroups
+    (257, 64, 16, 512), (383, 64, 32, 520), (511, 64, 16, 256), (512, 64, 32, 1024), (257, 128, 32, 520), (258, 128, 16, 256), (383, 128, 16, 1024),
+    (511, 128, 32, 520), (512, 128, 16, 512), (512, 128, 32, 64))]
+
+
+@pytest.mark.parametrize("P,d,Hkv,g,B,G,H", ONE_LAUNCH)
+def test_scoring_and_selection_in_one_launch(P, d, Hkv, g, B, G, H):
     """Short prefixes: a launch that scores and selects (and scores the tokens, where hidden states are short) against numpy's picks and,
-    bit for bit, against the separate launches.  Rows, values and sums as in the test of the bitmap above; two sequences."""
-    rng, d, g, dev = np.random.Generator(np.random.Philox(P + B)), 64, 16, "cuda:0"
+    bit for bit, against the separate launches; that it was one launch is seen from the score matrix.  Rows, values and sums as in the
+    test of the bitmap above; two sequences; a KV head's channels hold the kinds of row one further than those of the head before."""
+    rng, dev = np.random.Generator(np.random.Philox(P + B)), "cuda:0"
     lens = [P * g - 5, max(1, P * g // 3)]
     pages = [(n + g - 1) // g for n in lens]
     total = sum(pages)
     kinds = [rows_of_every_kind(rng, p, bf16=True) for p in pages]
+    nk = len(kinds[0])
     page_ids = rng.permutation(total).astype(np.int32)
     signs = rng.choice([-1.0, 1.0], (total, d)).astype(np.float32)              # by logical page, one sequence behind the other
-    meta, v_pages = torch.zeros((total, 1, 2, d)), torch.zeros((total, 1, d, g))
+    bf = lambda x: x.to(torch.bfloat16).to(dev)
+    meta, v_pages = torch.zeros((total, Hkv, 2, d)), torch.zeros((total, Hkv, d, g), dtype=torch.bfloat16)
     for b, first in enumerate((0, pages[0])):
         for c, value in enumerate(kinds[b]):
-            meta[page_ids[first:first + pages[b]], 0, :, c] = torch.from_numpy(value)[:, None]
-    v_pages[page_ids, 0] = torch.from_numpy(signs)[:, :, None]
-    kind_of = (np.arange(B * G) // 4 + np.arange(B * G)) % len(kinds[0])
-    q = torch.zeros((2, B * G, d))
-    q[:, torch.arange(B * G), torch.from_numpy(kind_of)] = 1.0
-    bf = lambda x: x.to(torch.bfloat16).to(dev)
-    kv = L.PagedKV(bf(torch.zeros((total, 1, g, d))), bf(v_pages), bf(meta), torch.tensor([0, pages[0], total], dtype=torch.int32, device=dev),
-                   torch.from_numpy(page_ids).to(dev), torch.tensor(lens, dtype=torch.int32, device=dev), max_seq_pages=P)
-    ctx = L.losa_create(L.make_config(max_batch=2, num_q_heads=G, num_kv_heads=1, head_dim=d, hidden_size=H, page_size=g,
+            for j in range(Hkv):
+                meta[page_ids[first:first + pages[b]], j, :, (c - j) % nk] = torch.from_numpy(value)[:, None]
+    v_pages[page_ids] = torch.from_numpy(signs).to(torch.bfloat16)[:, None, :, None].expand(-1, Hkv, -1, g)
+    kind_of = (np.arange(B * G) // 4 + np.arange(B * G)) % nk
+    one_hot = torch.nn.functional.one_hot(torch.from_numpy(kind_of), d).float().reshape(1, B, 1, G, d)
+    q = bf(one_hot.expand(2, B, Hkv, G, d).contiguous()).reshape(2 * B, Hkv * G, d)
+    kv = L.PagedKV(torch.zeros((total, Hkv, g, d), dtype=torch.bfloat16, device=dev), v_pages.to(dev), bf(meta),
+                   torch.tensor([0, pages[0], total], dtype=torch.int32, device=dev), torch.from_numpy(page_ids).to(dev),
+                   torch.tensor(lens, dtype=torch.int32, device=dev), max_seq_pages=P)
+    ctx = L.losa_create(L.make_config(max_batch=2, num_q_heads=Hkv * G, num_kv_heads=Hkv, head_dim=d, hidden_size=H, page_size=g,
                                       block_size=B, max_pages_per_seq=P, max_topk_pages=P), dev)
-    ctx.workspace.fill_(255)
     h = bf(torch.from_numpy((1.0 + rng.permutation(2 * B).astype(np.float32) / 64)[:, None].repeat(H, 1)))    # Delta = its square: no ties
     order = np.argsort(-to_host(h.float()).reshape(2, B, H)[:, :, 0], axis=1, kind="stable")
-    out = lambda: (torch.zeros((2 * B, G, d), device=dev), torch.zeros((2 * B, G), device=dev),
-                   torch.zeros(2 * B, dtype=torch.uint8, device=dev), torch.zeros((2, 1), dtype=torch.int32, device=dev))
+    out = lambda: (torch.zeros((2 * B, Hkv * G, d), device=dev), torch.zeros((2 * B, Hkv * G), device=dev),
+                   torch.zeros(2 * B, dtype=torch.uint8, device=dev), torch.zeros((2, Hkv), dtype=torch.int32, device=dev))
+    some = (B + 2) // 3 if Hkv == 1 else 33
+    modes = [(orc.SEL_TOPK, float(B), B), (orc.SEL_TOPK, float(some), some)]
+    if P <= 128:      # counts that only the device knows: beyond, the separate launches
+        modes += [(orc.SEL_THRESHOLD, 0.5, B), (orc.SEL_THRESHOLD, 1e9, 0), (orc.SEL_MASS, 0.4, None)]
     try:
-        for mode, param, n in ((orc.SEL_TOPK, float(B), B), (orc.SEL_TOPK, (B + 2) // 3, (B + 2) // 3), (orc.SEL_THRESHOLD, 0.5, B),
-                               (orc.SEL_THRESHOLD, 1e9, 0), (orc.SEL_MASS, 0.4, None)):
+        for mode, param, n in modes:
             for K in sorted({1, max(1, P // 8), max(1, P - 1), P}):
                 got, separate = out(), out()
-                for o, rnd in ((got, 0), (separate, 1 << 30)):
+                for o, rnd, one in ((got, 0, True), (separate, 1 << 30, n == 0)):      # (no active token: no scores either way)
                     L.losa_set_tuning(ctx, L.LOSA_TUNE_SELECT_ROUND, rnd)
-                    L.losa_step(ctx, kv, 1, h, torch.zeros_like(h), bf(q).reshape(2 * B, G, d), mode, float(param), K, *o)
-                torch.cuda.synchronize()
+                    step = lambda: L.losa_step(ctx, kv, 1, h, torch.zeros_like(h), q, mode, float(param), K, *o)
+                    assert scored_in_one_launch(ctx, step) == one, (mode, n, K, rnd)
                 assert all(torch.equal(x, y) for x, y in zip(got, separate)), (mode, n, K)
                 o_p, lse_p, mask, cnt = (x.cpu().numpy() for x in got)
                 for b, first in enumerate((0, pages[0])):
                     active = np.flatnonzero(mask[b * B:(b + 1) * B])
                     assert n is None or set(active) == set(order[b, :n]), (mode, n, K)
                     if not len(active):
-                        assert cnt[b, 0] == 0
+                        assert not cnt[b].any()
                         continue
-                    rows = np.concatenate([(np.arange(len(active) * G))])     # row r is the r-th of the active tokens' heads
-                    picks = [np.argsort(-kinds[b][kind_of[active[r // G] * G + r % G]], kind="stable")[:K] for r in rows]
-                    union = np.unique(np.concatenate(picks))
-                    assert cnt[b, 0] == len(union), (mode, n, K, b)
-                    last = lens[b] - (pages[b] - 1) * g                          # tokens of the last page
-                    weight = np.where(union == pages[b] - 1, last, g).astype(np.float64)
-                    want = (signs[first + union] * weight[:, None]).sum(axis=0) / weight.sum()
-                    err = np.abs(o_p[b * B + active].reshape(-1, d) - want).max()
-                    assert err * weight.sum() <= 0.25 * min(last, g), (mode, n, K, b)
+                    used = {int(k) for a in active for k in kind_of[a * G:a * G + G]}     # of head 0
+                    picks = [np.argsort(-value, kind="stable")[:K] for value in kinds[b]]
+                    last = lens[b] - (pages[b] - 1) * g                                   # tokens of the last page
+                    for j in range(Hkv):
+                        union = np.unique(np.concatenate([picks[(k + j) % nk] for k in used]))
+                        assert cnt[b, j] == len(union), (mode, n, K, b, j)
+                        weight = np.where(union == pages[b] - 1, last, g).astype(np.float64)
+                        want = (signs[first + union] * weight[:, None]).sum(axis=0) / weight.sum()
+                        err = np.abs(o_p[b * B + active].reshape(len(active), Hkv, G, d)[:, j] - want).max()
+                        assert err * weight.sum() <= 0.25 * min(last, g), (mode, n, K, b, j)
     finally:
         ctx.close()
 
@@ -778,15 +805,6 @@ def test_short_prefixes_are_split_into_shares_of_two_or_four_tiles(tokens, G, Hk
         assert r.dense_shares() == shares
     finally:
         r.ctx.close()
-
-
-def scored_in_one_launch(ctx, step):
-    """Whether the step that `step` makes scores and selects in one launch, which keeps no score matrix in memory.  (The scores of
-    pages that exist are no NaN of all ones.)"""
-    ctx.workspace.fill_(255)
-    step()
-    torch.cuda.synchronize()
-    return bool((workspace_parts(ctx)["scores"].view(torch.int32) == -1).all())
 
 
 @pytest.mark.parametrize("P,d,Hkv,batch,n,one", [   # 7 query heads per KV head

@@ -371,8 +371,9 @@ def _random_workload(seed: int):
                                    name=f"random-{seed}")
 
 
-@pytest.mark.parametrize("seed", list(range(64)) + [416, 488, 785, 789, 853])   # the last five: shapes that once caught a matrix-result read hazard
-def test_random_shapes_end_to_end(seed):
+@pytest.mark.parametrize("seed,select_round", [(seed, 0) for seed in list(range(64)) + [416, 488, 785, 789, 853]] +   # the last five: shapes that once caught a matrix-result read hazard
+                         [(seed, 1 << 30) for seed in range(0, 64, 3)])   # short prefixes in separate launches too
+def test_random_shapes_end_to_end(seed, select_round):
     """Seeded random head / block / page / batch shapes and prefix lengths (some shorter than a
     page or empty), dense initialisation then sparse steps in a randomly chosen selection mode,
     every output against the oracle."""
@@ -380,7 +381,7 @@ def test_random_shapes_end_to_end(seed):
     rng = np.random.Generator(np.random.Philox(100 + seed))
     mode, param = [(orc.SEL_TOPK, float(w.n_active)), (orc.SEL_FRACTION, w.n_active / w.B),
                    (orc.SEL_THRESHOLD, 0.01), (orc.SEL_MASS, 0.5)][int(rng.integers(0, 4))]
-    r = Rig(w)
+    r = Rig(w, tuning={L.LOSA_TUNE_SELECT_ROUND: select_round})
     try:
         check_page_bounds(r)
         run_steps_end_to_end(r, range(w.T), mode, param, w.topk_pages)
