@@ -380,6 +380,9 @@ def main():
         "union_pages_per_kv_head": round(pages_per_launch / (w.batch * w.Hkv), 1),
         "kv_density": round(float(density), 4),
         "stage_us": {k: (round(v, 3) if v is not None else None) for k, v in stage_us.items()},
+        # (the events need a launch per stage)
+        **({"stage_note": "stages timed in launches of their own; the timed steps of a prefix this short may score and select in one"}
+           if w.dtype == "bf16" and w.max_pages <= 512 else {}),
         # the same per-kernel figures grouped as the paper's latency breakdown names them (Latency
         # Analysis): reuse for stable tokens is "rows never written", so cache management has no kernel
         "paper_breakdown_us": {
