@@ -1224,9 +1224,12 @@ hipError_t launch_page_scores(hipStream_t st, int dtype, const KvView& kv, const
 //   375, 48 34.5 / 36.7; 96 42.0 / 42.0; 128 71.7 / 69.3; 192 61.8 / 57.6
 //   512, 64 51.7 / 55.2; 96 45.9 / 48.4; 128 50.3 / 51.4; 144 57.8 / 57.8; 192 69.0 / 67.4; 512 96.1 / 90.9
 //   (64 channels) 256, 1 17.1 / 15.0; 16 18.9 / 16.7
-// Beyond 256 pages a wavefront has two tiles of them, 1 us more in every workgroup, which few workgroups do not make up for:
+// Beyond 256 pages a wavefront has two tiles of them, 1 us more in every workgroup, which few workgroups do not make up for unless
+// the locality scores' launch goes as well:
 //   (64 channels) 288, 1 17.0 / 17.6; 16 18.6 / 20.5; 64 24.8 / 24.5; 128 28.4 / 26.2    384, 4 19.5 / 21.7; 16 19.0 / 21.3; 64 25.7 / 26.5;
 //   128 30.0 / 28.8; with ten tiles of rows 288, 10 25.2 / 24.6    384, 10 25.5 / 26.0; 40 30.9 / 30.3
+//   (256 hidden channels) 288, 1 17.0 / 16.5; 16 18.4 / 18.4    384, 1 16.9 / 17.3; 16 18.9 / 19.9, and issued one by one, where the host
+//   is what limits, 22.1 / 17.4; 22.3 / 20.0
 // A workgroup fills a compute unit, so that a second round of them pays where it is full, the more so the more pages there are:
 //   288, 288 57.0 / 56.9    352, 288 62.2 / 62.9; 384 70.6 / 67.3    384, 320 64.0 / 64.6; 640 96.1 / 96.9; 1024 143 / 137    512, 288 70.2 / 76.9;
 //   384 81.0 / 82.4; 640 111 / 116; 1280 197 / 195
@@ -1235,10 +1238,10 @@ hipError_t launch_page_scores(hipStream_t st, int dtype, const KvView& kv, const
 bool pick_pages_serves(const Shape& sh, int batch, int max_seq_pages, int rows, bool rows_known) {
   const int tiles = (rows + kPickRows - 1) / kPickRows;
   if (sh.B > 64 || max_seq_pages > kPickPages || tiles * kPickRows > kPickMostRows) return false;
-  const long workgroups = (long)tiles * sh.Hkv * batch, wide = (long)max_seq_pages * sh.d / 128;   // (wide: pages of 128 channels)
+  const long workgroups = (long)tiles * sh.Hkv * batch, wide = ((long)max_seq_pages * sh.d + 127) / 128;   // (wide: pages of 128 channels)
   if (!rows_known) return max_seq_pages <= 128 && workgroups <= 256;
-  if (max_seq_pages <= 256) return wide <= (tiles > 1 ? 192 : 160) || workgroups >= 40;
-  if (wide <= 192) return workgroups >= (wide <= 160 ? 64 : 128) || (tiles >= 8 && (wide <= 160 || workgroups >= 40));
+  if (max_seq_pages <= 256) return wide <= 192 || workgroups >= 40;
+  if (wide <= 192) return pick_takes_hidden(sh) || workgroups >= (wide <= 160 ? 64 : 128) || (tiles >= 8 && (wide <= 160 || workgroups >= 40));
   const long rounds = (workgroups + 255) / 256, percent = workgroups * 100 / (256 * rounds);   // compute units with a workgroup
   return workgroups >= 144 && (rounds == 1 || wide <= 288 || percent >= (wide <= 352 ? 70 : 90));
 }

@@ -745,7 +745,7 @@ class OnePagePrefix:
     """Sequences whose pages are all the same few, for launches over prefixes of any length: the values of a physical page are its
     number, so a dense step's output is known."""
 
-    def __init__(self, tokens, B, G, Hkv, d, g, batch=1):
+    def __init__(self, tokens, B, G, Hkv, d, g, batch=1, hidden=64):
         ints, self.heads, self.rows = (lambda *x: torch.tensor(x, dtype=torch.int32, device="cuda")), Hkv, B * G
         P = -(-tokens // g)
         ids = torch.arange(P, dtype=torch.int32, device="cuda") % 7
@@ -753,13 +753,13 @@ class OnePagePrefix:
         zeros = lambda *shape: torch.zeros(shape, device="cuda", dtype=torch.bfloat16)
         self.kv = L.PagedKV(zeros(7, Hkv, g, d), v, zeros(7, Hkv, 2, d), ints(*range(0, (batch + 1) * P, P)), ids.repeat(batch), ints(*[tokens] * batch),
                             max_seq_pages=P)
-        self.ctx = L.losa_create(L.make_config(max_batch=batch, num_q_heads=Hkv * G, num_kv_heads=Hkv, head_dim=d, hidden_size=64, page_size=g,
+        self.ctx = L.losa_create(L.make_config(max_batch=batch, num_q_heads=Hkv * G, num_kv_heads=Hkv, head_dim=d, hidden_size=hidden, page_size=g,
                                                block_size=B, max_pages_per_seq=P, max_topk_pages=P), "cuda:0")
         weights = torch.full((P,), float(g), dtype=torch.float64, device="cuda")
         weights[-1] = tokens - (P - 1) * g
         self.mean, self.tokens = float((ids.double() * weights).sum() / tokens), tokens
         self.q, self.o_p = zeros(batch * B, Hkv * G, d), torch.zeros((batch * B, Hkv * G, d), device="cuda")
-        self.lse_p, self.h = torch.zeros((batch * B, Hkv * G), device="cuda"), (zeros(batch * B, 64) + 1, zeros(batch * B, 64))
+        self.lse_p, self.h = torch.zeros((batch * B, Hkv * G), device="cuda"), (zeros(batch * B, hidden) + 1, zeros(batch * B, hidden))
 
     def dense_shares(self):
         """Shares that the dense step's page list was split into: work items whose partials were written."""
@@ -807,16 +807,18 @@ def test_short_prefixes_are_split_into_shares_of_two_or_four_tiles(tokens, G, Hk
         r.ctx.close()
 
 
-@pytest.mark.parametrize("P,d,Hkv,batch,n,one", [   # 7 query heads per KV head
-    (100, 128, 1, 1, 2, True), (160, 128, 4, 1, 2, True), (161, 128, 4, 1, 2, False),    # 14 rows, few workgroups
-    (192, 128, 4, 1, 3, True), (193, 128, 4, 1, 3, False),                               # two tiles of rows
-    (256, 128, 8, 4, 2, False), (256, 128, 8, 5, 2, True),                               # 32 and 40 workgroups
-    (256, 64, 1, 1, 2, True), (257, 64, 1, 1, 2, False), (384, 64, 4, 1, 8, False),      # 64 channels: up to 256 pages ...
-    (320, 64, 8, 8, 2, True), (322, 64, 8, 8, 2, False), (384, 64, 8, 16, 2, True),      # ... with 64, and with 128 workgroups
-    (320, 64, 1, 1, 16, False), (320, 64, 1, 1, 17, True), (384, 64, 1, 4, 17, False), (384, 64, 1, 5, 17, True),   # ... with eight tiles of rows
-    (512, 128, 8, 3, 13, True), (512, 128, 8, 6, 13, False), (288, 128, 8, 6, 13, True), (512, 128, 8, 16, 8, True), (513, 128, 8, 16, 8, False)])
-def test_which_prefixes_are_scored_and_selected_in_one_launch(P, d, Hkv, batch, n, one):
-    r = OnePagePrefix(16 * P - 5, 32, 7, Hkv, d, 16, batch)
+@pytest.mark.parametrize("P,d,Hkv,batch,n,hidden,one", [   # 7 query heads per KV head
+    (100, 128, 1, 1, 2, 520, True), (192, 128, 4, 1, 2, 520, True), (193, 128, 4, 1, 3, 520, False),
+    (256, 128, 8, 4, 2, 520, False), (256, 128, 8, 5, 2, 520, True),                         # 32 and 40 workgroups
+    (256, 64, 1, 1, 2, 520, True), (257, 64, 1, 1, 2, 520, False), (384, 64, 4, 1, 8, 520, False),   # 64 channels: up to 256 pages ...
+    (257, 64, 1, 1, 2, 512, True), (384, 64, 4, 1, 8, 64, True), (385, 64, 4, 1, 8, 64, False),     # ... to 384 where it scores the tokens too
+    (320, 64, 8, 8, 2, 520, True), (321, 64, 8, 8, 2, 520, False), (384, 64, 8, 16, 2, 520, True),  # ... with 64, and with 128 workgroups
+    (320, 64, 1, 1, 16, 520, False), (320, 64, 1, 1, 17, 520, True), (384, 64, 1, 4, 17, 520, False),
+    (384, 64, 1, 5, 17, 520, True),                                                                 # ... with eight tiles of rows
+    (512, 128, 8, 3, 13, 520, True), (512, 128, 8, 6, 13, 520, False), (288, 128, 8, 6, 13, 520, True), (512, 128, 8, 16, 8, 520, True),
+    (513, 128, 8, 16, 8, 520, False)])
+def test_which_prefixes_are_scored_and_selected_in_one_launch(P, d, Hkv, batch, n, hidden, one):
+    r = OnePagePrefix(16 * P - 5, 32, 7, Hkv, d, 16, batch, hidden)
     count, K = torch.zeros((batch, Hkv), dtype=torch.int32, device="cuda"), P // 3
     try:
         assert one == scored_in_one_launch(r.ctx, lambda: L.losa_step(r.ctx, r.kv, 1, *r.h, r.q, orc.SEL_TOPK, float(n), K, r.o_p, r.lse_p,
