@@ -26,6 +26,16 @@ struct KvView {
   int32_t seq_page_limit;   // the host's upper bound on pages per sequence (grids and register tiles are sized by it)
 };
 
+// An address among a kernel's leading arguments.  The runtime looks every plain pointer argument up among its allocations at every
+// launch; an integer it copies: 10 leading arguments with 5 pointers took 0.25 us of the host's time a launch, with 5 integers none that
+// shows, and a step of few heads is issued no faster than it runs.
+typedef uint64_t Address;
+inline Address address(const void* p) { return (Address)(uintptr_t)p; }
+template <typename T>
+__device__ __forceinline__ T* pointer(Address a) {   // (through the global address space: a bare conversion would make every access a flat one)
+  return (T*)(__attribute__((address_space(1))) T*)a;
+}
+
 // Static problem shape, passed to kernels by value.
 struct Shape {
   int32_t max_pages;   // row stride of the score matrix / bitmap sizing (config.max_pages_per_seq)

@@ -215,19 +215,19 @@ __global__ __launch_bounds__(256) void page_scores_f32_kernel(KvView kv, Shape s
 // the B operands are the sign-split query fragments.  Output leaves the matrix core as 4
 // consecutive pages per lane and query row: one 16-byte store.
 template <int D, int MAXT>
-__global__ __launch_bounds__(256) void page_scores_mfma_kernel(const float* delta, const int32_t* page_indptr, const int32_t* seq_lens,
-                                                               const int32_t* page_indices, void* meta, int block, int kv_heads, int num_pages,
+__global__ __launch_bounds__(256) void page_scores_mfma_kernel(Address delta, Address page_indptr, Address seq_lens,
+                                                               Address page_indices, Address meta, int block, int kv_heads, int num_pages,
                                                                int max_pages,
                                                                KvView kv, Shape sh, const bf16_t* __restrict__ q,
                                                                const int32_t* __restrict__ active_idx,
                                                                const int32_t* __restrict__ active_count,
                                                                float* __restrict__ scores, ScoreAux aux, RankArgs ra,
                                                                int tpw) {
-  ra.delta = delta;   // (leading arguments: see KvView)
-  kv.page_indptr = page_indptr;
-  kv.seq_lens = seq_lens;
-  kv.page_indices = page_indices;
-  kv.meta = meta;
+  ra.delta = pointer<const float>(delta);   // (leading arguments: see KvView)
+  kv.page_indptr = pointer<const int32_t>(page_indptr);
+  kv.seq_lens = pointer<const int32_t>(seq_lens);
+  kv.page_indices = pointer<const int32_t>(page_indices);
+  kv.meta = pointer<void>(meta);
   kv.num_pages = num_pages;
   sh.B = block;
   sh.Hkv = kv_heads;
@@ -640,10 +640,10 @@ __device__ __forceinline__ void radix_kth(uint32_t (&key)[E], int nmine, int Kp,
 // table, which a workgroup of this launch per head used to gather, come from the scoring kernel.
 template <int E, int NT, bool MULTI, bool LIST>
 __global__ __launch_bounds__(NT) void select_pages_kernel(const float* __restrict__ scores, const int32_t* __restrict__ active_count,
-                                                           const int32_t* page_indptr, const int32_t* seq_lens, int kv_heads, int rows_max,
+                                                           Address page_indptr, Address seq_lens, int kv_heads, int rows_max,
                                                            int max_pages, int rows_known, KvView kv, Shape sh, int topk, SelectOut out, int rpw) {
-  kv.page_indptr = page_indptr;   // (leading arguments: see KvView)
-  kv.seq_lens = seq_lens;
+  kv.page_indptr = pointer<const int32_t>(page_indptr);   // (leading arguments: see KvView)
+  kv.seq_lens = pointer<const int32_t>(seq_lens);
   sh.Hkv = kv_heads;
   sh.rows_max = rows_max;
   sh.max_pages = max_pages;
@@ -978,14 +978,15 @@ __global__ __launch_bounds__(NT) void shared_select_kernel(KvView kv, Shape sh, 
 // The locality scores too, for hidden states of up to 64 16-byte pieces (h_cur given): a wavefront per token, sums in the order
 // of the locality kernel's, whose three other wavefronts have nothing then.
 template <int D, int TPW>   // TPW: 16-page tiles per wavefront
-__global__ __launch_bounds__(1024) void pick_pages_kernel(const float* delta, const bf16_t* h_cur, const bf16_t* h_prev, const int32_t* page_indptr,
-                                                          const int32_t* seq_lens, int block, int hidden, KvView kv, Shape sh,
+__global__ __launch_bounds__(1024) void pick_pages_kernel(Address delta, Address hidden_cur, Address hidden_prev, Address page_indptr, Address seq_lens,
+                                                          int block, int hidden, KvView kv, Shape sh,
                                                           const bf16_t* __restrict__ q, ScoreAux aux, RankArgs ra, int topk) {
-  ra.delta = delta;   // (leading arguments: see KvView)
-  kv.page_indptr = page_indptr;
-  kv.seq_lens = seq_lens;
+  ra.delta = pointer<const float>(delta);   // (leading arguments: see KvView)
+  kv.page_indptr = pointer<const int32_t>(page_indptr);
+  kv.seq_lens = pointer<const int32_t>(seq_lens);
   sh.B = block;
   sh.H = hidden;
+  const bf16_t *h_cur = pointer<const bf16_t>(hidden_cur), *h_prev = pointer<const bf16_t>(hidden_prev);
   constexpr int NW = 16, KS = D / 32, VPR = D / 8, STRIDE = D * 2 + 16;
   constexpr int NP = NW * 16 * TPW, ROW = NP + 4;   // pages; floats per row of scores in LDS (the writes of 16 rows spread over the banks)
   constexpr int E = NP / 64, COPY = 16;             // keys per lane; words of a copy of the union bitmap
@@ -1197,17 +1198,10 @@ hipError_t launch_page_scores(hipStream_t st, int dtype, const KvView& kv, const
     int tpw = (int)((tiles * sh.Hkv * batch + round - 1) / round);
     tpw = max(1, min(tpw, kMaxTilesPerWg));
     dim3 mgrid((unsigned)((tiles + tpw - 1) / tpw), sh.Hkv, batch);
-    if (sh.d == 128) {
-      if (tpw == 1)
-        page_scores_mfma_kernel<128, 1><<<mgrid, 256, 0, st>>>(ra.delta, kv.page_indptr, kv.seq_lens, kv.page_indices, kv.meta, sh.B, sh.Hkv, kv.num_pages, sh.max_pages, kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, 1);
-      else
-        page_scores_mfma_kernel<128, kMaxTilesPerWg><<<mgrid, 256, 0, st>>>(ra.delta, kv.page_indptr, kv.seq_lens, kv.page_indices, kv.meta, sh.B, sh.Hkv, kv.num_pages, sh.max_pages, kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, tpw);
-    } else {
-      if (tpw == 1)
-        page_scores_mfma_kernel<64, 1><<<mgrid, 256, 0, st>>>(ra.delta, kv.page_indptr, kv.seq_lens, kv.page_indices, kv.meta, sh.B, sh.Hkv, kv.num_pages, sh.max_pages, kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, 1);
-      else
-        page_scores_mfma_kernel<64, kMaxTilesPerWg><<<mgrid, 256, 0, st>>>(ra.delta, kv.page_indptr, kv.seq_lens, kv.page_indices, kv.meta, sh.B, sh.Hkv, kv.num_pages, sh.max_pages, kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, tpw);
-    }
+    auto kern = sh.d == 128 ? (tpw == 1 ? page_scores_mfma_kernel<128, 1> : page_scores_mfma_kernel<128, kMaxTilesPerWg>)
+                            : (tpw == 1 ? page_scores_mfma_kernel<64, 1> : page_scores_mfma_kernel<64, kMaxTilesPerWg>);
+    kern<<<mgrid, 256, 0, st>>>(address(ra.delta), address(kv.page_indptr), address(kv.seq_lens), address(kv.page_indices), address(kv.meta), sh.B,
+                                sh.Hkv, kv.num_pages, sh.max_pages, kv, sh, (const bf16_t*)q, active_idx, active_count, scores, aux, ra, tpw);
   } else {
     (sh.d == 128 ? page_scores_f32_kernel<128> : page_scores_f32_kernel<64>)<<<grid, 256, 0, st>>>(
         kv, sh, (const float*)q, active_idx, active_count, scores, aux);
@@ -1257,7 +1251,7 @@ hipError_t launch_pick_pages(hipStream_t st, const KvView& kv, const Shape& sh, 
   const dim3 grid((rows + kPickRows - 1) / kPickRows, sh.Hkv, batch);
   auto kern = sh.d == 128 ? (max_seq_pages <= 256 ? pick_pages_kernel<128, 1> : pick_pages_kernel<128, 2>)
                           : (max_seq_pages <= 256 ? pick_pages_kernel<64, 1> : pick_pages_kernel<64, 2>);
-  kern<<<grid, 1024, 0, st>>>(ra.delta, (const bf16_t*)h_cur, (const bf16_t*)h_prev, kv.page_indptr, kv.seq_lens, sh.B, sh.H, kv, sh,
+  kern<<<grid, 1024, 0, st>>>(address(ra.delta), address(h_cur), address(h_prev), address(kv.page_indptr), address(kv.seq_lens), sh.B, sh.H, kv, sh,
                               (const bf16_t*)q, aux, ra, topk);
   return hipGetLastError();
 }
@@ -1308,7 +1302,7 @@ hipError_t launch_select_pages(hipStream_t st, const KvView& kv, const Shape& sh
 #define LOSA_SELECT(E, NT)                                                                                                             \
   (rpw == 1 ? (list ? select_pages_kernel<E, NT, false, true> : select_pages_kernel<E, NT, false, false>)                              \
             : (list ? select_pages_kernel<E, NT, true, true> : select_pages_kernel<E, NT, true, false>))<<<grid, NT, 0, st>>>(          \
-      scores, active_count, kv.page_indptr, kv.seq_lens, sh.Hkv, sh.rows_max, sh.max_pages, rows_known, kv, sh, topk, out, rpw)
+      scores, active_count, address(kv.page_indptr), address(kv.seq_lens), sh.Hkv, sh.rows_max, sh.max_pages, rows_known, kv, sh, topk, out, rpw)
   if (pages <= 256 * 8)
     LOSA_SELECT(8, 256);
   else if (pages <= 512 * 8)

@@ -351,13 +351,13 @@ __device__ __forceinline__ void merge_fragments(const Shape& sh, const int32_t* 
 }
 
 // The leading arguments of the merge kernels (see KvView) put where the code reads them.
-__device__ __forceinline__ void take_leading(const float* pm, const float* pl, const float* po, const int32_t* active_count,
+__device__ __forceinline__ void take_leading(Address pm, Address pl, Address po, Address active_count,
                                              int part_rows, int kv_heads, int group, int block, AttnInputs& in, Shape& sh, Partials& part) {
-  part.m = const_cast<float*>(pm);
-  part.l = const_cast<float*>(pl);
-  part.o = const_cast<float*>(po);
+  part.m = pointer<float>(pm);
+  part.l = pointer<float>(pl);
+  part.o = pointer<float>(po);
   part.rows = part_rows;
-  in.active_count = active_count;
+  in.active_count = pointer<const int32_t>(active_count);
   sh.Hkv = kv_heads;
   sh.G = group;
   sh.B = block;
@@ -387,7 +387,7 @@ __device__ __forceinline__ RowsPages rows_and_pages(const AttnInputs& in, const 
 
 // Every head's partials are laid out by fragments.  DENSE: every row, every page.
 template <int D, int WAVES, int PER, int KB, bool DENSE>
-__global__ __launch_bounds__(64 * WAVES) void attn_merge_fragments_kernel(const float* pm, const float* pl, const float* po, const int32_t* active_count,
+__global__ __launch_bounds__(64 * WAVES) void attn_merge_fragments_kernel(Address pm, Address pl, Address po, Address active_count,
                                                                     int part_rows, int nchunk, int kv_heads, int rows_known, int group, int block, KvView kv, Shape sh, AttnInputs in, Partials part,
                                                                           float* __restrict__ o_p, float* __restrict__ lse_p) {
   __shared__ __attribute__((aligned(16))) float lds[PER > 1 ? WAVES * kFragSlot : 4];
@@ -412,7 +412,7 @@ __global__ __launch_bounds__(64 * WAVES) void attn_merge_fragments_kernel(const 
 // MIXED (0: no): heads with more than 64 query rows have partials laid out by fragments; their workgroups take those, MIXED
 // wavefronts each (four chunks in flight, counts first: the plain form's registers and occupancy).
 template <int D, bool LOG2, int MIXED>
-__global__ __launch_bounds__(256) void attn_merge_kernel(const float* pm, const float* pl, const float* po, const int32_t* active_count,
+__global__ __launch_bounds__(256) void attn_merge_kernel(Address pm, Address pl, Address po, Address active_count,
                                                          int part_rows, int nchunk, int kv_heads, int rows_known, int group, int block, KvView kv, Shape sh, AttnInputs in, Partials part,
                                                          float* __restrict__ o_p, float* __restrict__ lse_p, int few_tile, int many_tile) {
   typedef typename std::conditional<LOG2, float, double>::type Acc;
@@ -549,7 +549,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const float* pm, const 
 // x 64 heads, 4 chunks 10.3 / 5.1 us; 112 rows 6.6 / 6.3).
 constexpr int kFewChunks = 8;
 template <int D, int KC, bool MIXED>
-__global__ __launch_bounds__(64 * (MIXED ? 4 : 1)) void attn_merge_few_kernel(const float* pm, const float* pl, const float* po, const int32_t* active_count,
+__global__ __launch_bounds__(64 * (MIXED ? 4 : 1)) void attn_merge_few_kernel(Address pm, Address pl, Address po, Address active_count,
                                                             int part_rows, int nchunk, int kv_heads, int rows_known, int group, int block, KvView kv, Shape sh, AttnInputs in, Partials part,
                                                             float* __restrict__ o_p, float* __restrict__ lse_p, int few_tile, int many_tile) {
   constexpr int C4 = D / 4, WAVES = MIXED ? 4 : 1;
@@ -657,7 +657,7 @@ hipError_t launch_attn_merge(hipStream_t st, const KvView& kv, const Shape& sh, 
   const int tiles = (rows + kPartialTile - 1) / kPartialTile, frags = sh.d / 8;
   if (few_tile == kManyRowStage) {   // every head's partials are laid out by fragments
     auto launch = [&](auto kern, int per_tile, int waves) {
-      kern<<<dim3(tiles * per_tile, sh.Hkv, batch), 64 * waves, 0, st>>>(part.m, part.l, part.o, in.active_count, part.rows, nchunk, sh.Hkv, known, sh.G, sh.B, kv, sh, in, part, o_p, lse_p);
+      kern<<<dim3(tiles * per_tile, sh.Hkv, batch), 64 * waves, 0, st>>>(address(part.m), address(part.l), address(part.o), address(in.active_count), part.rows, nchunk, sh.Hkv, known, sh.G, sh.B, kv, sh, in, part, o_p, lse_p);
     };
 #define LOSA_FRAGMENTS(W, PER, KB)                                                                                  \
   launch(sh.d == 128 ? (dense_step ? attn_merge_fragments_kernel<128, W, PER, KB, true>                             \
@@ -681,7 +681,7 @@ hipError_t launch_attn_merge(hipStream_t st, const KvView& kv, const Shape& sh, 
                       : (sh.d == 128 ? (nchunk <= 4 ? attn_merge_few_kernel<128, 4, false> : attn_merge_few_kernel<128, 8, false>)
                                      : (nchunk <= 4 ? attn_merge_few_kernel<64, 4, false> : attn_merge_few_kernel<64, 8, false>));
     const int waves = mixed ? 4 : 1, per_wg = waves * 256 / sh.d, few = ((mixed ? min(rows, kUnionRows) : rows) + per_wg - 1) / per_wg;
-    kern<<<dim3(mixed ? max(few, tiles * frags / 4) | 1 : few, sh.Hkv, batch), 64 * waves, 0, st>>>(part.m, part.l, part.o, in.active_count, part.rows, nchunk, sh.Hkv, known, sh.G, sh.B, kv, sh, in, part, o_p, lse_p,
+    kern<<<dim3(mixed ? max(few, tiles * frags / 4) | 1 : few, sh.Hkv, batch), 64 * waves, 0, st>>>(address(part.m), address(part.l), address(part.o), address(in.active_count), part.rows, nchunk, sh.Hkv, known, sh.G, sh.B, kv, sh, in, part, o_p, lse_p,
                                                                                                   few_tile, many_tile);
     return hipGetLastError();
   }
@@ -694,7 +694,7 @@ hipError_t launch_attn_merge(hipStream_t st, const KvView& kv, const Shape& sh, 
   // (mixed: an odd width.  Most of its workgroups leave at once, and with a multiple of 8 the ones that stay meet on a
   // few of every die's compute units: 14 of 64 rows, 40 heads 6.8 us, of 65 5.4)
   kern<<<dim3(mixed ? max(min(rows, kUnionRows), tiles * frags * mixed / 4) | 1 : rows, sh.Hkv, batch), 256, 0, st>>>(
-      part.m, part.l, part.o, in.active_count, part.rows, nchunk, sh.Hkv, known, sh.G, sh.B, kv, sh, in, part, o_p, lse_p, few_tile, many_tile);
+      address(part.m), address(part.l), address(part.o), address(in.active_count), part.rows, nchunk, sh.Hkv, known, sh.G, sh.B, kv, sh, in, part, o_p, lse_p, few_tile, many_tile);
   return hipGetLastError();
 }
 

@@ -693,28 +693,28 @@ __device__ __forceinline__ void attn_mfma_body(const AttnInputs& in, int nchunk,
 // The leading arguments (see KvView) put where the code reads them: union bitmap, entries and words per head; or list,
 // counts and capacity.
 template <bool UNION>
-__device__ __forceinline__ void take_leading(const void* first, const int32_t* second, const int32_t* active_count, const int32_t* page_indptr,
-                                             const int32_t* seq_lens, int stride, int copy_words, int max_pages, int kv_heads, AttnInputs& in,
+__device__ __forceinline__ void take_leading(Address first, Address second, Address active_count, Address page_indptr,
+                                             Address seq_lens, int stride, int copy_words, int max_pages, int kv_heads, AttnInputs& in,
                                              Shape& sh, KvView& kv, UnionInKernel& uni) {
-  in.active_count = active_count;
-  kv.page_indptr = page_indptr;
-  kv.seq_lens = seq_lens;
+  in.active_count = pointer<const int32_t>(active_count);
+  kv.page_indptr = pointer<const int32_t>(page_indptr);
+  kv.seq_lens = pointer<const int32_t>(seq_lens);
   sh.max_pages = max_pages;
   sh.Hkv = kv_heads;
   if constexpr (UNION) {
-    uni.bits = static_cast<const uint32_t*>(first);
-    uni.entries = second;
+    uni.bits = pointer<const uint32_t>(first);
+    uni.entries = pointer<const int32_t>(second);
     uni.stride = stride;
     uni.copy_words = copy_words;
   } else {
-    in.list = static_cast<const int32_t*>(first);
-    in.sel_count = second;
+    in.list = pointer<const int32_t>(first);
+    in.sel_count = pointer<const int32_t>(second);
     in.cap = stride;
   }
 }
 
 template <int D, int GP, int R, bool SPLIT_PAGES, int NBUF, bool UNION = false>
-__global__ __launch_bounds__(256) void attn_mfma_kernel(const void* first, const int32_t* second, const int32_t* active_count, const int32_t* page_indptr, const int32_t* seq_lens,
+__global__ __launch_bounds__(256) void attn_mfma_kernel(Address first, Address second, Address active_count, Address page_indptr, Address seq_lens,
                                                         int stride, int copy_words, int max_pages, int kv_heads, AttnInputs in,
                                                         int nchunk, int nrbg, Shape sh, KvView kv,
                                                         Partials part, float scale_log2e, int m_lo, int m_hi,
@@ -731,7 +731,7 @@ __global__ __launch_bounds__(256) void attn_mfma_kernel(const void* first, const
 // head with a few active rows does not pay for the 64 the launch has to allow.  Heads with more than
 // 64 rows are not served here.
 template <int D, int GP, bool UNION>
-__global__ __launch_bounds__(256) void attn_mfma_rows_kernel(const void* first, const int32_t* second, const int32_t* active_count, const int32_t* page_indptr, const int32_t* seq_lens,
+__global__ __launch_bounds__(256) void attn_mfma_rows_kernel(Address first, Address second, Address active_count, Address page_indptr, Address seq_lens,
                                                              int stride, int copy_words, int max_pages, int kv_heads, AttnInputs in,
                                                              int nchunk, Shape sh, KvView kv, Partials part,
                                                              float scale_log2e, int m_lo, int m_hi, UnionInKernel uni) {
@@ -774,11 +774,13 @@ static hipError_t launch_one(hipStream_t st, const KvView& kv, const Shape& sh, 
   const float scale_log2e = sh.sm_scale * 1.4426950408889634f;
   dim3 grid(nchunk, sh.Hkv * nrbg, batch);
   if (ev_start && ev_stop)   // events bound to this dispatch: they read the kernel's own begin and end
-    hipExtLaunchKernelGGL(kern, grid, dim3(256), (uint32_t)lds_bytes, st, ev_start, ev_stop, 0, UNION ? (const void*)uni.bits : in.list, UNION ? uni.entries : in.sel_count, in.active_count, kv.page_indptr, kv.seq_lens,
+    hipExtLaunchKernelGGL(kern, grid, dim3(256), (uint32_t)lds_bytes, st, ev_start, ev_stop, 0, address(UNION ? (const void*)uni.bits : in.list), address(UNION ? uni.entries : in.sel_count), address(in.active_count),
+                          address(kv.page_indptr), address(kv.seq_lens),
                           UNION ? uni.stride : in.cap, uni.copy_words, sh.max_pages, sh.Hkv, in, nchunk,
                           nrbg, sh, kv, part, scale_log2e, m_lo, m_hi, uni);
   else
-    kern<<<grid, 256, lds_bytes, st>>>(UNION ? (const void*)uni.bits : in.list, UNION ? uni.entries : in.sel_count, in.active_count, kv.page_indptr, kv.seq_lens,
+    kern<<<grid, 256, lds_bytes, st>>>(address(UNION ? (const void*)uni.bits : in.list), address(UNION ? uni.entries : in.sel_count), address(in.active_count),
+                          address(kv.page_indptr), address(kv.seq_lens),
                           UNION ? uni.stride : in.cap, uni.copy_words, sh.max_pages, sh.Hkv, in, nchunk, nrbg, sh, kv, part, scale_log2e, m_lo, m_hi, uni);
   return hipGetLastError();
 }
@@ -801,11 +803,13 @@ static hipError_t launch_dg(hipStream_t st, const KvView& kv, const Shape& sh, i
       const float scale_log2e = sh.sm_scale * 1.4426950408889634f;
       const UnionInKernel u = uni ? *uni : UnionInKernel{nullptr};
       if (e0 && e1)   // events bound to this dispatch, as in launch_one
-        hipExtLaunchKernelGGL(kern, grid, dim3(256), (uint32_t)lds_bytes, st, e0, e1, 0, uni ? (const void*)u.bits : in.list, uni ? u.entries : in.sel_count, in.active_count, kv.page_indptr, kv.seq_lens,
+        hipExtLaunchKernelGGL(kern, grid, dim3(256), (uint32_t)lds_bytes, st, e0, e1, 0, address(uni ? (const void*)u.bits : in.list), address(uni ? u.entries : in.sel_count), address(in.active_count),
+                              address(kv.page_indptr), address(kv.seq_lens),
                               uni ? u.stride : in.cap, u.copy_words, sh.max_pages, sh.Hkv, in, nchunk, sh, kv, part, scale_log2e, m_lo,
                               m_hi, u);
       else
-        kern<<<grid, 256, lds_bytes, st>>>(uni ? (const void*)u.bits : in.list, uni ? u.entries : in.sel_count, in.active_count, kv.page_indptr, kv.seq_lens,
+        kern<<<grid, 256, lds_bytes, st>>>(address(uni ? (const void*)u.bits : in.list), address(uni ? u.entries : in.sel_count), address(in.active_count),
+                              address(kv.page_indptr), address(kv.seq_lens),
                               uni ? u.stride : in.cap, u.copy_words, sh.max_pages, sh.Hkv, in, nchunk, sh, kv, part, scale_log2e, m_lo, m_hi, u);
       return hipGetLastError();
     };

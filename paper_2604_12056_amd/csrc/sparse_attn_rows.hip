@@ -594,22 +594,22 @@ __device__ __forceinline__ int own_pages(const UnionInKernel& uni, const KvView&
 }
 
 template <int D, int GP, bool HALF, PageSource SRC>
-__global__ __launch_bounds__(512) void attn_rows_kernel(const void* first, const int32_t* active_count, const int32_t* sel_count, const int32_t* page_indptr,
-                                                        const int32_t* seq_lens, int stride, int kv_heads, int nchunk, int row_groups,
+__global__ __launch_bounds__(512) void attn_rows_kernel(Address first, Address active_count, Address sel_count, Address page_indptr,
+                                                        Address seq_lens, int stride, int kv_heads, int nchunk, int row_groups,
                                                         AttnInputs in, Shape sh, KvView kv, Partials part,
                                                         float scale_log2e, int m_lo, UnionInKernel uni) {
   extern __shared__ __attribute__((aligned(16))) unsigned char stage_lds[];
-  in.active_count = active_count;   // (leading arguments: see KvView)
-  in.sel_count = sel_count;
-  kv.page_indptr = page_indptr;
-  kv.seq_lens = seq_lens;
+  in.active_count = pointer<const int32_t>(active_count);   // (leading arguments: see KvView)
+  in.sel_count = pointer<const int32_t>(sel_count);
+  kv.page_indptr = pointer<const int32_t>(page_indptr);
+  kv.seq_lens = pointer<const int32_t>(seq_lens);
   sh.Hkv = kv_heads;
   if constexpr (SRC == PageSource::list) {
-    in.list = static_cast<const int32_t*>(first);
+    in.list = pointer<const int32_t>(first);
     in.cap = stride;
   }
   if constexpr (SRC == PageSource::own) {
-    uni.bits = static_cast<const uint32_t*>(first);
+    uni.bits = pointer<const uint32_t>(first);
     uni.stride = stride;
   }
   const int j = blockIdx.y / row_groups, row_group = blockIdx.y % row_groups, b = blockIdx.z;
@@ -669,11 +669,13 @@ static hipError_t launch_rows(hipStream_t st, const KvView& kv, const Shape& sh,
   const float scale_log2e = sh.sm_scale * 1.4426950408889634f;
   dim3 grid(nchunk, sh.Hkv * row_groups, batch);
   if (e0 && e1)   // events bound to this dispatch: they read the kernel's own begin and end
-    hipExtLaunchKernelGGL(kern, grid, dim3(512), (uint32_t)lds_bytes, st, e0, e1, 0, OWN ? (const void*)uni.bits : in.list, in.active_count, in.sel_count, kv.page_indptr, kv.seq_lens,
+    hipExtLaunchKernelGGL(kern, grid, dim3(512), (uint32_t)lds_bytes, st, e0, e1, 0, address(OWN ? (const void*)uni.bits : in.list), address(in.active_count), address(in.sel_count),
+                          address(kv.page_indptr), address(kv.seq_lens),
                           OWN ? uni.stride : in.cap, sh.Hkv, nchunk, row_groups, in, sh, kv,
                           part, scale_log2e, m_lo, uni);
   else
-    kern<<<grid, 512, lds_bytes, st>>>(OWN ? (const void*)uni.bits : in.list, in.active_count, in.sel_count, kv.page_indptr, kv.seq_lens,
+    kern<<<grid, 512, lds_bytes, st>>>(address(OWN ? (const void*)uni.bits : in.list), address(in.active_count), address(in.sel_count),
+                          address(kv.page_indptr), address(kv.seq_lens),
                           OWN ? uni.stride : in.cap, sh.Hkv, nchunk, row_groups, in, sh, kv, part, scale_log2e, m_lo, uni);
   return hipGetLastError();
 }
