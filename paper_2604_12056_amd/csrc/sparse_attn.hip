@@ -82,7 +82,7 @@ __global__ __launch_bounds__(256, 2) void attn_f32_kernel(KvView kv, Shape sh, c
   int pg_phys = 0, pg_valid = 0;
   // (no branch around the load: what joins behind one waits for it.  An empty sequence has no entry: resolve() takes none.  The
   // choice is kept in scalar registers: as two vector registers over the loop, whose 256 are full with 128 channels, it put two others
-  // into scratch memory.  Within 0.5 % either way from 1000 to 32768 tokens)
+  // into scratch memory.  Steps of 1000 to 32768 tokens take the same time within 0.5 %, attention over lists alone 1 % more)
   const int32_t* table = __builtin_amdgcn_readfirstlane(P) > 0 ? kv.page_indices + base : kv.seq_lens + b;
   auto request = [&](int logical) { return table[max(0, min(logical, P - 1))]; };
   auto resolve = [&](int first, int logical, int ph) {
