@@ -68,6 +68,15 @@ def test_no_kernel_needs_scratch_memory(lib):
     assert not {n: k[".private_segment_fixed_size"] for n, k in kernels.items() if k[".private_segment_fixed_size"]}
 
 
+@pytest.mark.parametrize("kernel,pointers", [("attn_mfma", 0), ("attn_rows", 0), ("attn_merge", 2), ("page_scores_mfma", 4), ("select_pages", 2),
+                                             ("pick_pages", 1)])
+def test_kernels_of_a_step_take_few_plain_pointers(lib, kernel, pointers):
+    """Every plain pointer argument is looked up at every launch; the leading ones are passed as integers, the others in structs."""
+    counts = {sum(a[".value_kind"] == "global_buffer" for a in k[".args"]) for n, k in _kernels_of(binding.LIB_PATH).items()
+              if kernel in n and "shared_select" not in n}
+    assert counts == {pointers}
+
+
 def _cfg(**kw):
     base = dict(max_batch=2, num_q_heads=8, num_kv_heads=2, head_dim=128, hidden_size=1024, page_size=16,
                 block_size=32, max_pages_per_seq=64, max_topk_pages=16)
